@@ -104,6 +104,16 @@ int spdy_dp_solve_batched(const int32_t *tau, const float *err, int K, int L, in
                           int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
                           void *stream);
 
+/* spdy_dp_solve_batched for callers that only want the profiles: the same arguments, results (bit
+ * for bit) and status codes, but the workspace is scratch, its contents are unspecified
+ * afterwards.  Levels and cells of the table that provably lie on no optimal profile are then left
+ * out (the header of csrc/dp_core.h has the bound); a candidate on which that does not help gets the
+ * full table.  The other entry points below that do not say otherwise use their workspace the same
+ * way: only spdy_dp_solve_batched and spdy_dp_fill leave the table in it. */
+int spdy_dp_solve_profiles(const int32_t *tau, const float *err, int K, int L, int S, int B,
+                           int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
+                           void *stream);
+
 /* spdy_dp_solve_batched for callers that cannot allocate device memory or be handed a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
  * workspace is a fixed array of SPDY_DP_STATIC_WORKSPACE_BYTES inside the library's code object

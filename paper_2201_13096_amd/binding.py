@@ -20,7 +20,7 @@ ERR_STATIC_LIMIT = -10
 STATIC_WORKSPACE_BYTES = 64 << 20     # SPDY_DP_STATIC_WORKSPACE_BYTES in the header
 
 EXPORTS = ("spdy_dp_workspace_bytes", "spdy_dp_workspace_bytes_min", "spdy_dp_solve_batched",
-           "spdy_dp_solve_batched_static",
+           "spdy_dp_solve_profiles", "spdy_dp_solve_batched_static",
            "spdy_dp_solve_sensitivities", "spdy_dp_solve_budgets",
            "spdy_dp_solve_from_incumbent", "spdy_dp_workspace_bytes_checkpointed",
            "spdy_dp_solve_checkpointed", "spdy_dp_fill", "spdy_dp_backtrace",
@@ -49,6 +49,8 @@ def lib() -> ctypes.CDLL:
         L.spdy_dp_workspace_bytes_min.argtypes = [i, i, i, i]
         L.spdy_dp_solve_batched.restype = i
         L.spdy_dp_solve_batched.argtypes = [vp, vp, i, i, i, i, vp, vp, vp, sz, vp]
+        L.spdy_dp_solve_profiles.restype = i
+        L.spdy_dp_solve_profiles.argtypes = [vp, vp, i, i, i, i, vp, vp, vp, sz, vp]
         L.spdy_dp_solve_batched_static.restype = i
         L.spdy_dp_solve_batched_static.argtypes = [vp, vp, i, i, i, i, vp, vp, vp]
         L.spdy_dp_solve_sensitivities.restype = i
@@ -152,7 +154,9 @@ def _own_full_workspace(K: int, L: int, S: int, B: int, device, stream):
 
 def spdy_dp_solve_batched(tau, err, B: int, profile=None, cost=None, workspace=None, stream=None):
     """Whole of Alg. 1 for K candidates.  Returns ``(profile int16[K,L], cost fp32[K])`` (device
-    tensors, valid after the stream is synchronised)."""
+    tensors, valid after the stream is synchronised).  A ``workspace`` that is given holds the
+    table of Eq. 2 afterwards; without one nobody sees the table, and only the part of it that can
+    matter is computed (``spdy_dp_solve_profiles``)."""
     tau = _dev(tau, torch.int32, "tau")
     err = _dev(err, torch.float32, "err")
     K, L, S = _shapes(tau, err)
@@ -160,14 +164,15 @@ def spdy_dp_solve_batched(tau, err, B: int, profile=None, cost=None, workspace=N
         profile = torch.empty((K, L), dtype=torch.int16, device=err.device)
     if cost is None:
         cost = torch.empty((K,), dtype=torch.float32, device=err.device)
+    solve = lib().spdy_dp_solve_batched
     if workspace is None:
         workspace = _own_full_workspace(K, L, S, B, err.device, stream)
+        solve = lib().spdy_dp_solve_profiles
     _dev(profile, torch.int16, "profile")
     _dev(cost, torch.float32, "cost")
     _dev(workspace, torch.uint8, "workspace")
-    st = lib().spdy_dp_solve_batched(tau.data_ptr(), err.data_ptr(), K, L, S, int(B),
-                                     profile.data_ptr(), cost.data_ptr(), workspace.data_ptr(),
-                                     workspace.numel(), _stream(stream))
+    st = solve(tau.data_ptr(), err.data_ptr(), K, L, S, int(B), profile.data_ptr(),
+               cost.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream(stream))
     if st != OK:
         raise SpdyDpError(st)
     return profile, cost

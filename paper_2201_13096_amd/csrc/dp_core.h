@@ -1,0 +1,624 @@
+// The reduced problem ("core") of one candidate, solved by one workgroup.  Included by
+// spdy_dp.hip, inside its namespace.
+//
+// Eq. 1 is a multiple-choice knapsack problem.  For any multiplier lambda >= 0 the relaxed problem
+// (pick in every layer the level with the least err + lambda * tau, subtract lambda * B) bounds
+// every feasible profile from below, and a level whose excess over its layer's minimum is larger
+// than the distance from that bound to the cost of a known profile lies on no optimal one
+// (reduction by Lagrangian bounds: Dyer 1984, Zemel 1984; Pisinger 1995 for the core of a
+// multiple-choice problem).  The same test on a partial profile discards cells of the table.
+// On the tables this solver is for, one to three levels per layer and one to three hundred
+// buckets of a row are left, out of some thirty levels and thousands of buckets, so Eq. 2 over
+// what is left takes 10^4 updates where the whole table takes 10^7, in a few KB of LDS.
+//
+// Results are Alg. 1's, bit for bit, because only what can lie on NO profile of least fp32 cost is
+// left out.  With errors >= 0 every partial sum of a profile P of least cost V is at most
+// V <= U (U: the fp32 cost of a known profile), so each of its L - 1 rounded adds is off by at
+// most hu = 2^-24 * 2^floor(log2 U), and in real numbers c(P) <= U + (L - 1) hu.  Levels and cells
+// whose bound exceeds that are dropped, the bounds being formed in fp64 with a margin for its own
+// rounding; every profile that ties for the least cost survives, so the smallest t of the
+// argmin and the smallest level of each step of the walk back are found among the same
+// candidates as in the whole table.
+//
+// What it does not take is left to the full table (profile[0] = kTodo): a negative or NaN error,
+// a negative time, sums near the end of the fp32 range, more surviving levels, wider rows or
+// more work than the limits of the launch.
+//
+// What bounds it: latency.  A candidate is about 15 passes over its L * S table in LDS (a few
+// hundred clocks each, ended by a barrier), then L dependent steps of one wave for the reduced
+// table and L for the walk back.
+
+constexpr int16_t kTodo = -3;            // profile[0] of a candidate the full table has to solve
+constexpr int kCoreThreads = 256;
+constexpr int kCoreWaves = kCoreThreads / kWave;
+constexpr int kCoreMaxLayers = kCoreThreads;
+constexpr int kCoreMaxBudget = 1 << 22;  // times stay exact in fp32, a level and a shift in 32 bits
+constexpr int kCoreEntries = 1024;       // surviving levels of a candidate
+constexpr int kCoreBudgets = 64;         // budgets per launch
+constexpr float kCoreFar = 16777216.0f;  // "time" of a level that may not be chosen
+constexpr int kCoreShiftBits = 22;
+
+struct CoreStep {        // a layer of the reduced problem with more than one level left
+    int layer;
+    int first, count;    // its entries in the list
+    int span;            // largest shift among them
+};
+struct CoreEntry {       // a surviving level
+    float err;
+    uint32_t word;       // level << kCoreShiftBits | shift
+};
+
+struct CoreParams {
+    int parts, parts_log2;       // threads per layer (a power of two <= 64)
+    int per_part;        // levels per thread
+    int step_layers;     // kCoreThreads / S
+    int pitch;           // levels per layer in LDS (odd, so that a column of levels is conflict-free)
+    int window;          // buckets a row may span
+    int record;          // bytes of LDS for the recorded entries
+    int entries;         // room in the list
+    int table_bytes;     // LDS of the staged tables; the rows and the record reuse it
+    int work;            // sweeps of 64 buckets by one entry before a candidate is given up
+    unsigned char *spill;        // rows that do not fit the LDS record, per candidate and budget
+    long long spill_bytes;
+    int budgets;                 // J
+    int32_t budget[kCoreBudgets];
+};
+
+template <int kCtrl, int kRows, class T> __device__ __forceinline__ T dpp_from(T none, T x)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "words");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none),
+                                                                 __builtin_bit_cast(int, x), kCtrl,
+                                                                 kRows, 0xf, false));
+    } else {
+        const unsigned long long n = __builtin_bit_cast(unsigned long long, none);
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+        const unsigned lo = dpp_from<kCtrl, kRows>((unsigned)n, (unsigned)b);
+        const unsigned hi = dpp_from<kCtrl, kRows>((unsigned)(n >> 32), (unsigned)(b >> 32));
+        return __builtin_bit_cast(T, (unsigned long long)hi << 32 | lo);
+    }
+}
+template <class T> __device__ __forceinline__ T from_lane(T x, int lane)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T,
+                                  __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+    } else {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+        return __builtin_bit_cast(T, (unsigned long long)hi << 32 | lo);
+    }
+}
+
+// Inclusive scan over the 64 lanes (lane 63 holds the total): row_shr 1, 2, 4, 8, then the last
+// lane of a row is broadcast into the rows after it.
+template <class T, class Op> __device__ __forceinline__ T wave_scan(T v, T none, Op op)
+{
+    v = op(v, dpp_from<0x111, 0xf>(none, v));
+    v = op(v, dpp_from<0x112, 0xf>(none, v));
+    v = op(v, dpp_from<0x114, 0xf>(none, v));
+    v = op(v, dpp_from<0x118, 0xf>(none, v));
+    v = op(v, dpp_from<0x142, 0xa>(none, v));
+    v = op(v, dpp_from<0x143, 0xc>(none, v));
+    return v;
+}
+struct Add {
+    template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
+};
+struct Larger {
+    template <class T> __device__ __forceinline__ T operator()(T a, T b) const
+    {
+        return a > b ? a : b;
+    }
+};
+struct Smaller {
+    template <class T> __device__ __forceinline__ T operator()(T a, T b) const
+    {
+        return a < b ? a : b;
+    }
+};
+
+// Combines v over aligned groups of `parts` lanes, the result in every lane of the group.  A
+// step pairs each lane with one of the other half of its (twice as large) group; the halves
+// are uniform by then, so mirrors serve where no exchange of lanes at that distance exists.
+template <class T, class Op> __device__ __forceinline__ T group_join(T v, int parts, Op op)
+{
+    if (parts > 1)
+        v = op(v, dpp_from<0xB1, 0xf>(v, v));     // quad_perm 1 0 3 2
+    if (parts > 2)
+        v = op(v, dpp_from<0x4E, 0xf>(v, v));     // quad_perm 2 3 0 1
+    if (parts > 4)
+        v = op(v, dpp_from<0x141, 0xf>(v, v));    // row_half_mirror
+    if (parts > 8)
+        v = op(v, dpp_from<0x140, 0xf>(v, v));    // row_mirror
+    if (parts > 16)
+        v = op(v, __shfl_xor(v, 16, kWave));
+    if (parts > 32)
+        v = op(v, __shfl_xor(v, 32, kWave));
+    return v;
+}
+
+// Non-negative floats (or -0) order like their bits without the sign.
+__device__ __forceinline__ unsigned magnitude(float x)
+{
+    return __builtin_bit_cast(unsigned, x) & 0x7FFFFFFFu;
+}
+__device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned low)
+{
+    return (unsigned long long)high << 32 | low;
+}
+
+struct CoreShared {      // static LDS of the kernel
+    float2 sum[2][kCoreWaves];               // (err, tau) of a path, by wave; times as int bits
+    double wide[kCoreWaves];
+    unsigned long long key[2][kCoreWaves];
+    int2 change[2][kCoreWaves];              // of the wave's best exchange: error (bits), time
+    int count[kCoreWaves], times[kCoreWaves];
+    double least[kCoreWaves];
+};
+
+// One candidate (error source `src` seen from candidate k) under budget B.  Returns through
+// profile / cost; profile[0] = kTodo if the full table has to do it.
+__device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, const ErrSource src,
+                                           int L, int S, int B, const CoreParams &cp,
+                                           unsigned char *spill, unsigned char *lds,
+                                           CoreShared &sh, int16_t *__restrict__ profile,
+                                           float *__restrict__ cost)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    float2 *const table = reinterpret_cast<float2 *>(lds);           // [L][pitch] (err, tau)
+    CoreEntry *const list = reinterpret_cast<CoreEntry *>(lds + cp.table_bytes);
+    double *const limit = reinterpret_cast<double *>(list + cp.entries);   // [L], see below
+    CoreStep *const steps = reinterpret_cast<CoreStep *>(limit + ((L + 1) & ~1));  // [L]
+    float *const single = reinterpret_cast<float *>(steps + L);      // [L]
+    int *const row_at = reinterpret_cast<int *>(single + L);         // [L]
+
+    // ---- the tables, coalesced, twelve loads in flight
+    int bad = 0;
+    {
+        constexpr int kLoads = 12;
+        const int n = L * S;
+        const int step_l = cp.step_layers, step_s = kCoreThreads - step_l * S;
+        int l = tid / S, s = tid - l * S;
+        for (int i0 = tid; i0 < n; i0 += kLoads * kCoreThreads) {
+            float e[kLoads];
+            int t[kLoads], at[kLoads];
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) {
+                const int i = i0 + j * kCoreThreads;
+                const bool in = i < n;
+                at[j] = in ? l * cp.pitch + s : -1;
+                e[j] = src.err ? src.err[in ? i : 0]
+                               : __fmul_rn(src.c[in ? l : 0], src.w[in ? s : 0]);
+                t[j] = tau[in ? i : 0];
+                l += step_l;
+                s += step_s;
+                l += s >= S ? 1 : 0;
+                s -= s >= S ? S : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) {
+                if (at[j] >= 0) {
+                    bad |= !(e[j] >= 0.0f) || t[j] < 0;
+                    const bool out = t[j] > B || e[j] == __builtin_inff();
+                    table[at[j]] = out ? make_float2(__builtin_inff(), kCoreFar)
+                                       : make_float2(e[j], (float)t[j]);
+                }
+            }
+        }
+    }
+    if (__syncthreads_or(bad)) {
+        if (tid == 0)
+            profile[0] = kTodo;
+        return;
+    }
+
+    // Thread (layer, part) scans levels [s_begin, s_end) of its layer.
+    const int parts = cp.parts;
+    const int layer = tid >> cp.parts_log2, part = tid & (parts - 1);
+    const bool in_layer = layer < L;
+    const bool lead = in_layer && part == 0;
+    const int s_begin = in_layer ? min(S, part * cp.per_part) : 0;
+    const int s_end = in_layer ? min(S, s_begin + cp.per_part) : 0;
+    const float2 *const mine = table + (in_layer ? layer : 0) * cp.pitch;
+    int turn = 0;                                 // which half of the double-buffered words
+    // Error and time of the path on which this thread's layer has (e, t): sums over the layers.
+    // (fp32 is enough for the error: it only steers the choice of the multiplier.)
+    auto path_sum = [&](float e, float t, float &c, int &total) __attribute__((always_inline)) {
+        const float ce = from_lane(wave_scan(lead ? e : 0.0f, 0.0f, Add{}), kWave - 1);
+        const int ct = from_lane(wave_scan(lead ? (int)t : 0, 0, Add{}), kWave - 1);
+        if (lane == 0)
+            sh.sum[turn][wave] = make_float2(ce, __builtin_bit_cast(float, ct));
+        __syncthreads();
+        c = 0.0f;
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < kCoreWaves; ++w) {
+            c += sh.sum[turn][w].x;
+            total += __builtin_bit_cast(int, sh.sum[turn][w].y);
+        }
+        turn ^= 1;
+    };
+
+    // ---- the two ends of the multiplier's range: least error (lambda = 0), least time
+    float lo_e, lo_t, hi_e, hi_t;                 // (err, tau) of this layer on either path
+    float c_lo, c_hi;
+    int t_lo, t_hi;
+    {
+        unsigned long long by_err = ~0ull, by_time = ~0ull;
+        for (int s = s_begin; s < s_end; ++s) {
+            const float2 v = mine[s];
+            by_err = Smaller{}(by_err, pair_key(magnitude(v.x), magnitude(v.y)));
+            by_time = Smaller{}(by_time, pair_key(magnitude(v.y), magnitude(v.x)));
+        }
+        by_err = group_join(by_err, parts, Smaller{});
+        by_time = group_join(by_time, parts, Smaller{});
+        lo_e = __builtin_bit_cast(float, (unsigned)(by_err >> 32));
+        lo_t = __builtin_bit_cast(float, (unsigned)by_err);
+        hi_e = __builtin_bit_cast(float, (unsigned)by_time);
+        hi_t = __builtin_bit_cast(float, (unsigned)(by_time >> 32));
+        path_sum(hi_e, hi_t, c_hi, t_hi);
+        path_sum(lo_e, lo_t, c_lo, t_lo);
+    }
+    if (t_hi > B) {                               // also where a layer has no level to choose
+        if (tid < L)
+            profile[tid] = -1;
+        if (tid == 0)
+            *cost = __builtin_inff();
+        return;
+    }
+
+    // ---- the best multiplier: the chord between the two paths, until no path lies below it
+    float lambda_f = 0.0f;
+    const bool fits = t_lo <= B;                  // the least-error profile meets the budget
+    if (!fits) {
+        for (int trip = 0; trip < 40; ++trip) {
+            lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
+            float least = __builtin_inff();
+            int level = 0;
+            for (int s = s_begin; s < s_end; ++s) {
+                const float2 v = mine[s];
+                const float r = __builtin_fmaf(lambda_f, v.y, v.x);
+                level = r < least ? s : level;
+                least = r < least ? r : least;
+            }
+            level = (int)(unsigned)group_join(pair_key(magnitude(least), level), parts, Smaller{});
+            const float2 v = mine[level];
+            float c;
+            int t;
+            path_sum(v.x, v.y, c, t);
+            if (!(t > t_hi && t < t_lo))
+                break;
+            if (t <= B) {
+                c_hi = c;
+                t_hi = t;
+                hi_e = v.x;
+                hi_t = v.y;
+            } else {
+                c_lo = c;
+                t_lo = t;
+                lo_e = v.x;
+                lo_t = v.y;
+            }
+        }
+    }
+    const double lambda = lambda_f;
+
+    // ---- a profile that meets the budget: from either path by the best single exchanges
+    // mode 0: from the path below the budget, the level that saves most error and fits, as long as
+    // there is one; 1: from the path above it, the level that costs least and brings it below;
+    // 2: then as 0.
+    float inc_e = lo_e;
+    if (!fits) {
+        float cur_e = hi_e, cur_t = hi_t, c = c_hi, c_inc = __builtin_inff();
+        int room = B - t_hi, mode = 0;
+        for (int trip = 0; trip < 24; ++trip) {
+            const bool must = mode == 1;
+            const float top = cur_t + (float)room;
+            unsigned long long best = must ? ~0ull : pair_key(magnitude(cur_e), magnitude(cur_t));
+            for (int s = s_begin; s < s_end; ++s) {
+                const float2 v = mine[s];
+                const unsigned long long o = pair_key(magnitude(v.x), magnitude(v.y));
+                best = v.y <= top ? Smaller{}(best, o) : best;
+            }
+            best = group_join(best, parts, Smaller{});
+            const float e = __builtin_bit_cast(float, (unsigned)(best >> 32));
+            const float t = __builtin_bit_cast(float, (unsigned)best);
+            const float change = e - cur_e;
+            const unsigned bits = __builtin_bit_cast(unsigned, change);
+            const unsigned up = (bits >> 31) ? ~bits : (bits | 0x80000000u);   // orders as `change`
+            const bool valid = lead && (must ? e < __builtin_inff() : change < 0.0f);
+            const unsigned long long key = valid ? pair_key(~up, tid + 1) : 0ull;
+            const unsigned long long top_key =
+                from_lane(wave_scan(key, 0ull, Larger{}), kWave - 1);
+            if (top_key == 0 ? lane == 0 : key == top_key) {
+                sh.key[turn][wave] = top_key;
+                sh.change[turn][wave] = make_int2((int)bits, (int)t - (int)cur_t);
+            }
+            __syncthreads();
+            unsigned long long win = 0;
+            int2 d = make_int2(0, 0);
+#pragma unroll
+            for (int w = 0; w < kCoreWaves; ++w) {
+                const unsigned long long o = sh.key[turn][w];
+                const int2 od = sh.change[turn][w];
+                d.x = o > win ? od.x : d.x;
+                d.y = o > win ? od.y : d.y;
+                win = o > win ? o : win;
+            }
+            turn ^= 1;
+            if (win) {
+                if (layer == (int)((unsigned)win - 1u) >> cp.parts_log2) {
+                    cur_e = e;
+                    cur_t = t;
+                }
+                c += __builtin_bit_cast(float, d.x);
+                room -= d.y;
+                mode = must ? 2 : mode;
+            } else if (mode == 0) {
+                inc_e = cur_e;
+                c_inc = c;
+                cur_e = lo_e;
+                cur_t = lo_t;
+                c = c_lo;
+                room = B - t_lo;
+                mode = 1;
+            } else {
+                break;
+            }
+        }
+        if (mode != 1 && c < c_inc)               // (the last exchanges may have been cut short)
+            inc_e = cur_e;
+    }
+    if (lead)
+        single[layer] = inc_e;
+
+    // ---- the Lagrangian bound at lambda, in fp64
+    double least = __builtin_inf();               // min over the layer of err + lambda tau
+    for (int s = s_begin; s < s_end; ++s) {
+        const float2 v = mine[s];
+        least = Smaller{}(least, __builtin_fma(lambda, (double)v.y, (double)v.x));
+    }
+    least = group_join(least, parts, Smaller{});
+    const double run_least = wave_scan(lead ? least : 0.0, 0.0, Add{});
+    if (lane == kWave - 1)
+        sh.least[wave] = run_least;
+    __syncthreads();                              // (also publishes `single`)
+    double sum_least = 0.0, upto_least = run_least;
+#pragma unroll
+    for (int w = 0; w < kCoreWaves; ++w) {
+        const double o = sh.least[w];
+        upto_least += w < wave ? o : 0.0;
+        sum_least += o;
+    }
+    float upper = -0.0f;                          // U: the profile's cost, summed as Alg. 1 does
+    for (int base = 0; base < L; base += kWave) {
+        const float e = base + lane < L ? single[base + lane] : 0.0f;
+        const int n = min(kWave, L - base);
+        for (int i = 0; i < n; ++i)
+            upper += lane_value(e, i);
+    }
+    const double relaxed = sum_least - lambda * B;
+    const double hu = 0x1p-24 * (double)__builtin_bit_cast(
+                                    float, __builtin_bit_cast(unsigned, upper) & 0x7F800000u);
+    const double margin = 1e-11 * (sum_least + lambda * B + (double)upper);
+    const double slack = (double)upper + (L - 1) * hu - relaxed + margin;
+
+    // ---- survivors: count, place, write
+    const double keep_to = least + slack;
+    int count = 0, first_t = INT32_MAX, last_t = -1;
+    for (int s = s_begin; s < s_end; ++s) {
+        const float2 v = mine[s];
+        const bool keep = __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
+        count += keep ? 1 : 0;
+        first_t = keep ? min(first_t, (int)v.y) : first_t;
+        last_t = keep ? max(last_t, (int)v.y) : last_t;
+    }
+    const int of_layer = group_join(count, parts, Add{});
+    first_t = group_join(first_t, parts, Smaller{});
+    last_t = group_join(last_t, parts, Larger{});
+    // sums over the threads up to this one: entries, with the layers of more than one above bit 16;
+    // smallest times
+    const bool is_step = lead && of_layer > 1;
+    const int run = wave_scan(count + (is_step ? 1 << 16 : 0), 0, Add{});
+    const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
+    if (lane == kWave - 1) {
+        sh.count[wave] = run;
+        sh.times[wave] = run_t;
+    }
+    __syncthreads();                              // (every wave is through with `single`, too)
+    int before = run - count - (is_step ? 1 << 16 : 0), all = 0, upto_t = run_t, base_t = 0;
+#pragma unroll
+    for (int w = 0; w < kCoreWaves; ++w) {
+        const int o = sh.count[w], ot = sh.times[w];
+        before += w < wave ? o : 0;
+        upto_t += w < wave ? ot : 0;
+        all += o;
+        base_t += ot;
+    }
+    const int total = all & 0xFFFF, nsteps = all >> 16;
+    if (!(upper < 1e38f) || !(lambda_f < 1e30f) || total > cp.entries || base_t > B) {
+        if (tid == 0)                             // the same in every thread
+            profile[0] = kTodo;
+        return;
+    }
+    int place = before & 0xFFFF;
+    if (lead) {
+        // a partial profile of layers 0..l with fp32 cost D at time t can only be completed to a
+        // cost of at most U if D + lambda t <= U + (L - 1 - l) hu + lambda B - (least values above);
+        // times count from the sum of the smallest ones
+        limit[layer] = (double)upper + (L - 1 - layer) * hu + lambda * B -
+                       (sum_least - upto_least) + margin - lambda * upto_t;
+        if (is_step)
+            steps[before >> 16] = CoreStep{layer, place, of_layer, last_t - first_t};
+    }
+    for (int s = s_begin; s < s_end; ++s) {
+        const float2 v = mine[s];
+        if (__builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to) {
+            list[place++] = CoreEntry{v.x, (uint32_t)s << kCoreShiftBits |
+                                               (uint32_t)((int)v.y - first_t)};
+            if (of_layer == 1) {                  // this level it is
+                single[layer] = v.x;
+                profile[layer] = (int16_t)s;
+            }
+        }
+    }
+    __syncthreads();
+    if (wave != 0)
+        return;
+
+    // ---- Eq. 2 on what is left: one wave, two alternating rows over the staged tables' LDS
+    // A layer with one level left adds its error to every bucket and shifts nothing: the layers
+    // between two steps are added to the row of the step before them, in order.
+    float *const row0 = reinterpret_cast<float *>(lds), *const row1 = row0 + cp.window;
+    unsigned char *const rec = lds + 2 * cp.window * sizeof(float);
+    const int budget = B - base_t;                // buckets are counted from the smallest times
+    auto fence = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    int held_at = 0;                              // lane i holds `single` of layer held_at + i
+    float held = lane < L ? single[lane] : 0.0f;
+    auto add_singles = [&](float v, int from, int to) __attribute__((always_inline)) {
+        for (int l = from; l < to; ++l) {
+            if ((l & ~(kWave - 1)) != held_at) {
+                held_at = l & ~(kWave - 1);
+                held = held_at + lane < L ? single[held_at + lane] : 0.0f;
+            }
+            v += lane_value(held, l & (kWave - 1));
+        }
+        return v;
+    };
+    const CoreEntry none{__builtin_inff(), 0};
+    CoreStep next_step = steps[0];
+    CoreEntry next = nsteps && next_step.first + lane < total ? list[next_step.first + lane] : none;
+    float *prev = row0;
+    {
+        const float v = add_singles(-0.0f, 0, nsteps ? next_step.layer : L);
+        if (lane == 0)
+            prev[0] = v;
+    }
+    int a = 0, b = 0;                             // buckets of the previous row that still matter
+    int used = 0, spilled = 0, first_spilled = nsteps, work = 0;
+    fence();
+    for (int m = 0; m < nsteps; ++m) {
+        const int n = __builtin_amdgcn_readfirstlane(next_step.count);
+        const int first = __builtin_amdgcn_readfirstlane(next_step.first);
+        const int span = __builtin_amdgcn_readfirstlane(next_step.span);
+        const int layer_m = __builtin_amdgcn_readfirstlane(next_step.layer);
+        const CoreEntry held_entry = lane < n ? next : none;
+        int run_end = L;                          // the next step's layer
+        if (m + 1 < nsteps) {
+            next_step = steps[m + 1];
+            run_end = __builtin_amdgcn_readfirstlane(next_step.layer);
+            next = next_step.first + lane < total ? list[next_step.first + lane] : none;
+        }
+        const double lim = limit[run_end - 1];
+        const int top = min(b + span, budget);
+        const int width = top - a + 1;
+        const int chunks = (width + kWave - 1) / kWave;
+        work += n * chunks;
+        const bool spills = first_spilled < nsteps || used + width > cp.record;
+        if (width > cp.window || work > cp.work || (spills && spilled + width > cp.spill_bytes)) {
+            if (lane == 0)
+                profile[0] = kTodo;
+            return;
+        }
+        unsigned char *out = rec + used;
+        if (spills) {
+            first_spilled = min(first_spilled, m);
+            out = spill + spilled;
+        }
+        if (lane == 0)
+            row_at[m] = (spills ? spilled : used) - a;
+        spilled += spills ? width : 0;
+        used += spills ? 0 : width;
+        float *const cur = prev >= row1 ? row0 : row1;
+        const unsigned reach = (unsigned)(b - a);
+        int low = INT32_MAX, high = -1;           // live buckets of the new row, from a
+        for (int c = 0; c < chunks; ++c) {
+            const int x = c * kWave + lane;
+            float best = __builtin_inff();
+            int arg = 0;
+            for (int blk = 0; blk < n; blk += kWave) {
+                CoreEntry en = held_entry;
+                if (blk > 0)
+                    en = blk + lane < n ? list[first + blk + lane] : none;
+                const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
+                const int some = min(kWave, n - blk);
+                for (int i = 0; i < some; i += 2) {   // (an entry past the last: +inf)
+                    const int u0 = x - __builtin_amdgcn_readlane(shift, i);
+                    const int u1 = x - __builtin_amdgcn_readlane(shift, i + 1);
+                    const bool ok0 = (unsigned)u0 <= reach, ok1 = (unsigned)u1 <= reach;
+                    const float p0 = prev[ok0 ? u0 : 0] + lane_value(en.err, i);
+                    const float p1 = prev[ok1 ? u1 : 0] + lane_value(en.err, i + 1);
+                    const bool take0 = ok0 && p0 < best;
+                    best = take0 ? p0 : best;
+                    arg = take0 ? blk + i : arg;
+                    const bool take1 = ok1 && p1 < best;
+                    best = take1 ? p1 : best;
+                    arg = take1 ? blk + i + 1 : arg;
+                }
+            }
+            best = add_singles(best, layer_m + 1, run_end);
+            const bool in = x < width;
+            if (in) {
+                cur[x] = best;
+                out[x] = (unsigned char)arg;
+            }
+            const bool live = in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
+            const unsigned long long set = __ballot(live);
+            if (set) {
+                low = min(low, c * kWave + __builtin_ctzll(set));
+                high = c * kWave + 63 - __builtin_clzll(set);
+            }
+        }
+        if (high < 0) {                           // cannot happen: the known profile survives
+            if (lane == 0)
+                profile[0] = kTodo;
+            return;
+        }
+        fence();
+        b = a + high;
+        a = a + low;
+        prev = cur + low;
+    }
+
+    // ---- least cost, smallest time among equals, then the walk back
+    if (first_spilled < nsteps)
+        __threadfence();
+    unsigned long long key = ~0ull;
+    for (int x = lane; x <= b - a; x += kWave)
+        key = Smaller{}(key, pair_key(magnitude(prev[x]), x));
+    key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
+    int t = a + (int)(unsigned)key;
+    if (lane == 0)
+        *cost = prev[(unsigned)key];              // the sum over the profile in layer order
+    uint32_t next_word = 0;
+    CoreStep st{0, 0, 0, 0};
+    int at = 0;
+    if (nsteps) {
+        st = steps[nsteps - 1];
+        at = row_at[nsteps - 1];
+        next_word = st.first + lane < total ? list[st.first + lane].word : 0;
+    }
+    for (int m = nsteps - 1; m >= 0; --m) {
+        const uint32_t words = next_word;
+        const CoreStep now = st;
+        const int here = __builtin_amdgcn_readfirstlane(at) + t;
+        const int e = __builtin_amdgcn_readfirstlane(m >= first_spilled ? spill[here] : rec[here]);
+        if (m > 0) {
+            st = steps[m - 1];
+            at = row_at[m - 1];
+            next_word = list[min(st.first + lane, total - 1)].word;
+        }
+        const uint32_t word =
+            e < kWave ? (uint32_t)__builtin_amdgcn_readlane((int)words, e) : list[now.first + e].word;
+        if (lane == 0)
+            profile[now.layer] = (int16_t)(word >> kCoreShiftBits);
+        t -= __builtin_amdgcn_readfirstlane((int)(word & ((1u << kCoreShiftBits) - 1u)));
+    }
+}

@@ -121,7 +121,8 @@ enum MetaWord {
     kMetaWideWaves = 14, // waves of the wide in-place launch (0: not enqueued)
     kMetaWideGroup = 15, // most chunks one of its waves keeps in registers
     kMetaLdsWide = 16,   // its dynamic LDS bytes
-    kMetaGlobalWaves = 17 // waves of the global-row launch
+    kMetaGlobalWaves = 17, // waves of the global-row launch
+    kMetaTable = 18     // 1: the call leaves the whole table in the record (0: scratch)
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
@@ -459,23 +460,29 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
     }
 }
 
-__global__ __launch_bounds__(256) void dp_prepare(const int32_t *__restrict__ tau, int K,
-                                                  int slots, int L, int S,
-                                                  int s8, int B, int waves, int max_group,
-                                                  int lds_small, int lds_large, int lds_stage,
-                                                  int sorted, int split, int wide_waves,
-                                                  int wide_group, int lds_wide, int global_waves,
-                                                  int32_t *__restrict__ meta,
-                                                  int32_t *__restrict__ shifts,
-                                                  int32_t *__restrict__ order,
-                                                  int32_t *__restrict__ start,
-                                                  int32_t *__restrict__ entry_of)
+struct PrepareArgs {
+    int slots, s8, B, waves, max_group, lds_small, lds_large, lds_stage, sorted, split;
+    int wide_waves, wide_group, lds_wide, global_waves, table;
+    int32_t *meta, *shifts, *order, *start, *entry_of;
+};
+
+__device__ __forceinline__ void prepare(const int32_t *__restrict__ tau, int K, int L, int S,
+                                        const PrepareArgs &a, int block)
 {
-    if (blockIdx.x == 0)
-        prepare_budget(tau, K, slots, L, S, B, waves, max_group, lds_small, lds_large, lds_stage,
-                       split, wide_waves, wide_group, lds_wide, global_waves, meta);
+    if (block == 0 && threadIdx.x == 0)
+        a.meta[kMetaTable] = a.table;
+    if (block == 0)
+        prepare_budget(tau, K, a.slots, L, S, a.B, a.waves, a.max_group, a.lds_small, a.lds_large,
+                       a.lds_stage, a.split, a.wide_waves, a.wide_group, a.lds_wide,
+                       a.global_waves, a.meta);
     else
-        prepare_order(tau, blockIdx.x - 1, S, s8, sorted, shifts, order, start, entry_of);
+        prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of);
+}
+
+__global__ __launch_bounds__(256) void dp_prepare(const int32_t *__restrict__ tau, int K, int L,
+                                                  int S, PrepareArgs a)
+{
+    prepare(tau, K, L, S, a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -536,9 +543,10 @@ struct ErrSource {
 struct Resume {
     const int32_t *first_layer;   // [K] in [0, L], or nullptr: every candidate starts at layer 0
     const float *inc_rec;         // the incumbent's D record, float [L][pitch]
+    const int32_t *inc_meta;      // its header: without a whole table there is nothing to resume from
     __device__ __forceinline__ int start(int k, int L) const
     {
-        if (!first_layer)
+        if (!first_layer || !inc_meta[kMetaTable])
             return 0;
         const int f = first_layer[k];
         return f < 0 ? 0 : (f > L ? L : f);
@@ -702,6 +710,45 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
+
+#include "dp_core.h"
+
+// One workgroup per candidate (and budget); the first L + 1 workgroups do what dp_prepare does, for
+// the launches of the full table that follow and take the candidates this one gives up.
+__global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restrict__ tau,
+                                                        ErrSource src, int K, int L, int S,
+                                                        PrepareArgs prep, CoreParams cp,
+                                                        int16_t *__restrict__ profile,
+                                                        float *__restrict__ cost)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char core_lds[];
+    __shared__ CoreShared sh;
+    if ((int)blockIdx.x <= L) {
+        prepare(tau, K, L, S, prep, blockIdx.x);
+        return;
+    }
+    const int solve = (int)blockIdx.x - (L + 1);  // candidate k under budget j
+    const int j = solve / K, k = solve - j * K;
+    solve_core(tau, src.of_candidate(k, L, S), L, S, cp.budget[j], cp,
+               cp.spill + (size_t)solve * cp.spill_bytes, core_lds, sh, profile + (size_t)solve * L,
+               cost + solve);
+}
+
+// Whether the launches of the full table have to solve candidate k: every one, or (behind
+// dp_core) those it gave up under any of the `budgets` it tried.
+struct Todo {
+    const int16_t *profile = nullptr;   // [budgets][K][L]
+    int budgets = 0;
+    __device__ __forceinline__ bool has(int k, int K, int L) const
+    {
+        if (!profile)
+            return true;
+        bool any = false;
+        for (int j = 0; j < budgets; ++j)
+            any |= profile[((size_t)j * K + k) * L] == kTodo;
+        return any;
+    }
+};
 
 // The levels of one layer swept over one group of R chunks (R*64 consecutive reduced buckets
 // from t0); best[j] / arg[j] belong to bucket t0 + 64*j + lane.
@@ -1156,7 +1203,7 @@ void dp_fill(
     ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
     int S, int pitch, uint8_t *__restrict__ choice, float *__restrict__ drec,
     float *__restrict__ rows, int32_t *__restrict__ tstar, float *__restrict__ cost, Resume resume,
-    Blocks blocks)
+    Blocks blocks, Todo todo)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ float s_best[kMaxFillWaves];
@@ -1176,7 +1223,7 @@ void dp_fill(
     const int bp = meta[kMetaBudget];
     const int tid = threadIdx.x, nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
-        if (tid == 0 && !(kBlocks && blocks.pass == 1))
+        if (tid == 0 && !(kBlocks && blocks.pass == 1) && todo.has(blockIdx.x, K, L))
             write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
         return;
     }
@@ -1185,6 +1232,13 @@ void dp_fill(
     const int tw = meta[kMetaTeamWaves];
     if ((long long)blockIdx.x * teams >= K)
         return;                                  // the first ceil(K / teams) workgroups suffice
+    if (todo.profile) {
+        bool any = false;
+        for (int i = 0; i < teams && blockIdx.x * teams + i < (unsigned)K; ++i)
+            any |= todo.has(blockIdx.x * teams + i, K, L);
+        if (!any)
+            return;                              // solved already
+    }
     const int row = meta[kMetaRow];
     const int lane = tid & (kWave - 1);
     int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -1204,7 +1258,7 @@ void dp_fill(
     const bool mirrored = (tw & (tw - 1)) == 0 && ((wave >> 2) & 1);
     const int share = mirrored ? wv ^ (min(tw, 4) - 1) : wv;
     const int k = blockIdx.x * teams + team;
-    const bool active = team < teams && k < K;
+    const bool active = team < teams && k < K && todo.has(k, K, L);
 
     // rows: [apron | row] once (in place) or twice per team
     const int stride = kHalo + (kLds ? row : pitch);
@@ -1531,10 +1585,10 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
                                     const uint8_t *__restrict__ choice,
                                     const int32_t *__restrict__ tstar, int K, int L, int S,
                                     int pitch, int16_t *__restrict__ profile,
-                                    float *__restrict__ cost)
+                                    float *__restrict__ cost, Todo todo)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K)
+    if (k >= K || !todo.has(k, K, L))
         return;
     int16_t *prof = profile + (size_t)k * L;
     int t = tstar[k];
@@ -1615,11 +1669,12 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
     const float *__restrict__ drec,
     int32_t *__restrict__ tstar, int K, int L, int S, int pitch,
-    int16_t *__restrict__ profile, float *__restrict__ cost, Resume resume, Blocks blocks)
+    int16_t *__restrict__ profile, float *__restrict__ cost, Resume resume, Blocks blocks,
+    Todo todo)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
-    if (k >= K)
+    if (k >= K || !todo.has(k, K, L))
         return;
     int16_t *prof = profile + (size_t)k * L;
     const int lb = kBlocks ? blocks.begin : 0;   // layers [lb, le) are walked
@@ -1763,9 +1818,84 @@ int device_state(bool with_scratch, DeviceState *out)
     return SPDY_DP_OK;
 }
 
+// A call whose workspace is scratch: its candidates go through dp_core first.
+struct CoreCall {
+    int16_t *profile;                 // [budgets][K][L]
+    float *cost;                      // [budgets][K]
+    const int32_t *budget;            // host, [budgets]
+    int budgets;
+    unsigned char *spill;             // the record's memory
+    size_t spill_bytes;
+};
+
+// LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
+// The staged tables, L * S pairs, have to fit LDS.  Rows: the surviving window of a row was at
+// most 4 % of the budget over the timing tables of the benchmark's kind (typically 1 %); 1024
+// buckets cover that up to B = 16384 in less LDS than the staged tables of a network take, so
+// the number of candidates a compute unit holds is not reduced by them.
+constexpr int kCoreRecord = 8192;     // least LDS for the recorded entries (7 KB at the most seen)
+constexpr int kCoreWork = 4096;       // sweeps of 64 buckets; one wave takes some 20 ns for each
+bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
+{
+    if (L > kCoreMaxLayers || B > kCoreMaxBudget || S > 255)
+        return false;
+    int parts = 1;
+    while (2 * parts * L <= kCoreThreads && 2 * parts <= kWave && parts < S)
+        parts *= 2;
+    cp->parts = parts;
+    cp->parts_log2 = __builtin_ctz(parts);
+    cp->per_part = (S + parts - 1) / parts;
+    cp->step_layers = kCoreThreads / S;
+    cp->pitch = S | 1;
+    int window = B / 16 > 1024 ? B / 16 : 1024;
+    if (window > 8192)
+        window = 8192;
+    if (window > B + 1)
+        window = B + 1;
+    cp->window = (window + kWave - 1) / kWave * kWave;
+    cp->entries = L * S < kCoreEntries ? (L * S + 1) / 2 * 2 : kCoreEntries;
+    const size_t staged = (size_t)L * cp->pitch * sizeof(float2);
+    const size_t rows = 2 * sizeof(float) * (size_t)cp->window + kCoreRecord;
+    const size_t table = align_up(staged > rows ? staged : rows, 16);
+    const size_t need = table + cp->entries * sizeof(CoreEntry) + (size_t)(L + 1) * sizeof(double) +
+                        (size_t)L * (sizeof(CoreStep) + sizeof(float) + sizeof(int));
+    if (need > (size_t)kLdsBytes)
+        return false;
+    cp->table_bytes = (int)table;
+    cp->record = (int)(table - 2 * sizeof(float) * (size_t)cp->window);
+    cp->work = kCoreWork;
+    *lds = (int)need;
+    return true;
+}
+
+int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const PrepareArgs &prep,
+                const CoreCall &call, hipStream_t q)
+{
+    CoreParams cp{};
+    int lds = 0;
+    if (!core_params(L, S, prep.B, &cp, &lds))
+        return SPDY_DP_ERR_LAUNCH;               // callers ask first
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_core),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
+        return SPDY_DP_ERR_LAUNCH;
+    for (int j0 = 0; j0 < call.budgets; j0 += kCoreBudgets) {
+        cp.budgets = call.budgets - j0 < kCoreBudgets ? call.budgets - j0 : kCoreBudgets;
+        for (int j = 0; j < cp.budgets; ++j)
+            cp.budget[j] = call.budget[j0 + j];
+        cp.spill = call.spill;
+        const size_t each = call.spill_bytes / ((size_t)K * cp.budgets) / 16 * 16;
+        cp.spill_bytes = each < (size_t)INT32_MAX ? (long long)each : INT32_MAX;
+        hipLaunchKernelGGL(dp_core, dim3(L + 1 + K * cp.budgets), dim3(kCoreThreads), lds, q, tau,
+                           src, K, L, S, prep, cp, call.profile + (size_t)j0 * K * L,
+                           call.cost + (size_t)j0 * K);
+    }
+    return launch_status();
+}
+
 template <bool kLevel, bool kNarrow, bool kBlocks = false>
 int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
-                int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks = Blocks{})
+                int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks = Blocks{},
+                const CoreCall *core = nullptr)
 {
     int32_t *meta = reinterpret_cast<int32_t *>(ws + lay.meta_off);
     int32_t *shifts = reinterpret_cast<int32_t *>(ws + lay.shifts_off);
@@ -1866,24 +1996,33 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
 
-    if (!(kBlocks && blocks.pass == 1))          // the block passes reuse pass 0's tables
-        hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, 2 * units, L, S, s8,
-                           B, waves, max_group, lds_small, lds_large, lds_stage,
+    const PrepareArgs prep{2 * units, s8, B, waves, max_group, lds_small, lds_large, lds_stage,
                            kLevel ? 0 : (kNarrow ? 2 : 1), split ? 1 : 0, wide_waves, wide_group,
-                           lds_wide, global_waves, meta, shifts, order, start, entry);
+                           lds_wide, global_waves, core ? 0 : 1, meta, shifts, order, start, entry};
+    Todo todo;
+    if (core) {
+        todo = Todo{core->profile, core->budgets};
+        if (!(kBlocks && blocks.pass == 1)) {
+            const int st = launch_core(tau, src, K, L, S, prep, *core, q);
+            if (st != SPDY_DP_OK)
+                return st;
+        }
+    } else if (!(kBlocks && blocks.pass == 1)) { // the block passes reuse pass 0's tables
+        hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
+    }
     const LevelTables tables{shifts, order, start, entry, s8};
     hipLaunchKernelGGL(in_place, dim3(K), dim3(place_threads), place_lds, q, src, meta, tables,
-                       units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks);
+                       units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
     if (wide)
         hipLaunchKernelGGL(wide_place, dim3(K), dim3(wide_waves * kWave), lds_wide, q, src, meta,
                            tables, units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume,
-                           blocks);
+                           blocks, todo);
     if (lds_large)
         hipLaunchKernelGGL(two_rows, dim3(K), dim3(waves * kWave), lds_large, q, src, meta, tables,
-                           units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks);
+                           units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
     if (in_memory)
         hipLaunchKernelGGL(in_global, dim3(K), dim3(global_waves * kWave), lds_stage, q, src, meta, tables,
-                           units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks);
+                           units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
     return launch_status();
 }
 
@@ -1897,7 +2036,8 @@ int validate(const Layout &lay, const void *workspace)
 }
 
 int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, float *cost,
-              void *workspace, size_t workspace_bytes, void *stream, Resume resume = Resume{})
+              void *workspace, size_t workspace_bytes, void *stream, Resume resume = Resume{},
+              const CoreCall *core = nullptr)
 {
     if (!tau || !cost)
         return SPDY_DP_ERR_NULL;
@@ -1910,16 +2050,20 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
     (void)hipGetLastError();
     if (S <= kWave)
         return lay.variant == kLevelRecord
-                   ? launch_fill<true, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q)
-                   : launch_fill<false, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q);
+                   ? launch_fill<true, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
+                                             Blocks{}, core)
+                   : launch_fill<false, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
+                                             Blocks{}, core);
     return lay.variant == kLevelRecord
-               ? launch_fill<true, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q)
-               : launch_fill<false, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q);
+               ? launch_fill<true, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
+                                             Blocks{}, core)
+               : launch_fill<false, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
+                                             Blocks{}, core);
 }
 
 int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B,
                    int16_t *profile, float *cost, const void *workspace, size_t workspace_bytes,
-                   void *stream, Resume resume = Resume{})
+                   void *stream, Resume resume = Resume{}, Todo todo = Todo{})
 {
     if (!tau || !profile || !cost)
         return SPDY_DP_ERR_NULL;
@@ -1935,7 +2079,7 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     if (lay.variant == kLevelRecord) {
         hipLaunchKernelGGL(dp_backtrace_levels, dim3((K + kWave - 1) / kWave), dim3(kWave), 0, q,
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
-                           tstar, K, L, S, (int)lay.row, profile, cost);
+                           tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
         const int per_block = kWalkThreads / kWave;
         auto narrow = dp_backtrace_values<1, false>;
@@ -1943,20 +2087,36 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
         hipLaunchKernelGGL(S <= kWave ? narrow : wide, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q, tau,
                            src, meta, reinterpret_cast<const float *>(ws + lay.record_off),
                            const_cast<int32_t *>(tstar), K, L, S, (int)lay.row, profile, cost,
-                           resume, Blocks{});
+                           resume, Blocks{}, todo);
     }
     return launch_status();
 }
 
+// `scratch`: nobody looks at the workspace afterwards, so the table need not be in it.
 int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int16_t *profile,
-               float *cost, void *workspace, size_t workspace_bytes, void *stream)
+               float *cost, void *workspace, size_t workspace_bytes, void *stream, bool scratch,
+               Resume resume = Resume{})
 {
     if (!tau || !profile || !cost)
         return SPDY_DP_ERR_NULL;
-    const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream);
+    CoreParams cp{};
+    int lds = 0;
+    CoreCall core{profile, cost, &B, 1, nullptr, 0};
+    Todo todo;
+    if (scratch && L > 0 && S > 0 && core_params(L, S, B, &cp, &lds)) {
+        const Layout lay = make_layout(K, L, S, B, workspace_bytes);
+        if (lay.status == SPDY_DP_OK && workspace) {
+            core.spill = static_cast<unsigned char *>(workspace) + lay.record_off;
+            core.spill_bytes = workspace_bytes - lay.record_off;
+            todo = Todo{profile, 1};
+        }
+    }
+    const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
+                             todo.profile ? &core : nullptr);
     if (st != SPDY_DP_OK)
         return st;
-    return backtrace_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream);
+    return backtrace_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream,
+                          resume, todo);
 }
 
 // The stride of the solve with checkpoints: the caller's, or about sqrt(L), which makes the
@@ -2025,7 +2185,7 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
         auto wide = dp_backtrace_values<4, true>;
         hipLaunchKernelGGL(S <= kWave ? narrow : wide, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q, tau,
                            src, meta, nullptr, tstar, K, L, S, (int)lay.row, profile, cost,
-                           Resume{}, blocks);
+                           Resume{}, blocks, Todo{});
         st = launch_status();
         if (st != SPDY_DP_OK)
             return st;
@@ -2097,11 +2257,10 @@ int resume_impl(const int32_t *tau, ErrSource src, const int32_t *first_layer, i
     resume.first_layer = first_layer;
     resume.inc_rec =
         reinterpret_cast<const float *>(static_cast<const char *>(incumbent) + inc.record_off);
-    st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume);
-    if (st != SPDY_DP_OK)
-        return st;
-    return backtrace_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream,
-                          resume);
+    resume.inc_meta =
+        reinterpret_cast<const int32_t *>(static_cast<const char *>(incumbent) + inc.meta_off);
+    return solve_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream, true,
+                      resume);
 }
 
 }  // namespace
@@ -2164,7 +2323,17 @@ int spdy_dp_solve_batched(const int32_t *tau, const float *err, int K, int L, in
     if (!err)
         return SPDY_DP_ERR_NULL;
     return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost, workspace,
-                      workspace_bytes, stream);
+                      workspace_bytes, stream, false);
+}
+
+int spdy_dp_solve_profiles(const int32_t *tau, const float *err, int K, int L, int S, int B,
+                           int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
+                           void *stream)
+{
+    if (!err)
+        return SPDY_DP_ERR_NULL;
+    return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost, workspace,
+                      workspace_bytes, stream, true);
 }
 
 int spdy_dp_solve_batched_static(const int32_t *tau, const float *err, int K, int L, int S, int B,
@@ -2183,7 +2352,7 @@ int spdy_dp_solve_batched_static(const int32_t *tau, const float *err, int K, in
     if (st != SPDY_DP_OK)
         return st;
     return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost,
-                      dev.scratch, SPDY_DP_STATIC_WORKSPACE_BYTES, stream);
+                      dev.scratch, SPDY_DP_STATIC_WORKSPACE_BYTES, stream, true);
 }
 
 int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float *w, int K, int L,
@@ -2193,7 +2362,7 @@ int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float 
     if (!c || !w)
         return SPDY_DP_ERR_NULL;
     return solve_impl(tau, ErrSource{nullptr, c, w}, K, L, S, B, profile, cost, workspace,
-                      workspace_bytes, stream);
+                      workspace_bytes, stream, true);
 }
 
 int spdy_dp_solve_budgets(const int32_t *tau, const float *err, int K, int L, int S,
