@@ -34,6 +34,8 @@ constexpr int kCoreWaves = kCoreThreads / kWave;
 constexpr int kCoreMaxLayers = kCoreThreads;
 constexpr int kCoreMaxBudget = 1 << 22;  // times stay exact in fp32, a level and a shift in 32 bits
 constexpr int kCoreEntries = 1024;       // surviving levels of a candidate
+constexpr int kCoreExtra = 32;           // levels beyond one per layer that are not worth halving
+constexpr int kCoreTrips = 6;            // attempts, counting a halving before the first
 constexpr int kCoreBudgets = 64;         // budgets per launch
 constexpr float kCoreFar = 16777216.0f;  // "time" of a level that may not be chosen
 constexpr int kCoreShiftBits = 22;
@@ -152,10 +154,10 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
 
 struct CoreShared {      // static LDS of the kernel
     float2 sum[2][kCoreWaves];               // (err, tau) of a path, by wave; times as int bits
-    double wide[kCoreWaves];
     unsigned long long key[2][kCoreWaves];
     int2 change[2][kCoreWaves];              // of the wave's best exchange: error (bits), time
-    int count[kCoreWaves], times[kCoreWaves];
+    int2 place[2][kCoreWaves];               // sums of the entries (and steps), of the times
+    int2 live[2][kCoreWaves];                // first and last bucket of a row that matters
     double least[kCoreWaves];
 };
 
@@ -177,8 +179,8 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     int *const row_at = reinterpret_cast<int *>(single + L);         // [L]
 
     // ---- the tables, coalesced, twelve loads in flight
-    int bad = 0;
-    {
+    auto stage = [&]() __attribute__((always_inline)) {
+        int bad = 0;
         constexpr int kLoads = 12;
         const int n = L * S;
         const int step_l = cp.step_layers, step_s = kCoreThreads - step_l * S;
@@ -209,8 +211,9 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 }
             }
         }
-    }
-    if (__syncthreads_or(bad)) {
+        return bad;
+    };
+    if (__syncthreads_or(stage())) {
         if (tid == 0)
             profile[0] = kTodo;
         return;
@@ -221,9 +224,28 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     const int layer = tid >> cp.parts_log2, part = tid & (parts - 1);
     const bool in_layer = layer < L;
     const bool lead = in_layer && part == 0;
-    const int s_begin = in_layer ? min(S, part * cp.per_part) : 0;
+    const int s_begin = in_layer ? part * cp.per_part : 0;
     const int s_end = in_layer ? min(S, s_begin + cp.per_part) : 0;
     const float2 *const mine = table + (in_layer ? layer : 0) * cp.pitch;
+    // f(err and tau, level) for this thread's levels, four at a time and the next four already on
+    // their way.  Where the range ends early the layer's last level is seen again.
+    auto scan = [&](auto f) __attribute__((always_inline)) {
+        float2 v[4], next_v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            next_v[q] = mine[min(s_begin + q, S - 1)];
+        for (int i = 0; i < cp.per_part; i += 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                v[q] = next_v[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                next_v[q] = mine[min(s_begin + i + 4 + q, S - 1)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                f(v[q], s_begin + i + q);
+        }
+    };
     int turn = 0;                                 // which half of the double-buffered words
     // Error and time of the path on which this thread's layer has (e, t): sums over the layers.
     // (fp32 is enough for the error: it only steers the choice of the multiplier.)
@@ -249,11 +271,10 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     int t_lo, t_hi;
     {
         unsigned long long by_err = ~0ull, by_time = ~0ull;
-        for (int s = s_begin; s < s_end; ++s) {
-            const float2 v = mine[s];
+        scan([&](float2 v, int) {
             by_err = Smaller{}(by_err, pair_key(magnitude(v.x), magnitude(v.y)));
             by_time = Smaller{}(by_time, pair_key(magnitude(v.y), magnitude(v.x)));
-        }
+        });
         by_err = group_join(by_err, parts, Smaller{});
         by_time = group_join(by_time, parts, Smaller{});
         lo_e = __builtin_bit_cast(float, (unsigned)(by_err >> 32));
@@ -279,14 +300,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
             float least = __builtin_inff();
             int level = 0;
-            for (int s = s_begin; s < s_end; ++s) {
-                const float2 v = mine[s];
+            scan([&](float2 v, int s) {
                 const float r = __builtin_fmaf(lambda_f, v.y, v.x);
                 level = r < least ? s : level;
                 least = r < least ? r : least;
-            }
+            });
             level = (int)(unsigned)group_join(pair_key(magnitude(least), level), parts, Smaller{});
-            const float2 v = mine[level];
+            const float2 v = mine[min(level, S - 1)];
             float c;
             int t;
             path_sum(v.x, v.y, c, t);
@@ -319,11 +339,10 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             const bool must = mode == 1;
             const float top = cur_t + (float)room;
             unsigned long long best = must ? ~0ull : pair_key(magnitude(cur_e), magnitude(cur_t));
-            for (int s = s_begin; s < s_end; ++s) {
-                const float2 v = mine[s];
+            scan([&](float2 v, int) {
                 const unsigned long long o = pair_key(magnitude(v.x), magnitude(v.y));
                 best = v.y <= top ? Smaller{}(best, o) : best;
-            }
+            });
             best = group_join(best, parts, Smaller{});
             const float e = __builtin_bit_cast(float, (unsigned)(best >> 32));
             const float t = __builtin_bit_cast(float, (unsigned)best);
@@ -378,10 +397,9 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
 
     // ---- the Lagrangian bound at lambda, in fp64
     double least = __builtin_inf();               // min over the layer of err + lambda tau
-    for (int s = s_begin; s < s_end; ++s) {
-        const float2 v = mine[s];
+    scan([&](float2 v, int) {
         least = Smaller{}(least, __builtin_fma(lambda, (double)v.y, (double)v.x));
-    }
+    });
     least = group_join(least, parts, Smaller{});
     const double run_least = wave_scan(lead ? least : 0.0, 0.0, Add{});
     if (lane == kWave - 1)
@@ -405,220 +423,271 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     const double hu = 0x1p-24 * (double)__builtin_bit_cast(
                                     float, __builtin_bit_cast(unsigned, upper) & 0x7F800000u);
     const double margin = 1e-11 * (sum_least + lambda * B + (double)upper);
-    const double slack = (double)upper + (L - 1) * hu - relaxed + margin;
 
     // ---- survivors: count, place, write
-    const double keep_to = least + slack;
-    int count = 0, first_t = INT32_MAX, last_t = -1;
-    for (int s = s_begin; s < s_end; ++s) {
-        const float2 v = mine[s];
-        const bool keep = __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
-        count += keep ? 1 : 0;
-        first_t = keep ? min(first_t, (int)v.y) : first_t;
-        last_t = keep ? max(last_t, (int)v.y) : last_t;
-    }
-    const int of_layer = group_join(count, parts, Add{});
-    first_t = group_join(first_t, parts, Smaller{});
-    last_t = group_join(last_t, parts, Larger{});
-    // sums over the threads up to this one: entries, with the layers of more than one above bit 16;
-    // smallest times
-    const bool is_step = lead && of_layer > 1;
-    const int run = wave_scan(count + (is_step ? 1 << 16 : 0), 0, Add{});
-    const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
-    if (lane == kWave - 1) {
-        sh.count[wave] = run;
-        sh.times[wave] = run_t;
-    }
-    __syncthreads();                              // (every wave is through with `single`, too)
-    int before = run - count - (is_step ? 1 << 16 : 0), all = 0, upto_t = run_t, base_t = 0;
+    // `target`: the cost a profile must not exceed to be looked for.  U is safe, but often far above
+    // the least cost; where it leaves many levels, half the way from the bound to it is tried first,
+    // and is as good as U if a profile of at most that cost turns up (it usually does, and the
+    // rows are half as wide); if not, U comes next, or the cost that did turn up.  What exceeds the
+    // limits of the launch is halved, too.
+    double target = (double)upper, beyond = __builtin_inf();   // (beyond: exceeded the limits)
+    bool first_try = true;
+    auto halved = [&](double x) { return relaxed + 0.5 * (x - relaxed); };
+    for (int trip = 0; trip < kCoreTrips; ++trip) {
+        const double keep_to = least + (target + (L - 1) * hu - relaxed + margin);
+        int count = 0, first_t = INT32_MAX, last_t = -1;
+        scan([&](float2 v, int s) {
+            const bool keep =
+                s < s_end && __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
+            count += keep ? 1 : 0;
+            first_t = keep ? min(first_t, (int)v.y) : first_t;
+            last_t = keep ? max(last_t, (int)v.y) : last_t;
+        });
+        const int of_layer = group_join(count, parts, Add{});
+        first_t = group_join(first_t, parts, Smaller{});
+        last_t = group_join(last_t, parts, Larger{});
+        // sums over the threads up to this one: entries, with the layers of more than one above bit
+        // 16; smallest times
+        const bool is_step = lead && of_layer > 1;
+        const int run = wave_scan(count + (is_step ? 1 << 16 : 0), 0, Add{});
+        const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
+        if (lane == kWave - 1)
+            sh.place[turn][wave] = make_int2(run, run_t);
+        __syncthreads();                          // (every wave is through with `single`, too)
+        int before = run - count - (is_step ? 1 << 16 : 0), all = 0, upto_t = run_t, base_t = 0;
 #pragma unroll
-    for (int w = 0; w < kCoreWaves; ++w) {
-        const int o = sh.count[w], ot = sh.times[w];
-        before += w < wave ? o : 0;
-        upto_t += w < wave ? ot : 0;
-        all += o;
-        base_t += ot;
-    }
-    const int total = all & 0xFFFF, nsteps = all >> 16;
-    if (!(upper < 1e38f) || !(lambda_f < 1e30f) || total > cp.entries || base_t > B) {
-        if (tid == 0)                             // the same in every thread
-            profile[0] = kTodo;
-        return;
-    }
-    int place = before & 0xFFFF;
-    if (lead) {
-        // a partial profile of layers 0..l with fp32 cost D at time t can only be completed to a
-        // cost of at most U if D + lambda t <= U + (L - 1 - l) hu + lambda B - (least values above);
-        // times count from the sum of the smallest ones
-        limit[layer] = (double)upper + (L - 1 - layer) * hu + lambda * B -
-                       (sum_least - upto_least) + margin - lambda * upto_t;
-        if (is_step)
-            steps[before >> 16] = CoreStep{layer, place, of_layer, last_t - first_t};
-    }
-    for (int s = s_begin; s < s_end; ++s) {
-        const float2 v = mine[s];
-        if (__builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to) {
-            list[place++] = CoreEntry{v.x, (uint32_t)s << kCoreShiftBits |
-                                               (uint32_t)((int)v.y - first_t)};
-            if (of_layer == 1) {                  // this level it is
-                single[layer] = v.x;
-                profile[layer] = (int16_t)s;
-            }
+        for (int w = 0; w < kCoreWaves; ++w) {
+            const int2 o = sh.place[turn][w];
+            before += w < wave ? o.x : 0;
+            upto_t += w < wave ? o.y : 0;
+            all += o.x;
+            base_t += o.y;
         }
-    }
-    __syncthreads();
-    if (wave != 0)
-        return;
+        turn ^= 1;
+        const int total = all & 0xFFFF, nsteps = all >> 16;
+        if (first_try && total - L > kCoreExtra && upper < 1e38f) {
+            first_try = false;
+            target = halved(target);
+            continue;
+        }
+        first_try = false;
+        if (!(upper < 1e38f) || !(lambda_f < 1e30f))
+            break;
+        bool wide = total > cp.entries;           // exceeds the limits
+        bool failed = wide || base_t > B;
+        int place = before & 0xFFFF;
+        if (!failed) {
+            if (lead) {
+                // a partial profile of layers 0..l with fp32 cost D at time t can only be completed
+                // to a cost of at most `target` if D + lambda t <= target + (L - 1 - l) hu +
+                // lambda B - (least values above); times count from the sum of the smallest ones
+                limit[layer] = target + (L - 1 - layer) * hu + lambda * B -
+                               (sum_least - upto_least) + margin - lambda * upto_t;
+                if (is_step)
+                    steps[before >> 16] = CoreStep{layer, place, of_layer, last_t - first_t};
+            }
+            scan([&](float2 v, int s) {
+                if (s < s_end && __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to) {
+                    list[place++] = CoreEntry{v.x, (uint32_t)s << kCoreShiftBits |
+                                                       (uint32_t)((int)v.y - first_t)};
+                    if (of_layer == 1) {          // this level it is
+                        single[layer] = v.x;
+                        profile[layer] = (int16_t)s;
+                    }
+                }
+            });
+        }
+        __syncthreads();
 
-    // ---- Eq. 2 on what is left: one wave, two alternating rows over the staged tables' LDS
-    // A layer with one level left adds its error to every bucket and shifts nothing: the layers
-    // between two steps are added to the row of the step before them, in order.
-    float *const row0 = reinterpret_cast<float *>(lds), *const row1 = row0 + cp.window;
-    unsigned char *const rec = lds + 2 * cp.window * sizeof(float);
-    const int budget = B - base_t;                // buckets are counted from the smallest times
-    auto fence = []() __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
-    int held_at = 0;                              // lane i holds `single` of layer held_at + i
-    float held = lane < L ? single[lane] : 0.0f;
-    auto add_singles = [&](float v, int from, int to) __attribute__((always_inline)) {
-        for (int l = from; l < to; ++l) {
-            if ((l & ~(kWave - 1)) != held_at) {
-                held_at = l & ~(kWave - 1);
-                held = held_at + lane < L ? single[held_at + lane] : 0.0f;
+        // ---- Eq. 2 on what is left: two alternating rows over the staged tables' LDS
+        // A layer with one level left adds its error to every bucket and shifts nothing: the layers
+        // between two steps are added to the row of the step before them, in order.  A step's
+        // chunks of 64 buckets are divided among the waves; every wave keeps the same books.
+        float *const row0 = reinterpret_cast<float *>(lds), *const row1 = row0 + cp.window;
+        unsigned char *const rec = lds + 2 * cp.window * sizeof(float);
+        const int budget = B - base_t;            // buckets are counted from the smallest times
+        int held_at = 0;                          // lane i holds `single` of layer held_at + i
+        float held = lane < L ? single[lane] : 0.0f;
+        auto add_singles = [&](float v, int from, int to) __attribute__((always_inline)) {
+            for (int l = from; l < to; ++l) {
+                if ((l & ~(kWave - 1)) != held_at) {
+                    held_at = l & ~(kWave - 1);
+                    held = held_at + lane < L ? single[held_at + lane] : 0.0f;
+                }
+                v += lane_value(held, l & (kWave - 1));
             }
-            v += lane_value(held, l & (kWave - 1));
-        }
-        return v;
-    };
-    const CoreEntry none{__builtin_inff(), 0};
-    CoreStep next_step = steps[0];
-    CoreEntry next = nsteps && next_step.first + lane < total ? list[next_step.first + lane] : none;
-    float *prev = row0;
-    {
-        const float v = add_singles(-0.0f, 0, nsteps ? next_step.layer : L);
-        if (lane == 0)
-            prev[0] = v;
-    }
-    int a = 0, b = 0;                             // buckets of the previous row that still matter
-    int used = 0, spilled = 0, first_spilled = nsteps, work = 0;
-    fence();
-    for (int m = 0; m < nsteps; ++m) {
-        const int n = __builtin_amdgcn_readfirstlane(next_step.count);
-        const int first = __builtin_amdgcn_readfirstlane(next_step.first);
-        const int span = __builtin_amdgcn_readfirstlane(next_step.span);
-        const int layer_m = __builtin_amdgcn_readfirstlane(next_step.layer);
-        const CoreEntry held_entry = lane < n ? next : none;
-        int run_end = L;                          // the next step's layer
-        if (m + 1 < nsteps) {
-            next_step = steps[m + 1];
-            run_end = __builtin_amdgcn_readfirstlane(next_step.layer);
+            return v;
+        };
+        const CoreEntry none{__builtin_inff(), 0};
+        CoreStep next_step{L, 0, 0, 0};
+        CoreEntry next = none;
+        if (nsteps && !failed) {
+            next_step = steps[0];
             next = next_step.first + lane < total ? list[next_step.first + lane] : none;
         }
-        const double lim = limit[run_end - 1];
-        const int top = min(b + span, budget);
-        const int width = top - a + 1;
-        const int chunks = (width + kWave - 1) / kWave;
-        work += n * chunks;
-        const bool spills = first_spilled < nsteps || used + width > cp.record;
-        if (width > cp.window || work > cp.work || (spills && spilled + width > cp.spill_bytes)) {
-            if (lane == 0)
-                profile[0] = kTodo;
-            return;
+        float *prev = row0;
+        if (!failed) {
+            const float v = add_singles(-0.0f, 0, __builtin_amdgcn_readfirstlane(next_step.layer));
+            if (tid == 0)
+                prev[0] = v;
         }
-        unsigned char *out = rec + used;
-        if (spills) {
-            first_spilled = min(first_spilled, m);
-            out = spill + spilled;
-        }
-        if (lane == 0)
-            row_at[m] = (spills ? spilled : used) - a;
-        spilled += spills ? width : 0;
-        used += spills ? 0 : width;
-        float *const cur = prev >= row1 ? row0 : row1;
-        const unsigned reach = (unsigned)(b - a);
-        int low = INT32_MAX, high = -1;           // live buckets of the new row, from a
-        for (int c = 0; c < chunks; ++c) {
-            const int x = c * kWave + lane;
-            float best = __builtin_inff();
-            int arg = 0;
-            for (int blk = 0; blk < n; blk += kWave) {
-                CoreEntry en = held_entry;
-                if (blk > 0)
-                    en = blk + lane < n ? list[first + blk + lane] : none;
-                const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
-                const int some = min(kWave, n - blk);
-                for (int i = 0; i < some; i += 2) {   // (an entry past the last: +inf)
-                    const int u0 = x - __builtin_amdgcn_readlane(shift, i);
-                    const int u1 = x - __builtin_amdgcn_readlane(shift, i + 1);
-                    const bool ok0 = (unsigned)u0 <= reach, ok1 = (unsigned)u1 <= reach;
-                    const float p0 = prev[ok0 ? u0 : 0] + lane_value(en.err, i);
-                    const float p1 = prev[ok1 ? u1 : 0] + lane_value(en.err, i + 1);
-                    const bool take0 = ok0 && p0 < best;
-                    best = take0 ? p0 : best;
-                    arg = take0 ? blk + i : arg;
-                    const bool take1 = ok1 && p1 < best;
-                    best = take1 ? p1 : best;
-                    arg = take1 ? blk + i + 1 : arg;
+        int a = 0, b = 0;                         // buckets of the previous row that still matter
+        int used = 0, spilled = 0, first_spilled = nsteps, work = 0;
+        __syncthreads();
+        for (int m = 0; m < nsteps && !failed; ++m) {
+            const int n = __builtin_amdgcn_readfirstlane(next_step.count);
+            const int first = __builtin_amdgcn_readfirstlane(next_step.first);
+            const int span = __builtin_amdgcn_readfirstlane(next_step.span);
+            const int layer_m = __builtin_amdgcn_readfirstlane(next_step.layer);
+            const CoreEntry held_entry = lane < n ? next : none;
+            int run_end = L;                      // the next step's layer
+            if (m + 1 < nsteps) {
+                next_step = steps[m + 1];
+                run_end = __builtin_amdgcn_readfirstlane(next_step.layer);
+                next = next_step.first + lane < total ? list[next_step.first + lane] : none;
+            }
+            const double lim = limit[run_end - 1];
+            const int top = min(b + span, budget);
+            const int width = top - a + 1;
+            const int chunks = (width + kWave - 1) / kWave;
+            work += n * chunks;
+            const bool spills = first_spilled < nsteps || used + width > cp.record;
+            if (width > cp.window || work > cp.work ||
+                (spills && spilled + width > cp.spill_bytes)) {
+                failed = wide = true;
+                break;
+            }
+            unsigned char *out = rec + used;
+            if (spills) {
+                first_spilled = min(first_spilled, m);
+                out = spill + spilled;
+            }
+            if (tid == 0)
+                row_at[m] = (spills ? spilled : used) - a;
+            spilled += spills ? width : 0;
+            used += spills ? 0 : width;
+            float *const cur = prev >= row1 ? row0 : row1;
+            const unsigned reach = (unsigned)(b - a);
+            int low = INT32_MAX, high = -1;       // live buckets of the new row, from a
+            for (int c = wave; c < chunks; c += kCoreWaves) {
+                const int x = c * kWave + lane;
+                float best = __builtin_inff();
+                int arg = 0;
+                for (int blk = 0; blk < n; blk += kWave) {
+                    CoreEntry en = held_entry;
+                    if (blk > 0)
+                        en = blk + lane < n ? list[first + blk + lane] : none;
+                    const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
+                    const int some = min(kWave, n - blk);
+                    for (int i = 0; i < some; i += 4) {   // (entries past the last: +inf)
+                        float p[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int u = x - __builtin_amdgcn_readlane(shift, i + q);
+                            const bool ok = (unsigned)u <= reach;
+                            const float d = prev[ok ? u : 0];
+                            p[q] = (ok ? d : __builtin_inff()) + lane_value(en.err, i + q);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const bool take = p[q] < best;
+                            best = take ? p[q] : best;
+                            arg = take ? blk + i + q : arg;
+                        }
+                    }
+                }
+                best = add_singles(best, layer_m + 1, run_end);
+                const bool in = x < width;
+                if (in) {
+                    cur[x] = best;
+                    out[x] = (unsigned char)arg;
+                }
+                const bool live =
+                    in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
+                const unsigned long long set = __ballot(live);
+                if (set) {
+                    low = min(low, c * kWave + __builtin_ctzll(set));
+                    high = c * kWave + 63 - __builtin_clzll(set);
                 }
             }
-            best = add_singles(best, layer_m + 1, run_end);
-            const bool in = x < width;
-            if (in) {
-                cur[x] = best;
-                out[x] = (unsigned char)arg;
-            }
-            const bool live = in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
-            const unsigned long long set = __ballot(live);
-            if (set) {
-                low = min(low, c * kWave + __builtin_ctzll(set));
-                high = c * kWave + 63 - __builtin_clzll(set);
-            }
-        }
-        if (high < 0) {                           // cannot happen: the known profile survives
             if (lane == 0)
-                profile[0] = kTodo;
-            return;
+                sh.live[turn][wave] = make_int2(low, high);
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kCoreWaves; ++w) {
+                const int2 o = sh.live[turn][w];
+                low = min(low, o.x);
+                high = max(high, o.y);
+            }
+            turn ^= 1;
+            low = __builtin_amdgcn_readfirstlane(low);
+            high = __builtin_amdgcn_readfirstlane(high);
+            if (high < 0) {                       // no profile costs as little as `target`
+                failed = true;
+                break;
+            }
+            b = a + high;
+            a = a + low;
+            prev = cur + low;
         }
-        fence();
-        b = a + high;
-        a = a + low;
-        prev = cur + low;
-    }
 
-    // ---- least cost, smallest time among equals, then the walk back
-    if (first_spilled < nsteps)
-        __threadfence();
-    unsigned long long key = ~0ull;
-    for (int x = lane; x <= b - a; x += kWave)
-        key = Smaller{}(key, pair_key(magnitude(prev[x]), x));
-    key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
-    int t = a + (int)(unsigned)key;
-    if (lane == 0)
-        *cost = prev[(unsigned)key];              // the sum over the profile in layer order
-    uint32_t next_word = 0;
-    CoreStep st{0, 0, 0, 0};
-    int at = 0;
-    if (nsteps) {
-        st = steps[nsteps - 1];
-        at = row_at[nsteps - 1];
-        next_word = st.first + lane < total ? list[st.first + lane].word : 0;
-    }
-    for (int m = nsteps - 1; m >= 0; --m) {
-        const uint32_t words = next_word;
-        const CoreStep now = st;
-        const int here = __builtin_amdgcn_readfirstlane(at) + t;
-        const int e = __builtin_amdgcn_readfirstlane(m >= first_spilled ? spill[here] : rec[here]);
-        if (m > 0) {
-            st = steps[m - 1];
-            at = row_at[m - 1];
-            next_word = list[min(st.first + lane, total - 1)].word;
+        // ---- least cost, smallest time among equals, then the walk back
+        unsigned long long key = ~0ull;
+        if (!failed) {
+            for (int x = lane; x <= b - a; x += kWave)
+                key = Smaller{}(key, pair_key(magnitude(prev[x]), x));
+            key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
+            const float value = prev[(unsigned)key];   // the sum over the profile in layer order
+            failed = !((double)value <= target);
+            if (!failed) {
+                if (wave != 0)
+                    return;
+                if (lane == 0)
+                    *cost = value;
+            } else {
+                upper = fminf(upper, value);
+            }
         }
-        const uint32_t word =
-            e < kWave ? (uint32_t)__builtin_amdgcn_readlane((int)words, e) : list[now.first + e].word;
-        if (lane == 0)
-            profile[now.layer] = (int16_t)(word >> kCoreShiftBits);
-        t -= __builtin_amdgcn_readfirstlane((int)(word & ((1u << kCoreShiftBits) - 1u)));
+        if (failed) {
+            beyond = wide ? target : beyond;
+            target = wide ? halved(target) : (double)upper;
+            if (!(target < beyond))
+                break;
+            __syncthreads();                      // every wave is through with the rows
+            stage();
+            __syncthreads();
+            continue;
+        }
+        if (first_spilled < nsteps)
+            __threadfence();
+        int t = a + (int)(unsigned)key;
+        uint32_t next_word = 0;
+        CoreStep st{0, 0, 0, 0};
+        int at = 0;
+        if (nsteps) {
+            st = steps[nsteps - 1];
+            at = row_at[nsteps - 1];
+            next_word = st.first + lane < total ? list[st.first + lane].word : 0;
+        }
+        for (int m = nsteps - 1; m >= 0; --m) {
+            const uint32_t words = next_word;
+            const CoreStep now = st;
+            const int here = __builtin_amdgcn_readfirstlane(at) + t;
+            const int e =
+                __builtin_amdgcn_readfirstlane(m >= first_spilled ? spill[here] : rec[here]);
+            if (m > 0) {
+                st = steps[m - 1];
+                at = row_at[m - 1];
+                next_word = list[min(st.first + lane, total - 1)].word;
+            }
+            const uint32_t word = e < kWave ? (uint32_t)__builtin_amdgcn_readlane((int)words, e)
+                                            : list[now.first + e].word;
+            if (lane == 0)
+                profile[now.layer] = (int16_t)(word >> kCoreShiftBits);
+            t -= __builtin_amdgcn_readfirstlane((int)(word & ((1u << kCoreShiftBits) - 1u)));
+        }
+        return;
     }
+    if (tid == 0)                                 // the same in every thread
+        profile[0] = kTodo;
 }
