@@ -33,8 +33,8 @@ constexpr int kCoreThreads = 256;
 constexpr int kCoreWaves = kCoreThreads / kWave;
 constexpr int kCoreMaxLayers = kCoreThreads;
 constexpr int kCoreMaxBudget = 1 << 22;  // times stay exact in fp32, a level and a shift in 32 bits
-constexpr int kCoreEntries = 1024;       // surviving levels of a candidate
 constexpr int kCoreExtra = 32;           // levels beyond one per layer that are not worth halving
+constexpr int kCoreNarrow = 2;           // chunks of a row that one wave does alone
 constexpr int kCoreTrips = 6;            // attempts, counting a halving before the first
 constexpr int kCoreBudgets = 64;         // budgets per launch
 constexpr float kCoreFar = 16777216.0f;  // "time" of a level that may not be chosen
@@ -52,7 +52,8 @@ struct CoreEntry {       // a surviving level
 
 struct CoreParams {
     int parts, parts_log2;       // threads per layer (a power of two <= 64)
-    int per_part;        // levels per thread
+    int per_part;        // levels per thread, a multiple of four (<= 128)
+    int pad;             // levels per layer past the last one that are scanned with it
     int step_layers;     // kCoreThreads / S
     int pitch;           // levels per layer in LDS (odd, so that a column of levels is conflict-free)
     int window;          // buckets a row may span
@@ -90,6 +91,20 @@ template <class T> __device__ __forceinline__ T from_lane(T x, int lane)
         const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
         const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane);
         const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+        return __builtin_bit_cast(T, (unsigned long long)hi << 32 | lo);
+    }
+}
+
+// A value that is the same in every lane, in scalar registers: what is read from LDS is divergent to
+// the compiler, and loops and branches on it would run under an execution mask.
+template <class T> __device__ __forceinline__ T uniform(T x)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+    } else {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32));
         return __builtin_bit_cast(T, (unsigned long long)hi << 32 | lo);
     }
 }
@@ -152,6 +167,14 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
     return (unsigned long long)high << 32 | low;
 }
 
+template <int N> struct Many {
+    static constexpr int value = N;
+};
+
+struct CoreBooks {       // where the steps of the reduced table have got to
+    int m, a, b, used, spilled, first_spilled, work, prev, failed, wide;
+};
+
 struct CoreShared {      // static LDS of the kernel
     float2 sum[2][kCoreWaves];               // (err, tau) of a path, by wave; times as int bits
     unsigned long long key[2][kCoreWaves];
@@ -159,6 +182,7 @@ struct CoreShared {      // static LDS of the kernel
     int2 place[2][kCoreWaves];               // sums of the entries (and steps), of the times
     int2 live[2][kCoreWaves];                // first and last bucket of a row that matters
     double least[kCoreWaves];
+    CoreBooks books;
 };
 
 // One candidate (error source `src` seen from candidate k) under budget B.  Returns through
@@ -203,13 +227,17 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             }
 #pragma unroll
             for (int j = 0; j < kLoads; ++j) {
-                if (at[j] >= 0) {
+                if (at[j] >= 0) {                 // (else past the end of the tables)
                     bad |= !(e[j] >= 0.0f) || t[j] < 0;
                     const bool out = t[j] > B || e[j] == __builtin_inff();
                     table[at[j]] = out ? make_float2(__builtin_inff(), kCoreFar)
                                        : make_float2(e[j], (float)t[j]);
                 }
             }
+        }
+        for (int i = tid; i < L * cp.pad; i += kCoreThreads) {
+            const int pl = i / cp.pad;
+            table[pl * cp.pitch + S + (i - pl * cp.pad)] = make_float2(__builtin_inff(), kCoreFar);
         }
         return bad;
     };
@@ -225,25 +253,26 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     const bool in_layer = layer < L;
     const bool lead = in_layer && part == 0;
     const int s_begin = in_layer ? part * cp.per_part : 0;
-    const int s_end = in_layer ? min(S, s_begin + cp.per_part) : 0;
     const float2 *const mine = table + (in_layer ? layer : 0) * cp.pitch;
-    // f(err and tau, level) for this thread's levels, four at a time and the next four already on
-    // their way.  Where the range ends early the layer's last level is seen again.
+    // f(err and tau, i) for this thread's levels s_begin + i, four at a time and the next four already on
+    // their way (the last four once more at the end; per_part is a multiple of four).
     auto scan = [&](auto f) __attribute__((always_inline)) {
+        const float2 *from = mine + s_begin;
         float2 v[4], next_v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            next_v[q] = mine[min(s_begin + q, S - 1)];
+            next_v[q] = from[q];
         for (int i = 0; i < cp.per_part; i += 4) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 v[q] = next_v[q];
+            from += i + 4 < cp.per_part ? 4 : 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                next_v[q] = mine[min(s_begin + i + 4 + q, S - 1)];
+                next_v[q] = from[q];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                f(v[q], s_begin + i + q);
+                f(v[q], i + q);
         }
     };
     int turn = 0;                                 // which half of the double-buffered words
@@ -262,6 +291,8 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             c += sh.sum[turn][w].x;
             total += __builtin_bit_cast(int, sh.sum[turn][w].y);
         }
+        c = uniform(c);
+        total = uniform(total);
         turn ^= 1;
     };
 
@@ -300,13 +331,14 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
             float least = __builtin_inff();
             int level = 0;
-            scan([&](float2 v, int s) {
+            scan([&](float2 v, int i) {
                 const float r = __builtin_fmaf(lambda_f, v.y, v.x);
-                level = r < least ? s : level;
+                level = r < least ? i : level;
                 least = r < least ? r : least;
             });
-            level = (int)(unsigned)group_join(pair_key(magnitude(least), level), parts, Smaller{});
-            const float2 v = mine[min(level, S - 1)];
+            level = (int)(unsigned)group_join(pair_key(magnitude(least), s_begin + level), parts,
+                                              Smaller{});
+            const float2 v = mine[level];
             float c;
             int t;
             path_sum(v.x, v.y, c, t);
@@ -368,6 +400,9 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 d.y = o > win ? od.y : d.y;
                 win = o > win ? o : win;
             }
+            win = uniform(win);
+            d.x = uniform(d.x);
+            d.y = uniform(d.y);
             turn ^= 1;
             if (win) {
                 if (layer == (int)((unsigned)win - 1u) >> cp.parts_log2) {
@@ -412,12 +447,14 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         upto_least += w < wave ? o : 0.0;
         sum_least += o;
     }
+    sum_least = uniform(sum_least);
     float upper = -0.0f;                          // U: the profile's cost, summed as Alg. 1 does
     for (int base = 0; base < L; base += kWave) {
-        const float e = base + lane < L ? single[base + lane] : 0.0f;
-        const int n = min(kWave, L - base);
-        for (int i = 0; i < n; ++i)
-            upper += lane_value(e, i);
+        const float e = base + lane < L ? single[base + lane] : -0.0f;   // (x + -0 is x)
+        for (int i = 0; i < min(kWave, L - base); i += 8)
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                upper += lane_value(e, i + q);
     }
     const double relaxed = sum_least - lambda * B;
     const double hu = 0x1p-24 * (double)__builtin_bit_cast(
@@ -436,9 +473,12 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     for (int trip = 0; trip < kCoreTrips; ++trip) {
         const double keep_to = least + (target + (L - 1) * hu - relaxed + margin);
         int count = 0, first_t = INT32_MAX, last_t = -1;
-        scan([&](float2 v, int s) {
-            const bool keep =
-                s < s_end && __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
+        unsigned long long kept[2] = {0, 0};      // bit i: level s_begin + i (per_part <= 128)
+        scan([&](float2 v, int i) {
+            const bool keep = __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
+            const unsigned long long bit = keep ? 1ull << (i & 63) : 0ull;
+            kept[0] |= i < 64 ? bit : 0ull;
+            kept[1] |= i < 64 ? 0ull : bit;
             count += keep ? 1 : 0;
             first_t = keep ? min(first_t, (int)v.y) : first_t;
             last_t = keep ? max(last_t, (int)v.y) : last_t;
@@ -446,15 +486,16 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         const int of_layer = group_join(count, parts, Add{});
         first_t = group_join(first_t, parts, Smaller{});
         last_t = group_join(last_t, parts, Larger{});
-        // sums over the threads up to this one: entries, with the layers of more than one above bit
-        // 16; smallest times
+        // sums over the threads up to this one: entries of the layers that have more than one, with
+        // these layers above bit 16; smallest times
         const bool is_step = lead && of_layer > 1;
-        const int run = wave_scan(count + (is_step ? 1 << 16 : 0), 0, Add{});
+        const int listed = (of_layer > 1 && in_layer ? count : 0) + (is_step ? 1 << 16 : 0);
+        const int run = wave_scan(listed, 0, Add{});
         const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
         if (lane == kWave - 1)
             sh.place[turn][wave] = make_int2(run, run_t);
         __syncthreads();                          // (every wave is through with `single`, too)
-        int before = run - count - (is_step ? 1 << 16 : 0), all = 0, upto_t = run_t, base_t = 0;
+        int before = run - listed, all = 0, upto_t = run_t, base_t = 0;
 #pragma unroll
         for (int w = 0; w < kCoreWaves; ++w) {
             const int2 o = sh.place[turn][w];
@@ -463,9 +504,11 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             all += o.x;
             base_t += o.y;
         }
+        all = uniform(all);
+        base_t = uniform(base_t);
         turn ^= 1;
         const int total = all & 0xFFFF, nsteps = all >> 16;
-        if (first_try && total - L > kCoreExtra && upper < 1e38f) {
+        if (first_try && total - nsteps > kCoreExtra && upper < 1e38f) {
             first_try = false;
             target = halved(target);
             continue;
@@ -486,16 +529,22 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 if (is_step)
                     steps[before >> 16] = CoreStep{layer, place, of_layer, last_t - first_t};
             }
-            scan([&](float2 v, int s) {
-                if (s < s_end && __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to) {
-                    list[place++] = CoreEntry{v.x, (uint32_t)s << kCoreShiftBits |
-                                                       (uint32_t)((int)v.y - first_t)};
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                unsigned long long left = in_layer ? kept[half] : 0;
+                while (left) {
+                    const int s = s_begin + 64 * half + __builtin_ctzll(left);
+                    const float2 v = mine[s];
+                    left &= left - 1;
                     if (of_layer == 1) {          // this level it is
                         single[layer] = v.x;
                         profile[layer] = (int16_t)s;
+                    } else {
+                        list[place++] = CoreEntry{v.x, (uint32_t)s << kCoreShiftBits |
+                                                           (uint32_t)((int)v.y - first_t)};
                     }
                 }
-            });
+            }
         }
         __syncthreads();
 
@@ -519,116 +568,180 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             return v;
         };
         const CoreEntry none{__builtin_inff(), 0};
-        CoreStep next_step{L, 0, 0, 0};
-        CoreEntry next = none;
-        if (nsteps && !failed) {
-            next_step = steps[0];
-            next = next_step.first + lane < total ? list[next_step.first + lane] : none;
-        }
+        // lane i holds step base_step + i
+        int base_step = 0;
+        CoreStep held_step{L, 0, 0, 0};
+        double held_limit = 0.0;
+        auto load_steps = [&](int base) __attribute__((always_inline)) {
+            base_step = base;
+            const int i = base + lane;
+            held_step = i < nsteps ? steps[i] : CoreStep{L, 0, 0, 0};
+            // the layers up to the next step are added to this step's row before it is judged
+            const int until = i + 1 < nsteps ? steps[i + 1].layer : L;
+            held_step.layer |= until << 16;
+            held_limit = limit[until - 1];
+        };
         float *prev = row0;
-        if (!failed) {
-            const float v = add_singles(-0.0f, 0, __builtin_amdgcn_readfirstlane(next_step.layer));
-            if (tid == 0)
-                prev[0] = v;
-        }
         int a = 0, b = 0;                         // buckets of the previous row that still matter
         int used = 0, spilled = 0, first_spilled = nsteps, work = 0;
-        __syncthreads();
-        for (int m = 0; m < nsteps && !failed; ++m) {
-            const int n = __builtin_amdgcn_readfirstlane(next_step.count);
-            const int first = __builtin_amdgcn_readfirstlane(next_step.first);
-            const int span = __builtin_amdgcn_readfirstlane(next_step.span);
-            const int layer_m = __builtin_amdgcn_readfirstlane(next_step.layer);
-            const CoreEntry held_entry = lane < n ? next : none;
-            int run_end = L;                      // the next step's layer
-            if (m + 1 < nsteps) {
-                next_step = steps[m + 1];
-                run_end = __builtin_amdgcn_readfirstlane(next_step.layer);
-                next = next_step.first + lane < total ? list[next_step.first + lane] : none;
-            }
-            const double lim = limit[run_end - 1];
-            const int top = min(b + span, budget);
-            const int width = top - a + 1;
-            const int chunks = (width + kWave - 1) / kWave;
-            work += n * chunks;
-            const bool spills = first_spilled < nsteps || used + width > cp.record;
-            if (width > cp.window || work > cp.work ||
-                (spills && spilled + width > cp.spill_bytes)) {
-                failed = wide = true;
-                break;
-            }
-            unsigned char *out = rec + used;
-            if (spills) {
-                first_spilled = min(first_spilled, m);
-                out = spill + spilled;
-            }
+        CoreEntry next = none;
+        if (!failed) {
+            load_steps(0);
+            const float v = add_singles(-0.0f, 0, nsteps ? __builtin_amdgcn_readlane(
+                                                               held_step.layer, 0) & 0xFFFF
+                                                         : L);
             if (tid == 0)
-                row_at[m] = (spills ? spilled : used) - a;
-            spilled += spills ? width : 0;
-            used += spills ? 0 : width;
-            float *const cur = prev >= row1 ? row0 : row1;
-            const unsigned reach = (unsigned)(b - a);
-            int low = INT32_MAX, high = -1;       // live buckets of the new row, from a
-            for (int c = wave; c < chunks; c += kCoreWaves) {
-                const int x = c * kWave + lane;
-                float best = __builtin_inff();
-                int arg = 0;
-                for (int blk = 0; blk < n; blk += kWave) {
-                    CoreEntry en = held_entry;
-                    if (blk > 0)
-                        en = blk + lane < n ? list[first + blk + lane] : none;
-                    const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
-                    const int some = min(kWave, n - blk);
-                    for (int i = 0; i < some; i += 4) {   // (entries past the last: +inf)
-                        float p[4];
+                prev[0] = v;
+            next = lane < total ? list[lane] : none;
+        }
+        __syncthreads();
+        // The best of n entries, in order, for bucket a + x; `en`: lane i holds entry i.
+        auto visit = [&](CoreEntry en, int i, int x, unsigned reach, int index, float &best,
+                         int &arg, auto width) __attribute__((always_inline)) {
+            constexpr int kMany = decltype(width)::value;
+            const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
+            float p[kMany];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int u = x - __builtin_amdgcn_readlane(shift, i + q);
-                            const bool ok = (unsigned)u <= reach;
-                            const float d = prev[ok ? u : 0];
-                            p[q] = (ok ? d : __builtin_inff()) + lane_value(en.err, i + q);
-                        }
+            for (int q = 0; q < kMany; ++q) {
+                const int u = x - __builtin_amdgcn_readlane(shift, i + q);
+                const bool ok = (unsigned)u <= reach;
+                const float d = prev[ok ? u : 0];
+                p[q] = (ok ? d : __builtin_inff()) + lane_value(en.err, i + q);
+            }
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const bool take = p[q] < best;
-                            best = take ? p[q] : best;
-                            arg = take ? blk + i + q : arg;
+            for (int q = 0; q < kMany; ++q) {
+                const bool take = p[q] < best;
+                best = take ? p[q] : best;
+                arg = take ? index + q : arg;
+            }
+        };
+        int m = 0;
+        while (m < nsteps && !failed) {
+            // One step.  A row of one or two chunks is done by wave 0 alone, as are the narrow ones
+            // after it, without a barrier: the others wait for where it has got to.
+            bool alone = false;
+            for (;;) {
+                if (m - base_step >= kWave)
+                    load_steps(m);
+                const int i_m = m - base_step;
+                const int n = __builtin_amdgcn_readlane(held_step.count, i_m);
+                const int first = __builtin_amdgcn_readlane(held_step.first, i_m);
+                const int span = __builtin_amdgcn_readlane(held_step.span, i_m);
+                const int layers_m = __builtin_amdgcn_readlane(held_step.layer, i_m);
+                const double lim = from_lane(held_limit, i_m);
+                const int top = min(b + span, budget);
+                const int width = top - a + 1;
+                const int chunks = (width + kWave - 1) / kWave;
+                const bool narrow = chunks <= kCoreNarrow;
+                if (alone && !narrow)
+                    break;
+                if (narrow && wave != 0) {
+                    alone = true;
+                    break;
+                }
+                alone = narrow;
+                const CoreEntry held_entry = lane < n ? next : none;
+                const int follow = first + n + lane;   // the next step's entries
+                next = follow < total ? list[follow] : none;
+                work += n * chunks;
+                const bool spills = first_spilled < nsteps || used + width > cp.record;
+                if (width > cp.window || work > cp.work ||
+                    (spills && spilled + width > cp.spill_bytes)) {
+                    failed = wide = true;
+                    break;
+                }
+                unsigned char *out = rec + used;
+                if (spills) {
+                    first_spilled = min(first_spilled, m);
+                    out = spill + spilled;
+                }
+                if (tid == 0)
+                    row_at[m] = (spills ? spilled : used) - a;
+                spilled += spills ? width : 0;
+                used += spills ? 0 : width;
+                float *const cur = prev >= row1 ? row0 : row1;
+                const unsigned reach = (unsigned)(b - a);
+                int low = INT32_MAX, high = -1;   // live buckets of the new row, from a
+                for (int c = narrow ? 0 : wave; c < chunks; c += narrow ? 1 : kCoreWaves) {
+                    const int x = c * kWave + lane;
+                    float best = __builtin_inff();
+                    int arg = 0;
+                    if (n <= 2) {
+                        visit(held_entry, 0, x, reach, 0, best, arg, Many<2>{});
+                    } else {
+                        for (int blk = 0; blk < n; blk += kWave) {
+                            CoreEntry en = held_entry;
+                            if (blk > 0)
+                                en = blk + lane < n ? list[first + blk + lane] : none;
+                            for (int i = 0; i < min(kWave, n - blk); i += 4)
+                                visit(en, i, x, reach, blk + i, best, arg, Many<4>{});
                         }
                     }
+                    best = add_singles(best, (layers_m & 0xFFFF) + 1, layers_m >> 16);
+                    const bool in = x < width;
+                    if (in) {
+                        cur[x] = best;
+                        out[x] = (unsigned char)arg;
+                    }
+                    const bool live =
+                        in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
+                    const unsigned long long set = __ballot(live);
+                    if (set) {
+                        low = min(low, c * kWave + __builtin_ctzll(set));
+                        high = c * kWave + 63 - __builtin_clzll(set);
+                    }
                 }
-                best = add_singles(best, layer_m + 1, run_end);
-                const bool in = x < width;
-                if (in) {
-                    cur[x] = best;
-                    out[x] = (unsigned char)arg;
-                }
-                const bool live =
-                    in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
-                const unsigned long long set = __ballot(live);
-                if (set) {
-                    low = min(low, c * kWave + __builtin_ctzll(set));
-                    high = c * kWave + 63 - __builtin_clzll(set);
-                }
-            }
-            if (lane == 0)
-                sh.live[turn][wave] = make_int2(low, high);
-            __syncthreads();
+                if (!narrow) {
+                    if (lane == 0)
+                        sh.live[turn][wave] = make_int2(low, high);
+                    __syncthreads();
 #pragma unroll
-            for (int w = 0; w < kCoreWaves; ++w) {
-                const int2 o = sh.live[turn][w];
-                low = min(low, o.x);
-                high = max(high, o.y);
+                    for (int w = 0; w < kCoreWaves; ++w) {
+                        const int2 o = sh.live[turn][w];
+                        low = min(low, o.x);
+                        high = max(high, o.y);
+                    }
+                    turn ^= 1;
+                    low = __builtin_amdgcn_readfirstlane(low);
+                    high = __builtin_amdgcn_readfirstlane(high);
+                }
+                ++m;
+                if (high < 0) {                   // no profile costs as little as `target`
+                    failed = true;
+                    break;
+                }
+                b = a + high;
+                a = a + low;
+                prev = cur + low;
+                if (!narrow || m == nsteps)
+                    break;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
-            turn ^= 1;
-            low = __builtin_amdgcn_readfirstlane(low);
-            high = __builtin_amdgcn_readfirstlane(high);
-            if (high < 0) {                       // no profile costs as little as `target`
-                failed = true;
-                break;
+            if (alone) {                          // the same in every wave
+                if (tid == 0)
+                    sh.books = CoreBooks{m, a, b, used, spilled, first_spilled, work,
+                                         (int)(prev - row0), failed ? 1 : 0, wide ? 1 : 0};
+                __syncthreads();
+                const CoreBooks books = sh.books;
+                m = uniform(books.m);
+                a = uniform(books.a);
+                b = uniform(books.b);
+                used = uniform(books.used);
+                spilled = uniform(books.spilled);
+                first_spilled = uniform(books.first_spilled);
+                work = uniform(books.work);
+                prev = row0 + uniform(books.prev);
+                failed = uniform(books.failed) != 0;
+                wide = uniform(books.wide) != 0;
+                if (m < nsteps && !failed) {
+                    if (m - base_step >= kWave)
+                        load_steps(m);
+                    const int at = __builtin_amdgcn_readlane(held_step.first, m - base_step) + lane;
+                    next = at < total ? list[at] : none;
+                }
+                __syncthreads();                  // the books may be written again
             }
-            b = a + high;
-            a = a + low;
-            prev = cur + low;
         }
 
         // ---- least cost, smallest time among equals, then the walk back
@@ -637,7 +750,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             for (int x = lane; x <= b - a; x += kWave)
                 key = Smaller{}(key, pair_key(magnitude(prev[x]), x));
             key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
-            const float value = prev[(unsigned)key];   // the sum over the profile in layer order
+            const float value = uniform(prev[(unsigned)key]);   // the sum over the profile in layer order
             failed = !((double)value <= target);
             if (!failed) {
                 if (wave != 0)

@@ -556,19 +556,20 @@ struct Resume {
 // Solving with a fraction of the record (Sec. 3.2 counts O(L T) memory for the matrices): a
 // first pass over all layers keeps only every `stride`-th row of D (checkpoints) and finds the
 // final time; then, from the last block of `stride` layers to the first, the block's rows are
-// filled again from the checkpoint below it into a small block record and walked back.
+// filled again from the checkpoint below it into a small block record and walked back by the
+// candidate's own workgroup.
 //   pass 0 (checkpoints): layers [0, L); row l is kept at slot (l + 1) / stride - 1 when
 //                         (l + 1) is a multiple of stride and l + 1 < L
-//   pass 1 (one block)  : layers [begin, end), starting from checkpoint slot begin / stride - 1
+//   later passes (blocks): layers [begin, end), starting from checkpoint slot begin / stride - 1
 //                         (from scratch when begin = 0); row l is kept at slot l - begin of the
-//                         block record; no final argmin
+//                         block record
 struct Blocks {
-    int pass;
-    int begin, end;
     int stride;
     int slots;                    // checkpoint rows per candidate
     float *ckpt;                  // [K][slots][pitch]
     float *block;                 // [K][stride][pitch]
+    const int32_t *tau;
+    int16_t *profile;             // [K][L]
 };
 
 struct LevelEntry {   // one visited level of one layer of one candidate
@@ -1164,6 +1165,127 @@ __device__ __forceinline__ void write_result(float bv, int bt, int k, int32_t *t
 }
 
 // ---------------------------------------------------------------------------------------------
+// Walk back through the D record: one wave per candidate.  At (l, t) the lanes try the levels in parallel: lane s
+// forms D_{l-1}[t - shift_s] + err[l][s] with the same single fp32 add as the fill and compares
+// it with D_l[t]; the lowest matching level is the one a strict "<" sweep would have kept.
+// Only the gather of D_{l-1} depends on t, so it is issued first and the shifts and errors of the
+// next layer down are fetched behind it: one memory round trip per layer on the critical path.
+// The cost is then re-summed over the profile in layer order, which reproduces the sign of a
+// zero exactly as the level-tracking sweep would (min(+0, -0) is order-blind).
+// kLevelBlocks: 64-level blocks a lane holds (1 for S <= 64, 4 for S <= 255).
+template <int kLevelBlocks>
+struct LayerLevels {
+    int shift[kLevelBlocks];      // tau[l][s] - m_l for s = 64 b + lane (INT32_MAX past S)
+    float err[kLevelBlocks];
+    int reach;                    // computed buckets of row l - 1 (1 for l = 0: only t = 0)
+};
+
+template <int kLevelBlocks>
+__device__ __forceinline__ LayerLevels<kLevelBlocks> load_layer(
+    const int32_t *__restrict__ tau, ErrRow er, const int32_t *__restrict__ meta, int l, int L,
+    int S, int lane)
+{
+    LayerLevels<kLevelBlocks> v;
+    const int m = meta[kMetaHeader + l];
+    v.reach = l > 0 ? meta[kMetaHeader + L + l - 1] * kWave : 1;
+#pragma unroll
+    for (int b = 0; b < kLevelBlocks; ++b) {
+        const int s = b * kWave + lane;
+        v.shift[b] = INT32_MAX;
+        v.err[b] = __builtin_inff();
+        if (s < S) {
+            v.shift[b] = tau[(size_t)l * S + s] - m;
+            v.err[b] = er.at(s);
+        }
+    }
+    return v;
+}
+
+// One wave walks candidate k back through layers [lb, le) from time t, which it returns as it is
+// below layer lb (-1: no profile meets the budget; -2: a damaged record).  row_of(l): row of layer l.
+template <int kLevelBlocks, class RowOf>
+__device__ __forceinline__ int walk_layers(const int32_t *__restrict__ tau, const ErrSource src,
+                                           const int32_t *__restrict__ meta, RowOf row_of, int t,
+                                           int lb, int le, int L, int S,
+                                           int16_t *__restrict__ prof)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    if (t < 0) {
+        for (int l = lb + lane; l < le; l += kWave)
+            prof[l] = t == -1 ? -1 : -2;         // -1: no profile meets the budget
+        return t;
+    }
+    float target = row_of(le - 1)[t];
+    LayerLevels<kLevelBlocks> next =
+        load_layer<kLevelBlocks>(tau, src.layer(le - 1, S), meta, le - 1, L, S, lane);
+    for (int l = le - 1; l >= lb; --l) {
+        const LayerLevels<kLevelBlocks> cur = next;
+        const float *prow = row_of(l > 0 ? l - 1 : 0);       // row of layer l - 1
+        // issue the gather of D_{l-1} first, then the next layer's table behind it
+        int u[kLevelBlocks];
+        float pv[kLevelBlocks];
+        bool valid[kLevelBlocks];
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks; ++b) {
+            const long long uu = (long long)t - cur.shift[b];
+            valid[b] = b * kWave < S && uu >= 0 && uu < cur.reach;
+            u[b] = valid[b] ? (int)uu : 0;
+            pv[b] = __builtin_inff();
+            if (valid[b])
+                pv[b] = l > 0 ? __builtin_nontemporal_load(&prow[u[b]]) : -0.0f;
+        }
+        if (l > lb)
+            next = load_layer<kLevelBlocks>(tau, src.layer(l - 1, S), meta, l - 1, L, S, lane);
+        int found = -1, next_t = 0;
+        float next_target = 0.0f;
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks; ++b) {
+            if (b * kWave < S && found < 0) {
+                const bool match = valid[b] && pv[b] + cur.err[b] == target;
+                const unsigned long long mask = __ballot(match);
+                if (mask) {
+                    const int first = __builtin_ctzll(mask);
+                    found = b * kWave + first;
+                    next_t = __shfl(u[b], first, kWave);
+                    next_target = __shfl(pv[b], first, kWave);
+                }
+            }
+        }
+        if (found < 0) {     // cannot happen on a filled record
+            for (int i = lane; i < L; i += kWave)
+                prof[i] = -2;
+            return -2;
+        }
+        if (lane == 0)
+            prof[l] = (int16_t)found;
+        t = next_t;
+        target = next_target;
+    }
+    return t;
+}
+
+// The cost of a walked profile, summed in layer order.  Lane 0 wrote the profile; it is made visible
+// to the wave first.  Lane i fetches the error of layer 64 b + i (all layers of a block of 64 in one
+// round trip instead of one after the other); the sum itself runs over the lanes in order.
+__device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
+                                              const int16_t *__restrict__ prof)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    __threadfence();
+    float acc = -0.0f;
+    for (int base = 0; base < L; base += kWave) {
+        const int l = base + lane;
+        float e = 0.0f;
+        if (l < L)
+            e = src.layer(l, S).at(prof[l]);
+        const int n = min(kWave, L - base);
+        for (int i = 0; i < n; ++i)
+            acc += lane_value(e, i);
+    }
+    return acc;
+}
+
+// ---------------------------------------------------------------------------------------------
 // The fill (Eq. 2-3 for all L layers) and the final argmin over t.  The waves of a workgroup
 // form `teams` teams of `tw` waves; team i of workgroup b solves candidate b * teams + i.
 // Barriers are workgroup-wide, so every team steps through the layers together.
@@ -1183,7 +1305,7 @@ __device__ __forceinline__ void write_result(float bv, int bt, int k, int32_t *t
 //   kNarrow  : S <= 64, one lane per level: the next layer's table is loaded without dependent
 //              loads while a layer is swept (a separate instantiation, so that the waits of the
 //              two ways of loading do not meet in one control-flow join)
-//   kBlocks  : the checkpoint / block passes of the small-record solve (D record only); the
+//   kBlocks  : all passes of the small-record solve, with their walks back (D record only); the
 //              plain instantiation ignores `blocks`
 //   kTurns   : the workgroups that share a compute unit take turns at the instruction priority
 //              (see the layer loop); `units` is the number of compute units
@@ -1223,8 +1345,13 @@ void dp_fill(
     const int bp = meta[kMetaBudget];
     const int tid = threadIdx.x, nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
-        if (tid == 0 && !(kBlocks && blocks.pass == 1) && todo.has(blockIdx.x, K, L))
-            write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
+        if (todo.has(blockIdx.x, K, L)) {
+            if constexpr (kBlocks)
+                for (int l = tid; l < L; l += nthreads)
+                    blocks.profile[(size_t)blockIdx.x * L + l] = -1;
+            if (tid == 0)
+                write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
+        }
         return;
     }
     tables.limit = kGlobal ? bp : INT32_MAX;     // only the tiles of global rows depend on it
@@ -1268,6 +1395,10 @@ void dp_fill(
     float *buf0 = base + kHalo;
     float *buf1 = inplace ? buf0 : buf0 + stride;
 
+    // one pass, or those of the small-record solve: [lb, le) are the layers to fill
+    int lb = 0, le = L;
+    bool first_pass = true;
+next_pass:
     // D before the first layer: time 0 costs nothing, nothing else is reachable (Eq. 3 then is
     // the general update).  -0.0f + e returns e bit for bit for every e, +0.0f would not for
     // e = -0.0f.  Aprons and chunks a layer does not compute keep this +inf.
@@ -1299,8 +1430,6 @@ void dp_fill(
     if (resume.first_layer)
         __syncthreads();
     // a block pass starts from the checkpoint below the block
-    const int lb = kBlocks ? blocks.begin : 0;   // layers [lb, le) are filled
-    const int le = kBlocks ? blocks.end : L;
     if constexpr (kBlocks) {
         if (lb > 0) {
             float *dst = (lb & 1) ? buf1 : buf0;
@@ -1321,8 +1450,8 @@ void dp_fill(
     uint8_t *choice_k = kLevel ? choice + ke * L * pitch : nullptr;
     float *drec_k = kLevel ? nullptr : drec + ke * L * pitch;
     if constexpr (kBlocks)
-        drec_k = blocks.pass == 0 ? blocks.ckpt + ke * blocks.slots * pitch
-                                  : blocks.block + ke * blocks.stride * pitch;
+        drec_k = first_pass ? blocks.ckpt + ke * blocks.slots * pitch
+                            : blocks.block + ke * blocks.stride * pitch;
 
     // lane i keeps visited entry i of the layer being swept; the next layer's is fetched early
     const int s8 = tables.s8;
@@ -1412,7 +1541,7 @@ void dp_fill(
         uint8_t *choice_l = kLevel ? choice_k + (size_t)l * pitch : nullptr;
         float *drec_l = kLevel ? nullptr : drec_k + (size_t)l * pitch;
         if constexpr (kBlocks) {
-            if (blocks.pass == 1)
+            if (!first_pass)
                 drec_l = drec_k + (size_t)(l - lb) * pitch;
             else if ((l + 1) % blocks.stride == 0 && l + 1 < L)
                 drec_l = drec_k + (size_t)((l + 1) / blocks.stride - 1) * pitch;
@@ -1501,47 +1630,84 @@ void dp_fill(
         __syncthreads();
     }
 
-    if constexpr (kBlocks) {
-        if (blocks.pass == 1)
-            return;                              // the final time is known from pass 0
-    }
-    // final argmin over t' <= bp within each team
-    const float *last = (L & 1) ? buf1 : buf0;
-    float bv = __builtin_inff();
-    int bt = INT32_MAX;
-    if (active && lead)
-        for (int t = wv * kWave + lane; t <= bp; t += tw * kWave)
-            argmin_merge(bv, bt, last[t], t);
+    if (!kBlocks || first_pass) {
+        // final argmin over t' <= bp within each team
+        const float *last = (L & 1) ? buf1 : buf0;
+        float bv = __builtin_inff();
+        int bt = INT32_MAX;
+        if (active && lead)
+            for (int t = wv * kWave + lane; t <= bp; t += tw * kWave)
+                argmin_merge(bv, bt, last[t], t);
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const float ov = __shfl_down(bv, off, kWave);
-        const int ot = __shfl_down(bt, off, kWave);
-        argmin_merge(bv, bt, ov, ot);
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            const float ov = __shfl_down(bv, off, kWave);
+            const int ot = __shfl_down(bt, off, kWave);
+            argmin_merge(bv, bt, ov, ot);
+        }
+        if (lane == 0 && lead) {
+            s_best[wave] = bv;
+            s_time[wave] = bt;
+        }
+        __syncthreads();
+        if (active && lead && wv == 0 && lane == 0) {
+            for (int w = 1; w < tw; ++w)
+                argmin_merge(bv, bt, s_best[wave + w], s_time[wave + w]);
+            write_result(bv, bt, k, tstar, cost);
+        }
     }
-    if (lane == 0 && lead) {
-        s_best[wave] = bv;
-        s_time[wave] = bt;
-    }
-    __syncthreads();
-    if (active && lead && wv == 0 && lane == 0) {
-        for (int w = 1; w < tw; ++w)
-            argmin_merge(bv, bt, s_best[wave + w], s_time[wave + w]);
-        write_result(bv, bt, k, tstar, cost);
+    if constexpr (kBlocks) {
+        // the block's rows are walked by the first wave of the candidate's team, then comes the
+        // block below
+        __threadfence();
+        __syncthreads();
+        if (!first_pass && active && wv == 0) {
+            auto row_of = [&](int l) {
+                return l >= lb ? blocks.block + ((size_t)k * blocks.stride + (l - lb)) * pitch
+                               : blocks.ckpt + ((size_t)k * blocks.slots +
+                                                (lb / blocks.stride - 1)) * pitch;
+            };
+            int16_t *prof = blocks.profile + (size_t)k * L;
+            const int t = walk_layers<kNarrow ? 1 : 4>(blocks.tau, mine, meta, row_of, tstar[k],
+                                                       lb, le, L, S, prof);
+            if (lane == 0)
+                tstar[k] = t;
+            if (t == -2 && lane == 0)
+                cost[k] = __builtin_nanf("");
+            if (lb == 0 && t >= 0) {
+                const float acc = profile_cost(mine, L, S, prof);
+                if (lane == 0)
+                    cost[k] = acc;
+            }
+        }
+        if (lb == 0 && !first_pass)
+            return;
+        le = first_pass ? L : lb;
+        lb = (le - 1) / blocks.stride * blocks.stride;
+        first_pass = false;
+        __threadfence();
+        __syncthreads();
+        goto next_pass;
     }
 }
 
-// Final argmin for another budget on an already filled D record: the rows hold exact-time costs
+// Final argmin for other budgets on an already filled D record: the rows hold exact-time costs
 // and do not depend on the budget, so a smaller budget only shortens the range of the argmin
-// (Sec. 3.2: the answer is min over t <= T of the last row).  One workgroup per candidate.
+// (Sec. 3.2: the answer is min over t <= T of the last row).  One workgroup per candidate and
+// budget; the time found (-1: none) is left in tstar[j * K + k] for the walk back.
+struct Budgets {
+    int32_t at[kCoreBudgets];
+};
 __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restrict__ meta,
-                                                        const float *__restrict__ drec, int L,
-                                                        int pitch, int budget,
-                                                        int32_t *__restrict__ tstar,
-                                                        float *__restrict__ cost)
+                                                        const float *__restrict__ drec, int K,
+                                                        int L, int pitch, Budgets budgets,
+                                                        int32_t *__restrict__ tstar, Todo todo)
 {
     __shared__ float s_best[4];
     __shared__ int s_time[4];
-    const int k = blockIdx.x, tid = threadIdx.x;
+    const int solve = blockIdx.x, j = solve / K, k = solve - j * K, tid = threadIdx.x;
+    if (!todo.has(solve, K, L))
+        return;
+    const int budget = budgets.at[j];
     const int bp = meta[kMetaBudget];
     // reduced budget: t' <= budget - M, and never beyond what the fill computed
     const long long reduced = (long long)budget - meta[kMetaMinTime];
@@ -1571,7 +1737,7 @@ __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restric
     if (tid == 0) {
         for (int w = 1; w < 4; ++w)
             argmin_merge(bv, bt, s_best[w], s_time[w]);
-        write_result(bv, bt, k, tstar, cost);
+        tstar[solve] = bv < __builtin_inff() ? bt : -1;
     }
 }
 
@@ -1624,157 +1790,33 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
     cost[k] = acc;
 }
 
-// D record: one wave per candidate.  At (l, t) the lanes try the levels in parallel: lane s
-// forms D_{l-1}[t - shift_s] + err[l][s] with the same single fp32 add as the fill and compares
-// it with D_l[t]; the lowest matching level is the one a strict "<" sweep would have kept.
-// Only the gather of D_{l-1} depends on t, so it is issued first and the shifts and errors of the
-// next layer down are fetched behind it: one memory round trip per layer on the critical path.
-// The cost is then re-summed over the profile in layer order, which reproduces the sign of a
-// zero exactly as the level-tracking sweep would (min(+0, -0) is order-blind).
-// kLevelBlocks: 64-level blocks a lane holds (1 for S <= 64, 4 for S <= 255).
+// `budgets` > 1 (solve_budgets): solve j * K + k is candidate k under budget j, and its final time
+// comes in through cost (dp_budget_argmin).
 template <int kLevelBlocks>
-struct LayerLevels {
-    int shift[kLevelBlocks];      // tau[l][s] - m_l for s = 64 b + lane (INT32_MAX past S)
-    float err[kLevelBlocks];
-    int reach;                    // computed buckets of row l - 1 (1 for l = 0: only t = 0)
-};
-
-template <int kLevelBlocks>
-__device__ __forceinline__ LayerLevels<kLevelBlocks> load_layer(
-    const int32_t *__restrict__ tau, ErrRow er, const int32_t *__restrict__ meta, int l, int L,
-    int S, int lane)
-{
-    LayerLevels<kLevelBlocks> v;
-    const int m = meta[kMetaHeader + l];
-    v.reach = l > 0 ? meta[kMetaHeader + L + l - 1] * kWave : 1;
-#pragma unroll
-    for (int b = 0; b < kLevelBlocks; ++b) {
-        const int s = b * kWave + lane;
-        v.shift[b] = INT32_MAX;
-        v.err[b] = __builtin_inff();
-        if (s < S) {
-            v.shift[b] = tau[(size_t)l * S + s] - m;
-            v.err[b] = er.at(s);
-        }
-    }
-    return v;
-}
-
-// kBlocks: the walk through one block of layers [blocks.begin, blocks.end) of the small-record
-// solve: rows come from the block record, the row below the block from its checkpoint; tstar
-// holds the time to start from and receives the time below the block; the cost is re-summed
-// after the first block (the last one walked).
-template <int kLevelBlocks, bool kBlocks>
 __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
-    const float *__restrict__ drec,
-    int32_t *__restrict__ tstar, int K, int L, int S, int pitch,
-    int16_t *__restrict__ profile, float *__restrict__ cost, Resume resume, Blocks blocks,
-    Todo todo)
+    const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
+    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
-    if (k >= K || !todo.has(k, K, L))
+    const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    const int k = budgets > 1 ? solve % K : solve;
+    if (solve >= K * budgets || !todo.has(solve, K, L))
         return;
-    int16_t *prof = profile + (size_t)k * L;
-    const int lb = kBlocks ? blocks.begin : 0;   // layers [lb, le) are walked
-    const int le = kBlocks ? blocks.end : L;
-    int t = tstar[k];
-    if (t < 0) {
-        for (int l = lb + lane; l < le; l += kWave)
-            prof[l] = t == -1 ? -1 : -2;         // -1: no profile meets the budget
-        return;
-    }
+    int16_t *prof = profile + (size_t)solve * L;
+    const ErrSource mine = src.of_candidate(k, L, S);
     const float *drec_k = drec + (size_t)k * L * pitch;
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
-    auto row_of = [&](int l) {
-        if constexpr (kBlocks) {
-            if (l >= lb)
-                return blocks.block + ((size_t)k * blocks.stride + (l - lb)) * pitch;
-            return blocks.ckpt + ((size_t)k * blocks.slots + (lb / blocks.stride - 1)) * pitch;
-        } else {
-            return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch;
-        }
-    };
-    float target = row_of(le - 1)[t];
-    LayerLevels<kLevelBlocks> next =
-        load_layer<kLevelBlocks>(tau, src.row(k, le - 1, L, S), meta, le - 1, L, S, lane);
-    bool ok = true;
-    for (int l = le - 1; l >= lb; --l) {
-        const LayerLevels<kLevelBlocks> cur = next;
-        const float *prow = row_of(l > 0 ? l - 1 : 0);       // row of layer l - 1
-        // issue the gather of D_{l-1} first, then the next layer's table behind it
-        int u[kLevelBlocks];
-        float pv[kLevelBlocks];
-        bool valid[kLevelBlocks];
-#pragma unroll
-        for (int b = 0; b < kLevelBlocks; ++b) {
-            const long long uu = (long long)t - cur.shift[b];
-            valid[b] = b * kWave < S && uu >= 0 && uu < cur.reach;
-            u[b] = valid[b] ? (int)uu : 0;
-            pv[b] = __builtin_inff();
-            if (valid[b])
-                pv[b] = l > 0 ? __builtin_nontemporal_load(&prow[u[b]]) : -0.0f;
-        }
-        if (l > lb)
-            next = load_layer<kLevelBlocks>(tau, src.row(k, l - 1, L, S), meta, l - 1, L, S, lane);
-        int found = -1, next_t = 0;
-        float next_target = 0.0f;
-#pragma unroll
-        for (int b = 0; b < kLevelBlocks; ++b) {
-            if (b * kWave < S && found < 0) {
-                const bool match = valid[b] && pv[b] + cur.err[b] == target;
-                const unsigned long long mask = __ballot(match);
-                if (mask) {
-                    const int first = __builtin_ctzll(mask);
-                    found = b * kWave + first;
-                    next_t = __shfl(u[b], first, kWave);
-                    next_target = __shfl(pv[b], first, kWave);
-                }
-            }
-        }
-        if (found < 0) {     // cannot happen on a filled record
-            ok = false;
-            break;
-        }
+    auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
+    const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, tstar[solve], 0, L, L, S, prof);
+    if (t < 0) {
         if (lane == 0)
-            prof[l] = (int16_t)found;
-        t = next_t;
-        target = next_target;
-    }
-    if (!ok) {
-        for (int l = lane; l < L; l += kWave)
-            prof[l] = -2;
-        if (lane == 0) {
-            cost[k] = __builtin_nanf("");
-            if constexpr (kBlocks)
-                tstar[k] = -2;                   // the blocks below are marked the same way
-        }
+            cost[solve] = t == -1 ? __builtin_inff() : __builtin_nanf("");
         return;
     }
-    if constexpr (kBlocks) {
-        if (lb > 0) {                            // more blocks follow: hand the time down
-            if (lane == 0)
-                tstar[k] = t;
-            return;
-        }
-    }
-    // Lane 0 wrote the profile; make it visible to the wave, then re-sum the cost in layer order.
-    // Lane i fetches the error of layer 64 b + i (all layers of a block of 64 in one round trip
-    // instead of one after the other); the sum itself runs over the lanes in order.
-    __threadfence();
-    float acc = -0.0f;
-    for (int base = 0; base < L; base += kWave) {
-        const int l = base + lane;
-        float e = 0.0f;
-        if (l < L)
-            e = src.row(k, l, L, S).at(prof[l]);
-        const int n = min(kWave, L - base);
-        for (int i = 0; i < n; ++i)
-            acc += lane_value(e, i);
-    }
+    const float acc = profile_cost(mine, L, S, prof);
     if (lane == 0)
-        cost[k] = acc;
+        cost[solve] = acc;
 }
 
 int launch_status()
@@ -1844,16 +1886,21 @@ bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
         parts *= 2;
     cp->parts = parts;
     cp->parts_log2 = __builtin_ctz(parts);
-    cp->per_part = (S + parts - 1) / parts;
+    cp->per_part = ((S + parts - 1) / parts + 3) / 4 * 4;
+    cp->pad = parts * cp->per_part - S;
+    if (cp->per_part > 128)
+        return false;
     cp->step_layers = kCoreThreads / S;
-    cp->pitch = S | 1;
+    cp->pitch = (S + cp->pad) | 1;
     int window = B / 16 > 1024 ? B / 16 : 1024;
     if (window > 8192)
         window = 8192;
     if (window > B + 1)
         window = B + 1;
     cp->window = (window + kWave - 1) / kWave * kWave;
-    cp->entries = L * S < kCoreEntries ? (L * S + 1) / 2 * 2 : kCoreEntries;
+    // (some 30 levels beyond one per layer are usual, four per layer the most seen)
+    const int room = 4 * L > 256 ? 4 * L : 256;
+    cp->entries = L * S < room ? (L * S + 1) / 2 * 2 : room;
     const size_t staged = (size_t)L * cp->pitch * sizeof(float2);
     const size_t rows = 2 * sizeof(float) * (size_t)cp->window + kCoreRecord;
     const size_t table = align_up(staged > rows ? staged : rows, 16);
@@ -1865,6 +1912,24 @@ bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
     cp->record = (int)(table - 2 * sizeof(float) * (size_t)cp->window);
     cp->work = kCoreWork;
     *lds = (int)need;
+    return true;
+}
+
+// Sets up the call for the J budgets, the last of which `lay` is for; false: the full table at once.
+bool core_call(const Layout &lay, int L, int S, const int32_t *budget, int J, int16_t *profile,
+               float *cost, void *workspace, size_t workspace_bytes, CoreCall *call)
+{
+    CoreParams cp{};
+    int lds = 0, largest = 0;
+    if (lay.status != SPDY_DP_OK || !workspace)
+        return false;
+    for (int j = 0; j < J; ++j)
+        largest = budget[j] > largest ? budget[j] : largest;
+    if (!core_params(L, S, largest, &cp, &lds))
+        return false;
+    *call = CoreCall{profile, cost, budget, J,
+                     static_cast<unsigned char *>(workspace) + lay.record_off,
+                     workspace_bytes - lay.record_off};
     return true;
 }
 
@@ -2002,12 +2067,10 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
-        if (!(kBlocks && blocks.pass == 1)) {
-            const int st = launch_core(tau, src, K, L, S, prep, *core, q);
-            if (st != SPDY_DP_OK)
-                return st;
-        }
-    } else if (!(kBlocks && blocks.pass == 1)) { // the block passes reuse pass 0's tables
+        const int st = launch_core(tau, src, K, L, S, prep, *core, q);
+        if (st != SPDY_DP_OK)
+            return st;
+    } else {
         hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
     }
     const LevelTables tables{shifts, order, start, entry, s8};
@@ -2061,6 +2124,17 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
                                              Blocks{}, core);
 }
 
+void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const float *drec,
+                 const int32_t *tstar, int K, int budgets, int L, int S, int pitch,
+                 int16_t *profile, float *cost, Resume resume, Todo todo, hipStream_t q)
+{
+    const int per_block = kWalkThreads / kWave;
+    auto walk = S <= kWave ? dp_backtrace_values<1> : dp_backtrace_values<4>;
+    hipLaunchKernelGGL(walk, dim3((K * budgets + per_block - 1) / per_block), dim3(kWalkThreads), 0,
+                       q, tau, src, meta, drec, tstar, K, budgets, L, S, pitch, profile, cost,
+                       resume, todo);
+}
+
 int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B,
                    int16_t *profile, float *cost, const void *workspace, size_t workspace_bytes,
                    void *stream, Resume resume = Resume{}, Todo todo = Todo{})
@@ -2081,13 +2155,8 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
                            tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
-        const int per_block = kWalkThreads / kWave;
-        auto narrow = dp_backtrace_values<1, false>;
-        auto wide = dp_backtrace_values<4, false>;
-        hipLaunchKernelGGL(S <= kWave ? narrow : wide, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q, tau,
-                           src, meta, reinterpret_cast<const float *>(ws + lay.record_off),
-                           const_cast<int32_t *>(tstar), K, L, S, (int)lay.row, profile, cost,
-                           resume, Blocks{}, todo);
+        launch_walk(tau, src, meta, reinterpret_cast<const float *>(ws + lay.record_off), tstar, K,
+                    1, L, S, (int)lay.row, profile, cost, resume, todo, q);
     }
     return launch_status();
 }
@@ -2099,18 +2168,11 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
 {
     if (!tau || !profile || !cost)
         return SPDY_DP_ERR_NULL;
-    CoreParams cp{};
-    int lds = 0;
-    CoreCall core{profile, cost, &B, 1, nullptr, 0};
+    CoreCall core;
     Todo todo;
-    if (scratch && L > 0 && S > 0 && core_params(L, S, B, &cp, &lds)) {
-        const Layout lay = make_layout(K, L, S, B, workspace_bytes);
-        if (lay.status == SPDY_DP_OK && workspace) {
-            core.spill = static_cast<unsigned char *>(workspace) + lay.record_off;
-            core.spill_bytes = workspace_bytes - lay.record_off;
-            todo = Todo{profile, 1};
-        }
-    }
+    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), L, S, &B, 1, profile, cost,
+                             workspace, workspace_bytes, &core))
+        todo = Todo{profile, 1};
     const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
                              todo.profile ? &core : nullptr);
     if (st != SPDY_DP_OK)
@@ -2131,8 +2193,6 @@ int checkpoint_stride(int L, int stride)
     return j;
 }
 
-// Pass 0 over all layers (checkpoints, final time), then per block of `stride` layers, last
-// first: fill the block's rows from the checkpoint below it and walk through them.
 int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int stride,
                       int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
                       void *stream)
@@ -2158,39 +2218,17 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.slots = slots;
     blocks.ckpt = reinterpret_cast<float *>(ws + lay.record_off);
     blocks.block = blocks.ckpt + (size_t)K * slots * lay.row;
-    auto fill = [&]() {
-        return S <= kWave
-                   ? launch_fill<false, true, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost,
-                                                    q, blocks)
-                   : launch_fill<false, false, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost,
-                                                     q, blocks);
-    };
-    blocks.pass = 0;
-    blocks.begin = 0;
-    blocks.end = L;
-    st = fill();
-    if (st != SPDY_DP_OK)
-        return st;
-    const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
-    int32_t *tstar = reinterpret_cast<int32_t *>(ws + lay.tstar_off);
-    const int per_block = kWalkThreads / kWave;
-    blocks.pass = 1;
-    for (int b = nblocks - 1; b >= 0; --b) {
-        blocks.begin = b * j;
-        blocks.end = (b + 1) * j < L ? (b + 1) * j : L;
-        st = fill();
-        if (st != SPDY_DP_OK)
-            return st;
-        auto narrow = dp_backtrace_values<1, true>;
-        auto wide = dp_backtrace_values<4, true>;
-        hipLaunchKernelGGL(S <= kWave ? narrow : wide, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q, tau,
-                           src, meta, nullptr, tstar, K, L, S, (int)lay.row, profile, cost,
-                           Resume{}, blocks, Todo{});
-        st = launch_status();
-        if (st != SPDY_DP_OK)
-            return st;
-    }
-    return SPDY_DP_OK;
+    blocks.tau = tau;
+    blocks.profile = profile;
+    CoreCall core;
+    const bool reduced =
+        core_call(lay, L, S, &B, 1, profile, cost, workspace, workspace_bytes, &core);
+    const CoreCall *first = reduced ? &core : nullptr;
+    return S <= kWave
+               ? launch_fill<false, true, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost, q,
+                                                blocks, first)
+               : launch_fill<false, false, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost, q,
+                                                 blocks, first);
 }
 
 int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const int32_t *budgets,
@@ -2213,25 +2251,37 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
         return st;
     if (lay.variant != kValueRecord)
         return SPDY_DP_ERR_WORKSPACE;            // the last row of D is only kept in the D record
-    // one fill for the largest budget (cost[0..K) is scratch until its own walk back)
-    st = fill_impl(tau, src, K, L, S, bmax, cost, workspace, workspace_bytes, stream);
+    char *ws = static_cast<char *>(workspace);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
+    const float *drec = reinterpret_cast<const float *>(ws + lay.record_off);
+    CoreCall core;
+    Todo todo;
+    const bool reduced = core_call(lay, L, S, budgets, J, profile, cost, workspace,
+                                   workspace_bytes, &core);
+    if (reduced)
+        todo = Todo{profile, 1};
+    // one fill for the largest budget (its own argmin is not used: costs go to the words of t*)
+    st = fill_impl(tau, src, K, L, S, bmax, reinterpret_cast<float *>(ws + lay.tstar_off),
+                   workspace, workspace_bytes, stream, Resume{}, reduced ? &core : nullptr);
     if (st != SPDY_DP_OK)
         return st;
     hipStream_t q = static_cast<hipStream_t>(stream);
-    char *ws = static_cast<char *>(workspace);
-    const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
-    int32_t *tstar = reinterpret_cast<int32_t *>(ws + lay.tstar_off);
-    const float *drec = reinterpret_cast<const float *>(ws + lay.record_off);
-    for (int j = 0; j < J; ++j) {
-        float *cost_j = cost + (size_t)j * K;
-        hipLaunchKernelGGL(dp_budget_argmin, dim3(K), dim3(256), 0, q, meta, drec, L, (int)lay.row,
-                           budgets[j], tstar, cost_j);
-        st = backtrace_impl(tau, src, K, L, S, bmax, profile + (size_t)j * K * L, cost_j,
-                            workspace, workspace_bytes, stream);
-        if (st != SPDY_DP_OK)
-            return st;
+    for (int j0 = 0; j0 < J; j0 += kCoreBudgets) {
+        const int n = J - j0 < kCoreBudgets ? J - j0 : kCoreBudgets;
+        Budgets some;
+        for (int j = 0; j < n; ++j)
+            some.at[j] = budgets[j0 + j];
+        int16_t *prof = profile + (size_t)j0 * K * L;
+        float *c = cost + (size_t)j0 * K;
+        if (reduced)
+            todo.profile = prof;
+        // the times travel in the words of the costs
+        hipLaunchKernelGGL(dp_budget_argmin, dim3(K * n), dim3(256), 0, q, meta, drec, K, L,
+                           (int)lay.row, some, reinterpret_cast<int32_t *>(c), todo);
+        launch_walk(tau, src, meta, drec, reinterpret_cast<const int32_t *>(c), K, n, L, S,
+                    (int)lay.row, prof, c, Resume{}, todo, q);
     }
-    return SPDY_DP_OK;
+    return launch_status();
 }
 
 int resume_impl(const int32_t *tau, ErrSource src, const int32_t *first_layer, int K, int L, int S,
