@@ -772,7 +772,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             continue;
         }
         if (first_spilled < nsteps)
-            __threadfence();
+            __threadfence_block();
         int t = a + (int)(unsigned)key;
         uint32_t next_word = 0;
         CoreStep st{0, 0, 0, 0};

@@ -544,9 +544,9 @@ struct Resume {
     const int32_t *first_layer;   // [K] in [0, L], or nullptr: every candidate starts at layer 0
     const float *inc_rec;         // the incumbent's D record, float [L][pitch]
     const int32_t *inc_meta;      // its header: without a whole table there is nothing to resume from
-    __device__ __forceinline__ int start(int k, int L) const
+    template <bool kChecked = true> __device__ __forceinline__ int start(int k, int L) const
     {
-        if (!first_layer || !inc_meta[kMetaTable])
+        if (!first_layer || (kChecked && !inc_meta[kMetaTable]))
             return 0;
         const int f = first_layer[k];
         return f < 0 ? 0 : (f > L ? L : f);
@@ -556,20 +556,19 @@ struct Resume {
 // Solving with a fraction of the record (Sec. 3.2 counts O(L T) memory for the matrices): a
 // first pass over all layers keeps only every `stride`-th row of D (checkpoints) and finds the
 // final time; then, from the last block of `stride` layers to the first, the block's rows are
-// filled again from the checkpoint below it into a small block record and walked back by the
-// candidate's own workgroup.
+// filled again from the checkpoint below it into a small block record and walked back.
 //   pass 0 (checkpoints): layers [0, L); row l is kept at slot (l + 1) / stride - 1 when
 //                         (l + 1) is a multiple of stride and l + 1 < L
-//   later passes (blocks): layers [begin, end), starting from checkpoint slot begin / stride - 1
+//   pass 1 (one block)  : layers [begin, end), starting from checkpoint slot begin / stride - 1
 //                         (from scratch when begin = 0); row l is kept at slot l - begin of the
-//                         block record
+//                         block record; no final argmin
 struct Blocks {
+    int pass;
+    int begin, end;
     int stride;
     int slots;                    // checkpoint rows per candidate
     float *ckpt;                  // [K][slots][pitch]
     float *block;                 // [K][stride][pitch]
-    const int32_t *tau;
-    int16_t *profile;             // [K][L]
 };
 
 struct LevelEntry {   // one visited level of one layer of one candidate
@@ -748,6 +747,12 @@ struct Todo {
         for (int j = 0; j < budgets; ++j)
             any |= profile[((size_t)j * K + k) * L] == kTodo;
         return any;
+    }
+    // the same where k is the same in the whole wave, as a scalar: a row's plan depends on it, and a
+    // divergent plan would put the sweep under execution masks
+    __device__ __forceinline__ bool has_wave(int k, int K, int L) const
+    {
+        return !profile || __builtin_amdgcn_readfirstlane(has(k, K, L) ? 1 : 0) != 0;
     }
 };
 
@@ -1271,7 +1276,7 @@ __device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
                                               const int16_t *__restrict__ prof)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    __threadfence();
+    __threadfence_block();
     float acc = -0.0f;
     for (int base = 0; base < L; base += kWave) {
         const int l = base + lane;
@@ -1305,8 +1310,11 @@ __device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
 //   kNarrow  : S <= 64, one lane per level: the next layer's table is loaded without dependent
 //              loads while a layer is swept (a separate instantiation, so that the waits of the
 //              two ways of loading do not meet in one control-flow join)
-//   kBlocks  : all passes of the small-record solve, with their walks back (D record only); the
+//   kBlocks  : the checkpoint / block passes of the small-record solve (D record only); the
 //              plain instantiation ignores `blocks`
+//   kTodo    : behind dp_core, only the candidates it gave up (a separate instantiation: the test
+//              for them changes how the compiler lays out and schedules the loops of the other
+//              calls; B = 10^5, K = 128 was 1.5 % slower with it)
 //   kTurns   : the workgroups that share a compute unit take turns at the instruction priority
 //              (see the layer loop); `units` is the number of compute units
 //   kSplit   : launched with twice the waves the plan was made for (D record, in place, S <= 64,
@@ -1317,8 +1325,8 @@ __device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
 //              record, row and the final argmin are the first half's.  The partial rows of the
 //              second half lie in LDS behind the smaller allocation (the launch gets twice that).
 // `pitch` is the record's row pitch (elements per (k, l) row).
-template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTurns = false,
-          bool kSplit = false>
+template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo = false,
+          bool kTurns = false, bool kSplit = false>
 __global__ __launch_bounds__(fill_waves<kLevel>() * (kSplit || kPath >= 3 ? 2 : 1) * kWave,
                              kLevel ? 8 : 4)
 void dp_fill(
@@ -1345,13 +1353,9 @@ void dp_fill(
     const int bp = meta[kMetaBudget];
     const int tid = threadIdx.x, nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
-        if (todo.has(blockIdx.x, K, L)) {
-            if constexpr (kBlocks)
-                for (int l = tid; l < L; l += nthreads)
-                    blocks.profile[(size_t)blockIdx.x * L + l] = -1;
-            if (tid == 0)
-                write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
-        }
+        if (tid == 0 && !(kBlocks && blocks.pass == 1) &&
+            (!kTodo || todo.has_wave(blockIdx.x, K, L)))
+            write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
         return;
     }
     tables.limit = kGlobal ? bp : INT32_MAX;     // only the tiles of global rows depend on it
@@ -1359,10 +1363,10 @@ void dp_fill(
     const int tw = meta[kMetaTeamWaves];
     if ((long long)blockIdx.x * teams >= K)
         return;                                  // the first ceil(K / teams) workgroups suffice
-    if (todo.profile) {
+    if constexpr (kTodo) {
         bool any = false;
         for (int i = 0; i < teams && blockIdx.x * teams + i < (unsigned)K; ++i)
-            any |= todo.has(blockIdx.x * teams + i, K, L);
+            any |= todo.has_wave(blockIdx.x * teams + i, K, L);
         if (!any)
             return;                              // solved already
     }
@@ -1385,7 +1389,7 @@ void dp_fill(
     const bool mirrored = (tw & (tw - 1)) == 0 && ((wave >> 2) & 1);
     const int share = mirrored ? wv ^ (min(tw, 4) - 1) : wv;
     const int k = blockIdx.x * teams + team;
-    const bool active = team < teams && k < K && todo.has(k, K, L);
+    const bool active = team < teams && k < K && (!kTodo || todo.has_wave(k, K, L));
 
     // rows: [apron | row] once (in place) or twice per team
     const int stride = kHalo + (kLds ? row : pitch);
@@ -1395,10 +1399,6 @@ void dp_fill(
     float *buf0 = base + kHalo;
     float *buf1 = inplace ? buf0 : buf0 + stride;
 
-    // one pass, or those of the small-record solve: [lb, le) are the layers to fill
-    int lb = 0, le = L;
-    bool first_pass = true;
-next_pass:
     // D before the first layer: time 0 costs nothing, nothing else is reachable (Eq. 3 then is
     // the general update).  -0.0f + e returns e bit for bit for every e, +0.0f would not for
     // e = -0.0f.  Aprons and chunks a layer does not compute keep this +inf.
@@ -1417,7 +1417,8 @@ next_pass:
 
     // a candidate that shares its first l0 layers with the incumbent starts from the incumbent's
     // row l0 - 1, placed where layer l0 reads its previous row
-    const int l0 = active ? resume.start(k, L) : 0;
+    // (a call that does not go through dp_core resumes from one that did not either)
+    const int l0 = active ? resume.start<kTodo>(k, L) : 0;
     if (l0 > 0 && lead) {
         float *dst = (l0 & 1) ? buf1 : buf0;
         const float *from = resume.inc_rec + (size_t)(l0 - 1) * pitch;
@@ -1430,6 +1431,8 @@ next_pass:
     if (resume.first_layer)
         __syncthreads();
     // a block pass starts from the checkpoint below the block
+    const int lb = kBlocks ? blocks.begin : 0;   // layers [lb, le) are filled
+    const int le = kBlocks ? blocks.end : L;
     if constexpr (kBlocks) {
         if (lb > 0) {
             float *dst = (lb & 1) ? buf1 : buf0;
@@ -1450,8 +1453,8 @@ next_pass:
     uint8_t *choice_k = kLevel ? choice + ke * L * pitch : nullptr;
     float *drec_k = kLevel ? nullptr : drec + ke * L * pitch;
     if constexpr (kBlocks)
-        drec_k = first_pass ? blocks.ckpt + ke * blocks.slots * pitch
-                            : blocks.block + ke * blocks.stride * pitch;
+        drec_k = blocks.pass == 0 ? blocks.ckpt + ke * blocks.slots * pitch
+                                  : blocks.block + ke * blocks.stride * pitch;
 
     // lane i keeps visited entry i of the layer being swept; the next layer's is fetched early
     const int s8 = tables.s8;
@@ -1541,7 +1544,7 @@ next_pass:
         uint8_t *choice_l = kLevel ? choice_k + (size_t)l * pitch : nullptr;
         float *drec_l = kLevel ? nullptr : drec_k + (size_t)l * pitch;
         if constexpr (kBlocks) {
-            if (!first_pass)
+            if (blocks.pass == 1)
                 drec_l = drec_k + (size_t)(l - lb) * pitch;
             else if ((l + 1) % blocks.stride == 0 && l + 1 < L)
                 drec_l = drec_k + (size_t)((l + 1) / blocks.stride - 1) * pitch;
@@ -1630,63 +1633,32 @@ next_pass:
         __syncthreads();
     }
 
-    if (!kBlocks || first_pass) {
-        // final argmin over t' <= bp within each team
-        const float *last = (L & 1) ? buf1 : buf0;
-        float bv = __builtin_inff();
-        int bt = INT32_MAX;
-        if (active && lead)
-            for (int t = wv * kWave + lane; t <= bp; t += tw * kWave)
-                argmin_merge(bv, bt, last[t], t);
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-            const float ov = __shfl_down(bv, off, kWave);
-            const int ot = __shfl_down(bt, off, kWave);
-            argmin_merge(bv, bt, ov, ot);
-        }
-        if (lane == 0 && lead) {
-            s_best[wave] = bv;
-            s_time[wave] = bt;
-        }
-        __syncthreads();
-        if (active && lead && wv == 0 && lane == 0) {
-            for (int w = 1; w < tw; ++w)
-                argmin_merge(bv, bt, s_best[wave + w], s_time[wave + w]);
-            write_result(bv, bt, k, tstar, cost);
-        }
-    }
     if constexpr (kBlocks) {
-        // the block's rows are walked by the first wave of the candidate's team, then comes the
-        // block below
-        __threadfence();
-        __syncthreads();
-        if (!first_pass && active && wv == 0) {
-            auto row_of = [&](int l) {
-                return l >= lb ? blocks.block + ((size_t)k * blocks.stride + (l - lb)) * pitch
-                               : blocks.ckpt + ((size_t)k * blocks.slots +
-                                                (lb / blocks.stride - 1)) * pitch;
-            };
-            int16_t *prof = blocks.profile + (size_t)k * L;
-            const int t = walk_layers<kNarrow ? 1 : 4>(blocks.tau, mine, meta, row_of, tstar[k],
-                                                       lb, le, L, S, prof);
-            if (lane == 0)
-                tstar[k] = t;
-            if (t == -2 && lane == 0)
-                cost[k] = __builtin_nanf("");
-            if (lb == 0 && t >= 0) {
-                const float acc = profile_cost(mine, L, S, prof);
-                if (lane == 0)
-                    cost[k] = acc;
-            }
-        }
-        if (lb == 0 && !first_pass)
-            return;
-        le = first_pass ? L : lb;
-        lb = (le - 1) / blocks.stride * blocks.stride;
-        first_pass = false;
-        __threadfence();
-        __syncthreads();
-        goto next_pass;
+        if (blocks.pass == 1)
+            return;                              // the final time is known from pass 0
+    }
+    // final argmin over t' <= bp within each team
+    const float *last = (L & 1) ? buf1 : buf0;
+    float bv = __builtin_inff();
+    int bt = INT32_MAX;
+    if (active && lead)
+        for (int t = wv * kWave + lane; t <= bp; t += tw * kWave)
+            argmin_merge(bv, bt, last[t], t);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const float ov = __shfl_down(bv, off, kWave);
+        const int ot = __shfl_down(bt, off, kWave);
+        argmin_merge(bv, bt, ov, ot);
+    }
+    if (lane == 0 && lead) {
+        s_best[wave] = bv;
+        s_time[wave] = bt;
+    }
+    __syncthreads();
+    if (active && lead && wv == 0 && lane == 0) {
+        for (int w = 1; w < tw; ++w)
+            argmin_merge(bv, bt, s_best[wave + w], s_time[wave + w]);
+        write_result(bv, bt, k, tstar, cost);
     }
 }
 
@@ -1705,7 +1677,7 @@ __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restric
     __shared__ float s_best[4];
     __shared__ int s_time[4];
     const int solve = blockIdx.x, j = solve / K, k = solve - j * K, tid = threadIdx.x;
-    if (!todo.has(solve, K, L))
+    if (!todo.has_wave(solve, K, L))
         return;
     const int budget = budgets.at[j];
     const int bp = meta[kMetaBudget];
@@ -1783,7 +1755,7 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
         cost[k] = __builtin_nanf("");
         return;
     }
-    __threadfence();
+    __threadfence_block();
     float acc = -0.0f;
     for (int l = 0; l < L; ++l)
         acc += src.row(k, l, L, S).at(prof[l]);
@@ -1801,7 +1773,7 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int lane = threadIdx.x & (kWave - 1);
     const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
     const int k = budgets > 1 ? solve % K : solve;
-    if (solve >= K * budgets || !todo.has(solve, K, L))
+    if (solve >= K * budgets || !todo.has_wave(solve, K, L))
         return;
     int16_t *prof = profile + (size_t)solve * L;
     const ErrSource mine = src.of_candidate(k, L, S);
@@ -1817,6 +1789,41 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const float acc = profile_cost(mine, L, S, prof);
     if (lane == 0)
         cost[solve] = acc;
+}
+
+// The walk through one block of layers [blocks.begin, blocks.end) of the small-record solve: rows
+// come from the block record, the row below the block from its checkpoint; tstar holds the time
+// to start from and receives the time below the block; the cost is summed after the first block
+// (the last one walked).
+template <int kLevelBlocks>
+__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    int32_t *__restrict__ tstar, int K, int L, int S, int pitch, int16_t *__restrict__ profile,
+    float *__restrict__ cost, Blocks blocks, Todo todo)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    if (k >= K || !todo.has_wave(k, K, L))
+        return;
+    int16_t *prof = profile + (size_t)k * L;
+    const ErrSource mine = src.of_candidate(k, L, S);
+    const int lb = blocks.begin;
+    auto row_of = [&](int l) {
+        return l >= lb ? blocks.block + ((size_t)k * blocks.stride + (l - lb)) * pitch
+                       : blocks.ckpt + ((size_t)k * blocks.slots + (lb / blocks.stride - 1)) * pitch;
+    };
+    const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, tstar[k], lb, blocks.end, L, S,
+                                            prof);
+    if (lane == 0) {
+        tstar[k] = t;                            // -2: the blocks below are marked the same way
+        if (t == -2)
+            cost[k] = __builtin_nanf("");
+    }
+    if (t < 0 || lb > 0)
+        return;
+    const float acc = profile_cost(mine, L, S, prof);
+    if (lane == 0)
+        cost[k] = acc;
 }
 
 int launch_status()
@@ -1957,10 +1964,10 @@ int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const Pr
     return launch_status();
 }
 
-template <bool kLevel, bool kNarrow, bool kBlocks = false>
+template <bool kLevel, bool kNarrow, bool kBlocks, bool kTodo>
 int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
-                int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks = Blocks{},
-                const CoreCall *core = nullptr)
+                int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks,
+                const CoreCall *core)
 {
     int32_t *meta = reinterpret_cast<int32_t *>(ws + lay.meta_off);
     int32_t *shifts = reinterpret_cast<int32_t *>(ws + lay.shifts_off);
@@ -2012,8 +2019,8 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
         wide ? ((long long)nchunks > (long long)wide_waves * wide_group ||
                 row_bytes > (size_t)kLdsBytes)
              : need > (size_t)kLdsBytes;
-    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, true>
-                          : dp_fill<kLevel, 1, kNarrow, kBlocks, false>;
+    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, true>
+                          : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false>;
     // A candidate that has a compute unit to itself gets twice the waves (the second half takes
     // every other pair of each layer's entries and needs a second row in LDS for its minima).
     constexpr bool can_split = !kLevel && kNarrow && !kBlocks;
@@ -2021,7 +2028,7 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     int place_threads = waves * kWave, place_lds = lds_small;
     if constexpr (can_split) {
         if (split) {
-            in_place = dp_fill<kLevel, 1, kNarrow, kBlocks, false, true>;
+            in_place = dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, true>;
             place_threads *= 2;
             place_lds *= 2;
             static_assert(2 * kLdsHalf <= kLdsBytes, "two half allocations fit one workgroup");
@@ -2031,9 +2038,9 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
                 return SPDY_DP_ERR_LAUNCH;
         }
     }
-    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks>;
-    auto in_global = dp_fill<kLevel, 0, kNarrow, kBlocks>;
-    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks>;   // (3 when it exists)
+    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kTodo>;
+    auto in_global = dp_fill<kLevel, 0, kNarrow, kBlocks, kTodo>;
+    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kTodo>;   // (3 when it exists)
     // The D record's global-row launch also has twice the waves (one workgroup per compute unit
     // with all of its LDS for the window; measured against two workgroups of the usual size with
     // half the LDS each: 11 % faster on a batch of four candidates per unit).
@@ -2041,7 +2048,7 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     const int global_waves = wide_global ? 2 * waves : waves;
     if constexpr (can_widen) {
         if (wide_global)
-            in_global = dp_fill<kLevel, 4, kNarrow, kBlocks>;
+            in_global = dp_fill<kLevel, 4, kNarrow, kBlocks, kTodo>;
     }
     if (wide &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(wide_place),
@@ -2067,10 +2074,12 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
-        const int st = launch_core(tau, src, K, L, S, prep, *core, q);
-        if (st != SPDY_DP_OK)
-            return st;
-    } else {
+        if (!(kBlocks && blocks.pass == 1)) {
+            const int st = launch_core(tau, src, K, L, S, prep, *core, q);
+            if (st != SPDY_DP_OK)
+                return st;
+        }
+    } else if (!(kBlocks && blocks.pass == 1)) { // the block passes reuse pass 0's tables
         hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
     }
     const LevelTables tables{shifts, order, start, entry, s8};
@@ -2087,6 +2096,16 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
         hipLaunchKernelGGL(in_global, dim3(K), dim3(global_waves * kWave), lds_stage, q, src, meta, tables,
                            units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
     return launch_status();
+}
+
+template <bool kLevel, bool kNarrow, bool kBlocks = false>
+int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
+                int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks,
+                const CoreCall *core)
+{
+    auto launch = core ? launch_fill<kLevel, kNarrow, kBlocks, true>
+                       : launch_fill<kLevel, kNarrow, kBlocks, false>;
+    return launch(lay, tau, src, resume, K, L, S, B, ws, cost, q, blocks, core);
 }
 
 int validate(const Layout &lay, const void *workspace)
@@ -2193,6 +2212,8 @@ int checkpoint_stride(int L, int stride)
     return j;
 }
 
+// Pass 0 over all layers (checkpoints, final time), then per block of `stride` layers, last
+// first: fill the block's rows from the checkpoint below it and walk through them.
 int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int stride,
                       int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
                       void *stream)
@@ -2218,17 +2239,43 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.slots = slots;
     blocks.ckpt = reinterpret_cast<float *>(ws + lay.record_off);
     blocks.block = blocks.ckpt + (size_t)K * slots * lay.row;
-    blocks.tau = tau;
-    blocks.profile = profile;
     CoreCall core;
     const bool reduced =
         core_call(lay, L, S, &B, 1, profile, cost, workspace, workspace_bytes, &core);
-    const CoreCall *first = reduced ? &core : nullptr;
-    return S <= kWave
-               ? launch_fill<false, true, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost, q,
-                                                blocks, first)
-               : launch_fill<false, false, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost, q,
-                                                 blocks, first);
+    const Todo todo = reduced ? Todo{profile, 1} : Todo{};
+    auto fill = [&]() {
+        const CoreCall *first = reduced ? &core : nullptr;
+        return S <= kWave
+                   ? launch_fill<false, true, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost,
+                                                    q, blocks, first)
+                   : launch_fill<false, false, true>(lay, tau, src, Resume{}, K, L, S, B, ws, cost,
+                                                     q, blocks, first);
+    };
+    blocks.pass = 0;
+    blocks.begin = 0;
+    blocks.end = L;
+    st = fill();
+    if (st != SPDY_DP_OK)
+        return st;
+    const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
+    int32_t *tstar = reinterpret_cast<int32_t *>(ws + lay.tstar_off);
+    const int per_block = kWalkThreads / kWave;
+    blocks.pass = 1;
+    for (int b = nblocks - 1; b >= 0; --b) {
+        blocks.begin = b * j;
+        blocks.end = (b + 1) * j < L ? (b + 1) * j : L;
+        st = fill();
+        if (st != SPDY_DP_OK)
+            return st;
+        auto walk = S <= kWave ? dp_backtrace_blocks<1> : dp_backtrace_blocks<4>;
+        hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
+                           tau, src, meta, tstar, K, L, S, (int)lay.row, profile, cost, blocks,
+                           todo);
+        st = launch_status();
+        if (st != SPDY_DP_OK)
+            return st;
+    }
+    return SPDY_DP_OK;
 }
 
 int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const int32_t *budgets,

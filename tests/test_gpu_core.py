@@ -1,0 +1,144 @@
+"""The reduced problem (csrc/dp_core.h) against the oracle, bit for bit, at the sizes where its
+mapping changes: threads per layer and layers per workgroup, levels per thread, rows and records that
+outgrow their LDS, and batches in which some candidates have to fall back to the full table."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dp():
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2201_13096_amd as m
+    m.binding.lib()
+    return m
+
+
+def smooth(rng, K, L, S, B, speedup=2.5):
+    """Tables of a compressed network: times fall and errors rise with the level."""
+    keep = 0.05 ** (np.arange(S) / max(1, S - 1))
+    dense = rng.lognormal(0.0, 0.8, L)
+    t = dense[:, None] * (0.2 + 0.8 * keep) * (speedup * B / dense.sum())
+    err = rng.random((K, L, 1)) * (1.0 - keep) ** 2
+    return np.floor(t + 0.5).astype(np.int32), err.astype(np.float32)
+
+
+def same(got, want, what):
+    (p, c), (p_ref, c_ref) = got, want
+    assert (c.cpu().numpy().view(np.uint32) == c_ref.view(np.uint32)).all(), f"{what}: costs"
+    assert (p.cpu().numpy() == p_ref).all(), f"{what}: profiles"
+
+
+def check(dp, tau, err, B, what):
+    print(f"[core] {what} K={err.shape[0]} L={err.shape[1]} S={err.shape[2]} B={B}", flush=True)
+    want = oracle.solve_ref(tau, err, B, threads=16)
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(np.ascontiguousarray(err)).cuda()
+    same(dp.spdy_dp_solve_batched(tau_d, err_d, B), want, what)
+    return tau_d, err_d, want
+
+
+# layers: one thread to 64 per layer, the last layer of a workgroup, one more than it takes;
+# levels: remainders of four, of the threads of a layer and of 64 levels per thread
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 31, 64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("S", [1, 2, 5, 64, 67])
+def test_layers_and_levels(dp, L, S):
+    rng = np.random.default_rng(1000 * L + S)
+    B = 3 * L + 40
+    tau, err = smooth(rng, 5, L, S, B)
+    check(dp, tau, err, B, "smooth")
+    tau, err, _ = workloads.random_instance(rng, 3, L, S, B, tau_max=8, zero_tau_frac=0.1,
+                                            inf_err_frac=0.05, over_budget_frac=0.05)
+    err[2] = -0.0                                # ties everywhere, and the sign of a zero
+    check(dp, tau, err, B, "unstructured")
+
+
+@pytest.mark.parametrize("S", [128, 129, 255])
+def test_many_levels(dp, S):
+    rng = np.random.default_rng(S)
+    for L in (9, 130):                           # 130: more than 64 levels per thread, or no LDS
+        tau, err = smooth(rng, 3, L, S, 1500)
+        check(dp, tau, err, 1500, "many levels")
+
+
+def test_rows_and_records_that_outgrow_their_lds(dp):
+    """Few layers with large times: windows of thousands of buckets, records that spill, limits
+    that are exceeded (then the target is halved, or the full table takes over)."""
+    rng = np.random.default_rng(77)
+    for (K, L, S, B) in [(6, 6, 40, 60000), (4, 24, 60, 30000), (5, 12, 12, 100000)]:
+        tau, err = smooth(rng, K, L, S, B)
+        check(dp, tau, err, B, "long rows")
+        tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=B // 4)
+        check(dp, tau, err, B, "long rows, unstructured")
+
+
+def test_batches_that_only_partly_reduce(dp):
+    """A negative error or a NaN-free overflow sends a candidate to the full table; its neighbours
+    (teams share a workgroup there) must not be touched.  All calls that reduce."""
+    rng = np.random.default_rng(5)
+    K, L, S, B = 37, 20, 30, 3000
+    tau, err = smooth(rng, K, L, S, B)
+    err[3::5, L // 2] -= 0.125
+    err[6] *= np.float32(2.0 ** 126)             # sums beyond the range of fp32
+    tau[7, 3] = 2 ** 31 - 1
+    tau_d, err_d, want = check(dp, tau, err, B, "mixed")
+    for stride in (0, 3):
+        same(dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, stride), want, f"stride {stride}")
+    budgets = [B, B // 2, int(tau.min(axis=1).sum()) - 1, 0] + [B - 7 * j for j in range(66)]
+    p, c = dp.spdy_dp_solve_budgets(tau_d, err_d, budgets)
+    for j, b in enumerate(budgets):
+        same((p[j], c[j]), oracle.solve_ref(tau, err, b, threads=16), f"budget {b}")
+    # an incumbent whose workspace holds no table: the candidates are solved from the first layer
+    first = torch.full((K,), L // 4, dtype=torch.int32, device="cuda")
+    shared = err.copy()
+    shared[:, :L // 4] = err[:1, :L // 4]
+    for negative in (False, True):
+        ws = dp.alloc_workspace(1, L, S, B)
+        c0, w0 = torch.rand((1, L), device="cuda"), torch.rand(S, device="cuda")
+        dp.spdy_dp_solve_sensitivities(tau_d, -c0 if negative else c0, w0, B, workspace=ws)
+        got = dp.spdy_dp_solve_from_incumbent(tau_d, torch.from_numpy(shared).cuda(), first, B, ws)
+        same(got, oracle.solve_ref(tau, shared, B, threads=16), "incumbent without a table")
+
+
+def test_subnormal_and_infinite_errors(dp):
+    rng = np.random.default_rng(9)
+    for scale in (2.0 ** -140, 2.0 ** -126, 1.0):
+        tau, err = smooth(rng, 6, 15, 20, 900)
+        err = (err * np.float32(scale)).astype(np.float32)
+        err[1, 4] = np.inf                       # a layer without a level
+        err[2, :, ::2] = np.inf
+        check(dp, tau, err, 900, f"scale {scale}")
+
+
+def test_a_reduced_solve_replays_from_a_graph(dp):
+    rng = np.random.default_rng(12)
+    K, L, S, B = 9, 14, 20, 2500
+    tables = [smooth(rng, K, L, S, B) for _ in range(2)]
+    tau = tables[0][0]
+    errs = [t[1] for t in tables]
+    errs[1][4, 2] -= 0.5                         # one candidate for the full table
+    want = [oracle.solve_ref(tau, e, B) for e in errs]
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(errs[0]).cuda()
+    ws = torch.empty(dp.spdy_dp_workspace_bytes_checkpointed(K, L, S, B), dtype=torch.uint8,
+                     device="cuda")
+    profile = torch.empty((K, L), dtype=torch.int16, device="cuda")
+    cost = torch.empty((K,), dtype=torch.float32, device="cuda")
+    dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, 0, profile, cost, ws)
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, 0, profile, cost, ws)
+    for rep in range(4):
+        err_d.copy_(torch.from_numpy(errs[rep % 2]).cuda())
+        profile.fill_(-9)
+        cost.fill_(-9.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        same((profile, cost), want[rep % 2], f"replay {rep}")
