@@ -34,7 +34,9 @@
  *     add is monotone in the addend: when D itself is recorded they are served by one update
  *     with the smallest of their errors (the walk back still picks the smallest level); when
  *     the level is recorded, a level is not visited if an earlier one of the same time has an
- *     error no larger (the strict "<" could never select it).
+ *     error no larger (the strict "<" could never select it);
+ *   - where the table is not left to the caller (see spdy_dp_solve_profiles), levels and cells
+ *     that a Lagrangian bound proves to lie on no optimal profile are not visited at all.
  *
  * What is recorded per cell for the walk back depends on the workspace the caller provides:
  *   - spdy_dp_workspace_bytes():     D itself (fp32 per cell); the fill then needs only an add
@@ -155,7 +157,7 @@ int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float 
                                 int S, int B, int16_t *profile, float *cost, void *workspace,
                                 size_t workspace_bytes, void *stream);
 
-/* Several budgets from one fill.  D_l[t] is the least error at EXACTLY time t (Eq. 2-3), so the
+/* Several budgets from one call.  D_l[t] is the least error at EXACTLY time t (Eq. 2-3), so the
  * table does not depend on the budget: it is filled once for max_j budgets[j], and for every
  * budget the final argmin runs over t <= budgets[j] and the levels are walked back from there
  * (profiles for a range of speed-up targets at the cost of one fill).  Results equal J separate
@@ -220,7 +222,8 @@ int spdy_dp_solve_checkpointed(const int32_t *tau, const float *err, int K, int 
  *          twice the waves of [8], the second half dividing each layer's levels with the first
  *          (D record, S <= 64, no more candidates than compute units), [14] waves of launch 3
  *          (0: not enqueued), [15] most chunks one of them keeps in registers, [16] its dynamic
- *          LDS bytes, [17] waves of the global-row launch.  Per-layer arrays follow the
+ *          LDS bytes, [17] waves of the global-row launch, [18] 1 if the call left the whole table
+ *          in the record, 0 if the workspace was scratch.  Per-layer arrays follow the
  *          out[6] header words: m_l at [out[6] + l], the number of computed 64-bucket chunks of
  *          layer l at [out[6] + L + l], the largest usable shift of layer l at
  *          [out[6] + (2 + out[7]) L + l]

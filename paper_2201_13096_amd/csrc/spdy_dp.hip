@@ -92,6 +92,7 @@ constexpr bool kInPlaceFits =
     2 * (kFillWaves * kMaxGroup * kWave + kWave + kHalo) * 4 > kLdsHalf &&
     2 * (kFillWavesLevel * kMaxGroupLevel * kWave + kWave + kHalo) * 4 > kLdsHalf;
 static_assert(kInPlaceFits, "path 1 must be exactly the in-place case");
+constexpr int kPrepareLoads = 20;         // times a thread of the prepare kernel loads at once
 constexpr int kBatch = 8;                 // level tables are padded to a multiple of this
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
@@ -260,13 +261,13 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
     for (int l = l0; l < l1; ++l) {
         const int32_t *tau_l = tau + (size_t)l * S;
         int m = INT32_MAX;
-        for (int s0 = 0; s0 < S; s0 += 8) {       // eight loads in flight per round trip
-            int v[8];
+        for (int s0 = 0; s0 < S; s0 += kPrepareLoads) {   // so many in flight per round trip
+            int v[kPrepareLoads];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < kPrepareLoads; ++i)
                 v[i] = tau_l[min(s0 + i, S - 1)];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < kPrepareLoads; ++i)
                 m = min(m, v[i]);
         }
         mn[l] = m;
@@ -340,13 +341,13 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         if (bp >= 0) {
             const int32_t *tau_l = tau + (size_t)l * S;
             const int m = mn[l];
-            for (int s0 = 0; s0 < S; s0 += 8) {
-                int v[8];
+            for (int s0 = 0; s0 < S; s0 += kPrepareLoads) {
+                int v[kPrepareLoads];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
+                for (int i = 0; i < kPrepareLoads; ++i)
                     v[i] = tau_l[min(s0 + i, S - 1)];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < kPrepareLoads; ++i) {
                     const long long d = (long long)v[i] - m;
                     if (d <= bp)
                         span = max(span, (int)d);
@@ -392,21 +393,25 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
 {
     __shared__ int32_t s_shift[256];
     __shared__ int32_t s_level[256];
+    __shared__ int32_t s_tau[256];                // the layer's times: every thread reads them all
     __shared__ int s_entries;
     const int s = threadIdx.x;
     int32_t *shifts_l = shifts + (size_t)l * s8;
     int32_t *order_l = order + (size_t)l * s8;
     bool twin = false;                            // a later level of the layer takes the same time
+    const int mine = s < S ? tau[(size_t)l * S + s] : INT32_MAX;
+    s_tau[s] = mine;
+    __syncthreads();
     if (s < S) {
-        const int32_t *tau_l = tau + (size_t)l * S;
-        const int mine = tau_l[s];
         int rank = 0, m = INT32_MAX;
+#pragma unroll 8
         for (int o = 0; o < S; ++o)
-            m = min(m, tau_l[o]);
+            m = min(m, s_tau[o]);
         const int residues = sorted == 2 ? 3 : 0;
         const int mine_class = (mine - m) & residues;
+#pragma unroll 8
         for (int o = 0; o < S; ++o) {
-            const int other = tau_l[o];
+            const int other = s_tau[o];
             const int other_class = (other - m) & residues;
             const bool before = other_class != mine_class ? other_class < mine_class
                                                           : (other < mine || (other == mine && o < s));
@@ -1922,9 +1927,22 @@ bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
     return true;
 }
 
-// Sets up the call for the J budgets, the last of which `lay` is for; false: the full table at once.
-bool core_call(const Layout &lay, int L, int S, const int32_t *budget, int J, int16_t *profile,
-               float *cost, void *workspace, size_t workspace_bytes, CoreCall *call)
+// A few candidates with a handful of layers and short rows are through the full table before dp_core
+// is through its dozen passes.  Measured, in 0.1 us of latency: the table 1.2 us a layer for its
+// barriers, 0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a
+// layer (L = 8, S = 8, B = 256: 21.5 us a call with the table, 21.9 us with dp_core; L = 54, S = 40,
+// B = 10^4: 224 and 60 us).  (Of the sizes and K <= 256 alone, so that a call that resumes from an
+// incumbent is only taken directly where the incumbent's, K = 1, was.)
+bool table_is_short(int K, int L, int S, int B)
+{
+    return K <= 256 && 19LL * L + (long long)L * S * (B + 1LL) / 5000 < 140 + 6LL * L;
+}
+
+// Sets up the call for the J budgets, the largest of which `lay` is for; false: the full table at
+// once.
+bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, int J,
+               int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
+               CoreCall *call)
 {
     CoreParams cp{};
     int lds = 0, largest = 0;
@@ -1932,7 +1950,7 @@ bool core_call(const Layout &lay, int L, int S, const int32_t *budget, int J, in
         return false;
     for (int j = 0; j < J; ++j)
         largest = budget[j] > largest ? budget[j] : largest;
-    if (!core_params(L, S, largest, &cp, &lds))
+    if (!core_params(L, S, largest, &cp, &lds) || table_is_short(K, L, S, largest))
         return false;
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
@@ -2189,7 +2207,7 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
         return SPDY_DP_ERR_NULL;
     CoreCall core;
     Todo todo;
-    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), L, S, &B, 1, profile, cost,
+    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1, profile, cost,
                              workspace, workspace_bytes, &core))
         todo = Todo{profile, 1};
     const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
@@ -2241,7 +2259,7 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.block = blocks.ckpt + (size_t)K * slots * lay.row;
     CoreCall core;
     const bool reduced =
-        core_call(lay, L, S, &B, 1, profile, cost, workspace, workspace_bytes, &core);
+        core_call(lay, K, L, S, &B, 1, profile, cost, workspace, workspace_bytes, &core);
     const Todo todo = reduced ? Todo{profile, 1} : Todo{};
     auto fill = [&]() {
         const CoreCall *first = reduced ? &core : nullptr;
@@ -2303,7 +2321,7 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
     const float *drec = reinterpret_cast<const float *>(ws + lay.record_off);
     CoreCall core;
     Todo todo;
-    const bool reduced = core_call(lay, L, S, budgets, J, profile, cost, workspace,
+    const bool reduced = core_call(lay, K, L, S, budgets, J, profile, cost, workspace,
                                    workspace_bytes, &core);
     if (reduced)
         todo = Todo{profile, 1};

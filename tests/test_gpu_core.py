@@ -50,9 +50,10 @@ def check(dp, tau, err, B, what):
 def test_layers_and_levels(dp, L, S):
     rng = np.random.default_rng(1000 * L + S)
     B = 3 * L + 40
-    tau, err = smooth(rng, 5, L, S, B)
+    K = 260 if L <= 10 else 5                    # (a few candidates of few layers take the table)
+    tau, err = smooth(rng, K, L, S, B)
     check(dp, tau, err, B, "smooth")
-    tau, err, _ = workloads.random_instance(rng, 3, L, S, B, tau_max=8, zero_tau_frac=0.1,
+    tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=8, zero_tau_frac=0.1,
                                             inf_err_frac=0.05, over_budget_frac=0.05)
     err[2] = -0.0                                # ties everywhere, and the sign of a zero
     check(dp, tau, err, B, "unstructured")
