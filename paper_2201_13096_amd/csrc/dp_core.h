@@ -24,9 +24,14 @@
 // a negative time, sums near the end of the fp32 range, more surviving levels, wider rows or
 // more work than the limits of the launch.
 //
-// What bounds it: latency.  A candidate is about 15 passes over its L * S table in LDS (a few
-// hundred clocks each, ended by a barrier), then L dependent steps of one wave for the reduced
-// table and L for the walk back.
+// What bounds it: latency.  A candidate of L = 54, S = 40 is about 11 passes over its table in LDS for
+// the multiplier (2300 clocks each: a scan of twelve levels per thread, two joins, a barrier),
+// five for the known profile, then 15 dependent steps of 1700 clocks for the reduced table and 500
+// for each step back; one wave per SIMD issues an instruction every seven or eight clocks whatever
+// it is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Kernel time
+// against fill and walk back of the whole table: K = 100, L = 52, S = 42, B = 10^4: 71 us / 297 us;
+// K = 4096, L = 72, S = 40, B = 16384: 290 us / 3.34 ms; K = 333, S = 127: 101 us / 0.92 ms;
+// K = 256, L = 200, S = 64, B = 65536: 0.36 / 4.2 ms.
 
 constexpr int16_t kTodo = -3;            // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
@@ -177,6 +182,7 @@ struct CoreBooks {       // where the steps of the reduced table have got to
 
 struct CoreShared {      // static LDS of the kernel
     float2 sum[2][kCoreWaves];               // (err, tau) of a path, by wave; times as int bits
+    float2 ends[2][kCoreWaves];              // the same of the least-time and the least-error path
     unsigned long long key[2][kCoreWaves];
     int2 change[2][kCoreWaves];              // of the wave's best exchange: error (bits), time
     int2 place[2][kCoreWaves];               // sums of the entries (and steps), of the times
@@ -312,8 +318,29 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         lo_t = __builtin_bit_cast(float, (unsigned)by_err);
         hi_e = __builtin_bit_cast(float, (unsigned)by_time);
         hi_t = __builtin_bit_cast(float, (unsigned)(by_time >> 32));
-        path_sum(hi_e, hi_t, c_hi, t_hi);
-        path_sum(lo_e, lo_t, c_lo, t_lo);
+        // both sums through one barrier
+        const float he = from_lane(wave_scan(lead ? hi_e : 0.0f, 0.0f, Add{}), kWave - 1);
+        const float le = from_lane(wave_scan(lead ? lo_e : 0.0f, 0.0f, Add{}), kWave - 1);
+        const int ht = from_lane(wave_scan(lead ? (int)hi_t : 0, 0, Add{}), kWave - 1);
+        const int lt = from_lane(wave_scan(lead ? (int)lo_t : 0, 0, Add{}), kWave - 1);
+        if (lane == 0) {
+            sh.ends[0][wave] = make_float2(he, __builtin_bit_cast(float, ht));
+            sh.ends[1][wave] = make_float2(le, __builtin_bit_cast(float, lt));
+        }
+        __syncthreads();
+        c_hi = c_lo = 0.0f;
+        t_hi = t_lo = 0;
+#pragma unroll
+        for (int w = 0; w < kCoreWaves; ++w) {
+            c_hi += sh.ends[0][w].x;
+            t_hi += __builtin_bit_cast(int, sh.ends[0][w].y);
+            c_lo += sh.ends[1][w].x;
+            t_lo += __builtin_bit_cast(int, sh.ends[1][w].y);
+        }
+        c_hi = uniform(c_hi);
+        c_lo = uniform(c_lo);
+        t_hi = uniform(t_hi);
+        t_lo = uniform(t_lo);
     }
     if (t_hi > B) {                               // also where a layer has no level to choose
         if (tid < L)

@@ -92,7 +92,7 @@ constexpr bool kInPlaceFits =
     2 * (kFillWaves * kMaxGroup * kWave + kWave + kHalo) * 4 > kLdsHalf &&
     2 * (kFillWavesLevel * kMaxGroupLevel * kWave + kWave + kHalo) * 4 > kLdsHalf;
 static_assert(kInPlaceFits, "path 1 must be exactly the in-place case");
-constexpr int kPrepareLoads = 20;         // times a thread of the prepare kernel loads at once
+constexpr int kPrepareLoads = 10;         // times a thread of the prepare kernel loads at once
 constexpr int kBatch = 8;                 // level tables are padded to a multiple of this
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
@@ -1930,7 +1930,7 @@ bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
 // A few candidates with a handful of layers and short rows are through the full table before dp_core
 // is through its dozen passes.  Measured, in 0.1 us of latency: the table 1.2 us a layer for its
 // barriers, 0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a
-// layer (L = 8, S = 8, B = 256: 21.5 us a call with the table, 21.9 us with dp_core; L = 54, S = 40,
+// layer (L = 8, S = 8, B = 256: 22.5 us a call with the table, 22 - 23 us with dp_core; L = 54, S = 40,
 // B = 10^4: 224 and 60 us).  (Of the sizes and K <= 256 alone, so that a call that resumes from an
 // incumbent is only taken directly where the incumbent's, K = 1, was.)
 bool table_is_short(int K, int L, int S, int B)
