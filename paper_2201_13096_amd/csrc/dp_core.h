@@ -38,12 +38,14 @@ constexpr int kCoreThreads = 256;
 constexpr int kCoreWaves = kCoreThreads / kWave;
 constexpr int kCoreMaxLayers = kCoreThreads;
 constexpr int kCoreMaxBudget = 1 << 22;  // times stay exact in fp32, a level and a shift in 32 bits
+constexpr int kCoreShiftBits = 23;       // a shift is at most the budget
+static_assert(kCoreMaxBudget < 1 << kCoreShiftBits && 255ull << kCoreShiftBits <= UINT32_MAX,
+              "a level and a shift share a word");
 constexpr int kCoreExtra = 32;           // levels beyond one per layer that are not worth halving
 constexpr int kCoreNarrow = 2;           // chunks of a row that one wave does alone
 constexpr int kCoreTrips = 6;            // attempts, counting a halving before the first
 constexpr int kCoreBudgets = 64;         // budgets per launch
 constexpr float kCoreFar = 16777216.0f;  // "time" of a level that may not be chosen
-constexpr int kCoreShiftBits = 22;
 
 struct CoreStep {        // a layer of the reduced problem with more than one level left
     int layer;

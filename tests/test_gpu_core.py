@@ -143,3 +143,15 @@ def test_a_reduced_solve_replays_from_a_graph(dp):
         graph.replay()
         torch.cuda.synchronize()
         same((profile, cost), want[rep % 2], f"replay {rep}")
+
+
+@pytest.mark.parametrize("B", [2 ** 22 - 1, 2 ** 22, 2 ** 22 + 1])
+def test_a_shift_as_long_as_the_largest_budget(dp, B):
+    """A level that takes the whole budget in a layer whose fastest takes none: its shift needs one
+    bit more than the budget below, and must not run into the level it is packed with."""
+    tau = np.array([[5, B, 0], [B - 100] * 3], dtype=np.int32)
+    err = np.array([[[1, .5, .5], [.1, .2, .3]], [[9, 0, 5], [0, 0, 0]], [[5, 0, 9], [1, 0, 0]]],
+                   dtype=np.float32)
+    check(dp, tau, err, B, "three levels")
+    tau = np.array([[B, 5, 0], [B - 100, B, B]], dtype=np.int32)
+    check(dp, tau, np.array([[[0, 9, 5], [0, 0, 0]]], dtype=np.float32), B, "one usable level")
