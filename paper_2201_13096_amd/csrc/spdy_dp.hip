@@ -1958,6 +1958,15 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
     return true;
 }
 
+// Budgets that one launch takes with a workgroup of 256 threads per (candidate, budget): a grid of
+// 2^32 threads is refused.
+int budgets_per_launch(int K, int L)
+{
+    static_assert(kCoreThreads == 256, "2^24 workgroups are 2^32 threads");
+    const long long fit = ((1LL << 24) - 1 - (L + 1LL)) / K;
+    return fit < 1 ? 1 : (fit < kCoreBudgets ? (int)fit : kCoreBudgets);
+}
+
 int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const PrepareArgs &prep,
                 const CoreCall &call, hipStream_t q)
 {
@@ -1968,14 +1977,15 @@ int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const Pr
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_core),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
-    for (int j0 = 0; j0 < call.budgets; j0 += kCoreBudgets) {
-        cp.budgets = call.budgets - j0 < kCoreBudgets ? call.budgets - j0 : kCoreBudgets;
+    const int most = budgets_per_launch(K, L);
+    for (int j0 = 0; j0 < call.budgets; j0 += most) {
+        cp.budgets = call.budgets - j0 < most ? call.budgets - j0 : most;
         for (int j = 0; j < cp.budgets; ++j)
             cp.budget[j] = call.budget[j0 + j];
         cp.spill = call.spill;
         const size_t each = call.spill_bytes / ((size_t)K * cp.budgets) / 16 * 16;
         cp.spill_bytes = each < (size_t)INT32_MAX ? (long long)each : INT32_MAX;
-        hipLaunchKernelGGL(dp_core, dim3(L + 1 + K * cp.budgets), dim3(kCoreThreads), lds, q, tau,
+        hipLaunchKernelGGL(dp_core, dim3(L + 1 + (unsigned)K * cp.budgets), dim3(kCoreThreads), lds, q, tau,
                            src, K, L, S, prep, cp, call.profile + (size_t)j0 * K * L,
                            call.cost + (size_t)j0 * K);
     }
@@ -2331,8 +2341,9 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
     if (st != SPDY_DP_OK)
         return st;
     hipStream_t q = static_cast<hipStream_t>(stream);
-    for (int j0 = 0; j0 < J; j0 += kCoreBudgets) {
-        const int n = J - j0 < kCoreBudgets ? J - j0 : kCoreBudgets;
+    const int most = budgets_per_launch(K, L);
+    for (int j0 = 0; j0 < J; j0 += most) {
+        const int n = J - j0 < most ? J - j0 : most;
         Budgets some;
         for (int j = 0; j < n; ++j)
             some.at[j] = budgets[j0 + j];

@@ -155,3 +155,25 @@ def test_a_shift_as_long_as_the_largest_budget(dp, B):
     check(dp, tau, err, B, "three levels")
     tau = np.array([[B, 5, 0], [B - 100, B, B]], dtype=np.int32)
     check(dp, tau, np.array([[[0, 9, 5], [0, 0, 0]]], dtype=np.float32), B, "one usable level")
+
+
+def test_more_solves_than_one_launch_takes(dp):
+    """K * J beyond 2^24 workgroups of 256 threads, the largest grid: several launches, of the reduced
+    solve and of what stands behind it (every tenth candidate has a negative error)."""
+    rng = np.random.default_rng(24)
+    n, L, S, B, J = 110, 2, 3, 9, 70
+    K = 2 ** 24 // 64 + 37
+    tau = rng.integers(0, 7, size=(L, S)).astype(np.int32)
+    err = rng.random((n, L, S), dtype=np.float32)
+    err[::10, 1, 1] = -0.25
+    budgets = [int(b) for b in rng.integers(0, B + 1, size=J)]
+    p_ref, c_ref = oracle.solve_budgets_ref(tau, err, budgets)
+    which = torch.arange(K, device="cuda") % n
+    print(f"[core] budgets J={J} K={K} L={L} S={S} B={B}", flush=True)
+    p, c = dp.spdy_dp_solve_budgets(torch.from_numpy(tau).cuda(),
+                                    torch.from_numpy(err).cuda()[which], budgets)
+    want_p, want_c = torch.from_numpy(p_ref).cuda(), torch.from_numpy(c_ref).cuda()
+    for j in range(J):
+        assert torch.equal(p[j], want_p[j][which]), f"budget {j}: profiles"
+        assert torch.equal(c[j].view(torch.int32), want_c[j][which].view(torch.int32)), \
+            f"budget {j}: costs"
