@@ -45,7 +45,8 @@ constexpr int kCoreExtra = 32;           // levels beyond one per layer that are
 constexpr int kCoreNarrow = 2;           // chunks of a row that one wave does alone
 constexpr int kCoreTrips = 6;            // attempts, counting a halving before the first
 constexpr int kCoreBudgets = 64;         // budgets per launch
-constexpr float kCoreFar = 16777216.0f;  // "time" of a level that may not be chosen
+constexpr float kCoreFar = kCoreMaxBudget + 1;   // "time" of a level that may not be chosen
+static_assert(kCoreMaxLayers * (long long)kCoreFar <= INT32_MAX, "times are summed in int");
 
 struct CoreStep {        // a layer of the reduced problem with more than one level left
     int layer;
@@ -499,7 +500,8 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     double target = (double)upper, beyond = __builtin_inf();   // (beyond: exceeded the limits)
     bool first_try = true;
     auto halved = [&](double x) { return relaxed + 0.5 * (x - relaxed); };
-    for (int trip = 0; trip < kCoreTrips; ++trip) {
+    const bool in_range = upper < 1e38f && lambda_f < 1e30f;   // (false for a NaN, too)
+    for (int trip = 0; trip < kCoreTrips && in_range; ++trip) {
         const double keep_to = least + (target + (L - 1) * hu - relaxed + margin);
         int count = 0, first_t = INT32_MAX, last_t = -1;
         unsigned long long kept[2] = {0, 0};      // bit i: level s_begin + i (per_part <= 128)
@@ -537,14 +539,12 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         base_t = uniform(base_t);
         turn ^= 1;
         const int total = all & 0xFFFF, nsteps = all >> 16;
-        if (first_try && total - nsteps > kCoreExtra && upper < 1e38f) {
+        if (first_try && total - nsteps > kCoreExtra) {
             first_try = false;
             target = halved(target);
             continue;
         }
         first_try = false;
-        if (!(upper < 1e38f) || !(lambda_f < 1e30f))
-            break;
         bool wide = total > cp.entries;           // exceeds the limits
         bool failed = wide || base_t > B;
         int place = before & 0xFFFF;

@@ -43,6 +43,24 @@ def check(dp, tau, err, B, what):
     return tau_d, err_d, want
 
 
+def solve_marked(dp, tau_d, err_d, B):
+    """spdy_dp_solve_profiles on a workspace of a known pattern.  The words of t* are written by the
+    launches of the full table alone, so which candidates went there can be read off them."""
+    K, L, S = err_d.shape
+    ws = dp.alloc_workspace(K, L, S, B)
+    at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
+    ws[at:at + 4 * K].fill_(0xAB)
+    profile = torch.empty((K, L), dtype=torch.int16, device="cuda")
+    cost = torch.empty((K,), dtype=torch.float32, device="cuda")
+    status = dp.binding.lib().spdy_dp_solve_profiles(
+        tau_d.data_ptr(), err_d.data_ptr(), K, L, S, B, profile.data_ptr(), cost.data_ptr(),
+        ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert status == 0, dp.spdy_dp_strerror(status)
+    torch.cuda.synchronize()
+    words = ws[at:at + 4 * K].cpu().numpy().view(np.uint32)
+    return (profile, cost), words != 0xABABABAB
+
+
 # layers: one thread to 64 per layer, the last layer of a workgroup, one more than it takes;
 # levels: remainders of four, of the threads of a layer and of 64 levels per thread
 @pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 31, 64, 65, 128, 129, 256, 257])
@@ -177,3 +195,18 @@ def test_more_solves_than_one_launch_takes(dp):
         assert torch.equal(p[j], want_p[j][which]), f"budget {j}: profiles"
         assert torch.equal(c[j].view(torch.int32), want_c[j][which].view(torch.int32)), \
             f"budget {j}: costs"
+
+
+@pytest.mark.parametrize("L", [127, 128, 130, 255, 256])
+def test_layers_without_a_level(dp, L):
+    """Many layers without a level that may be chosen: the sum of their least times stays beyond
+    every budget, so such a candidate is settled without the full table."""
+    rng = np.random.default_rng(L)
+    K, S, B = 300, 5, 4 * L
+    tau, err = smooth(rng, K, L, S, B)
+    err[::3] = np.inf
+    err[1::3, ::2] = np.inf
+    tau_d, err_d, want = check(dp, tau, err, B, "layers without a level")
+    got, filled = solve_marked(dp, tau_d, err_d, B)
+    same(got, want, "marked workspace")
+    assert np.isinf(want[1][::3]).all() and not filled.any()
