@@ -1168,9 +1168,12 @@ __device__ __forceinline__ void argmin_merge(float &bv, int &bt, float v, int t)
     }
 }
 
+// kNoCost: `cost` may be nullptr, the time is all that the caller asked for.
+template <bool kNoCost>
 __device__ __forceinline__ void write_result(float bv, int bt, int k, int32_t *tstar, float *cost)
 {
-    cost[k] = bv;
+    if (!kNoCost || cost)
+        cost[k] = bv;
     tstar[k] = (bv < __builtin_inff()) ? bt : -1;   // -1: no profile meets the budget
 }
 
@@ -1360,7 +1363,7 @@ void dp_fill(
     if (bp < 0) {                                // even the fastest levels exceed the budget
         if (tid == 0 && !(kBlocks && blocks.pass == 1) &&
             (!kTodo || todo.has_wave(blockIdx.x, K, L)))
-            write_result(__builtin_inff(), 0, blockIdx.x, tstar, cost);
+            write_result<kTodo>(__builtin_inff(), 0, blockIdx.x, tstar, cost);
         return;
     }
     tables.limit = kGlobal ? bp : INT32_MAX;     // only the tiles of global rows depend on it
@@ -1663,7 +1666,7 @@ void dp_fill(
     if (active && lead && wv == 0 && lane == 0) {
         for (int w = 1; w < tw; ++w)
             argmin_merge(bv, bt, s_best[wave + w], s_time[wave + w]);
-        write_result(bv, bt, k, tstar, cost);
+        write_result<kTodo>(bv, bt, k, tstar, cost);
     }
 }
 
@@ -2149,7 +2152,7 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
               void *workspace, size_t workspace_bytes, void *stream, Resume resume = Resume{},
               const CoreCall *core = nullptr)
 {
-    if (!tau || !cost)
+    if (!tau || (!cost && !core))
         return SPDY_DP_ERR_NULL;
     const Layout lay = make_layout(K, L, S, B, workspace_bytes);
     const int st = validate(lay, workspace);
@@ -2335,9 +2338,10 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
                                    workspace_bytes, &core);
     if (reduced)
         todo = Todo{profile, 1};
-    // one fill for the largest budget (its own argmin is not used: costs go to the words of t*)
-    st = fill_impl(tau, src, K, L, S, bmax, reinterpret_cast<float *>(ws + lay.tstar_off),
-                   workspace, workspace_bytes, stream, Resume{}, reduced ? &core : nullptr);
+    // one fill for the largest budget; its own costs are not used, and behind the reduced problem
+    // they are not written (cost[0..K) holds what that found under the first budget)
+    st = fill_impl(tau, src, K, L, S, bmax, reduced ? nullptr : cost, workspace, workspace_bytes,
+                   stream, Resume{}, reduced ? &core : nullptr);
     if (st != SPDY_DP_OK)
         return st;
     hipStream_t q = static_cast<hipStream_t>(stream);

@@ -210,3 +210,30 @@ def test_layers_without_a_level(dp, L):
     got, filled = solve_marked(dp, tau_d, err_d, B)
     same(got, want, "marked workspace")
     assert np.isinf(want[1][::3]).all() and not filled.any()
+
+
+def test_several_budgets_behind_the_reduced_solve(dp):
+    """What one budget's reduced solve found stays when another budget sends the candidate to the
+    full table, and the fill leaves that table's time for the largest budget."""
+    rng = np.random.default_rng(41)
+    K, L, S, B = 300, 3, 6, 4000
+    tau, err = smooth(rng, K, L, S, B)
+    fastest = int(tau.min(axis=1).sum())
+    err[1::2, 1, 2] = -0.125                     # (refused before its tables are looked at further)
+    budgets = [fastest - 1, B, fastest, B // 2]
+    ws = dp.alloc_workspace(K, L, S, B)
+    lay = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())
+    at = lay["tstar_offset"]
+    ws[at:at + 4 * K].fill_(0xAB)
+    print(f"[core] budgets {budgets} K={K} L={L} S={S}", flush=True)
+    p, c = dp.spdy_dp_solve_budgets(torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda(),
+                                    budgets, workspace=ws)
+    p_ref, c_ref = oracle.solve_budgets_ref(tau, err, budgets)
+    for j, b in enumerate(budgets):
+        same((p[j], c[j]), (p_ref[j], c_ref[j]), f"budget {b}")
+    words = ws[at:at + 4 * K].cpu().numpy().view(np.uint32)
+    filled = np.flatnonzero(words != 0xABABABAB)
+    assert np.isin(np.arange(1, K, 2), filled).all() and filled.size < K
+    for k in filled[::20]:
+        D = oracle.tables_ref(tau, err[k], B)[0]
+        assert words[k] == int(np.argmin(D[L - 1])) - fastest
