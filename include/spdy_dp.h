@@ -110,8 +110,8 @@ int spdy_dp_solve_batched(const int32_t *tau, const float *err, int K, int L, in
  * for bit) and status codes, but the workspace is scratch, its contents are unspecified
  * afterwards.  Levels and cells of the table that provably lie on no optimal profile are then left
  * out (the header of csrc/dp_core.h has the bound); a candidate on which that does not help gets the
- * full table.  The other entry points below that do not say otherwise use their workspace the same
- * way: only spdy_dp_solve_batched and spdy_dp_fill leave the table in it. */
+ * full table.  The other entry points below use their workspace the same way: only
+ * spdy_dp_solve_batched and spdy_dp_fill leave the table in it. */
 int spdy_dp_solve_profiles(const int32_t *tau, const float *err, int K, int L, int S, int B,
                            int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
                            void *stream);
@@ -140,7 +140,8 @@ int spdy_dp_fill(const int32_t *tau, const float *err, int K, int L, int S, int 
 
 /* Last loop of Alg. 1: walks back from (L-1, t*[k]) and writes profile[k] and cost[k].
  * `workspace` (same size) must be the one a spdy_dp_fill call with the same tau, err, K, L, S, B
- * has filled earlier on the same stream (or on a stream already synchronised with it). */
+ * has filled earlier on the same stream (or on a stream already synchronised with it).  If another
+ * call has used it as scratch since, no table is there: profile[k] is -2 and cost[k] NaN. */
 int spdy_dp_backtrace(const int32_t *tau, const float *err, int K, int L, int S, int B,
                       int16_t *profile, float *cost, const void *workspace,
                       size_t workspace_bytes, void *stream);
@@ -152,7 +153,9 @@ int spdy_dp_backtrace(const int32_t *tau, const float *err, int K, int L, int S,
  * the table err = fl32(c * w), bit for bit.
  *   c  in  fp32 [K][L]  sensitivities, finite (inf * 0 would be NaN)
  *   w  in  fp32 [S]     level weights, finite
- * Workspace, outputs and status codes as for spdy_dp_solve_batched. */
+ * Outputs, status codes and the sizes of the workspace as for spdy_dp_solve_batched; the workspace
+ * is scratch.  (For a table to resume from, or to walk back through, form err and call
+ * spdy_dp_solve_batched.) */
 int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float *w, int K, int L,
                                 int S, int B, int16_t *profile, float *cost, void *workspace,
                                 size_t workspace_bytes, void *stream);
@@ -166,7 +169,8 @@ int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float 
  *   profile  out int16 [J][K][L]  device
  *   cost     out fp32  [J][K]     device
  * The workspace must have at least spdy_dp_workspace_bytes(K, L, S, max budget) bytes (the D
- * record keeps the last row the argmin needs); a smaller one returns SPDY_DP_ERR_WORKSPACE. */
+ * record keeps the last row the argmin needs); a smaller one returns SPDY_DP_ERR_WORKSPACE.  It is
+ * scratch. */
 int spdy_dp_solve_budgets(const int32_t *tau, const float *err, int K, int L, int S,
                           const int32_t *budgets, int J, int16_t *profile, float *cost,
                           void *workspace, size_t workspace_bytes, void *stream);
@@ -184,9 +188,10 @@ int spdy_dp_solve_budgets(const int32_t *tau, const float *err, int K, int L, in
  *   incumbent_workspace              DEVICE; the workspace of a finished spdy_dp_solve_batched /
  *                                   spdy_dp_fill call with K = 1, the same tau, L, S, B, and at
  *                                   least spdy_dp_workspace_bytes(1, L, S, B) bytes (D record);
- *                                   it is only read
- * `workspace` (distinct from the incumbent's) needs spdy_dp_workspace_bytes(K, L, S, B) bytes; a
- * smaller one of either returns SPDY_DP_ERR_WORKSPACE.  Candidates of one workgroup step through
+ *                                   it is only read (if the call that used it last left no table
+ *                                   there, the candidates are solved from layer 0)
+ * `workspace` (distinct from the incumbent's; scratch) needs spdy_dp_workspace_bytes(K, L, S, B)
+ * bytes; a smaller one of either returns SPDY_DP_ERR_WORKSPACE.  Candidates of one workgroup step through
  * the layers together, so sorting the candidates by first_layer wastes the least. */
 int spdy_dp_solve_from_incumbent(const int32_t *tau, const float *err, const int32_t *first_layer,
                                  int K, int L, int S, int B, const void *incumbent_workspace,
@@ -202,7 +207,7 @@ int spdy_dp_solve_from_incumbent(const int32_t *tau, const float *err, const int
  *   stride   layers per block; <= 0 picks ceil(sqrt(L)); values above L act as L
  * Workspace: spdy_dp_workspace_bytes_checkpointed(K, L, S, B, stride) bytes with the SAME stride
  * (about 4 * K * (L / stride + stride) * (B + 1)); a smaller one returns SPDY_DP_ERR_WORKSPACE.
- * Everything else is as for spdy_dp_solve_batched. */
+ * It is scratch; everything else is as for spdy_dp_solve_batched. */
 size_t spdy_dp_workspace_bytes_checkpointed(int K, int L, int S, int B, int stride);
 int spdy_dp_solve_checkpointed(const int32_t *tau, const float *err, int K, int L, int S, int B,
                                int stride, int16_t *profile, float *cost, void *workspace,

@@ -1722,7 +1722,8 @@ __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// Walk back (last loop of Alg. 1).
+// Walk back (last loop of Alg. 1).  `by_itself`: not enqueued by the call that filled the record, whose
+// workspace may therefore have been scratch since; it then holds no table, and t* anything.
 
 // Level record: one lane per candidate, L dependent one-byte reads; the cost is re-summed over
 // the profile in layer order (exactly the sum Alg. 1's strict "<" sweep carries to the cell).
@@ -1731,13 +1732,19 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
                                     const uint8_t *__restrict__ choice,
                                     const int32_t *__restrict__ tstar, int K, int L, int S,
                                     int pitch, int16_t *__restrict__ profile,
-                                    float *__restrict__ cost, Todo todo)
+                                    float *__restrict__ cost, Todo todo, bool by_itself)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= K || !todo.has(k, K, L))
         return;
     int16_t *prof = profile + (size_t)k * L;
     int t = tstar[k];
+    if (by_itself && !meta[kMetaTable]) {
+        for (int l = 0; l < L; ++l)
+            prof[l] = -2;
+        cost[k] = __builtin_nanf("");
+        return;
+    }
     if (t < 0) {
         for (int l = 0; l < L; ++l)
             prof[l] = -1;
@@ -1776,7 +1783,7 @@ template <int kLevelBlocks>
 __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
     const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
-    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
+    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo, bool by_itself)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
@@ -1788,7 +1795,8 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const float *drec_k = drec + (size_t)k * L * pitch;
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
     auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
-    const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, tstar[solve], 0, L, L, S, prof);
+    const int from = by_itself && !meta[kMetaTable] ? -2 : tstar[solve];
+    const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, from, 0, L, L, S, prof);
     if (t < 0) {
         if (lane == 0)
             cost[solve] = t == -1 ? __builtin_inff() : __builtin_nanf("");
@@ -2101,7 +2109,7 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
 
     const PrepareArgs prep{2 * units, s8, B, waves, max_group, lds_small, lds_large, lds_stage,
                            kLevel ? 0 : (kNarrow ? 2 : 1), split ? 1 : 0, wide_waves, wide_group,
-                           lds_wide, global_waves, core ? 0 : 1, meta, shifts, order, start, entry};
+                           lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1, meta, shifts, order, start, entry};
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
@@ -2176,18 +2184,19 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
 
 void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const float *drec,
                  const int32_t *tstar, int K, int budgets, int L, int S, int pitch,
-                 int16_t *profile, float *cost, Resume resume, Todo todo, hipStream_t q)
+                 int16_t *profile, float *cost, Resume resume, Todo todo, bool by_itself,
+                 hipStream_t q)
 {
     const int per_block = kWalkThreads / kWave;
     auto walk = S <= kWave ? dp_backtrace_values<1> : dp_backtrace_values<4>;
     hipLaunchKernelGGL(walk, dim3((K * budgets + per_block - 1) / per_block), dim3(kWalkThreads), 0,
                        q, tau, src, meta, drec, tstar, K, budgets, L, S, pitch, profile, cost,
-                       resume, todo);
+                       resume, todo, by_itself);
 }
 
 int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B,
                    int16_t *profile, float *cost, const void *workspace, size_t workspace_bytes,
-                   void *stream, Resume resume = Resume{}, Todo todo = Todo{})
+                   void *stream, bool by_itself, Resume resume = Resume{}, Todo todo = Todo{})
 {
     if (!tau || !profile || !cost)
         return SPDY_DP_ERR_NULL;
@@ -2203,10 +2212,10 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     if (lay.variant == kLevelRecord) {
         hipLaunchKernelGGL(dp_backtrace_levels, dim3((K + kWave - 1) / kWave), dim3(kWave), 0, q,
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
-                           tstar, K, L, S, (int)lay.row, profile, cost, todo);
+                           tstar, K, L, S, (int)lay.row, profile, cost, todo, by_itself);
     } else {
         launch_walk(tau, src, meta, reinterpret_cast<const float *>(ws + lay.record_off), tstar, K,
-                    1, L, S, (int)lay.row, profile, cost, resume, todo, q);
+                    1, L, S, (int)lay.row, profile, cost, resume, todo, by_itself, q);
     }
     return launch_status();
 }
@@ -2228,7 +2237,7 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
     if (st != SPDY_DP_OK)
         return st;
     return backtrace_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream,
-                          resume, todo);
+                          false, resume, todo);
 }
 
 // The stride of the solve with checkpoints: the caller's, or about sqrt(L), which makes the
@@ -2359,7 +2368,7 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
         hipLaunchKernelGGL(dp_budget_argmin, dim3(K * n), dim3(256), 0, q, meta, drec, K, L,
                            (int)lay.row, some, reinterpret_cast<int32_t *>(c), todo);
         launch_walk(tau, src, meta, drec, reinterpret_cast<const int32_t *>(c), K, n, L, S,
-                    (int)lay.row, prof, c, Resume{}, todo, q);
+                    (int)lay.row, prof, c, Resume{}, todo, false, q);
     }
     return launch_status();
 }
@@ -2443,7 +2452,7 @@ int spdy_dp_backtrace(const int32_t *tau, const float *err, int K, int L, int S,
     if (!err)
         return SPDY_DP_ERR_NULL;
     return backtrace_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost,
-                          workspace, workspace_bytes, stream);
+                          workspace, workspace_bytes, stream, true);
 }
 
 int spdy_dp_solve_batched(const int32_t *tau, const float *err, int K, int L, int S, int B,

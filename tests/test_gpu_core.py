@@ -237,3 +237,41 @@ def test_several_budgets_behind_the_reduced_solve(dp):
     for k in filled[::20]:
         D = oracle.tables_ref(tau, err[k], B)[0]
         assert words[k] == int(np.argmin(D[L - 1])) - fastest
+
+
+@pytest.mark.parametrize("compact", [False, True], ids=["d_record", "level_record"])
+@pytest.mark.parametrize("S", [30, 70])
+def test_a_walk_back_through_a_workspace_that_was_scratch(dp, S, compact):
+    """Whatever a call leaves in its scratch workspace, t* included, a walk back through it reads no
+    table and says so; once it has been filled it walks."""
+    rng = np.random.default_rng(50 + S)
+    K, L, B = 21, 12, 2500
+    tau, err = smooth(rng, K, L, S, B)
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+    c = torch.rand((K, L), device="cuda")
+    w = torch.from_numpy(err[0, 0]).cuda()
+    want = oracle.solve_ref(tau, err, B, threads=16)
+    inc = dp.alloc_workspace(1, L, S, B)
+    dp.spdy_dp_solve_batched(tau_d, err_d[:1].contiguous(), B, workspace=inc)
+    first = torch.zeros((K,), dtype=torch.int32, device="cuda")
+    calls = {"sensitivities": lambda ws: dp.spdy_dp_solve_sensitivities(tau_d, c, w, B, workspace=ws)}
+    if not compact:
+        calls["budgets"] = lambda ws: dp.spdy_dp_solve_budgets(tau_d, err_d, [B, B // 2],
+                                                               workspace=ws)
+        calls["incumbent"] = lambda ws: dp.spdy_dp_solve_from_incumbent(tau_d, err_d, first, B, inc,
+                                                                        workspace=ws)
+        calls["checkpointed"] = lambda ws: dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, L,
+                                                                         workspace=ws)
+    for name, call in calls.items():
+        ws = dp.alloc_workspace(K, L, S, B, compact=compact)
+        at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
+        ws[at:at + 4 * K].fill_(0x7A)            # a time far outside every row
+        print(f"[core] walk back after {name} K={K} L={L} S={S} B={B}", flush=True)
+        call(ws)
+        profile = torch.full((K, L), 7, dtype=torch.int16, device="cuda")
+        cost = torch.full((K,), 7.0, dtype=torch.float32, device="cuda")
+        dp.spdy_dp_backtrace(tau_d, err_d, B, profile, cost, ws)
+        assert (profile == -2).all() and torch.isnan(cost).all(), name
+        dp.spdy_dp_fill(tau_d, err_d, B, cost, ws)
+        dp.spdy_dp_backtrace(tau_d, err_d, B, profile, cost, ws)
+        same((profile, cost), want, f"filled after {name}")
