@@ -21,8 +21,8 @@
 // candidates as in the whole table.
 //
 // What it does not take is left to the full table (profile[0] = kTodo): a negative or NaN error,
-// a negative time, sums near the end of the fp32 range, more surviving levels, wider rows or
-// more work than the limits of the launch.
+// a negative time, sums near the end of the fp32 range, more surviving levels, rows wider than both LDS
+// and memory hold, or more work than the limits of the launch.
 //
 // What bounds it: latency.  A candidate of L = 54, S = 40 is about 11 passes over its table in LDS for
 // the multiplier (2300 clocks each: a scan of twelve levels per thread, two joins, a barrier),
@@ -43,7 +43,7 @@ static_assert(kCoreMaxBudget < 1 << kCoreShiftBits && 255ull << kCoreShiftBits <
               "a level and a shift share a word");
 constexpr int kCoreExtra = 32;           // levels beyond one per layer that are not worth halving
 constexpr int kCoreNarrow = 2;           // chunks of a row that one wave does alone
-constexpr int kCoreTrips = 6;            // attempts, counting a halving before the first
+constexpr int kCoreTrips = 4;            // attempts, counting a halving before the first (two are usual)
 constexpr int kCoreBudgets = 64;         // budgets per launch
 constexpr float kCoreFar = kCoreMaxBudget + 1;   // "time" of a level that may not be chosen
 static_assert(kCoreMaxLayers * (long long)kCoreFar <= INT32_MAX, "times are summed in int");
@@ -64,13 +64,14 @@ struct CoreParams {
     int pad;             // levels per layer past the last one that are scanned with it
     int step_layers;     // kCoreThreads / S
     int pitch;           // levels per layer in LDS (odd, so that a column of levels is conflict-free)
-    int window;          // buckets a row may span
+    int window;          // buckets a row may span in LDS
     int record;          // bytes of LDS for the recorded entries
     int entries;         // room in the list
     int table_bytes;     // LDS of the staged tables; the rows and the record reuse it
     int work;            // sweeps of 64 buckets by one entry before a candidate is given up
     unsigned char *spill;        // rows that do not fit the LDS record, per candidate and budget
     long long spill_bytes;
+    int far;                     // kFar: buckets of the two rows in memory, before each record there
     int budgets;                 // J
     int32_t budget[kCoreBudgets];
 };
@@ -175,6 +176,9 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
     return (unsigned long long)high << 32 | low;
 }
 
+// A row in memory.  (A pointer that might also be one to LDS would be read by flat instructions.)
+using FarRow = __attribute__((address_space(1))) float *;
+
 template <int N> struct Many {
     static constexpr int value = N;
 };
@@ -195,7 +199,10 @@ struct CoreShared {      // static LDS of the kernel
 };
 
 // One candidate (error source `src` seen from candidate k) under budget B.  Returns through
-// profile / cost; profile[0] = kTodo if the full table has to do it.
+// profile / cost; profile[0] = kTodo if the full table has to do it.  kFar: a row that spans more
+// buckets than the window lies in memory, before the record that `spill` is for (wide steps end
+// with a barrier, which makes them visible); otherwise it is too wide.
+template <bool kFar>
 __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, const ErrSource src,
                                            int L, int S, int B, const CoreParams &cp,
                                            unsigned char *spill, unsigned char *lds,
@@ -499,6 +506,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     // limits of the launch is halved, too.
     double target = (double)upper, beyond = __builtin_inf();   // (beyond: exceeded the limits)
     bool first_try = true;
+    int work = 0;                                 // of all attempts
     auto halved = [&](double x) { return relaxed + 0.5 * (x - relaxed); };
     const bool in_range = upper < 1e38f && lambda_f < 1e30f;   // (false for a NaN, too)
     for (int trip = 0; trip < kCoreTrips && in_range; ++trip) {
@@ -596,7 +604,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             }
             return v;
         };
-        const CoreEntry none{__builtin_inff(), 0};
+        auto none = []() __attribute__((always_inline)) { return CoreEntry{__builtin_inff(), 0}; };
         // lane i holds step base_step + i
         int base_step = 0;
         CoreStep held_step{L, 0, 0, 0};
@@ -611,9 +619,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             held_limit = limit[until - 1];
         };
         float *prev = row0;
+        int far_prev = -1;                        // where the previous row is, if it lies in memory
+        auto far_row = [&](int at) __attribute__((always_inline)) {
+            return (FarRow) reinterpret_cast<float *>(spill) - 2 * cp.far + at;
+        };
         int a = 0, b = 0;                         // buckets of the previous row that still matter
-        int used = 0, spilled = 0, first_spilled = nsteps, work = 0;
-        CoreEntry next = none;
+        int used = 0, spilled = 0, first_spilled = nsteps;
+        CoreEntry next = none();
         if (!failed) {
             load_steps(0);
             const float v = add_singles(-0.0f, 0, nsteps ? __builtin_amdgcn_readlane(
@@ -621,11 +633,11 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                                                          : L);
             if (tid == 0)
                 prev[0] = v;
-            next = lane < total ? list[lane] : none;
+            next = lane < total ? list[lane] : none();
         }
         __syncthreads();
         // The best of n entries, in order, for bucket a + x; `en`: lane i holds entry i.
-        auto visit = [&](CoreEntry en, int i, int x, unsigned reach, int index, float &best,
+        auto visit = [&](auto row, CoreEntry en, int i, int x, unsigned reach, int index, float &best,
                          int &arg, auto width) __attribute__((always_inline)) {
             constexpr int kMany = decltype(width)::value;
             const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
@@ -634,7 +646,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             for (int q = 0; q < kMany; ++q) {
                 const int u = x - __builtin_amdgcn_readlane(shift, i + q);
                 const bool ok = (unsigned)u <= reach;
-                const float d = prev[ok ? u : 0];
+                const float d = row[ok ? u : 0];
                 p[q] = (ok ? d : __builtin_inff()) + lane_value(en.err, i + q);
             }
 #pragma unroll
@@ -669,12 +681,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                     break;
                 }
                 alone = narrow;
-                const CoreEntry held_entry = lane < n ? next : none;
+                const CoreEntry held_entry = lane < n ? next : none();
                 const int follow = first + n + lane;   // the next step's entries
-                next = follow < total ? list[follow] : none;
+                next = follow < total ? list[follow] : none();
                 work += n * chunks;
                 const bool spills = first_spilled < nsteps || used + width > cp.record;
-                if (width > cp.window || work > cp.work ||
+                const bool to_far = kFar && width > cp.window;
+                if (width > (to_far ? cp.far : cp.window) || work > cp.work ||
                     (spills && spilled + width > cp.spill_bytes)) {
                     failed = wide = true;
                     break;
@@ -689,27 +702,44 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 spilled += spills ? width : 0;
                 used += spills ? 0 : width;
                 float *const cur = prev >= row1 ? row0 : row1;
+                const int far_cur = far_prev >= 0 && far_prev < cp.far ? cp.far : 0;
                 const unsigned reach = (unsigned)(b - a);
                 int low = INT32_MAX, high = -1;   // live buckets of the new row, from a
                 for (int c = narrow ? 0 : wave; c < chunks; c += narrow ? 1 : kCoreWaves) {
                     const int x = c * kWave + lane;
                     float best = __builtin_inff();
                     int arg = 0;
-                    if (n <= 2) {
-                        visit(held_entry, 0, x, reach, 0, best, arg, Many<2>{});
-                    } else {
+                    auto visit_all = [&](auto row) __attribute__((always_inline)) {
                         for (int blk = 0; blk < n; blk += kWave) {
                             CoreEntry en = held_entry;
                             if (blk > 0)
-                                en = blk + lane < n ? list[first + blk + lane] : none;
+                                en = blk + lane < n ? list[first + blk + lane] : none();
                             for (int i = 0; i < min(kWave, n - blk); i += 4)
-                                visit(en, i, x, reach, blk + i, best, arg, Many<4>{});
+                                visit(row, en, i, x, reach, blk + i, best, arg, Many<4>{});
+                        }
+                    };
+                    if (kFar && far_prev >= 0) {
+                        visit_all(far_row(far_prev));
+                    } else if (n <= 2) {
+                        visit(prev, held_entry, 0, x, reach, 0, best, arg, Many<2>{});
+                    } else if constexpr (kFar) {
+                        visit_all(prev);
+                    } else {                      // (as visit_all; through it 2 - 3 % slower at L = 10)
+                        for (int blk = 0; blk < n; blk += kWave) {
+                            CoreEntry en = held_entry;
+                            if (blk > 0)
+                                en = blk + lane < n ? list[first + blk + lane] : none();
+                            for (int i = 0; i < min(kWave, n - blk); i += 4)
+                                visit(prev, en, i, x, reach, blk + i, best, arg, Many<4>{});
                         }
                     }
                     best = add_singles(best, (layers_m & 0xFFFF) + 1, layers_m >> 16);
                     const bool in = x < width;
                     if (in) {
-                        cur[x] = best;
+                        if (kFar && to_far)
+                            far_row(far_cur)[x] = best;
+                        else
+                            cur[x] = best;
                         out[x] = (unsigned char)arg;
                     }
                     const bool live =
@@ -741,7 +771,10 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 }
                 b = a + high;
                 a = a + low;
-                prev = cur + low;
+                if constexpr (kFar)
+                    far_prev = to_far ? far_cur + low : -1;
+                if (!kFar || !to_far)
+                    prev = cur + low;
                 if (!narrow || m == nsteps)
                     break;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -761,13 +794,14 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 first_spilled = uniform(books.first_spilled);
                 work = uniform(books.work);
                 prev = row0 + uniform(books.prev);
+                far_prev = -1;                    // (narrow rows fit the window)
                 failed = uniform(books.failed) != 0;
                 wide = uniform(books.wide) != 0;
                 if (m < nsteps && !failed) {
                     if (m - base_step >= kWave)
                         load_steps(m);
                     const int at = __builtin_amdgcn_readlane(held_step.first, m - base_step) + lane;
-                    next = at < total ? list[at] : none;
+                    next = at < total ? list[at] : none();
                 }
                 __syncthreads();                  // the books may be written again
             }
@@ -777,9 +811,11 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         unsigned long long key = ~0ull;
         if (!failed) {
             for (int x = lane; x <= b - a; x += kWave)
-                key = Smaller{}(key, pair_key(magnitude(prev[x]), x));
+                key = Smaller{}(key, pair_key(magnitude(kFar && far_prev >= 0 ? far_row(far_prev)[x] : prev[x]), x));
             key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
-            const float value = uniform(prev[(unsigned)key]);   // the sum over the profile in layer order
+            const unsigned at = (unsigned)key;
+            // the sum over the profile in layer order
+            const float value = uniform(kFar && far_prev >= 0 ? far_row(far_prev)[at] : prev[at]);
             failed = !((double)value <= target);
             if (!failed) {
                 if (wave != 0)
@@ -793,7 +829,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         if (failed) {
             beyond = wide ? target : beyond;
             target = wide ? halved(target) : (double)upper;
-            if (!(target < beyond))
+            if (!(target < beyond) || work > cp.work)
                 break;
             __syncthreads();                      // every wave is through with the rows
             stage();

@@ -720,6 +720,7 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 
 // One workgroup per candidate (and budget); the first L + 1 workgroups do what dp_prepare does, for
 // the launches of the full table that follow and take the candidates this one gives up.
+template <bool kFar>
 __global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restrict__ tau,
                                                         ErrSource src, int K, int L, int S,
                                                         PrepareArgs prep, CoreParams cp,
@@ -734,9 +735,10 @@ __global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restric
     }
     const int solve = (int)blockIdx.x - (L + 1);  // candidate k under budget j
     const int j = solve / K, k = solve - j * K;
-    solve_core(tau, src.of_candidate(k, L, S), L, S, cp.budget[j], cp,
-               cp.spill + (size_t)solve * cp.spill_bytes, core_lds, sh, profile + (size_t)solve * L,
-               cost + solve);
+    const size_t rows = kFar ? 2 * (size_t)cp.far * sizeof(float) : 0;
+    solve_core<kFar>(tau, src.of_candidate(k, L, S), L, S, cp.budget[j], cp,
+                     cp.spill + (size_t)solve * (rows + cp.spill_bytes) + rows, core_lds, sh,
+                     profile + (size_t)solve * L, cost + solve);
 }
 
 // Whether the launches of the full table have to solve candidate k: every one, or (behind
@@ -1894,13 +1896,24 @@ struct CoreCall {
 };
 
 // LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
-// The staged tables, L * S pairs, have to fit LDS.  Rows: the surviving window of a row was at
-// most 4 % of the budget over the timing tables of the benchmark's kind (typically 1 %); 1024
-// buckets cover that up to B = 16384 in less LDS than the staged tables of a network take, so
-// the number of candidates a compute unit holds is not reduced by them.
-constexpr int kCoreRecord = 8192;     // least LDS for the recorded entries (7 KB at the most seen)
-constexpr int kCoreWork = 4096;       // sweeps of 64 buckets; one wave takes some 20 ns for each
-bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
+// The staged tables, L * S pairs, have to fit LDS.  What a row may span is taken from the LDS that a
+// workgroup can have without lowering how many a compute unit holds (registers allow four).  On
+// the timing tables of the performance cases' kinds the widest row of one candidate in a hundred
+// spans 3 B / L buckets and more, none in three thousand spanned 6 B / L (L = 8 - 48), so no more is
+// asked for.  Where there is less than 4 B / L, rows that need more lie in memory, which an
+// instantiation of its own allows for (4 % slower where none does: the registers).  Giving such a
+// candidate up costs most of the reduced solve and then the whole table: L = 17, S = 14, B = 43125, K = 20:
+// 235 us with eight of them given up, 132 with the rows in LDS, 124 for the full table at
+// once; L = 11, S = 9, B = 30006, K = 1407 (806 given up): 329, 211 with rows in memory, 272.
+// Rows are not worth any price, though: fewer than one candidate in a hundred needed a sixteenth of the
+// sweeps of the full table, and a table that needs more (ties everywhere, errors linear in the
+// times) is given up there, after as long again as the full table takes at the worst measured.
+constexpr int kCoreRecord = 8192;     // least LDS for the recorded entries
+constexpr int kCoreWork = 4096;       // sweeps of 64 buckets in any case; one wave takes 20 ns for each
+constexpr int kCorePerUnit = 4;       // workgroups that a compute unit has registers for
+constexpr int kCoreStatic = 4096;     // static LDS of dp_core, rounded up
+static_assert(sizeof(CoreShared) + 3 * 256 * sizeof(int32_t) + 128 <= kCoreStatic, "static LDS");
+bool core_params(int L, int S, int B, long long workgroups, int units, CoreParams *cp, int *lds)
 {
     if (L > kCoreMaxLayers || B > kCoreMaxBudget || S > 255)
         return false;
@@ -1915,26 +1928,39 @@ bool core_params(int L, int S, int B, CoreParams *cp, int *lds)
         return false;
     cp->step_layers = kCoreThreads / S;
     cp->pitch = (S + cp->pad) | 1;
-    int window = B / 16 > 1024 ? B / 16 : 1024;
-    if (window > 8192)
-        window = 8192;
-    if (window > B + 1)
-        window = B + 1;
-    cp->window = (window + kWave - 1) / kWave * kWave;
-    // (some 30 levels beyond one per layer are usual, four per layer the most seen)
+    // (some 30 levels beyond one per layer are usual, nine per layer the most seen)
     const int room = 4 * L > 256 ? 4 * L : 256;
     cp->entries = L * S < room ? (L * S + 1) / 2 * 2 : room;
-    const size_t staged = (size_t)L * cp->pitch * sizeof(float2);
-    const size_t rows = 2 * sizeof(float) * (size_t)cp->window + kCoreRecord;
-    const size_t table = align_up(staged > rows ? staged : rows, 16);
-    const size_t need = table + cp->entries * sizeof(CoreEntry) + (size_t)(L + 1) * sizeof(double) +
-                        (size_t)L * (sizeof(CoreStep) + sizeof(float) + sizeof(int));
-    if (need > (size_t)kLdsBytes)
+    const size_t lists = cp->entries * sizeof(CoreEntry) + (size_t)(L + 1) * sizeof(double) +
+                         (size_t)L * (sizeof(CoreStep) + sizeof(float) + sizeof(int));
+    const size_t staged = align_up((size_t)L * cp->pitch * sizeof(float2), 16);
+
+    const long long rounds = (workgroups + units - 1) / units;
+    // (LDS is given out in steps of 1280 bytes: a third of it, to the byte, fits only twice)
+    const size_t share = rounds <= 1 ? (size_t)kLdsBytes
+                                     : 160 * 1024 / (rounds < kCorePerUnit ? rounds : kCorePerUnit) /
+                                               1280 * 1280 - kCoreStatic;
+    const long long most = align_up((size_t)B + 1, kWave);
+    long long wanted = (6LL * B / L > 1024 ? 6LL * B / L : 1024) / kWave * kWave;
+    wanted = wanted < most ? wanted : most;
+    const size_t row = sizeof(float) * kWave;     // (LDS is divided in these units)
+    size_t table = (kCoreRecord + 2 * row * (wanted / kWave)) * 5 / 4;
+    if (table + lists > share)
+        table = share > lists ? share - lists : 0;
+    const size_t least = kCoreRecord + 2 * row * ((most < 1024 ? most : 1024) / kWave);
+    table = table > least ? table : least;
+    table = (table > staged ? table : staged) / 16 * 16;
+    if (table + lists > (size_t)kLdsBytes)
         return false;
+    const size_t record = table / 5 > (size_t)kCoreRecord ? table / 5 : (size_t)kCoreRecord;
+    const long long fit = (long long)((table - record) / (2 * row)) * kWave;
+    cp->window = (int)(fit < most ? fit : most);
+    cp->far = cp->window < most && cp->window < 4LL * B / L ? 1 : 0;        // (how far is for the caller, who knows the memory)
     cp->table_bytes = (int)table;
     cp->record = (int)(table - 2 * sizeof(float) * (size_t)cp->window);
-    cp->work = kCoreWork;
-    *lds = (int)need;
+    const long long part = (long long)L * S * (B / kWave + 1) / 16;
+    cp->work = part < kCoreWork ? kCoreWork : (part < INT32_MAX / 2 ? (int)part : INT32_MAX / 2);
+    *lds = (int)(table + lists);
     return true;
 }
 
@@ -1961,7 +1987,7 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
         return false;
     for (int j = 0; j < J; ++j)
         largest = budget[j] > largest ? budget[j] : largest;
-    if (!core_params(L, S, largest, &cp, &lds) || table_is_short(K, L, S, largest))
+    if (!core_params(L, S, largest, 1, 1, &cp, &lds) || table_is_short(K, L, S, largest))
         return false;
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
@@ -1979,25 +2005,34 @@ int budgets_per_launch(int K, int L)
 }
 
 int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const PrepareArgs &prep,
-                const CoreCall &call, hipStream_t q)
+                const CoreCall &call, int units, hipStream_t q)
 {
-    CoreParams cp{};
-    int lds = 0;
-    if (!core_params(L, S, prep.B, &cp, &lds))
-        return SPDY_DP_ERR_LAUNCH;               // callers ask first
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_core),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
-        return SPDY_DP_ERR_LAUNCH;
     const int most = budgets_per_launch(K, L);
     for (int j0 = 0; j0 < call.budgets; j0 += most) {
-        cp.budgets = call.budgets - j0 < most ? call.budgets - j0 : most;
-        for (int j = 0; j < cp.budgets; ++j)
+        const int n = call.budgets - j0 < most ? call.budgets - j0 : most;
+        const long long blocks = L + 1LL + (long long)K * n;
+        CoreParams cp{};
+        int lds = 0;
+        if (!core_params(L, S, prep.B, blocks, units, &cp, &lds))
+            return SPDY_DP_ERR_LAUNCH;           // callers ask first
+        cp.budgets = n;
+        for (int j = 0; j < n; ++j)
             cp.budget[j] = call.budget[j0 + j];
+        const size_t each = call.spill_bytes / ((size_t)K * n) / 16 * 16;
+        const bool far = cp.far != 0;
+        if (far)                                 // half of the memory for two rows
+            cp.far = (int)(each / 16 < prep.B + 1u ? each / 16 : prep.B + 1u);
+        const size_t left = each - (far ? 2 * cp.far * sizeof(float) : 0);
         cp.spill = call.spill;
-        const size_t each = call.spill_bytes / ((size_t)K * cp.budgets) / 16 * 16;
-        cp.spill_bytes = each < (size_t)INT32_MAX ? (long long)each : INT32_MAX;
-        hipLaunchKernelGGL(dp_core, dim3(L + 1 + (unsigned)K * cp.budgets), dim3(kCoreThreads), lds, q, tau,
-                           src, K, L, S, prep, cp, call.profile + (size_t)j0 * K * L,
+        constexpr size_t kMost = INT32_MAX / 16 * 16;        // (rows stay aligned)
+        cp.spill_bytes = (long long)(left < kMost ? left : kMost);
+        auto core = far ? dp_core<true> : dp_core<false>;
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(core),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) !=
+            hipSuccess)
+            return SPDY_DP_ERR_LAUNCH;
+        hipLaunchKernelGGL(core, dim3((unsigned)blocks), dim3(kCoreThreads), lds, q, tau, src, K, L,
+                           S, prep, cp, call.profile + (size_t)j0 * K * L,
                            call.cost + (size_t)j0 * K);
     }
     return launch_status();
@@ -2114,7 +2149,7 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     if (core) {
         todo = Todo{core->profile, core->budgets};
         if (!(kBlocks && blocks.pass == 1)) {
-            const int st = launch_core(tau, src, K, L, S, prep, *core, q);
+            const int st = launch_core(tau, src, K, L, S, prep, *core, units, q);
             if (st != SPDY_DP_OK)
                 return st;
         }

@@ -45,11 +45,16 @@ def check(dp, tau, err, B, what):
 
 def solve_marked(dp, tau_d, err_d, B):
     """spdy_dp_solve_profiles on a workspace of a known pattern.  The words of t* are written by the
-    launches of the full table alone, so which candidates went there can be read off them."""
+    launches of the full table alone, so which candidates went there can be read off them; the first
+    word of a candidate's share of the record tells whether the reduced solve wrote to it."""
     K, L, S = err_d.shape
     ws = dp.alloc_workspace(K, L, S, B)
-    at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
+    lay = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())
+    at, record = lay["tstar_offset"], lay["record_offset"]
     ws[at:at + 4 * K].fill_(0xAB)
+    each = (ws.numel() - record) // K // 16 * 16
+    of_each = ws[record:record + K * each].view(K, each)[:, :4]
+    of_each.fill_(0xAB)
     profile = torch.empty((K, L), dtype=torch.int16, device="cuda")
     cost = torch.empty((K,), dtype=torch.float32, device="cuda")
     status = dp.binding.lib().spdy_dp_solve_profiles(
@@ -58,7 +63,8 @@ def solve_marked(dp, tau_d, err_d, B):
     assert status == 0, dp.spdy_dp_strerror(status)
     torch.cuda.synchronize()
     words = ws[at:at + 4 * K].cpu().numpy().view(np.uint32)
-    return (profile, cost), words != 0xABABABAB
+    memory = of_each.contiguous().cpu().numpy().view(np.uint32)[:, 0] != 0xABABABAB
+    return (profile, cost), words != 0xABABABAB, memory
 
 
 # layers: one thread to 64 per layer, the last layer of a workgroup, one more than it takes;
@@ -207,7 +213,7 @@ def test_layers_without_a_level(dp, L):
     err[::3] = np.inf
     err[1::3, ::2] = np.inf
     tau_d, err_d, want = check(dp, tau, err, B, "layers without a level")
-    got, filled = solve_marked(dp, tau_d, err_d, B)
+    got, filled, _ = solve_marked(dp, tau_d, err_d, B)
     same(got, want, "marked workspace")
     assert np.isinf(want[1][::3]).all() and not filled.any()
 
@@ -275,3 +281,19 @@ def test_a_walk_back_through_a_workspace_that_was_scratch(dp, S, compact):
         dp.spdy_dp_fill(tau_d, err_d, B, cost, ws)
         dp.spdy_dp_backtrace(tau_d, err_d, B, profile, cost, ws)
         same((profile, cost), want, f"filled after {name}")
+
+
+@pytest.mark.parametrize("K, L, S, B", [(20, 17, 14, 43125), (9, 21, 10, 44234), (600, 12, 11, 50000),
+                                        (5, 12, 24, 100000), (520, 12, 9, 90000)])
+def test_few_layers_with_long_rows(dp, K, L, S, B):
+    """Rows that span a tenth of the budget and more: in LDS as far as a workgroup can have it, in
+    memory beyond that (hundreds of candidates share it).  None is given up after the work is done."""
+    rng = np.random.default_rng(L * S)
+    tau, err = smooth(rng, K, L, S, B)
+    tau_d, err_d, want = check(dp, tau, err, B, "few layers, long rows")
+    got, filled, memory = solve_marked(dp, tau_d, err_d, B)
+    same(got, want, "marked workspace")
+    assert not filled.any(), f"{int(filled.sum())} of {K} went to the full table"
+    assert K < 500 or memory.any(), "some rows were meant to lie in memory"
+    for stride in (0, 1):                        # less memory for the rows of each
+        same(dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, stride), want, f"stride {stride}")
