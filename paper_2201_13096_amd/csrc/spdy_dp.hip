@@ -1724,24 +1724,26 @@ __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// Walk back (last loop of Alg. 1).  `by_itself`: not enqueued by the call that filled the record, whose
-// workspace may therefore have been scratch since; it then holds no table, and t* anything.
+// Walk back (last loop of Alg. 1).  kByItself: not enqueued by the call that filled the record, whose
+// workspace may therefore have been scratch since; it then holds no table, and t* anything.  (Not a
+// run-time flag: the load that it guards was issued all the same, 0.3 us of a walk of 6 us.)
 
 // Level record: one lane per candidate, L dependent one-byte reads; the cost is re-summed over
 // the profile in layer order (exactly the sum Alg. 1's strict "<" sweep carries to the cell).
+template <bool kByItself>
 __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource src,
                                     const int32_t *__restrict__ meta,
                                     const uint8_t *__restrict__ choice,
                                     const int32_t *__restrict__ tstar, int K, int L, int S,
                                     int pitch, int16_t *__restrict__ profile,
-                                    float *__restrict__ cost, Todo todo, bool by_itself)
+                                    float *__restrict__ cost, Todo todo)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= K || !todo.has(k, K, L))
         return;
     int16_t *prof = profile + (size_t)k * L;
     int t = tstar[k];
-    if (by_itself && !meta[kMetaTable]) {
+    if (kByItself && !meta[kMetaTable]) {
         for (int l = 0; l < L; ++l)
             prof[l] = -2;
         cost[k] = __builtin_nanf("");
@@ -1781,11 +1783,11 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
 
 // `budgets` > 1 (solve_budgets): solve j * K + k is candidate k under budget j, and its final time
 // comes in through cost (dp_budget_argmin).
-template <int kLevelBlocks>
+template <int kLevelBlocks, bool kByItself>
 __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
     const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
-    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo, bool by_itself)
+    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
@@ -1797,7 +1799,7 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const float *drec_k = drec + (size_t)k * L * pitch;
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
     auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
-    const int from = by_itself && !meta[kMetaTable] ? -2 : tstar[solve];
+    const int from = kByItself && !meta[kMetaTable] ? -2 : tstar[solve];
     const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, from, 0, L, L, S, prof);
     if (t < 0) {
         if (lane == 0)
@@ -2223,10 +2225,12 @@ void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const f
                  hipStream_t q)
 {
     const int per_block = kWalkThreads / kWave;
-    auto walk = S <= kWave ? dp_backtrace_values<1> : dp_backtrace_values<4>;
+    auto walk = S <= kWave ? dp_backtrace_values<1, false> : dp_backtrace_values<4, false>;
+    if (by_itself)
+        walk = S <= kWave ? dp_backtrace_values<1, true> : dp_backtrace_values<4, true>;
     hipLaunchKernelGGL(walk, dim3((K * budgets + per_block - 1) / per_block), dim3(kWalkThreads), 0,
                        q, tau, src, meta, drec, tstar, K, budgets, L, S, pitch, profile, cost,
-                       resume, todo, by_itself);
+                       resume, todo);
 }
 
 int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B,
@@ -2245,9 +2249,10 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     const int32_t *tstar = reinterpret_cast<const int32_t *>(ws + lay.tstar_off);
     (void)hipGetLastError();
     if (lay.variant == kLevelRecord) {
-        hipLaunchKernelGGL(dp_backtrace_levels, dim3((K + kWave - 1) / kWave), dim3(kWave), 0, q,
+        auto walk = by_itself ? dp_backtrace_levels<true> : dp_backtrace_levels<false>;
+        hipLaunchKernelGGL(walk, dim3((K + kWave - 1) / kWave), dim3(kWave), 0, q,
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
-                           tstar, K, L, S, (int)lay.row, profile, cost, todo, by_itself);
+                           tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
         launch_walk(tau, src, meta, reinterpret_cast<const float *>(ws + lay.record_off), tstar, K,
                     1, L, S, (int)lay.row, profile, cost, resume, todo, by_itself, q);
