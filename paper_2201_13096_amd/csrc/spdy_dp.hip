@@ -549,9 +549,9 @@ struct Resume {
     const int32_t *first_layer;   // [K] in [0, L], or nullptr: every candidate starts at layer 0
     const float *inc_rec;         // the incumbent's D record, float [L][pitch]
     const int32_t *inc_meta;      // its header: without a whole table there is nothing to resume from
-    template <bool kChecked = true> __device__ __forceinline__ int start(int k, int L) const
+    __device__ __forceinline__ int start(int k, int L) const
     {
-        if (!first_layer || (kChecked && !inc_meta[kMetaTable]))
+        if (!first_layer || !inc_meta[kMetaTable])
             return 0;
         const int f = first_layer[k];
         return f < 0 ? 0 : (f > L ? L : f);
@@ -1427,8 +1427,7 @@ void dp_fill(
 
     // a candidate that shares its first l0 layers with the incumbent starts from the incumbent's
     // row l0 - 1, placed where layer l0 reads its previous row
-    // (a call that does not go through dp_core resumes from one that did not either)
-    const int l0 = active ? resume.start<kTodo>(k, L) : 0;
+    const int l0 = active ? resume.start(k, L) : 0;
     if (l0 > 0 && lead) {
         float *dst = (l0 & 1) ? buf1 : buf0;
         const float *from = resume.inc_rec + (size_t)(l0 - 1) * pitch;
@@ -1966,20 +1965,29 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
     return true;
 }
 
-// A few candidates with a handful of layers and short rows are through the full table before dp_core
-// is through its dozen passes.  Measured, in 0.1 us of latency: the table 1.2 us a layer for its
-// barriers, 0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a
-// layer (L = 8, S = 8, B = 256: 22.5 us a call with the table, 22 - 23 us with dp_core; L = 54, S = 40,
-// B = 10^4: 224 and 60 us).  (Of the sizes and K <= 256 alone, so that a call that resumes from an
-// incumbent is only taken directly where the incumbent's, K = 1, was.)
-bool table_is_short(int K, int L, int S, int B)
+// Where the full table is taken at once: tables of a handful of layers with short rows are through it
+// before dp_core is through its dozen passes.
+//   - Whatever the call, up to 256 candidates, in 0.1 us of latency: the table 1.2 us a layer for its
+//     barriers, 0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a
+//     layer.  K = 1, L = 4, S = 10, B = 4351: 20 us with the table, 29 with dp_core; K = 3, L = 5, S = 54,
+//     B = 382: 27 and 40; four budgets, K = 61, L = 8, S = 51, B = 420: 41 and 61; L = S = 8, B = 256: 22 and
+//     22 - 23.
+//   - Where one fill and one walk back are all that the table takes, more candidates, too: the slowest
+//     of them sets dp_core's time, the table's hardly grows.  Of 631 drawn calls (L = 4 - 200) 58 were more
+//     than 5 % slower than the better side without this line, 36 are with it.  K = 2247, L = 8, S = 10,
+//     B = 982: 52 and 84; K = 428, L = 6, S = 16, B = 134: 31 and 41; K = 188, L = 9, S = 15, B = 15627: 58
+//     and 77.
+bool table_is_short(int K, int L, int S, int B, bool one_fill)
 {
-    return K <= 256 && 19LL * L + (long long)L * S * (B + 1LL) / 5000 < 140 + 6LL * L;
+    const long long updates = (long long)L * S * (B + 1LL);
+    if (K <= 256 && 19LL * L + updates / 5000 < 140 + 6LL * L)
+        return true;
+    return one_fill && K >= 8 && L <= 9 && L * S <= 300 && updates * ((K + 255LL) / 256) <= 4000000;
 }
 
 // Sets up the call for the J budgets, the largest of which `lay` is for; false: the full table at
-// once.
-bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, int J,
+// once.  `one_fill`: all that the full table would take is one fill and one walk back.
+bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, int J, bool one_fill,
                int16_t *profile, float *cost, void *workspace, size_t workspace_bytes,
                CoreCall *call)
 {
@@ -1989,7 +1997,8 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
         return false;
     for (int j = 0; j < J; ++j)
         largest = budget[j] > largest ? budget[j] : largest;
-    if (!core_params(L, S, largest, 1, 1, &cp, &lds) || table_is_short(K, L, S, largest))
+    if (!core_params(L, S, largest, 1, 1, &cp, &lds) ||
+        table_is_short(K, L, S, largest, one_fill))
         return false;
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
@@ -2269,8 +2278,8 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
         return SPDY_DP_ERR_NULL;
     CoreCall core;
     Todo todo;
-    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1, profile, cost,
-                             workspace, workspace_bytes, &core))
+    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1, true,
+                             profile, cost, workspace, workspace_bytes, &core))
         todo = Todo{profile, 1};
     const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
                              todo.profile ? &core : nullptr);
@@ -2321,7 +2330,7 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.block = blocks.ckpt + (size_t)K * slots * lay.row;
     CoreCall core;
     const bool reduced =
-        core_call(lay, K, L, S, &B, 1, profile, cost, workspace, workspace_bytes, &core);
+        core_call(lay, K, L, S, &B, 1, false, profile, cost, workspace, workspace_bytes, &core);
     const Todo todo = reduced ? Todo{profile, 1} : Todo{};
     auto fill = [&]() {
         const CoreCall *first = reduced ? &core : nullptr;
@@ -2383,7 +2392,7 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
     const float *drec = reinterpret_cast<const float *>(ws + lay.record_off);
     CoreCall core;
     Todo todo;
-    const bool reduced = core_call(lay, K, L, S, budgets, J, profile, cost, workspace,
+    const bool reduced = core_call(lay, K, L, S, budgets, J, J == 1, profile, cost, workspace,
                                    workspace_bytes, &core);
     if (reduced)
         todo = Todo{profile, 1};

@@ -297,3 +297,30 @@ def test_few_layers_with_long_rows(dp, K, L, S, B):
     assert K < 500 or memory.any(), "some rows were meant to lie in memory"
     for stride in (0, 1):                        # less memory for the rows of each
         same(dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, stride), want, f"stride {stride}")
+
+
+def test_short_tables_are_taken_at_once(dp):
+    """Calls that go to the full table without the reduced solve, on either side of the limits; and one that
+    resumes from an incumbent whose own call (K = 1) did not and left no table."""
+    rng = np.random.default_rng(69)
+    for (K, L, S, B, at_once) in [(428, 6, 16, 134, True), (8, 9, 33, 1000, True), (8, 9, 34, 1000, False),
+                                  (8, 10, 29, 1000, False), (8, 8, 20, 24998, True),
+                                  (8, 8, 20, 25000, False), (257, 8, 20, 12498, True),
+                                  (257, 8, 20, 12500, False), (7, 9, 33, 1000, False), (1, 8, 8, 256, True)]:
+        tau, err = smooth(rng, K, L, S, B)
+        tau_d, err_d, want = check(dp, tau, err, B, "around the limits")
+        got, filled, _ = solve_marked(dp, tau_d, err_d, B)
+        same(got, want, "marked workspace")
+        assert filled.all() if at_once else not filled.all()
+    K, L, S, B = 40, 9, 30, 4000
+    tau, err = smooth(rng, K, L, S, B)
+    c, w = rng.random((1, L)).astype(np.float32), np.sort(rng.random(S)).astype(np.float32)
+    err[:, :L // 2] = (c[0, :, None] * w)[:L // 2]
+    tau_d = torch.from_numpy(tau).cuda()
+    inc = dp.alloc_workspace(1, L, S, B)
+    inc.fill_(0x3D)
+    dp.spdy_dp_solve_sensitivities(tau_d, torch.from_numpy(c).cuda(), torch.from_numpy(w).cuda(), B,
+                                   workspace=inc)
+    first = torch.full((K,), L // 2, dtype=torch.int32, device="cuda")
+    got = dp.spdy_dp_solve_from_incumbent(tau_d, torch.from_numpy(err).cuda(), first, B, inc)
+    same(got, oracle.solve_ref(tau, err, B, threads=16), "incumbent without a table")
