@@ -157,6 +157,16 @@ def spdy_dp_solve_batched(tau, err, B: int, profile=None, cost=None, workspace=N
     tensors, valid after the stream is synchronised).  A ``workspace`` that is given holds the
     table of Eq. 2 afterwards; without one nobody sees the table, and only the part of it that can
     matter is computed (``spdy_dp_solve_profiles``)."""
+    entry = "spdy_dp_solve_batched" if workspace is not None else "spdy_dp_solve_profiles"
+    return _solve(entry, tau, err, B, profile, cost, workspace, stream)
+
+
+def spdy_dp_solve_profiles(tau, err, B: int, profile=None, cost=None, workspace=None, stream=None):
+    """``spdy_dp_solve_batched`` without the table: the ``workspace``, of either size, is scratch."""
+    return _solve("spdy_dp_solve_profiles", tau, err, B, profile, cost, workspace, stream)
+
+
+def _solve(entry, tau, err, B, profile, cost, workspace, stream):
     tau = _dev(tau, torch.int32, "tau")
     err = _dev(err, torch.float32, "err")
     K, L, S = _shapes(tau, err)
@@ -164,15 +174,14 @@ def spdy_dp_solve_batched(tau, err, B: int, profile=None, cost=None, workspace=N
         profile = torch.empty((K, L), dtype=torch.int16, device=err.device)
     if cost is None:
         cost = torch.empty((K,), dtype=torch.float32, device=err.device)
-    solve = lib().spdy_dp_solve_batched
     if workspace is None:
         workspace = _own_full_workspace(K, L, S, B, err.device, stream)
-        solve = lib().spdy_dp_solve_profiles
     _dev(profile, torch.int16, "profile")
     _dev(cost, torch.float32, "cost")
     _dev(workspace, torch.uint8, "workspace")
-    st = solve(tau.data_ptr(), err.data_ptr(), K, L, S, int(B), profile.data_ptr(),
-               cost.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream(stream))
+    st = getattr(lib(), entry)(tau.data_ptr(), err.data_ptr(), K, L, S, int(B), profile.data_ptr(),
+                               cost.data_ptr(), workspace.data_ptr(), workspace.numel(),
+                               _stream(stream))
     if st != OK:
         raise SpdyDpError(st)
     return profile, cost

@@ -195,6 +195,12 @@ def test_binding_refuses_cpu_tensors(binding):
         binding.spdy_dp_solve_batched(tau, err, 4)
 
 
+def test_every_declared_function_can_be_called_from_python(binding):
+    import paper_2201_13096_amd as m
+    for name in declared_functions():
+        assert callable(getattr(m, name)), name
+
+
 def test_executed_update_counts_bracket_the_necessary_work():
     """The roofline's numerator is the update count bench.py derives from tau.  It must cover every
     update Alg. 1 needs (a finite D_{l-1}[t - tau] that can still end within the budget) and may
