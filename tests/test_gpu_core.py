@@ -55,12 +55,7 @@ def solve_marked(dp, tau_d, err_d, B):
     each = (ws.numel() - record) // K // 16 * 16
     of_each = ws[record:record + K * each].view(K, each)[:, :4]
     of_each.fill_(0xAB)
-    profile = torch.empty((K, L), dtype=torch.int16, device="cuda")
-    cost = torch.empty((K,), dtype=torch.float32, device="cuda")
-    status = dp.binding.lib().spdy_dp_solve_profiles(
-        tau_d.data_ptr(), err_d.data_ptr(), K, L, S, B, profile.data_ptr(), cost.data_ptr(),
-        ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
-    assert status == 0, dp.spdy_dp_strerror(status)
+    profile, cost = dp.spdy_dp_solve_profiles(tau_d, err_d, B, workspace=ws)
     torch.cuda.synchronize()
     words = ws[at:at + 4 * K].cpu().numpy().view(np.uint32)
     memory = of_each.contiguous().cpu().numpy().view(np.uint32)[:, 0] != 0xABABABAB
@@ -324,3 +319,83 @@ def test_short_tables_are_taken_at_once(dp):
     first = torch.full((K,), L // 2, dtype=torch.int32, device="cuda")
     got = dp.spdy_dp_solve_from_incumbent(tau_d, torch.from_numpy(err).cuda(), first, B, inc)
     same(got, oracle.solve_ref(tau, err, B, threads=16), "incumbent without a table")
+
+
+# Candidates that the reduced solve refuses (a negative error, seen as the tables are staged) among
+# candidates that it takes, at the shapes of the launches behind it: teams of a workgroup and one
+# candidate per workgroup, two waves per share, turns, long rows in LDS and in memory, many levels.
+GIVEN_UP_SHAPES = [(48, 54, 40, 10000), (21, 12, 8, 2000), (9, 12, 40, 30000), (5, 11, 12, 70000),
+                   (11, 10, 130, 5000), (4, 10, 70, 30000), (700, 10, 6, 1500), (1300, 10, 5, 300),
+                   (300, 11, 5, 30000)]
+
+
+def some_given_up(K, L, S, B):
+    rng = np.random.default_rng(K + 7 * L + 31 * S)
+    tau, err = smooth(rng, K, L, S, B)
+    refused = np.arange(K) % 3 == 1
+    return rng, tau, err, refused
+
+
+@pytest.mark.parametrize("K, L, S, B", GIVEN_UP_SHAPES)
+def test_given_up_candidates_of_profiles_and_checkpoints(dp, K, L, S, B):
+    rng, tau, err, refused = some_given_up(K, L, S, B)
+    err[refused, L - 1, S // 2] = -2.0 ** -10
+    tau_d, err_d, want = check(dp, tau, err, B, "given up")
+    got, filled, _ = solve_marked(dp, tau_d, err_d, B)
+    same(got, want, "profiles")
+    assert filled[refused].all() and not filled.all()
+    small = dp.alloc_workspace(K, L, S, B, compact=True)
+    small.fill_(0xC3)
+    same(dp.spdy_dp_solve_profiles(tau_d, err_d, B, workspace=small), want, "level record")
+    for stride in (0, 1, 4):
+        same(dp.spdy_dp_solve_checkpointed(tau_d, err_d, B, stride), want, f"stride {stride}")
+
+
+@pytest.mark.parametrize("K, L, S, B", GIVEN_UP_SHAPES)
+def test_given_up_candidates_resume_from_the_incumbent(dp, K, L, S, B):
+    rng, tau, err, refused = some_given_up(K, L, S, B)
+    base = err[:1].copy()
+    first = rng.integers(0, L, size=K).astype(np.int32)
+    first[:3] = [0, L - 1, 1]
+    for k in range(K):
+        err[k, :first[k]] = base[0, :first[k]]
+    err[refused, L - 1, S // 2] = -2.0 ** -10
+    tau_d = torch.from_numpy(tau).cuda()
+    inc, ws = dp.alloc_workspace(1, L, S, B), dp.alloc_workspace(K, L, S, B)
+    dp.spdy_dp_solve_batched(tau_d, torch.from_numpy(base).cuda(), B, workspace=inc)
+    at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
+    for order in (np.arange(K), np.argsort(first, kind="stable")):
+        print(f"[core] resume K={K} L={L} S={S} B={B}", flush=True)
+        ws.fill_(0xAB)
+        got = dp.spdy_dp_solve_from_incumbent(
+            tau_d, torch.from_numpy(err[order]).cuda(), torch.from_numpy(first[order]).cuda(), B,
+            inc, workspace=ws)
+        same(got, oracle.solve_ref(tau, err[order], B, threads=16), "resumed")
+        filled = ws[at:at + 4 * K].cpu().numpy().view(np.uint32) != 0xABABABAB
+        assert filled[refused[order]].all() and not filled.all()
+
+
+@pytest.mark.parametrize("K, L, S, B", GIVEN_UP_SHAPES[:6])
+def test_given_up_candidates_of_budgets_and_sensitivities(dp, K, L, S, B):
+    rng, tau, err, refused = some_given_up(K, L, S, B)
+    err[refused, L - 1, S // 2] = -2.0 ** -10
+    tau_d = torch.from_numpy(tau).cuda()
+    budgets = [B // 2, B, int(tau.min(axis=1).sum()), 0]
+    print(f"[core] budgets {budgets} K={K} L={L} S={S}", flush=True)
+    p, c = dp.spdy_dp_solve_budgets(tau_d, torch.from_numpy(err).cuda(), budgets)
+    p_ref, c_ref = oracle.solve_budgets_ref(tau, err, budgets)
+    for j, b in enumerate(budgets):
+        same((p[j], c[j]), (p_ref[j], c_ref[j]), f"budget {b}")
+    sens = rng.random((K, L), dtype=np.float32)
+    sens[refused, 0] *= -1
+    w = np.square(np.arange(S) / (S - 1)).astype(np.float32)
+    want = oracle.solve_sens_ref(tau, sens, w, B)
+    for compact in (False, True):
+        ws = dp.alloc_workspace(K, L, S, B, compact=compact)
+        ws.fill_(0xAB)
+        same(dp.spdy_dp_solve_sensitivities(tau_d, torch.from_numpy(sens).cuda(),
+                                            torch.from_numpy(w).cuda(), B, workspace=ws), want,
+             f"sensitivities compact={compact}")
+        at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
+        filled = ws[at:at + 4 * K].cpu().numpy().view(np.uint32) != 0xABABABAB
+        assert filled[refused].all() and not filled.all()
