@@ -549,9 +549,9 @@ struct Resume {
     const int32_t *first_layer;   // [K] in [0, L], or nullptr: every candidate starts at layer 0
     const float *inc_rec;         // the incumbent's D record, float [L][pitch]
     const int32_t *inc_meta;      // its header: without a whole table there is nothing to resume from
-    __device__ __forceinline__ int start(int k, int L) const
+    template <bool kChecked = true> __device__ __forceinline__ int start(int k, int L) const
     {
-        if (!first_layer || !inc_meta[kMetaTable])
+        if (!first_layer || (kChecked && !inc_meta[kMetaTable]))
             return 0;
         const int f = first_layer[k];
         return f < 0 ? 0 : (f > L ? L : f);
@@ -1427,7 +1427,8 @@ void dp_fill(
 
     // a candidate that shares its first l0 layers with the incumbent starts from the incumbent's
     // row l0 - 1, placed where layer l0 reads its previous row
-    const int l0 = active ? resume.start(k, L) : 0;
+    // (a call that does not go through dp_core resumes from one that did not either, see table_is_short)
+    const int l0 = active ? resume.start<kTodo>(k, L) : 0;
     if (l0 > 0 && lead) {
         float *dst = (l0 & 1) ? buf1 : buf0;
         const float *from = resume.inc_rec + (size_t)(l0 - 1) * pitch;
@@ -1976,7 +1977,10 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
 //     of them sets dp_core's time, the table's hardly grows.  Of 631 drawn calls (L = 4 - 200) 58 were more
 //     than 5 % slower than the better side without this line, 36 are with it.  K = 2247, L = 8, S = 10,
 //     B = 982: 52 and 84; K = 428, L = 6, S = 16, B = 134: 31 and 41; K = 188, L = 9, S = 15, B = 15627: 58
-//     and 77.
+//     and 77.  (Not for a call that resumes from an incumbent: its fill takes the rows below
+//     first_layer as they are, so it may only be direct where the incumbent's call, K = 1, was whatever
+//     entry point that went through.  The first line is one of the sizes alone and holds for K = 1 where
+//     it holds for K; a check of the incumbent's header in those fills costs the others half a per cent.)
 bool table_is_short(int K, int L, int S, int B, bool one_fill)
 {
     const long long updates = (long long)L * S * (B + 1LL);
@@ -2278,8 +2282,8 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
         return SPDY_DP_ERR_NULL;
     CoreCall core;
     Todo todo;
-    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1, true,
-                             profile, cost, workspace, workspace_bytes, &core))
+    if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1,
+                             !resume.first_layer, profile, cost, workspace, workspace_bytes, &core))
         todo = Todo{profile, 1};
     const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
                              todo.profile ? &core : nullptr);
