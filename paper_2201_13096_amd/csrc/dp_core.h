@@ -20,7 +20,7 @@
 // argmin and the smallest level of each step of the walk back are found among the same
 // candidates as in the whole table.
 //
-// What it does not take is left to the full table (profile[0] = kTodo): a negative or NaN error,
+// What it does not take is left to the full table (profile[0] = kGivenUp): a negative or NaN error,
 // a negative time, sums near the end of the fp32 range, more surviving levels, rows wider than both LDS
 // and memory hold, or more work than the limits of the launch.
 //
@@ -33,7 +33,7 @@
 // K = 4096, L = 72, S = 40, B = 16384: 290 us / 3.34 ms; K = 333, S = 127: 101 us / 0.92 ms;
 // K = 256, L = 200, S = 64, B = 65536: 0.36 / 4.2 ms.
 
-constexpr int16_t kTodo = -3;            // profile[0] of a candidate the full table has to solve
+constexpr int16_t kGivenUp = -3;            // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
 constexpr int kCoreWaves = kCoreThreads / kWave;
 constexpr int kCoreMaxLayers = kCoreThreads;
@@ -199,7 +199,7 @@ struct CoreShared {      // static LDS of the kernel
 };
 
 // One candidate (error source `src` seen from candidate k) under budget B.  Returns through
-// profile / cost; profile[0] = kTodo if the full table has to do it.  kFar: a row that spans more
+// profile / cost; profile[0] = kGivenUp if the full table has to do it.  kFar: a row that spans more
 // buckets than the window lies in memory, before the record that `spill` is for (wide steps end
 // with a barrier, which makes them visible); otherwise it is too wide.
 template <bool kFar>
@@ -259,7 +259,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     };
     if (__syncthreads_or(stage())) {
         if (tid == 0)
-            profile[0] = kTodo;
+            profile[0] = kGivenUp;
         return;
     }
 
@@ -867,5 +867,5 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         return;
     }
     if (tid == 0)                                 // the same in every thread
-        profile[0] = kTodo;
+        profile[0] = kGivenUp;
 }

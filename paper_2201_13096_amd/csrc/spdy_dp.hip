@@ -752,7 +752,7 @@ struct Todo {
             return true;
         bool any = false;
         for (int j = 0; j < budgets; ++j)
-            any |= profile[((size_t)j * K + k) * L] == kTodo;
+            any |= profile[((size_t)j * K + k) * L] == kGivenUp;
         return any;
     }
     // the same where k is the same in the whole wave, as a scalar: a row's plan depends on it, and a
