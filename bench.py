@@ -40,16 +40,20 @@ ALU_PEAK_LANE_OPS = COMPUTE_UNITS * 128 * CLOCK_HZ
 LANE_OPS_PER_UPDATE = {"d": 2.0, "level": 4.0}
 LANE_OPS_AS_BUILT = {"d": 1.5, "level": 4.0}
 PROFILES = os.path.join(ROOT, "profiles")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2201_13096_amd", "csrc", "spdy_dp.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
+                  for f in ("spdy_dp.hip", "dp_core.h")]
 PROBE = os.path.join(ROOT, "paper_2201_13096_amd", "peaks_probe")
 
 
 def kernel_source_id() -> str:
-    """Short hash of the HIP source: counter figures taken from a tracked profile only count while
-    the kernel they were taken on is the one in the tree."""
+    """Short hash of the HIP sources: counter figures taken from a tracked profile only count while
+    the kernels they were taken on are those in the tree."""
     import hashlib
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:12]
+    digest = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()[:12]
 
 
 def tracked_traffic(workload: str, record: str):

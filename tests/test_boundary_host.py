@@ -267,6 +267,28 @@ def test_traffic_table_only_counts_for_the_source_it_was_taken_on(tmp_path, monk
     assert bench.tracked_traffic("rn50_k1024", "d") is None
 
 
+def test_source_id_covers_every_kernel_source(tmp_path, monkeypatch):
+    """A change in any file that the fill's launches are compiled from makes old counters stale."""
+    import bench
+    csrc = os.path.join(ROOT, "paper_2201_13096_amd", "csrc")
+    text = open(os.path.join(csrc, "spdy_dp.hip")).read()
+    included = re.findall(r'#include "(\w+\.h)"', text)
+    own = {"spdy_dp.hip"} | {f for f in included if os.path.exists(os.path.join(csrc, f))}
+    assert {os.path.basename(p) for p in bench.KERNEL_SOURCES} == own
+    copies = []
+    for p in bench.KERNEL_SOURCES:
+        copies.append(str(tmp_path / os.path.basename(p)))
+        with open(p, "rb") as src, open(copies[-1], "wb") as dst:
+            dst.write(src.read())
+    monkeypatch.setattr(bench, "KERNEL_SOURCES", copies)
+    ids = {bench.kernel_source_id()}
+    for p in copies:
+        with open(p, "ab") as f:
+            f.write(b"// changed\n")
+        ids.add(bench.kernel_source_id())
+    assert len(ids) == 1 + len(copies)
+
+
 def test_rate_probe_output_is_optional(monkeypatch, tmp_path):
     import bench
     monkeypatch.setattr(bench, "PROBE", str(tmp_path / "no_such_probe"))
