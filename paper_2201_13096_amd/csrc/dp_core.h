@@ -29,11 +29,11 @@
 // five for the known profile, then 15 dependent steps of 1700 clocks for the reduced table and 500
 // for each step back; one wave per SIMD issues an instruction every seven or eight clocks whatever
 // it is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Kernel time
-// against fill and walk back of the whole table: K = 100, L = 52, S = 42, B = 10^4: 71 us / 297 us;
-// K = 4096, L = 72, S = 40, B = 16384: 290 us / 3.34 ms; K = 333, S = 127: 101 us / 0.92 ms;
-// K = 256, L = 200, S = 64, B = 65536: 0.36 / 4.2 ms.
+// against fill and walk back of the whole table: K = 100, L = 52, S = 42, B = 10^4: 73 us / 297 us;
+// K = 4096, L = 72, S = 40, B = 16384: 303 us / 3.34 ms; K = 333, S = 127: 104 us / 0.92 ms;
+// K = 256, L = 200, S = 64, B = 65536: 0.37 / 4.2 ms.
 
-constexpr int16_t kGivenUp = -3;            // profile[0] of a candidate the full table has to solve
+constexpr int16_t kGivenUp = -3;         // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
 constexpr int kCoreWaves = kCoreThreads / kWave;
 constexpr int kCoreMaxLayers = kCoreThreads;

@@ -1900,14 +1900,14 @@ struct CoreCall {
 // LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
 // The staged tables, L * S pairs, have to fit LDS.  What a row may span is taken from the LDS that a
 // workgroup can have without lowering how many a compute unit holds (registers allow four).  On
-// the timing tables of the performance cases' kinds the widest row of one candidate in a hundred
-// spans 3 B / L buckets and more, none in three thousand spanned 6 B / L (L = 8 - 48), so no more is
-// asked for.  Where there is less than 4 B / L, rows that need more lie in memory, which an
+// the timing tables of the performance cases' kinds (2729 candidates, L = 8 - 48, counted on the
+// host) the widest row of one candidate in a hundred spans 3 B / L buckets and more, of none
+// 4.8 B / L, so no more than 6 B / L is asked for.  Where there is less than 4 B / L, rows that need more lie in memory, which an
 // instantiation of its own allows for (4 % slower where none does: the registers).  Giving such a
 // candidate up costs most of the reduced solve and then the whole table: L = 17, S = 14, B = 43125, K = 20:
 // 235 us with eight of them given up, 132 with the rows in LDS, 124 for the full table at
 // once; L = 11, S = 9, B = 30006, K = 1407 (806 given up): 329, 211 with rows in memory, 272.
-// Rows are not worth any price, though: fewer than one candidate in a hundred needed a sixteenth of the
+// Rows are not worth any price, though: fewer than one candidate in a thousand needed a sixteenth of the
 // sweeps of the full table, and a table that needs more (ties everywhere, errors linear in the
 // times) is given up there, after as long again as the full table takes at the worst measured.
 constexpr int kCoreRecord = 8192;     // least LDS for the recorded entries
