@@ -41,7 +41,7 @@ LANE_OPS_PER_UPDATE = {"d": 2.0, "level": 4.0}
 LANE_OPS_AS_BUILT = {"d": 1.5, "level": 4.0}
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
-                  for f in ("spdy_dp.hip", "dp_core.h")]
+                  for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h")]
 PROBE = os.path.join(ROOT, "paper_2201_13096_amd", "peaks_probe")
 
 

@@ -92,7 +92,6 @@ constexpr bool kInPlaceFits =
     2 * (kFillWaves * kMaxGroup * kWave + kWave + kHalo) * 4 > kLdsHalf &&
     2 * (kFillWavesLevel * kMaxGroupLevel * kWave + kWave + kHalo) * 4 > kLdsHalf;
 static_assert(kInPlaceFits, "path 1 must be exactly the in-place case");
-constexpr int kPrepareLoads = 10;         // times a thread of the prepare kernel loads at once
 constexpr int kBatch = 8;                 // level tables are padded to a multiple of this
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
@@ -123,7 +122,8 @@ enum MetaWord {
     kMetaWideGroup = 15, // most chunks one of its waves keeps in registers
     kMetaLdsWide = 16,   // its dynamic LDS bytes
     kMetaGlobalWaves = 17, // waves of the global-row launch
-    kMetaTable = 18     // 1: the call leaves the whole table in the record (0: scratch)
+    kMetaTable = 18,    // 1: the call leaves the whole table in the record (0: scratch)
+    kMetaTiles = 19     // not 0: dp_tiles does the work (see there), not the launch of kMetaPath
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
@@ -206,6 +206,8 @@ Layout make_layout(int K, int L, int S, int B, size_t workspace_bytes, long long
     return lay;
 }
 
+#include "wave_ops.h"
+
 // ---------------------------------------------------------------------------------------------
 // Sum of `v` over a workgroup of 256 threads (returned to every thread); if `exclusive` is given
 // it receives the sum over the threads before this one.  part: 8 words of LDS.
@@ -213,13 +215,7 @@ __device__ __forceinline__ long long block_scan_256(long long v, long long *part
                                                     long long *exclusive)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    long long incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const long long o = __shfl_up(incl, off, kWave);
-        if (lane >= off)
-            incl += o;
-    }
+    const long long incl = wave_scan(v, 0ll, Add{});
     __syncthreads();                              // part may still be read from a previous call
     if (lane == kWave - 1)
         part[wave] = incl;
@@ -236,46 +232,190 @@ __device__ __forceinline__ long long block_scan_256(long long v, long long *part
     return total;
 }
 
+// What the prepare kernel plans the tiles of a row with (see dp_tiles.h).
+struct TileArgs {
+    int units;               // compute units
+    int only_memory;         // 1: only where rows would lie in memory
+    int most;                // tiles that the launch has workgroups for (0: not enqueued)
+    int lds;                 // floats of its LDS
+    int *books;              // ticket, keys and counters of the tiles
+    int room;                // their words
+};
+
+constexpr int kTileWaves = 16;
+constexpr int kTileChunks = 7;       // short tiles: chunks a wave takes at most
+constexpr int kTileUnits = 6;        // long tiles: quad chunks a wave takes at most
+constexpr int kTileMost = 16;        // tiles of a row at most
+constexpr int kTileLayers = 8;       // layers whose entries have to fit LDS at once
+constexpr int kTileBuckets = 252;    // buckets of a quad chunk
+// what kMetaTiles holds: tiles | kTileLong | quads of the apron << 12
+constexpr int kTileLong = 1 << 11;
+// books: ticket | - | key of every tile [K][tiles] (two words) | counters of every tile [K][tiles][4]:
+//        rows in memory (short tiles: up to the last even one, up to the last odd one), -, done
+constexpr int kTileFlags = 4, kTileDone = 3;
+__device__ __forceinline__ int *tile_flags(int *books, int solves) { return books + 2 + 2 * solves; }
+
+// Into how many tiles the rows of `chunks` chunks are cut, and of which kind: what is estimated to be
+// fastest, one pair per lane; 0 where nothing fits.  One wave.
+__device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chunks, int row_chunks,
+                                           int span, int mean_span, const TileArgs &ta, int *plan)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    if (bp < 0 || ta.most == 0) {
+        if (lane == 0)
+            *plan = bp < 0 && ta.most > 0 && ta.only_memory == 0 ? 1 : 0;
+        return;
+    }
+    const int tiles = (lane & (kTileMost - 1)) + 1;
+    const bool is_long = lane >= kTileMost;
+    const int grain = is_long ? kTileBuckets : kWave;
+    const int apron = (span + 3) / 4 + 2;         // quads
+    const int all = (chunks * kWave + grain - 1) / grain;
+    const int units = (all + tiles - 1) / tiles;
+    const int waves = is_long ? kTileWaves : kTileWaves - (tiles > 1 ? 4 : 2);
+    const int mine = (units + waves - 1) / waves;
+    const int s8 = (S + kBatch - 1) / kBatch * kBatch;
+    const long long lines = (is_long ? 1 : 2) * (4LL * apron + (long long)units * grain);
+    const bool fits = tiles <= ta.most && (tiles - 1) * units < all && lane < 2 * kTileMost &&
+                      mine <= (is_long ? kTileUnits : kTileChunks) && (!is_long || S <= kWave) &&
+                      (tiles == 1 || (long long)K * tiles * (2 + kTileFlags) + 2 <= ta.room) &&
+                      apron < 1 << 20 &&
+                      lines + min(L, kTileLayers) * (2LL * s8 + 1) <= ta.lds;
+    // Clocks, fitted to measured fills (a lone S = 40 candidate of 4955 buckets in 1, 2, 4, 8 short
+    // tiles: 8400, 5900, 3700, 2900 a layer; one of 49581 in 3, 4, 6, 8 long ones: 26300, 21000, 17300, 13000).
+    // A SIMD issues an instruction every four clocks or so, whichever of its waves it is from.
+    const float pairs = 0.42f * S;                // entries are fewer than levels
+    const float of_simd = (float)((units + 3) / 4), waves_of_simd = (float)((min(waves, units) + 3) / 4);
+    // (A wave brings a short tile's apron, and all tiles on all compute units slow the memory down; of long
+    // tiles 21200 and 25700 clocks a layer.)
+    const bool crowded = 2 * K * tiles > ta.units;
+    const float bring = tiles == 1 ? 0.0f : mean_span * (crowded ? 2.0f : 1.2f);
+    const float layer =
+        is_long ? (1500.0f + fmaxf(4.2f * pairs * (of_simd * 17.5f + waves_of_simd * 12.0f),
+                                   13.0f * pairs * (mine * 17.5f + 12.0f))) *
+                      (crowded ? 1.25f : 1.0f)    // (the second: a wave by itself)
+                : 700.0f + bring +
+                      4.2f * (of_simd * pairs * 4.9f + waves_of_simd * (pairs * 3.0f + 50.0f));
+    // what a tile is behind the one below it: more with more workgroups at the same memory
+    const float lag = 1.5f * layer + 3000.0f + 60.0f * min(K * tiles, ta.units);
+    const float rounds = (float)((K * tiles + ta.units - 1) / ta.units);
+    float clocks = rounds * L * layer + (tiles - 1) * lag;
+    clocks = fits ? clocks : __builtin_inff();
+    float best = clocks;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1)
+        best = fminf(best, __shfl_xor(best, off, kWave));
+    const unsigned long long set = __ballot(fits && clocks == best);
+    // rows in memory, one workgroup per candidate: 21 updates a clock (K = 200: 1.90 ms, 2.10 in tiles;
+    // K = 300: 3.69 and 2.79; K = 1000: 7.47 and 8.10)
+    const float untiled = (float)((K + ta.units - 1) / ta.units) * L *
+                          (1500.0f + row_chunks * pairs * 6.15f);
+    const bool tiled = set != 0 && (ta.only_memory == 0 || best < untiled);
+    if (lane == 0 && !tiled)
+        *plan = 0;
+    if (tiled && lane == __builtin_ctzll(set))
+        *plan = tiles | (is_long ? kTileLong : 0) | apron << 12;
+}
+
 // Prepare, workgroup 0: per-layer smallest time m_l, M = sum m_l, reduced budget B - M, and how
 // many 64-bucket chunks of each reduced row can hold a finite value (the largest reachable
 // reduced time after layer l is sum_{j<=l} max_s (tau[j][s] - m_j) over the levels that fit the
 // reduced budget).  It also picks the path: which launch of the fill kernel (LDS allocation
 // lds_small or lds_large bytes, `waves` waves per workgroup) fits, into how many teams its waves
 // split, and whether one row per candidate is enough; and it records each layer's largest usable
-// shift (the tiles of the global-row path size their window in LDS by it).  Thread i owns a slice
-// of layers.
+// shift (the tiles of the global-row path size their window in LDS by it).  Thread i owns layers i,
+// i + 256, ...; a layer's times are read by a wave, four layers on their way at a time.
 __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots, int L, int S,
                                int B, int waves, int max_group, int lds_small, int lds_large,
                                int lds_stage, int split, int wide_waves, int wide_group,
-                               int lds_wide, int global_waves, int32_t *__restrict__ meta)
+                               int lds_wide, int global_waves, const TileArgs &ta,
+                               int32_t *words, int32_t *__restrict__ meta)
 {
     __shared__ long long s_sum[8];
-    __shared__ int s_budget, s_team_waves;
+    __shared__ int s_team_waves, s_span, s_tiles;
+    int32_t *const s_least = words, *const s_most = words + 256;
     const int tid = threadIdx.x;
+    if (tid == 0)
+        s_span = 0;
     int32_t *mn = meta + kMetaHeader;
     int32_t *nact = meta + kMetaHeader + L;
-    const int per = (L + 255) / 256;
-    const int l0 = min(L, tid * per), l1 = min(L, l0 + per);
+    int32_t *spans = meta + kMetaHeader + (2 + (size_t)kRangeStride) * L;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
 
     long long local = 0;
-    for (int l = l0; l < l1; ++l) {
-        const int32_t *tau_l = tau + (size_t)l * S;
-        int m = INT32_MAX;
-        for (int s0 = 0; s0 < S; s0 += kPrepareLoads) {   // so many in flight per round trip
-            int v[kPrepareLoads];
+    for (int base = 0; base < L; base += 256) {
+        const int n = min(256, L - base);
+        for (int i0 = wave; i0 < n; i0 += 16) {
+            const int32_t *tau_i[4];
+            int least[4], most[4];
 #pragma unroll
-            for (int i = 0; i < kPrepareLoads; ++i)
-                v[i] = tau_l[min(s0 + i, S - 1)];
+            for (int q = 0; q < 4; ++q) {         // (past the last layer: that one once more)
+                tau_i[q] = tau + (size_t)(base + min(i0 + 4 * q, n - 1)) * S;
+                least[q] = INT32_MAX;
+                most[q] = 0;
+            }
+            for (int s = lane; s < S; s += kWave) {
 #pragma unroll
-            for (int i = 0; i < kPrepareLoads; ++i)
-                m = min(m, v[i]);
+                for (int q = 0; q < 4; ++q) {
+                    const int v = tau_i[q][s];
+                    least[q] = min(least[q], v);
+                    most[q] = max(most[q], v);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int lo = wave_scan(least[q], INT32_MAX, Smaller{});
+                const int hi = wave_scan(most[q], 0, Larger{});
+                if (lane == kWave - 1 && i0 + 4 * q < n) {
+                    s_least[i0 + 4 * q] = lo;
+                    s_most[i0 + 4 * q] = hi;
+                }
+            }
         }
-        mn[l] = m;
-        local += m;
+        __syncthreads();
+        if (tid < n) {
+            mn[base + tid] = s_least[tid];
+            spans[base + tid] = s_most[tid];      // (the largest time, for now)
+            local += s_least[tid];
+        }
+        __syncthreads();
     }
     const long long M = block_scan_256(local, s_sum, nullptr);
+    const int bp = (M > B) ? -1 : (int)(B - M);
+    int widest = 0;
+    long long reach = 0;                          // sum of the spans of the layers so far
+    for (int base = 0; base < L; base += 256) {
+        const int l = base + tid;
+        int span = 0;
+        if (l < L && bp >= 0) {
+            const int m = mn[l];
+            const long long d = (long long)spans[l] - m;
+            span = (int)(d <= bp ? d : 0);
+            for (int s = 0; d > bp && s < S; ++s) {         // some level is beyond the budget
+                const long long v = (long long)tau[(size_t)l * S + s] - m;
+                span = v <= bp ? max(span, (int)v) : span;
+            }
+        }
+        long long h = 0;                          // sum over the layers of this block before this one
+        const long long total = block_scan_256(span, s_sum, &h);
+        if (l < L) {
+            h += reach + span;
+            const long long top = h < bp ? h : bp;
+            nact[l] = bp < 0 ? 0 : (int)((top + kWave) / kWave);
+            spans[l] = span;
+        }
+        reach += total;
+        widest = max(widest, span);
+    }
+    atomicMax(&s_span, widest);
+    __syncthreads();
+    if (tid < kWave) {
+        const long long top = reach < bp ? reach : bp;
+        plan_tiles(K, L, S, bp, bp < 0 ? 0 : (int)((top + kWave) / kWave), (bp + kWave) / kWave,
+                   s_span, (int)(reach / L), ta, &s_tiles);
+    }
+    __syncthreads();
     if (tid == 0) {
-        const int bp = (M > B) ? -1 : (int)(B - M);
         const int rowp = bp < 0 ? 0 : (bp + kWave) / kWave * kWave;
         meta[kMetaBudget] = bp;
         meta[kMetaMinTime] = M > INT32_MAX ? INT32_MAX : (int)M;
@@ -329,46 +469,26 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         meta[kMetaWideGroup] = wide_group;
         meta[kMetaLdsWide] = lds_wide;
         meta[kMetaGlobalWaves] = global_waves;
-        s_budget = bp;
         s_team_waves = plan_waves / teams;
+        if (ta.only_memory != 0 && path != 0 && path != 4)
+            s_tiles = 0;
+        meta[kMetaTiles] = s_tiles;
     }
     __syncthreads();
-    const int bp = s_budget;
     const int tw = s_team_waves;
-    local = 0;
-    for (int l = l0; l < l1; ++l) {
-        int span = 0;
-        if (bp >= 0) {
-            const int32_t *tau_l = tau + (size_t)l * S;
-            const int m = mn[l];
-            for (int s0 = 0; s0 < S; s0 += kPrepareLoads) {
-                int v[kPrepareLoads];
-#pragma unroll
-                for (int i = 0; i < kPrepareLoads; ++i)
-                    v[i] = tau_l[min(s0 + i, S - 1)];
-#pragma unroll
-                for (int i = 0; i < kPrepareLoads; ++i) {
-                    const long long d = (long long)v[i] - m;
-                    if (d <= bp)
-                        span = max(span, (int)d);
-                }
-            }
-        }
-        nact[l] = span;
-        meta[kMetaHeader + (2 + (size_t)kRangeStride) * L + l] = span;
-        local += span;
+    if (const int tiles = s_tiles & 0xFF; tiles > 1) {
+        int *const flags = tile_flags(ta.books, K * tiles);
+        for (int i = tid; i < K * tiles * kTileFlags; i += 256)
+            flags[i] = 0;
+        if (tid == 0)
+            ta.books[0] = 0;
     }
-    long long h = 0;                              // sum of the slices before this thread's
-    block_scan_256(local, s_sum, &h);
-    for (int l = l0; l < l1; ++l) {
-        h += nact[l];
-        const long long top = h < bp ? h : bp;
-        const int n = bp < 0 ? 0 : (int)((top + kWave) / kWave);
-        nact[l] = n;
+    for (int l = tid; l < L; l += 256) {
         // wave w of a team sweeps chunks [w n / tw, (w + 1) n / tw) of this row
+        const int n = nact[l];
         int32_t *range = meta + kMetaHeader + 2 * L + (size_t)l * kRangeStride;
         for (int w = 0; w <= tw; ++w)
-            range[w] = (int)((long long)w * n / tw);
+            range[w] = (int)((unsigned)(w * n) / (unsigned)tw);   // (16 rows of 2^25 chunks fit)
     }
 }
 
@@ -385,15 +505,18 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
 //   D record, at most 64 levels (sorted = 2): as above, but the entries are ordered by
 //     (shift mod 4, shift): the sweep reads four consecutive buckets per lane with one aligned
 //     128-bit LDS read and treats the four residues of the shift separately; the usable entries
-//     of a residue then form a prefix of that residue's run.
+//     of a residue then form a prefix of that residue's run.  Nothing reads order and start then;
+//     dp_tiles has its books there.
+//   D record, where dp_tiles is known to do the work whatever the number of levels (sorted = 3): by
+//     shift, and order and start are left alone for the same reason.
 // One thread per level (S <= 255).
 __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int s8, int sorted,
                               int32_t *__restrict__ shifts, int32_t *__restrict__ order,
-                              int32_t *__restrict__ start, int32_t *__restrict__ entry_of)
+                              int32_t *__restrict__ start, int32_t *__restrict__ entry_of,
+                              int32_t *words)
 {
-    __shared__ int32_t s_shift[256];
-    __shared__ int32_t s_level[256];
-    __shared__ int32_t s_tau[256];                // the layer's times: every thread reads them all
+    int32_t *const s_shift = words, *const s_level = words + 256;
+    int32_t *const s_tau = words + 512;           // the layer's times: every thread reads them all
     __shared__ int s_entries;
     const int s = threadIdx.x;
     int32_t *shifts_l = shifts + (size_t)l * s8;
@@ -420,14 +543,15 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
         }
         if (!sorted)
             rank = s;
-        order_l[rank] = s;
+        if (sorted < 2)
+            order_l[rank] = s;
         if (sorted) {
             s_shift[rank] = mine - m;
             s_level[rank] = s;
         } else {
             shifts_l[rank] = mine - m;
         }
-    } else if (s < s8) {
+    } else if (s < s8 && sorted < 2) {
         order_l[s] = 0;
         if (!sorted)
             shifts_l[s] = INT32_MAX;
@@ -451,7 +575,8 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
             entry += s_shift[o] != s_shift[o - 1] ? 1 : 0;
         if (r == 0 || s_shift[r] != s_shift[r - 1]) {
             shifts_l[entry] = s_shift[r];
-            start_l[entry] = r;
+            if (sorted < 2)
+                start_l[entry] = r;
         }
         entry_of[(size_t)l * s8 + s_level[r]] = entry;
         if (r == S - 1)
@@ -459,7 +584,8 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
     }
     __syncthreads();
     for (int e = s_entries + r; e < s8 + kBatch; e += 256) {
-        start_l[e] = S;                           // the last entry ends here; padding is empty
+        if (sorted < 2)
+            start_l[e] = S;                       // the last entry ends here; padding is empty
         if (e < s8)
             shifts_l[e] = INT32_MAX;
     }
@@ -469,19 +595,22 @@ struct PrepareArgs {
     int slots, s8, B, waves, max_group, lds_small, lds_large, lds_stage, sorted, split;
     int wide_waves, wide_group, lds_wide, global_waves, table;
     int32_t *meta, *shifts, *order, *start, *entry_of;
+    TileArgs tiles;
 };
 
 __device__ __forceinline__ void prepare(const int32_t *__restrict__ tau, int K, int L, int S,
                                         const PrepareArgs &a, int block)
 {
+    __shared__ int32_t words[3 * 256];
     if (block == 0 && threadIdx.x == 0)
         a.meta[kMetaTable] = a.table;
     if (block == 0)
         prepare_budget(tau, K, a.slots, L, S, a.B, a.waves, a.max_group, a.lds_small, a.lds_large,
                        a.lds_stage, a.split, a.wide_waves, a.wide_group, a.lds_wide,
-                       a.global_waves, a.meta);
+                       a.global_waves, a.tiles, words, a.meta);
     else
-        prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of);
+        prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of,
+                      words);
 }
 
 __global__ __launch_bounds__(256) void dp_prepare(const int32_t *__restrict__ tau, int K, int L,
@@ -1356,10 +1485,11 @@ void dp_fill(
     static_assert(kPath < 3 || (!kLevel && !kBlocks && !kTurns && !kSplit),
                   "the launches of twice the waves are plain D-record fills");
     constexpr bool kQuads = !kLevel && kNarrow;  // the D-record sweep with 128-bit LDS reads
+    constexpr bool kCanTile = !kLevel && !kBlocks && !kTodo && !(kPath == 1 && kNarrow);
     static_assert(!kSplit || (kQuads && kPath == 1 && !kBlocks && !kTurns),
                   "the split launch is the plain in-place D-record fill");
-    if (meta[kMetaPath] != kPath)
-        return;                                  // another launch does the work
+    if (meta[kMetaPath] != kPath || (kCanTile && meta[kMetaTiles] != 0))
+        return;                                  // another launch does the work (or dp_tiles)
     const int bp = meta[kMetaBudget];
     const int tid = threadIdx.x, nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
@@ -1671,6 +1801,8 @@ void dp_fill(
         write_result<kTodo>(bv, bt, k, tstar, cost);
     }
 }
+
+#include "dp_tiles.h"
 
 // Final argmin for other budgets on an already filled D record: the rows hold exact-time costs
 // and do not depend on the budget, so a smaller budget only shortens the range of the argmin
@@ -2157,9 +2289,33 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
 
+    // Several workgroups per candidate, or one with less to do between the layers (see dp_tiles.h): where
+    // each has two compute units, and up to one per unit where rows are short (B = 8000 of S = 40, K = 256:
+    // 224 us and 234 otherwise; B = 1000: 107 and 156; B = 10000: 262 and 256); and where rows may have to lie
+    // in memory otherwise.
+    constexpr bool can_tile = !kLevel && !kBlocks && !kTodo;
+    const bool tiles_do = can_tile && !resume.first_layer &&
+                          (2LL * K <= units || (K <= units && B <= kTileLone));
+    const bool tiles_sure = tiles_do && B <= (kNarrow ? kTileSure : kTileSureWide);
+    TileArgs ta{units, tiles_do ? 0 : 1, 0, kTileLds / (int)sizeof(float), nullptr, 0};
+    if (tiles_do || (can_tile && !resume.first_layer && in_memory)) {
+        ta.most = in_memory ? (K <= 512 ? kTileMost : (K <= 2048 ? 8192 / K : 4)) : units / K;
+        ta.most = ta.most < kTileMost ? ta.most : kTileMost;
+        // the books lie where the rows in memory would, or in tables that nothing else reads then; they
+        // are for more than one tile only
+        size_t room = 0;
+        if (lay.may_spill) {
+            ta.books = reinterpret_cast<int *>(rows);
+            room = lay.total_value - lay.rows_value;
+        } else if (kNarrow || tiles_sure) {
+            ta.books = order;
+            room = lay.entry_off - lay.order_off;
+        }
+        ta.room = (int)(room / sizeof(int) < (1u << 30) ? room / sizeof(int) : (1u << 30));
+    }
     const PrepareArgs prep{2 * units, s8, B, waves, max_group, lds_small, lds_large, lds_stage,
-                           kLevel ? 0 : (kNarrow ? 2 : 1), split ? 1 : 0, wide_waves, wide_group,
-                           lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1, meta, shifts, order, start, entry};
+                           kLevel ? 0 : (kNarrow ? 2 : (tiles_sure ? 3 : 1)), split ? 1 : 0, wide_waves, wide_group,
+                           lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1, meta, shifts, order, start, entry, ta};
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
@@ -2172,8 +2328,22 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
         hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
     }
     const LevelTables tables{shifts, order, start, entry, s8};
-    hipLaunchKernelGGL(in_place, dim3(K), dim3(place_threads), place_lds, q, src, meta, tables,
-                       units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
+    if constexpr (can_tile) {
+        if (ta.most > 0) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_tiles),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds) !=
+                hipSuccess)
+                return SPDY_DP_ERR_LAUNCH;
+            hipLaunchKernelGGL(dp_tiles, dim3(K * ta.most), dim3(kTileThreads), kTileLds, q, src,
+                               meta, tables, K, L, S, pitch, drec, tstar, cost, ta.books);
+        }
+    }
+    if (tiles_sure)
+        return launch_status();
+    if (!kNarrow || !tiles_do)
+        hipLaunchKernelGGL(in_place, dim3(K), dim3(place_threads), place_lds, q, src, meta, tables,
+                           units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks,
+                           todo);
     if (wide)
         hipLaunchKernelGGL(wide_place, dim3(K), dim3(wide_waves * kWave), lds_wide, q, src, meta,
                            tables, units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume,
