@@ -630,6 +630,12 @@ __device__ __forceinline__ void vmin3(float &b, float x, float y)
 {
     asm("v_min3_f32 %0, %0, %1, %2" : "+v"(b) : "v"(x), "v"(y));
 }
+__device__ __forceinline__ float min3(float x, float y, float z)
+{
+    float least;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(least) : "v"(x), "v"(y), "v"(z));
+    return least;
+}
 
 // Where err[k][l][s] comes from: an explicit table, or the product of a per-layer sensitivity
 // c[k][l] and a per-level weight w[s] (Eq. 4), formed with one fp32 multiply when it is needed.
@@ -925,20 +931,74 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
         if (blk == 0)
             use &= first.keep;
         if constexpr (kLevel) {
-            while (use) {
-                const int i = __builtin_ctzll(use);
+            // Two levels (in index order) share one comparison: where the smaller of the two is below
+            // what came before, the cell notes the pair, and which of the two it was is found out
+            // once at the end.  Strict "<" decides; the value is the min either way (the sign of
+            // a zero may differ from a select's, the walk back re-sums the cost).  Add, compare, select
+            // and min for every level, 4 operations, are 2.5 for half of a pair: K = 1001, L = 52,
+            // S = 42, B = 9973: 1533 us a solve and 1312.  (Comparing once for four levels saves no
+            // more: three of them have to be looked at again at the end.)
+            auto take_pair = [&](int &p0, int &p1, float &e0, float &e1) __attribute__((always_inline)) {
+                const int i0 = __builtin_ctzll(use);
                 use &= use - 1;
+                const int i1 = __builtin_ctzll(use);
+                use &= use - 1;
+                p0 = __builtin_amdgcn_readlane(mine.shift, i0);
+                p1 = __builtin_amdgcn_readlane(mine.shift, i1);
+                e0 = lane_value(mine.err, i0);
+                e1 = lane_value(mine.err, i1);
+                return (unsigned)(blk + i0) | (unsigned)(blk + i1) << 8;   // (>= 256: i1 > 0)
+            };
+            int n_use = __builtin_popcountll(use);
+            for (; n_use >= 4; n_use -= 4) {      // two pairs a trip, so that no minimum is moved
+                int sa, sb, sc, sd;
+                float ea, eb, ec, ed;
+                const unsigned ab = take_pair(sa, sb, ea, eb), cd = take_pair(sc, sd, ec, ed);
+                const float *const pa = row_at(sa), *const pb = row_at(sb);
+                const float *const pc = row_at(sc), *const pd = row_at(sd);
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const float m = min3(best[j], pa[j * kWave] + ea, pb[j * kWave] + eb);
+                    arg[j] = m < best[j] ? ab : arg[j];
+                    best[j] = min3(m, pc[j * kWave] + ec, pd[j * kWave] + ed);
+                    arg[j] = best[j] < m ? cd : arg[j];
+                }
+            }
+            if (n_use >= 2) {
+                int sa, sb;
+                float ea, eb;
+                const unsigned ab = take_pair(sa, sb, ea, eb);
+                const float *const pa = row_at(sa), *const pb = row_at(sb);
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const float m = min3(best[j], pa[j * kWave] + ea, pb[j * kWave] + eb);
+                    arg[j] = m < best[j] ? ab : arg[j];
+                    best[j] = m;
+                }
+            }
+            if (use) {
+                const int i = __builtin_ctzll(use);
                 const float *p = row_at(__builtin_amdgcn_readlane(mine.shift, i));
                 const float e = lane_value(mine.err, i);
                 const unsigned s = (unsigned)(blk + i);   // visiting order = level index here
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
-                    // strict "<" decides the level; the value is the min either way (the sign
-                    // of a zero may differ from a select's, the walk back re-sums the cost)
                     const float v = p[j * kWave] + e;
                     arg[j] = v < best[j] ? s : arg[j];
                     vmin(best[j], v);
                 }
+            }
+            // the first of a noted pair if it gives the cell's value, otherwise the second (what a
+            // later single level beat is below 256 and stays)
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const bool pair = arg[j] > kNoLevel;
+                const int i = (int)(arg[j] & 0xFF) - blk;
+                const int shift = __shfl(mine.shift, i, kWave);
+                const float e = __shfl(mine.err, i, kWave);
+                const float v = row_at(pair ? shift : 0)[j * kWave] + e;
+                const unsigned s = v == best[j] ? arg[j] & 0xFF : arg[j] >> 8;
+                arg[j] = pair ? s : arg[j];
             }
         } else {
             // sorted by shift: the applicable levels are the first n_use of the block

@@ -295,6 +295,24 @@ def test_every_group_size_of_the_sweep(dp):
         assert set(range(1, most + 1)) <= seen[K], (K, sorted(set(range(1, most + 1)) - seen[K]))
 
 
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 6, 7, 8, 63, 64, 65, 66, 67, 129, 255])
+def test_level_record_of_tied_pairs(dp, S):
+    """Level record: two levels in index order share a comparison, and blocks of 64 levels follow each
+    other.  Errors of two and three values tie within pairs, between pairs and between blocks, and
+    times from one bucket to beyond the row leave any number of levels applicable."""
+    rng = np.random.default_rng(500 + S)
+    for B, tau_max in ((63, 3), (700, 40), (1300, 1300), (5000, 900)):
+        for values in (2, 3, None):
+            tau, err, _ = workloads.random_instance(
+                rng, 5, 7, S, B, tau_max=tau_max, integer_err=values,
+                inf_err_frac=0.1 if values == 3 else 0.0, zero_tau_frac=0.1)
+            what = f"S={S} B={B} tau_max={tau_max} values={values}"
+            p_gpu, c_gpu, ws = gpu_solve(dp, tau, err, B, compact=True)
+            assert_same(p_gpu, c_gpu, *oracle.solve_ref(tau, err, B, threads=CPU_THREADS), what)
+            for k in (0, 4):
+                check_tables(dp, tau, err[k], B, ws, k, 5)
+
+
 def test_infeasible_and_mixed_batches(dp):
     # candidate 0 feasible, candidate 1 has every level of layer 2 forbidden, budget too small
     tau = np.array([[5, 3, 1], [4, 2, 1], [6, 2, 2]], dtype=np.int32)
