@@ -1524,22 +1524,23 @@ __device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
 //              record, row and the final argmin are the first half's.  The partial rows of the
 //              second half lie in LDS behind the smaller allocation (the launch gets twice that).
 // `pitch` is the record's row pitch (elements per (k, l) row).
-template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo = false,
-          bool kTurns = false, bool kSplit = false>
-__global__ __launch_bounds__(fill_waves<kLevel>() * (kSplit || kPath >= 3 ? 2 : 1) * kWave,
-                             kLevel ? 8 : 4)
-void dp_fill(
+struct FillShared {      // static LDS of the kernels
+    float best[kMaxFillWaves];
+    int time[kMaxFillWaves];
+    // per team and for two layers: merged errors (D record), or in the same storage one 64-bit
+    // set of levels to visit (level record)
+    __attribute__((aligned(8))) float entries[2][kMaxFillWaves][kWave];
+};
+template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo, bool kTurns, bool kSplit>
+__device__ __forceinline__ void fill_candidates(
     ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
     int S, int pitch, uint8_t *__restrict__ choice, float *__restrict__ drec,
     float *__restrict__ rows, int32_t *__restrict__ tstar, float *__restrict__ cost, Resume resume,
-    Blocks blocks, Todo todo)
+    Blocks blocks, Todo todo, float *lds, FillShared &sh)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    __shared__ float s_best[kMaxFillWaves];
-    __shared__ int s_time[kMaxFillWaves];
-    // per team and for two layers: merged errors (D record), or in the same storage one 64-bit
-    // set of levels to visit (level record)
-    __shared__ __attribute__((aligned(8))) float s_entries[2][kMaxFillWaves][kWave];
+    auto &s_best = sh.best;
+    auto &s_time = sh.time;
+    auto &s_entries = sh.entries;
     constexpr bool kGlobal = kPath == 0 || kPath == 4;     // rows in global memory
     constexpr bool kLds = !kGlobal, inplace = kPath == 1 || kPath == 3;
     static_assert(kPath < 3 || (!kLevel && !kBlocks && !kTurns && !kSplit),
@@ -1862,6 +1863,23 @@ void dp_fill(
     }
 }
 
+template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo = false,
+          bool kTurns = false, bool kSplit = false>
+__global__ __launch_bounds__(fill_waves<kLevel>() * (kSplit || kPath >= 3 ? 2 : 1) * kWave,
+                             kLevel ? 8 : 4)
+void dp_fill(
+    ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
+    int S, int pitch, uint8_t *__restrict__ choice, float *__restrict__ drec,
+    float *__restrict__ rows, int32_t *__restrict__ tstar, float *__restrict__ cost, Resume resume,
+    Blocks blocks, Todo todo)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ FillShared sh;
+    fill_candidates<kLevel, kPath, kNarrow, kBlocks, kTodo, kTurns, kSplit>(
+        src, meta, tables, units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks,
+        todo, lds, sh);
+}
+
 #include "dp_tiles.h"
 
 // Final argmin for other budgets on an already filled D record: the rows hold exact-time costs
@@ -1973,19 +1991,16 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
     cost[k] = acc;
 }
 
-// `budgets` > 1 (solve_budgets): solve j * K + k is candidate k under budget j, and its final time
-// comes in through cost (dp_budget_argmin).
+// One wave walks solve `solve`, which is candidate k under some budget.
 template <int kLevelBlocks, bool kByItself>
-__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
-    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
-    const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
-    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
+__device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrSource src,
+                                           const int32_t *__restrict__ meta,
+                                           const float *__restrict__ drec, const int32_t *tstar,
+                                           int solve, int k, int L, int S, int pitch,
+                                           int16_t *__restrict__ profile, float *cost,
+                                           Resume resume)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
-    const int k = budgets > 1 ? solve % K : solve;
-    if (solve >= K * budgets || !todo.has_wave(solve, K, L))
-        return;
     int16_t *prof = profile + (size_t)solve * L;
     const ErrSource mine = src.of_candidate(k, L, S);
     const float *drec_k = drec + (size_t)k * L * pitch;
@@ -2003,27 +2018,40 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
         cost[solve] = acc;
 }
 
+// `budgets` > 1 (solve_budgets): solve j * K + k is candidate k under budget j, and its final time
+// comes in through cost (dp_budget_argmin).
+template <int kLevelBlocks, bool kByItself>
+__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
+    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
+{
+    const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    const int k = budgets > 1 ? solve % K : solve;
+    if (solve < K * budgets && todo.has_wave(solve, K, L))
+        walk_table<kLevelBlocks, kByItself>(tau, src, meta, drec, tstar, solve, k, L, S, pitch,
+                                            profile, cost, resume);
+}
+
 // The walk through one block of layers [blocks.begin, blocks.end) of the small-record solve: rows
 // come from the block record, the row below the block from its checkpoint; tstar holds the time
 // to start from and receives the time below the block; the cost is summed after the first block
 // (the last one walked).
 template <int kLevelBlocks>
-__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
-    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
-    int32_t *__restrict__ tstar, int K, int L, int S, int pitch, int16_t *__restrict__ profile,
-    float *__restrict__ cost, Blocks blocks, Todo todo)
+__device__ __forceinline__ void walk_block(const int32_t *__restrict__ tau, ErrSource src,
+                                           const int32_t *__restrict__ meta,
+                                           int32_t *__restrict__ tstar, int k, int L, int S,
+                                           int pitch, int16_t *__restrict__ profile,
+                                           float *__restrict__ cost, Blocks blocks)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
-    if (k >= K || !todo.has_wave(k, K, L))
-        return;
     int16_t *prof = profile + (size_t)k * L;
     const ErrSource mine = src.of_candidate(k, L, S);
     const int lb = blocks.begin;
-    auto row_of = [&](int l) {
-        return l >= lb ? blocks.block + ((size_t)k * blocks.stride + (l - lb)) * pitch
-                       : blocks.ckpt + ((size_t)k * blocks.slots + (lb / blocks.stride - 1)) * pitch;
-    };
+    const float *const rows = blocks.block + (size_t)k * blocks.stride * pitch;
+    const float *const below =
+        lb > 0 ? blocks.ckpt + ((size_t)k * blocks.slots + (lb / blocks.stride - 1)) * pitch : rows;
+    auto row_of = [=](int l) { return l >= lb ? rows + (size_t)(l - lb) * pitch : below; };
     const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, tstar[k], lb, blocks.end, L, S,
                                             prof);
     if (lane == 0) {
@@ -2036,6 +2064,57 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
     const float acc = profile_cost(mine, L, S, prof);
     if (lane == 0)
         cost[k] = acc;
+}
+
+template <int kLevelBlocks>
+__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    int32_t *__restrict__ tstar, int K, int L, int S, int pitch, int16_t *__restrict__ profile,
+    float *__restrict__ cost, Blocks blocks, Todo todo)
+{
+    const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    if (k < K && todo.has_wave(k, K, L))
+        walk_block<kLevelBlocks>(tau, src, meta, tstar, k, L, S, pitch, profile, cost, blocks);
+}
+
+// Behind dp_core, D record, no more candidates than compute units: fill and walk back of the few
+// candidates it gave up, in one launch.  A candidate has a unit to itself then whatever LDS its
+// workgroup asks for, so the launches for rows of different lengths need not be kept apart, and its
+// walk only needs its own rows.  Nearly always there is nothing to do, and what counts is the number of
+// launches, 1.9 us each: K = 256, L = 200, S = 64, B = 65536 with checkpoints has 15 instead of 59.
+// (With more candidates a table that does not reduce is filled by workgroups that share a unit.)
+// `profile`: nullptr where there are budgets to choose from first.
+template <bool kNarrow, bool kBlocks>
+__global__ __launch_bounds__((kBlocks ? 1 : 2) * kFillWaves * kWave, 4) void dp_rest(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    LevelTables tables, int units, int K, int L, int S, int pitch, float *drec, float *rows,
+    int32_t *tstar, int16_t *profile, float *cost, Resume resume, Blocks blocks, Todo todo)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ FillShared sh;
+    const int k = blockIdx.x;
+    if (!todo.has_wave(k, K, L))
+        return;
+    auto fill = [&](auto path) __attribute__((always_inline)) {
+        constexpr int kPath = decltype(path)::value;
+        fill_candidates<false, kPath, kNarrow, kBlocks, true, false,
+                        kPath == 1 && kNarrow && !kBlocks>(
+            src, meta, tables, units, K, L, S, pitch, nullptr, drec, rows, tstar, cost, resume,
+            blocks, todo, lds, sh);
+    };
+    fill(Many<1>{});                              // (each only where the path is its own)
+    fill(Many<kBlocks ? 2 : 3>{});
+    fill(Many<kBlocks ? 0 : 4>{});
+    if (!profile || (kBlocks && blocks.pass == 0))
+        return;
+    __syncthreads();                              // the rows and the final time are written
+    if (threadIdx.x >= kWave)
+        return;
+    if constexpr (kBlocks)
+        walk_block<kNarrow ? 1 : 4>(tau, src, meta, tstar, k, L, S, pitch, profile, cost, blocks);
+    else
+        walk_table<kNarrow ? 1 : 4, false>(tau, src, meta, drec, tstar, k, k, L, S, pitch, profile,
+                                           cost, resume);
 }
 
 int launch_status()
@@ -2087,6 +2166,7 @@ struct CoreCall {
     int budgets;
     unsigned char *spill;             // the record's memory
     size_t spill_bytes;
+    bool rest;                        // dp_rest does what is left, except the walks under several budgets
 };
 
 // LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
@@ -2189,7 +2269,8 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
 {
     CoreParams cp{};
     int lds = 0, largest = 0;
-    if (lay.status != SPDY_DP_OK || !workspace)
+    DeviceState dev;
+    if (lay.status != SPDY_DP_OK || !workspace || device_state(false, &dev) != SPDY_DP_OK)
         return false;
     for (int j = 0; j < J; ++j)
         largest = budget[j] > largest ? budget[j] : largest;
@@ -2198,7 +2279,8 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
         return false;
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
-                     workspace_bytes - lay.record_off};
+                     workspace_bytes - lay.record_off,
+                     lay.variant == kValueRecord && K <= dev.units};
     return true;
 }
 
@@ -2304,15 +2386,17 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
                           : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false>;
     // A candidate that has a compute unit to itself gets twice the waves (the second half takes
     // every other pair of each layer's entries and needs a second row in LDS for its minima).
-    constexpr bool can_split = !kLevel && kNarrow && !kBlocks;
+    constexpr bool can_split = !kLevel && kNarrow && !kBlocks;       // (behind dp_core: dp_rest)
     const bool split = can_split && K <= units;
     int place_threads = waves * kWave, place_lds = lds_small;
-    if constexpr (can_split) {
+    if (split) {
+        place_threads *= 2;
+        place_lds *= 2;
+        static_assert(2 * kLdsHalf <= kLdsBytes, "two half allocations fit one workgroup");
+    }
+    if constexpr (can_split && !kTodo) {
         if (split) {
             in_place = dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, true>;
-            place_threads *= 2;
-            place_lds *= 2;
-            static_assert(2 * kLdsHalf <= kLdsBytes, "two half allocations fit one workgroup");
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(in_place),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     kLdsBytes) != hipSuccess)
@@ -2388,6 +2472,23 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
         hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
     }
     const LevelTables tables{shifts, order, start, entry, s8};
+    if constexpr (kTodo && !kLevel) {
+        if (core->rest) {
+            auto rest = dp_rest<kNarrow, kBlocks>;
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(rest),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) !=
+                hipSuccess)
+                return SPDY_DP_ERR_LAUNCH;
+            int lds = place_lds > lds_wide ? place_lds : lds_wide;
+            lds = lds_large > lds ? lds_large : lds;
+            lds = in_memory && lds_stage > lds ? lds_stage : lds;
+            const int threads = wide ? wide_waves * kWave : place_threads;
+            hipLaunchKernelGGL(rest, dim3(K), dim3(threads), lds, q, tau, src, meta, tables, units, K, L,
+                               S, pitch, drec, rows, tstar, cost ? core->profile : nullptr, cost,
+                               resume, blocks, todo);
+            return launch_status();
+        }
+    }
     if constexpr (can_tile) {
         if (ta.most > 0) {
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_tiles),
@@ -2517,7 +2618,7 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
         todo = Todo{profile, 1};
     const int st = fill_impl(tau, src, K, L, S, B, cost, workspace, workspace_bytes, stream, resume,
                              todo.profile ? &core : nullptr);
-    if (st != SPDY_DP_OK)
+    if (st != SPDY_DP_OK || (todo.profile && core.rest))
         return st;
     return backtrace_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream,
                           false, resume, todo);
@@ -2590,6 +2691,8 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
         st = fill();
         if (st != SPDY_DP_OK)
             return st;
+        if (reduced && core.rest)
+            continue;                             // walked already
         auto walk = S <= kWave ? dp_backtrace_blocks<1> : dp_backtrace_blocks<4>;
         hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
                            tau, src, meta, tstar, K, L, S, (int)lay.row, profile, cost, blocks,
