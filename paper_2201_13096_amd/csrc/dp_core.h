@@ -26,8 +26,9 @@
 //
 // What bounds it: latency.  A candidate of L = 54, S = 40 is about 11 passes over its table in LDS for
 // the multiplier (2300 clocks each: a scan of twelve levels per thread, two joins, a barrier),
-// five for the known profile, then 15 dependent steps of 1700 clocks for the reduced table and 500
-// for each step back; one wave per SIMD issues an instruction every seven or eight clocks whatever
+// five of 2900 for the known profile, then dependent steps for the reduced table, 15 usually, 20 to 45 for
+// the slowest candidates and some of those twice (2000 clocks each and 500 for each step back before the rows
+// of one chunk stayed in a register); one wave per SIMD issues an instruction every seven or eight clocks whatever
 // it is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Kernel time
 // against fill and walk back of the whole table: K = 100, L = 52, S = 42, B = 10^4: 73 us / 297 us;
 // K = 4096, L = 72, S = 40, B = 16384: 303 us / 3.34 ms; K = 333, S = 127: 104 us / 0.92 ms;
@@ -86,8 +87,10 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
     return (unsigned long long)high << 32 | low;
 }
 
-// A row in memory.  (A pointer that might also be one to LDS would be read by flat instructions.)
+// A row and a record in memory.  (A pointer that might also be one to LDS would be used by flat
+// instructions, and the waits for LDS would wait for memory, too.)
 using FarRow = __attribute__((address_space(1))) float *;
+using FarBytes = __attribute__((address_space(1))) unsigned char *;
 
 template <int N> struct Many {
     static constexpr int value = N;
@@ -567,6 +570,86 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             }
         };
         int m = 0;
+        // Steps whose rows fit one chunk, most of them, by one wave: the row stays in a register, lane
+        // `off` + x holding bucket a + x, and entries fetch their cells from other lanes.  What bounds a
+        // step is the number of instructions one wave issues one after the other; here there is no row to
+        // write and read again, no choice of where it lies, and half the branches.  Takes at least
+        // the step that the caller has looked at; the row is left in LDS.  us a call, with the walk back
+        // in registers, before and after: K = 64 under six budgets, L = 54, S = 40: 79.2 and 76.4;
+        // K = 4096, L = 72: 302 and 290; K = 100, L = 52 (wide rows): 74.0 and 73.1.
+        auto one_chunk = [&]() __attribute__((always_inline)) {
+            float row = prev[min(lane, b - a)];
+            int off = 0;
+            for (;;) {
+                if (m - base_step >= kWave)
+                    load_steps(m);
+                const int i_m = m - base_step;
+                const int n = __builtin_amdgcn_readlane(held_step.count, i_m);
+                const int top = min(b + __builtin_amdgcn_readlane(held_step.span, i_m), budget);
+                const int width = top - a + 1;
+                if (width > kWave || n > kWave || used + width > cp.record || work + n > cp.work)
+                    break;
+                const int first = __builtin_amdgcn_readlane(held_step.first, i_m);
+                const int layers_m = __builtin_amdgcn_readlane(held_step.layer, i_m);
+                const double lim = from_lane(held_limit, i_m);
+                const CoreEntry en = lane < n ? next : none();
+                const int follow = first + n + lane;
+                next = follow < total ? list[follow] : none();
+                work += n;
+                row_at[m] = used - a;             // (every lane, the same)
+                const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
+                const unsigned reach = (unsigned)(b - a);
+                float best = __builtin_inff();
+                int arg = 0;
+                auto some = [&](int i, auto many) __attribute__((always_inline)) {
+                    constexpr int kMany = decltype(many)::value;
+                    float v[kMany];
+#pragma unroll
+                    for (int q = 0; q < kMany; ++q) {
+                        const int u = lane - __builtin_amdgcn_readlane(shift, i + q);
+                        const float d = __builtin_bit_cast(
+                            float, __builtin_amdgcn_ds_bpermute((u + off) * 4,
+                                                                __builtin_bit_cast(int, row)));
+                        v[q] = ((unsigned)u <= reach ? d : __builtin_inff()) +
+                               lane_value(en.err, i + q);
+                    }
+#pragma unroll
+                    for (int q = 0; q < kMany; ++q) {
+                        const bool take = v[q] < best;
+                        best = take ? v[q] : best;
+                        arg = take ? i + q : arg;
+                    }
+                };
+                if (n <= 2)
+                    some(0, Many<2>{});
+                else
+                    for (int i = 0; i < n; i += 4)
+                        some(i, Many<4>{});
+                best = add_singles(best, (layers_m & 0xFFFF) + 1, layers_m >> 16);
+                const bool in = lane < width;
+                if (in)
+                    rec[used + lane] = (unsigned char)arg;
+                const unsigned long long set = __ballot(
+                    in && __builtin_fma(lambda, (double)(a + lane), (double)best) <= lim);
+                used += width;
+                row = best;
+                ++m;
+                if (set == 0) {                   // no profile costs as little as `target`
+                    failed = true;
+                    break;
+                }
+                off = __builtin_ctzll(set);
+                b = a + 63 - __builtin_clzll(set);
+                a += off;
+                if (m == nsteps)
+                    break;
+            }
+            float *const to = prev >= row1 ? row0 : row1;
+            to[lane] = row;
+            prev = to + off;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
         while (m < nsteps && !failed) {
             // One step.  A row of one or two chunks is done by wave 0 alone, as are the narrow ones
             // after it, without a barrier: the others wait for where it has got to.
@@ -591,6 +674,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                     break;
                 }
                 alone = narrow;
+                if ((!kFar || far_prev < 0) && chunks == 1 && n <= kWave &&
+                    first_spilled == nsteps && used + width <= cp.record && work + n <= cp.work) {
+                    one_chunk();
+                    if (failed || m == nsteps)
+                        break;
+                    continue;
+                }
                 const CoreEntry held_entry = lane < n ? next : none();
                 const int follow = first + n + lane;   // the next step's entries
                 next = follow < total ? list[follow] : none();
@@ -602,13 +692,10 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                     failed = wide = true;
                     break;
                 }
-                unsigned char *out = rec + used;
-                if (spills) {
-                    first_spilled = min(first_spilled, m);
-                    out = spill + spilled;
-                }
+                const int out = spills ? spilled : used;
+                first_spilled = spills ? min(first_spilled, m) : first_spilled;
                 if (tid == 0)
-                    row_at[m] = (spills ? spilled : used) - a;
+                    row_at[m] = out - a;
                 spilled += spills ? width : 0;
                 used += spills ? 0 : width;
                 float *const cur = prev >= row1 ? row0 : row1;
@@ -650,7 +737,10 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                             far_row(far_cur)[x] = best;
                         else
                             cur[x] = best;
-                        out[x] = (unsigned char)arg;
+                        if (spills)
+                            ((FarBytes)spill)[out + x] = (unsigned char)arg;
+                        else
+                            rec[out + x] = (unsigned char)arg;
                     }
                     const bool live =
                         in && __builtin_fma(lambda, (double)(a + x), (double)best) <= lim;
@@ -749,30 +839,33 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         if (first_spilled < nsteps)
             __threadfence_block();
         int t = a + (int)(unsigned)key;
-        uint32_t next_word = 0;
-        CoreStep st{0, 0, 0, 0};
-        int at = 0;
-        if (nsteps) {
-            st = steps[nsteps - 1];
-            at = row_at[nsteps - 1];
-            next_word = st.first + lane < total ? list[st.first + lane].word : 0;
-        }
-        for (int m = nsteps - 1; m >= 0; --m) {
-            const uint32_t words = next_word;
-            const CoreStep now = st;
-            const int here = __builtin_amdgcn_readfirstlane(at) + t;
-            const int e =
-                __builtin_amdgcn_readfirstlane(m >= first_spilled ? spill[here] : rec[here]);
-            if (m > 0) {
-                st = steps[m - 1];
-                at = row_at[m - 1];
-                next_word = list[min(st.first + lane, total - 1)].word;
+        for (int base = (nsteps - 1) & ~(kWave - 1); nsteps > 0 && base >= 0; base -= kWave) {
+            // lane i holds step base + i, and what it chose
+            const int n = min(kWave, nsteps - base);
+            const CoreStep st = steps[min(base + lane, nsteps - 1)];
+            const int at = row_at[min(base + lane, nsteps - 1)];
+            auto words_of = [&](int i) __attribute__((always_inline)) {
+                return list[min(__builtin_amdgcn_readlane(st.first, i) + lane, total - 1)].word;
+            };
+            uint32_t next_words = words_of(n - 1), chosen = 0;
+            for (int i = n - 1; i >= 0; --i) {
+                const uint32_t words = next_words;
+                const int here = __builtin_amdgcn_readlane(at, i) + t;
+                int e;
+                if (base + i >= first_spilled)
+                    e = __builtin_amdgcn_readfirstlane(((FarBytes)spill)[here]);
+                else
+                    e = __builtin_amdgcn_readfirstlane(rec[here]);
+                if (i > 0)
+                    next_words = words_of(i - 1);
+                const uint32_t word =
+                    e < kWave ? (uint32_t)__builtin_amdgcn_readlane((int)words, e)
+                              : uniform(list[__builtin_amdgcn_readlane(st.first, i) + e].word);
+                chosen = lane == i ? word : chosen;
+                t -= (int)(word & ((1u << kCoreShiftBits) - 1u));
             }
-            const uint32_t word = e < kWave ? (uint32_t)__builtin_amdgcn_readlane((int)words, e)
-                                            : list[now.first + e].word;
-            if (lane == 0)
-                profile[now.layer] = (int16_t)(word >> kCoreShiftBits);
-            t -= __builtin_amdgcn_readfirstlane((int)(word & ((1u << kCoreShiftBits) - 1u)));
+            if (lane < n)
+                profile[st.layer] = (int16_t)(chosen >> kCoreShiftBits);
         }
         return;
     }

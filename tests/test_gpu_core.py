@@ -399,3 +399,18 @@ def test_given_up_candidates_of_budgets_and_sensitivities(dp, K, L, S, B):
         at = dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["tstar_offset"]
         filled = ws[at:at + 4 * K].cpu().numpy().view(np.uint32) != 0xABABABAB
         assert filled[refused].all() and not filled.all()
+
+
+@pytest.mark.parametrize("B", [70, 200, 500, 900, 1500, 2600, 5000, 12000])
+@pytest.mark.parametrize("S", [3, 12, 67])
+def test_rows_around_one_chunk(dp, B, S):
+    """A row of at most 64 buckets stays in a register from step to step and goes back to LDS where the
+    next one is wider: rows on either side of that line and across it, more than 64 steps, layers
+    between two steps on either side of a block of 64, ties, levels of equal time."""
+    rng = np.random.default_rng(B + S)
+    tau, err = smooth(rng, 9, 140, S, B)
+    check(dp, tau, err, B, "smooth")
+    check(dp, tau, np.floor(err * 8).astype(np.float32), B, "ties")
+    tau, err, _ = workloads.random_instance(rng, 9, 70, S, B, tau_max=max(2, B // 35),
+                                            integer_err=50, zero_tau_frac=0.1)
+    check(dp, tau, err, B, "unstructured")
