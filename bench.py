@@ -36,9 +36,10 @@ ALU_PEAK_LANE_OPS = COMPUTE_UNITS * 128 * CLOCK_HZ
 #   LDS: one 4-byte read of the shifted previous row plus the 4 / S bytes the new row's write
 #        costs per update.
 #   ALU, D record: an fp32 add and an fp32 min; as built one v_min3_f32 folds two updates, so 1.5
-#        issued instructions per update.  Level record: add, compare, select of the level, min.
+#        issued instructions per update.  Level record: add, compare, select of the level, min;
+#        as built two levels share a min3, a compare and a select, so 2.5.
 LANE_OPS_PER_UPDATE = {"d": 2.0, "level": 4.0}
-LANE_OPS_AS_BUILT = {"d": 1.5, "level": 4.0}
+LANE_OPS_AS_BUILT = {"d": 1.5, "level": 2.5}
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
                   for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h")]

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void valu_add_add_min3(float *out, float c, in
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-// Level-record update as built: add, compare, select of the level, min (4 instructions).
+// Level-record update by itself: add, compare, select of the level, min (4 instructions).
 __global__ __launch_bounds__(256) void valu_add_cmp_sel_min(float *out, float c, int iters)
 {
     float a[kChains], b[kChains];
