@@ -92,10 +92,6 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
 using FarRow = __attribute__((address_space(1))) float *;
 using FarBytes = __attribute__((address_space(1))) unsigned char *;
 
-template <int N> struct Many {
-    static constexpr int value = N;
-};
-
 struct CoreBooks {       // where the steps of the reduced table have got to
     int m, a, b, used, spilled, first_spilled, work, prev, failed, wide;
 };

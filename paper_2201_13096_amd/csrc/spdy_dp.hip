@@ -324,7 +324,8 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
 // lds_small or lds_large bytes, `waves` waves per workgroup) fits, into how many teams its waves
 // split, and whether one row per candidate is enough; and it records each layer's largest usable
 // shift (the tiles of the global-row path size their window in LDS by it).  Thread i owns layers i,
-// i + 256, ...; a layer's times are read by a wave, four layers on their way at a time.
+// i + 256, ...; a layer's times are read by eight lanes.
+// What bounds it: latency, about 11000 clocks of dependent steps for L = 54, S = 40.
 __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots, int L, int S,
                                int B, int waves, int max_group, int lds_small, int lds_large,
                                int lds_stage, int split, int wide_waves, int wide_group,
@@ -332,51 +333,70 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
                                int32_t *words, int32_t *__restrict__ meta)
 {
     __shared__ long long s_sum[8];
-    __shared__ int s_team_waves, s_span, s_tiles;
+    __shared__ int s_team_waves, s_span, s_tiles, s_beyond;
     int32_t *const s_least = words, *const s_most = words + 256;
     const int tid = threadIdx.x;
     if (tid == 0)
-        s_span = 0;
+        s_span = s_beyond = 0;
     int32_t *mn = meta + kMetaHeader;
     int32_t *nact = meta + kMetaHeader + L;
     int32_t *spans = meta + kMetaHeader + (2 + (size_t)kRangeStride) * L;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
 
-    long long local = 0;
-    for (int base = 0; base < L; base += 256) {
-        const int n = min(256, L - base);
-        for (int i0 = wave; i0 < n; i0 += 16) {
-            const int32_t *tau_i[4];
-            int least[4], most[4];
+    // Least and largest time of the layers [base, base + n), or (kCapped) the largest that is not above
+    // the layer's word of s_least (nothing where that is negative).  Eight lanes per layer, so that all
+    // loads of 32 layers are on their way at once and three steps across lanes join them: L = 54 takes
+    // 2000 clocks (a wave per layer, four or eight layers at a time: 4800 and 7400, most of it scans).
+    // The second reading costs 1000; by one thread, a level after the other, it made the shortest
+    // fills 1.15 of what they are (K = 1, L = 8, S = 40, B = 500: 27.5 us and 24.6).
+    auto read_times = [&](int base, int n, auto capped) __attribute__((always_inline)) {
+        constexpr bool kCapped = decltype(capped)::value != 0;
+        constexpr int kLanes = 8, kLoads = 8;
+        const int part = lane & (kLanes - 1);
+        for (int i0 = wave * (kWave / kLanes); i0 < n; i0 += 256 / kLanes) {
+            const int i = i0 + lane / kLanes, at = min(i, n - 1);
+            const int32_t *const tau_i = tau + (size_t)(base + at) * S;
+            const int cap = kCapped ? s_least[at] : INT32_MAX;
+            if (kCapped && !__any(cap >= 0))
+                continue;
+            int least = INT32_MAX, most = 0;
+            for (int s0 = 0; s0 < S; s0 += kLanes * kLoads) {
+                int v[kLoads];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {         // (past the last layer: that one once more)
-                tau_i[q] = tau + (size_t)(base + min(i0 + 4 * q, n - 1)) * S;
-                least[q] = INT32_MAX;
-                most[q] = 0;
-            }
-            for (int s = lane; s < S; s += kWave) {
+                for (int q = 0; q < kLoads; ++q)  // (past the last level: that one once more)
+                    v[q] = tau_i[min(s0 + q * kLanes + part, S - 1)];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int v = tau_i[q][s];
-                    least[q] = min(least[q], v);
-                    most[q] = max(most[q], v);
+                for (int q = 0; q < kLoads; ++q) {
+                    least = min(least, v[q]);
+                    most = v[q] <= cap ? max(most, v[q]) : most;
                 }
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int lo = wave_scan(least[q], INT32_MAX, Smaller{});
-                const int hi = wave_scan(most[q], 0, Larger{});
-                if (lane == kWave - 1 && i0 + 4 * q < n) {
-                    s_least[i0 + 4 * q] = lo;
-                    s_most[i0 + 4 * q] = hi;
-                }
+            if (!kCapped)
+                least = group_join(least, kLanes, Smaller{});
+            most = group_join(most, kLanes, Larger{});
+            if (part == 0 && i < n) {
+                if (!kCapped)
+                    s_least[i] = least;
+                s_most[i] = most;
             }
         }
         __syncthreads();
+    };
+
+    long long local = 0;
+    int m_first = 0, most_first = 0;              // of the first block of layers: not read again
+    for (int base = 0; base < L; base += 256) {
+        const int n = min(256, L - base);
+        read_times(base, n, Many<0>{});
         if (tid < n) {
-            mn[base + tid] = s_least[tid];
-            spans[base + tid] = s_most[tid];      // (the largest time, for now)
-            local += s_least[tid];
+            const int m = s_least[tid], most = s_most[tid];
+            mn[base + tid] = m;
+            spans[base + tid] = most;             // (the largest time, for now)
+            local += m;
+            if (base == 0) {
+                m_first = m;
+                most_first = most;
+            }
         }
         __syncthreads();
     }
@@ -386,15 +406,19 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
     long long reach = 0;                          // sum of the spans of the layers so far
     for (int base = 0; base < L; base += 256) {
         const int l = base + tid;
-        int span = 0;
+        int m = 0, span = 0, cap = -1;
         if (l < L && bp >= 0) {
-            const int m = mn[l];
-            const long long d = (long long)spans[l] - m;
-            span = (int)(d <= bp ? d : 0);
-            for (int s = 0; d > bp && s < S; ++s) {         // some level is beyond the budget
-                const long long v = (long long)tau[(size_t)l * S + s] - m;
-                span = v <= bp ? max(span, (int)v) : span;
-            }
+            m = base == 0 ? m_first : mn[l];
+            span = (base == 0 ? most_first : spans[l]) - m;
+            cap = span > bp ? m + bp : -1;        // (at most B)
+        }
+        s_least[tid] = cap;
+        if (cap >= 0)
+            s_beyond = 1;
+        __syncthreads();
+        if (s_beyond != 0) {                      // some level is beyond the budget: once more without
+            read_times(base, min(256, L - base), Many<1>{});
+            span = cap >= 0 ? s_most[tid] - m : span;
         }
         long long h = 0;                          // sum over the layers of this block before this one
         const long long total = block_scan_256(span, s_sum, &h);

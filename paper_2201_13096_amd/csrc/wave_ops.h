@@ -1,6 +1,11 @@
 // Scans and reductions over the lanes of a wavefront, by DPP.  Included by spdy_dp.hip, inside its
 // namespace.
 
+// A number that a generic lambda takes as a constant.
+template <int N> struct Many {
+    static constexpr int value = N;
+};
+
 template <int kCtrl, int kRows, class T> __device__ __forceinline__ T dpp_from(T none, T x)
 {
     static_assert(sizeof(T) == 4 || sizeof(T) == 8, "words");
