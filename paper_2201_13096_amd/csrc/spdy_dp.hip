@@ -1022,8 +1022,9 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
             for (int j = 0; j < R; ++j) {
                 const bool pair = arg[j] > kNoLevel;
                 const int i = (int)(arg[j] & 0xFF) - blk;
-                const int shift = __shfl(mine.shift, i, kWave);
-                const float e = __shfl(mine.err, i, kWave);
+                const int shift = __builtin_amdgcn_ds_bpermute(4 * i, mine.shift);
+                const float e = __builtin_bit_cast(
+                    float, __builtin_amdgcn_ds_bpermute(4 * i, __builtin_bit_cast(int, mine.err)));
                 const float v = row_at(pair ? shift : 0)[j * kWave] + e;
                 const unsigned s = v == best[j] ? arg[j] & 0xFF : arg[j] >> 8;
                 arg[j] = pair ? s : arg[j];
@@ -1753,10 +1754,16 @@ __device__ __forceinline__ void fill_candidates(
         if (l + 1 < le) {
             const LayerTable tn = tables.layer(l + 1);
             const ErrRow en = mine.layer(l + 1, S);
+            // Rows in memory with the level record need all of their 64 registers for the sweep: addresses of
+            // a lane that stayed in registers over all layers (these, and those of the copy to LDS below)
+            // drove four others to scratch memory.
+            int mine_of = lane;
+            if constexpr (kGlobal && kLevel)
+                asm("" : "+v"(mine_of));
             if constexpr (kNarrow)
-                next_fetch = fetch_levels<kLevel>(tn, en, S, s8, lane, producer);
+                next_fetch = fetch_levels<kLevel>(tn, en, S, s8, mine_of, producer);
             else
-                next_first = load_level<kLevel>(tn, en, s8, 0, lane);
+                next_first = load_level<kLevel>(tn, en, s8, 0, mine_of);
         }
         const float *prev = (l & 1) ? buf1 : buf0;
         float *cur = (l & 1) ? buf0 : buf1;
@@ -1818,12 +1825,15 @@ __device__ __forceinline__ void fill_candidates(
                     float4 *to = reinterpret_cast<float4 *>(lds);
                     for (int i0 = 0; i0 < len4; i0 += 8 * nthreads) {
                         float4 v[8];
+                        int first_quad = i0 + tid;
+                        if constexpr (kLevel)     // (not eight of them in registers over all layers)
+                            asm("" : "+v"(first_quad));
 #pragma unroll
                         for (int j = 0; j < 8; ++j)   // (past the end: the last element again)
-                            v[j] = from[min(i0 + j * nthreads + tid, len4 - 1)];
+                            v[j] = from[min(first_quad + j * nthreads, len4 - 1)];
 #pragma unroll
                         for (int j = 0; j < 8; ++j) {
-                            const int i = i0 + j * nthreads + tid;
+                            const int i = first_quad + j * nthreads;
                             if (i < len4)
                                 to[i] = v[j];
                         }

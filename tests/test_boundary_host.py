@@ -293,3 +293,15 @@ def test_rate_probe_output_is_optional(monkeypatch, tmp_path):
     import bench
     monkeypatch.setattr(bench, "PROBE", str(tmp_path / "no_such_probe"))
     assert bench.measured_peaks() is None
+
+
+def test_no_kernel_needs_scratch_memory(binding):
+    """A kernel with a private segment makes the runtime provide scratch memory at its first launch, and
+    the library promises that nothing is allocated.  (What the compiler noted down for each kernel of
+    this library, in the metadata of its own code object.)"""
+    noted = re.findall(rb"\.name(?:\xd9.|\xda..)(_Z\w+)\xbb\.private_segment_fixed_size(.)",
+                       open(binding.LIB_PATH, "rb").read(), flags=re.S)
+    kernels = {name.decode(): size for name, size in noted}
+    assert {"dp_fill", "dp_tiles", "dp_core", "dp_rest", "dp_prepare"} <= \
+        {m.group() for m in (re.search(r"dp_[a-z]+", n) for n in kernels) if m}
+    assert [n for n, size in kernels.items() if size != b"\0"] == []
