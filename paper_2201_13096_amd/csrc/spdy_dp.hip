@@ -71,6 +71,11 @@ template <bool kLevel, bool kTurns> constexpr int group_limit()
 {
     return kLevel ? kMaxGroupLevel : (kTurns ? kMaxGroupTurns : kMaxGroup);
 }
+// Level record: least levels per layer for comparisons that two levels share.  Finding out which of the two
+// it was costs every cell two lane exchanges, a read and an add; below some 14 levels that is more than
+// the comparisons saved.  K = 1024, L = 52, B = 10000, us a solve with and without: S = 2 217 and 181,
+// S = 8 298 and 274, S = 12 425 and 413, S = 16 471 and 477, S = 40 774 and 901.
+constexpr int kPairsFrom = 14;
 constexpr int kFillWaves = 8;        // waves of a fill workgroup (D record)
 constexpr int kFillWavesLevel = 16;  // (level record)
 constexpr int kMaxFillWaves = 16;
@@ -934,7 +939,7 @@ struct Todo {
 // A level applies to the group if its shift does not exceed the group's last bucket; lanes
 // left of the shift then read the +inf apron.  The applicable levels of a 64-block are found
 // with one ballot and walked in ascending position.
-template <int R, bool kLevel>
+template <int R, bool kLevel, bool kPairs>
 __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, LevelEntry first,
                                             LayerTable tl, ErrRow er, int s8, int t0, int lane,
                                             float (&best)[R], unsigned (&arg)[R])
@@ -977,7 +982,8 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
                 e1 = lane_value(mine.err, i1);
                 return (unsigned)(blk + i0) | (unsigned)(blk + i1) << 8;   // (>= 256: i1 > 0)
             };
-            int n_use = __builtin_popcountll(use);
+            int n_use = kPairs ? __builtin_popcountll(use) : 0;
+            const bool noted = n_use >= 2;
             for (; n_use >= 4; n_use -= 4) {      // two pairs a trip, so that no minimum is moved
                 int sa, sb, sc, sd;
                 float ea, eb, ec, ed;
@@ -1004,8 +1010,9 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
                     best[j] = m;
                 }
             }
-            if (use) {
+            while (use) {
                 const int i = __builtin_ctzll(use);
+                use &= use - 1;
                 const float *p = row_at(__builtin_amdgcn_readlane(mine.shift, i));
                 const float e = lane_value(mine.err, i);
                 const unsigned s = (unsigned)(blk + i);   // visiting order = level index here
@@ -1019,7 +1026,7 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
             // the first of a noted pair if it gives the cell's value, otherwise the second (what a
             // later single level beat is below 256 and stays)
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
+            for (int j = 0; noted && j < R; ++j) {
                 const bool pair = arg[j] > kNoLevel;
                 const int i = (int)(arg[j] & 0xFF) - blk;
                 const int shift = __builtin_amdgcn_ds_bpermute(4 * i, mine.shift);
@@ -1297,7 +1304,7 @@ __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, 
 // With `inplace` cur aliases prev, so a workgroup barrier separates the last read of the row
 // from the first write (every wave of the workgroup calls this exactly once per layer then,
 // with R = 0 if it has no chunks).
-template <int R, bool kLevel, bool inplace>
+template <int R, bool kLevel, bool inplace, bool kPairs>
 __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_t *choice,
                                            float *rec, LevelEntry first, LayerTable tl, ErrRow er,
                                            int s8, int t0, int lane, Pending pending)
@@ -1309,7 +1316,7 @@ __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_
     } else {
         float best[R];
         unsigned arg[R];
-        sweep_group<R, kLevel>(prev, first, tl, er, s8, t0, lane, best, arg);
+        sweep_group<R, kLevel, kPairs>(prev, first, tl, er, s8, t0, lane, best, arg);
         pending.settle();
         const int tl = t0 + lane;
 #pragma unroll
@@ -1327,7 +1334,7 @@ __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_
     }
 }
 
-template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit = false>
+template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kPairs>
 __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cur, uint8_t *choice,
                                              float *rec, LevelEntry first, LayerTable tl,
                                              ErrRow er, int s8, int t0, int lane, Pending pending,
@@ -1342,7 +1349,7 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
                 fill_group_quads<RR, inplace, kSplit>(prev, cur, rec, first, t0, lane,         \
                                                       pending, half, part);                    \
             else                                                                               \
-                fill_group<RR, kLevel, inplace>(prev, cur, choice, rec, first, tl, er, s8, t0, \
+                fill_group<RR, kLevel, inplace, kPairs>(prev, cur, choice, rec, first, tl, er, s8, t0, \
                                                 lane, pending);                                \
         }                                                                                      \
         break;
@@ -1560,7 +1567,8 @@ struct FillShared {      // static LDS of the kernels
     // set of levels to visit (level record)
     __attribute__((aligned(8))) float entries[2][kMaxFillWaves][kWave];
 };
-template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo, bool kTurns, bool kSplit>
+template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo, bool kTurns, bool kSplit,
+          bool kPairs>
 __device__ __forceinline__ void fill_candidates(
     ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
     int S, int pitch, uint8_t *__restrict__ choice, float *__restrict__ drec,
@@ -1794,9 +1802,9 @@ __device__ __forceinline__ void fill_candidates(
         constexpr int kMax = group_limit<kLevel, kTurns>();
         const Pending pending{&next_fetch, &next_first};
         if constexpr (inplace) {                 // c_end - c <= kMax by construction
-            fill_group_n<kLevel, true, kMax, kQuads, kSplit>(min(c_end - c, kMax), prev, cur,
-                                                             choice_l, drec_l, first, tl, er, s8,
-                                                             c * kWave, lane, pending, half, part);
+            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPairs>(
+                min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, tl, er, s8, c * kWave, lane,
+                pending, half, part);
         } else {
             // Rows in global memory: the row is computed in tiles of at most kMax chunks per
             // wave, and the part of the previous row a tile reads (the tile itself and the
@@ -1841,9 +1849,9 @@ __device__ __forceinline__ void fill_candidates(
                     __syncthreads();
                     const int cb = c0 + (int)((long long)share * nt / tw);
                     const int ce = c0 + (int)((long long)(share + 1) * nt / tw);
-                    fill_group_n<kLevel, false, kMax, kQuads>(ce - cb, lds - lo, cur, choice_l, drec_l,
-                                                      first, tl, er, s8, cb * kWave, lane,
-                                                      pending);
+                    fill_group_n<kLevel, false, kMax, kQuads, false, kPairs>(
+                        ce - cb, lds - lo, cur, choice_l, drec_l, first, tl, er, s8, cb * kWave, lane,
+                        pending);
                     __syncthreads();             // the next tile overwrites the staged part
                 }
             } else {
@@ -1851,8 +1859,8 @@ __device__ __forceinline__ void fill_candidates(
                     const int n = c_end - c;
                     const int groups = (n + kMax - 1) / kMax;
                     const int r = (n + groups - 1) / groups;
-                    fill_group_n<kLevel, false, kMax, kQuads>(r, prev, cur, choice_l, drec_l, first, tl,
-                                                      er, s8, c * kWave, lane, pending);
+                    fill_group_n<kLevel, false, kMax, kQuads, false, kPairs>(
+                        r, prev, cur, choice_l, drec_l, first, tl, er, s8, c * kWave, lane, pending);
                     c += r;
                 }
             }
@@ -1902,7 +1910,7 @@ __device__ __forceinline__ void fill_candidates(
 }
 
 template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo = false,
-          bool kTurns = false, bool kSplit = false>
+          bool kTurns = false, bool kSplit = false, bool kPairs = false>
 __global__ __launch_bounds__(fill_waves<kLevel>() * (kSplit || kPath >= 3 ? 2 : 1) * kWave,
                              kLevel ? 8 : 4)
 void dp_fill(
@@ -1913,7 +1921,7 @@ void dp_fill(
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ FillShared sh;
-    fill_candidates<kLevel, kPath, kNarrow, kBlocks, kTodo, kTurns, kSplit>(
+    fill_candidates<kLevel, kPath, kNarrow, kBlocks, kTodo, kTurns, kSplit, kPairs>(
         src, meta, tables, units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks,
         todo, lds, sh);
 }
@@ -2136,7 +2144,7 @@ __global__ __launch_bounds__((kBlocks ? 1 : 2) * kFillWaves * kWave, 4) void dp_
     auto fill = [&](auto path) __attribute__((always_inline)) {
         constexpr int kPath = decltype(path)::value;
         fill_candidates<false, kPath, kNarrow, kBlocks, true, false,
-                        kPath == 1 && kNarrow && !kBlocks>(
+                        kPath == 1 && kNarrow && !kBlocks, false>(
             src, meta, tables, units, K, L, S, pitch, nullptr, drec, rows, tstar, cost, resume,
             blocks, todo, lds, sh);
     };
@@ -2365,8 +2373,8 @@ int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const Pr
     return launch_status();
 }
 
-template <bool kLevel, bool kNarrow, bool kBlocks, bool kTodo>
-int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
+template <bool kLevel, bool kNarrow, bool kBlocks, bool kPairs, bool kTodo>
+int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
                 int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks,
                 const CoreCall *core)
 {
@@ -2420,8 +2428,8 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
         wide ? ((long long)nchunks > (long long)wide_waves * wide_group ||
                 row_bytes > (size_t)kLdsBytes)
              : need > (size_t)kLdsBytes;
-    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, true>
-                          : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false>;
+    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, true, false, kPairs>
+                          : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, false, kPairs>;
     // A candidate that has a compute unit to itself gets twice the waves (the second half takes
     // every other pair of each layer's entries and needs a second row in LDS for its minima).
     constexpr bool can_split = !kLevel && kNarrow && !kBlocks;       // (behind dp_core: dp_rest)
@@ -2441,9 +2449,10 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
                 return SPDY_DP_ERR_LAUNCH;
         }
     }
-    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kTodo>;
-    auto in_global = dp_fill<kLevel, 0, kNarrow, kBlocks, kTodo>;
-    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kTodo>;   // (3 when it exists)
+    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kTodo, false, false, kPairs>;
+    auto in_global = dp_fill<kLevel, 0, kNarrow, kBlocks, kTodo, false, false, kPairs>;
+    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kTodo, false, false,
+                              kPairs>;           // (3 when it exists)
     // The D record's global-row launch also has twice the waves (one workgroup per compute unit
     // with all of its LDS for the window; measured against two workgroups of the usual size with
     // half the LDS each: 11 % faster on a batch of four candidates per unit).
@@ -2556,13 +2565,13 @@ int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume res
     return launch_status();
 }
 
-template <bool kLevel, bool kNarrow, bool kBlocks = false>
+template <bool kLevel, bool kNarrow, bool kBlocks = false, bool kPairs = false>
 int launch_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
                 int S, int B, char *ws, float *cost, hipStream_t q, Blocks blocks,
                 const CoreCall *core)
 {
-    auto launch = core ? launch_fill<kLevel, kNarrow, kBlocks, true>
-                       : launch_fill<kLevel, kNarrow, kBlocks, false>;
+    auto launch = core ? enqueue_fill<kLevel, kNarrow, kBlocks, kPairs, true>
+                       : enqueue_fill<kLevel, kNarrow, kBlocks, kPairs, false>;
     return launch(lay, tau, src, resume, K, L, S, B, ws, cost, q, blocks, core);
 }
 
@@ -2588,17 +2597,12 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
     hipStream_t q = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
     (void)hipGetLastError();
-    if (S <= kWave)
-        return lay.variant == kLevelRecord
-                   ? launch_fill<true, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
-                                             Blocks{}, core)
-                   : launch_fill<false, true>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
-                                             Blocks{}, core);
-    return lay.variant == kLevelRecord
-               ? launch_fill<true, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
-                                             Blocks{}, core)
-               : launch_fill<false, false>(lay, tau, src, resume, K, L, S, B, ws, cost, q,
-                                             Blocks{}, core);
+    auto launch = S <= kWave ? launch_fill<false, true> : launch_fill<false, false>;
+    if (lay.variant == kLevelRecord)
+        launch = S > kWave        ? launch_fill<true, false, false, true>
+                 : S >= kPairsFrom ? launch_fill<true, true, false, true>
+                                   : launch_fill<true, true, false, false>;
+    return launch(lay, tau, src, resume, K, L, S, B, ws, cost, q, Blocks{}, core);
 }
 
 void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const float *drec,

@@ -313,6 +313,22 @@ def test_level_record_of_tied_pairs(dp, S):
                 check_tables(dp, tau, err[k], B, ws, k, 5)
 
 
+@pytest.mark.parametrize("S", [9, 12, 13, 14, 15, 17])
+def test_level_record_of_few_levels(dp, S):
+    """Level record around the number of levels from which pairs of them share a comparison, with rows
+    in LDS and in memory; times that leave none, one or a few levels to the low buckets."""
+    rng = np.random.default_rng(900 + S)
+    for K, L, B, tau_max in ((5, 7, 700, 700), (3, 6, 9000, 4000), (2, 5, 60000, 50000)):
+        tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=tau_max, integer_err=3,
+                                                zero_tau_frac=0.1, inf_err_frac=0.05)
+        tau[:, 0] = 0
+        what = f"S={S} B={B} tau_max={tau_max}"
+        p_gpu, c_gpu, ws = gpu_solve(dp, tau, err, B, compact=True)
+        assert_same(p_gpu, c_gpu, *oracle.solve_ref(tau, err, B, threads=CPU_THREADS), what)
+        for k in range(K):
+            check_tables(dp, tau, err[k], B, ws, k, K)
+
+
 def test_infeasible_and_mixed_batches(dp):
     # candidate 0 feasible, candidate 1 has every level of layer 2 forbidden, budget too small
     tau = np.array([[5, 3, 1], [4, 2, 1], [6, 2, 2]], dtype=np.int32)
