@@ -210,33 +210,24 @@ struct TileShared {      // static LDS of the kernel
     int ticket;
 };
 
-template <bool kLong>
+template <bool kLong, int kLds>
 __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__restrict__ meta,
                                           const LevelTables tables, int K, int L, int S, int pitch,
                                           float *__restrict__ drec, int32_t *__restrict__ tstar,
                                           float *__restrict__ cost, int *books, float *lds,
-                                          TileShared &sh)
+                                          TileShared &sh, int k, int p)
 {
     const int plan = meta[kMetaTiles];
     const int tiles = plan & 0xFF;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int tid = threadIdx.x;
+    asm("" : "+v"(tid));                         // (nothing of it kept in registers from tile to tile)
+    const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int bp = meta[kMetaBudget];
     if (bp < 0) {                                // even the fastest levels exceed the budget
         if (tid == 0)
-            write_result<false>(__builtin_inff(), 0, blockIdx.x, tstar, cost);
+            write_result<false>(__builtin_inff(), 0, k, tstar, cost);
         return;
-    }
-    int k = blockIdx.x, p = 0;
-    if (tiles > 1) {
-        // Tiles are taken in the order in which workgroups start, so a tile only ever waits for
-        // workgroups that are running already, whatever else runs on the device.
-        if (tid == 0)
-            sh.ticket = __hip_atomic_fetch_add(books, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int ticket = __builtin_amdgcn_readfirstlane(sh.ticket);
-        k = ticket / tiles;
-        p = ticket - k * tiles;
     }
     int *const flags = tile_flags(books, K * tiles) + k * tiles * kTileFlags;
     const int apron = (int)((unsigned)plan >> 12) * 4;
@@ -247,22 +238,19 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
     const int units_all = (nact[L - 1] * kWave + kGrain - 1) / kGrain;
     const int tile = (units_all + tiles - 1) / tiles * kGrain, start = p * tile;
     // Short tiles: behind the sweeping waves two that store rows and, where there are tiles below, two
-    // that fetch aprons.  (Barriers count the waves that are left.)
+    // that fetch aprons; waves that are left only meet the others at the barriers.
     const int sweepers = kLong ? kTileWaves : min(tile / kWave, kTileWaves - (tiles > 1 ? 4 : 2));
-    const int threads =
-        kLong ? kTileThreads : (sweepers + (below_me ? 4 : 2)) * kWave;
-    if (tid >= threads)
-        return;
+    const int fetchers = sweepers + 2, idlers = fetchers + (below_me ? 2 : 0);
     // LDS: [apron | row] once (long) or twice, then the entries of `room` layers and their counts
     const int line = apron + tile, lines = kLong ? line : 2 * line;
     float *const row0 = lds + apron, *const row1 = kLong ? row0 : row0 + line;
     const int s8 = tables.s8;
-    const int room = min((kTileLds / (int)sizeof(float) - lines) / (2 * s8 + 1), L);
+    const int room = min((kLds / (int)sizeof(float) - lines) / (2 * s8 + 1), L);
     int2 *const entries = reinterpret_cast<int2 *>(lds + lines);
     int *const counts = reinterpret_cast<int *>(entries + room * s8);
 
     // D before the first layer: see dp_fill
-    for (int i = tid * 4; i < lines; i += threads * 4)
+    for (int i = tid * 4; i < lines; i += kTileThreads * 4)
         *reinterpret_cast<float4v *>(lds + i) =
             float4v{__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
     // the first layer whose row reaches this tile
@@ -303,8 +291,8 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         };
 #pragma unroll
         for (int j = 0; j < kFirst; ++j)
-            level(min(tid + j * threads, n * S - 1), entry[j], error[j]);
-        for (int i = tid; i < n * s8; i += threads) {
+            level(min(tid + j * kTileThreads, n * S - 1), entry[j], error[j]);
+        for (int i = tid; i < n * s8; i += kTileThreads) {
             const int layer = i / s8, r = i - layer * s8;
             const int shift = shifts[i];
             const int after = r + 1 < s8 ? shifts[i + 1] : INT32_MAX;
@@ -315,9 +303,10 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kFirst; ++j)          // (past the end: the last level once more)
-            merge(entry[j], error[j]);
-        for (int i = tid + kFirst * threads; i < n * S; i += threads) {
+        for (int j = 0; j < kFirst; ++j)          // (not the last level once more: atomics on one word
+            if (tid + j * kTileThreads < n * S)   // are slow)
+                merge(entry[j], error[j]);
+        for (int i = tid + kFirst * kTileThreads; i < n * S; i += kTileThreads) {
             int e;
             float x;
             level(i, e, x);
@@ -325,7 +314,7 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         }
         __syncthreads();
         if constexpr (!kLong) {                   // shifts in bytes; what is beyond the budget gives +inf
-            for (int i = tid; i < n * s8; i += threads) {
+            for (int i = tid; i < n * s8; i += kTileThreads) {
                 const int2 v = entries[i];
                 entries[i] = v.x == INT32_MAX
                                  ? make_int2(0, __builtin_bit_cast(int, __builtin_inff()))
@@ -384,7 +373,7 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         seen = watch();
         wait_for(l0, lo, limit);
         put_quads(l0 & 1 ? row1 : row0, row_buffer(rec_k + (size_t)(l0 - 1) * pitch, pitch), lo,
-                  limit, tid, threads);
+                  limit, tid, kTileThreads);
     }
     __syncthreads();
     // What this wave does in layer base + i, in lane i: its chunks (units) | the first of them << 4 |
@@ -493,7 +482,7 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
             own += s8;
             __syncthreads();
         }
-    } else if (wave < sweepers + 2) {
+    } else if (wave < fetchers) {
         // Row l goes to the record while layer l + 1 is swept.  With tiles above, the wave that stored it
         // waits until it is there and says so: a layer later would be a layer more that each of them lags.
         const int odd = wave - sweepers;          // of the rows this wave stores
@@ -535,6 +524,14 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         }
         if (l0 < L && ((L - 1) & 1) == odd)
             store_row(L - 1);
+    } else if (wave >= idlers) {
+        for (int l = l0; l < L; ++l) {
+            if (l == staged) {
+                stage(l);
+                staged += room;
+            }
+            __syncthreads();
+        }
     } else {
         // The aprons of every other layer: asked for a layer ahead where the rows are there by then.
         which = (wave - sweepers) & 1;            // parity of the rows this wave fetches
@@ -585,7 +582,7 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
     const float *const last = L & 1 ? row1 : row0;
     unsigned long long key = result_key(__builtin_inff(), 0);
     if (l0 < L)
-        for (int i = tid; i < min(tile, bp + 1 - start); i += threads)
+        for (int i = tid; i < min(tile, bp + 1 - start); i += kTileThreads)
             key = Smaller{}(key, result_key(last[i], start + i));
     key = from_lane(wave_scan(key, ~0ull, Smaller{}), kWave - 1);
     wait_but<0>();                                // this wave's record is in memory
@@ -594,7 +591,7 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
     __syncthreads();
     if (wave > 0)
         return;
-    key = lane < threads / kWave ? sh.key[lane] : ~0ull;
+    key = lane < kTileWaves ? sh.key[lane] : ~0ull;
     if (tiles > 1) {
         unsigned long long *const keys =
             reinterpret_cast<unsigned long long *>(books + 2) + (size_t)k * tiles;
@@ -622,6 +619,38 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
         write_result<false>(result_value(key), (int)((unsigned)key >> 1), k, tstar, cost);
 }
 
+// Tiles are taken in the order in which workgroups come for them, so a tile only ever waits for
+// tiles that running workgroups have, whatever else runs on the device.  A workgroup takes them until
+// none is left.
+template <int kLds>
+__device__ __forceinline__ void take_tiles(const ErrSource src, const int32_t *__restrict__ meta,
+                                           const LevelTables tables, int K, int L, int S, int pitch,
+                                           float *__restrict__ drec, int32_t *__restrict__ tstar,
+                                           float *__restrict__ cost, int *books, float *lds,
+                                           TileShared &sh)
+{
+    const int plan = meta[kMetaTiles], tiles = plan & 0xFF;
+    const int all = K * tiles;                   // (0 where another launch does the work)
+    for (int next = blockIdx.x;; next += gridDim.x) {
+        if (tiles > 1) {
+            if (threadIdx.x == 0)
+                sh.ticket =
+                    __hip_atomic_fetch_add(books, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            next = __builtin_amdgcn_readfirstlane(sh.ticket);
+        }
+        if (next >= all)
+            return;
+        const int k = next / tiles, p = next - k * tiles;
+        if (plan & kTileLong)
+            fill_tile<true, kLds>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, lds, sh,
+                                  k, p);
+        else
+            fill_tile<false, kLds>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, lds, sh,
+                                   k, p);
+    }
+}
+
 __global__ __launch_bounds__(kTileThreads, 4) void dp_tiles(
     ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int K, int L, int S,
     int pitch, float *__restrict__ drec, int32_t *__restrict__ tstar, float *__restrict__ cost,
@@ -629,11 +658,29 @@ __global__ __launch_bounds__(kTileThreads, 4) void dp_tiles(
 {
     extern __shared__ __attribute__((aligned(16))) float tile_lds[];
     __shared__ TileShared sh;
-    const int plan = meta[kMetaTiles];
-    if ((long long)blockIdx.x >= (long long)K * (plan & 0xFF))
-        return;                                  // (also where another launch does the work)
-    if (plan & kTileLong)
-        fill_tile<true>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, tile_lds, sh);
+    take_tiles<kTileLds>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, tile_lds, sh);
+}
+
+// Where rows may have to lie in memory: in tiles, or in place in the wide launch (path 3 of dp_fill),
+// whichever was planned, in one launch.  (A launch by itself that finds no tiles costs 1.9 us, and 9 - 19
+// with a workgroup for every tile there might be: K = 1024, L = 8, S = 16, B = 30000, rows that fit LDS
+// after all: 48.9 us, 40.5 with no more workgroups than units, 38.1 in one launch.  Together with path 4
+// instead of 3 it takes rows in memory 1.5 % longer.)
+template <bool kNarrow>
+__global__ __launch_bounds__(kTileThreads, 4) void dp_wide(
+    ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
+    int S, int pitch, float *__restrict__ drec, int32_t *__restrict__ tstar,
+    float *__restrict__ cost, Resume resume, int *books)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ union {
+        FillShared fill;
+        TileShared tile;
+    } sh;
+    if (meta[kMetaTiles] != 0)
+        take_tiles<kLdsBytes>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, lds, sh.tile);
     else
-        fill_tile<false>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, tile_lds, sh);
+        fill_candidates<false, 3, kNarrow, false, false, false, false, false>(
+            src, meta, tables, units, K, L, S, pitch, nullptr, drec, nullptr, tstar, cost, resume,
+            Blocks{}, Todo{}, lds, sh.fill);
 }

@@ -241,7 +241,7 @@ __device__ __forceinline__ long long block_scan_256(long long v, long long *part
 struct TileArgs {
     int units;               // compute units
     int only_memory;         // 1: only where rows would lie in memory
-    int most;                // tiles that the launch has workgroups for (0: not enqueued)
+    int most;                // tiles of a row at most (0: dp_tiles is not enqueued)
     int lds;                 // floats of its LDS
     int *books;              // ticket, keys and counters of the tiles
     int room;                // their words
@@ -2450,7 +2450,6 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
         }
     }
     auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kTodo, false, false, kPairs>;
-    auto in_global = dp_fill<kLevel, 0, kNarrow, kBlocks, kTodo, false, false, kPairs>;
     auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kTodo, false, false,
                               kPairs>;           // (3 when it exists)
     // The D record's global-row launch also has twice the waves (one workgroup per compute unit
@@ -2458,10 +2457,9 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // half the LDS each: 11 % faster on a batch of four candidates per unit).
     const bool wide_global = can_widen && waves == fill_waves<kLevel>();
     const int global_waves = wide_global ? 2 * waves : waves;
-    if constexpr (can_widen) {
-        if (wide_global)
-            in_global = dp_fill<kLevel, 4, kNarrow, kBlocks, kTodo>;
-    }
+    // (rows that may lie in memory are long: `waves` is the full number then)
+    constexpr bool can_tile = !kLevel && !kBlocks && !kTodo;
+    auto in_global = dp_fill<kLevel, can_widen ? 4 : 0, kNarrow, kBlocks, kTodo, false, false, kPairs>;
     if (wide &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(wide_place),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
@@ -2484,11 +2482,11 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // each has two compute units, and up to one per unit where rows are short (B = 8000 of S = 40, K = 256:
     // 224 us and 234 otherwise; B = 1000: 107 and 156; B = 10000: 262 and 256); and where rows may have to lie
     // in memory otherwise.
-    constexpr bool can_tile = !kLevel && !kBlocks && !kTodo;
     const bool tiles_do = can_tile && !resume.first_layer &&
                           (2LL * K <= units || (K <= units && B <= kTileLone));
     const bool tiles_sure = tiles_do && B <= (kNarrow ? kTileSure : kTileSureWide);
-    TileArgs ta{units, tiles_do ? 0 : 1, 0, kTileLds / (int)sizeof(float), nullptr, 0};
+    TileArgs ta{units, tiles_do ? 0 : 1, 0, (in_memory ? kLdsBytes : kTileLds) / (int)sizeof(float),
+                nullptr, 0};
     if (tiles_do || (can_tile && !resume.first_layer && in_memory)) {
         ta.most = in_memory ? (K <= 512 ? kTileMost : (K <= 2048 ? 8192 / K : 4)) : units / K;
         ta.most = ta.most < kTileMost ? ta.most : kTileMost;
@@ -2537,13 +2535,15 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
         }
     }
     if constexpr (can_tile) {
-        if (ta.most > 0) {
+        if (ta.most > 0 && !in_memory) {
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(dp_tiles),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds) !=
                 hipSuccess)
                 return SPDY_DP_ERR_LAUNCH;
-            hipLaunchKernelGGL(dp_tiles, dim3(K * ta.most), dim3(kTileThreads), kTileLds, q, src,
-                               meta, tables, K, L, S, pitch, drec, tstar, cost, ta.books);
+            const long long most = (long long)K * ta.most;
+            hipLaunchKernelGGL(dp_tiles, dim3((unsigned)(most < units ? most : units)),
+                               dim3(kTileThreads), kTileLds, q, src, meta, tables, K, L, S, pitch,
+                               drec, tstar, cost, ta.books);
         }
     }
     if (tiles_sure)
@@ -2552,10 +2552,22 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
         hipLaunchKernelGGL(in_place, dim3(K), dim3(place_threads), place_lds, q, src, meta, tables,
                            units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks,
                            todo);
-    if (wide)
+    if (wide && !(can_tile && in_memory))
         hipLaunchKernelGGL(wide_place, dim3(K), dim3(wide_waves * kWave), lds_wide, q, src, meta,
                            tables, units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume,
                            blocks, todo);
+    if constexpr (can_tile) {
+        if (in_memory) {
+            auto wide_or_tiles = dp_wide<kNarrow>;
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(wide_or_tiles),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) !=
+                hipSuccess)
+                return SPDY_DP_ERR_LAUNCH;
+            hipLaunchKernelGGL(wide_or_tiles, dim3(ta.most > 0 && K < units ? units : K),
+                               dim3(kTileThreads), kLdsBytes, q, src, meta, tables, units, K, L, S,
+                               pitch, drec, tstar, cost, resume, ta.books);
+        }
+    }
     if (lds_large)
         hipLaunchKernelGGL(two_rows, dim3(K), dim3(waves * kWave), lds_large, q, src, meta, tables,
                            units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks, todo);
