@@ -515,7 +515,8 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
             if (l > l0 && ((l - 1) & 1) == odd) {
                 store_row(l - 1);
                 if (above_me) {
-                    wait_but<0>();
+                    wait_but<0>();                // (the fence keeps the compiler from moving the stores)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     if (lane == 0)
                         store_agent(flags + p * kTileFlags + odd, l);
                 }
