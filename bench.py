@@ -37,9 +37,12 @@ ALU_PEAK_LANE_OPS = COMPUTE_UNITS * 128 * CLOCK_HZ
 #        costs per update.
 #   ALU, D record: an fp32 add and an fp32 min; as built one v_min3_f32 folds two updates, so 1.5
 #        issued instructions per update.  Level record: add, compare, select of the level, min;
-#        as built two levels share a min3, a compare and a select, so 2.5.
+#        as built, from 14 levels on, two levels share a min3, a compare and a select, so 2.5
+#        (finding out once per cell and layer which of the two it was is not counted).
 LANE_OPS_PER_UPDATE = {"d": 2.0, "level": 4.0}
-LANE_OPS_AS_BUILT = {"d": 1.5, "level": 2.5}
+LANE_OPS_AS_BUILT = {"valu_add_add_min3": 1.5, "valu_add_cmp_sel_min": 4.0,
+                     "valu_add_add_min3_cmp_sel": 2.5}      # by the mix that the rate probe times
+LEVEL_PAIRS_FROM = 14            # kPairsFrom of csrc/spdy_dp.hip
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
                   for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h")]
@@ -363,14 +366,16 @@ def main() -> int:
     seconds = fill_ms * 1e-3
     lds_bytes = executed * 4.0 * (1.0 + 1.0 / S)
     lane_ops = executed * LANE_OPS_PER_UPDATE[args.record]
-    lane_ops_built = executed * LANE_OPS_AS_BUILT[args.record]
+    probe_mix = ("valu_add_add_min3" if args.record == "d" else
+                 "valu_add_add_min3_cmp_sel" if S >= LEVEL_PAIRS_FROM else "valu_add_cmp_sel_min")
+    lane_ops_built = executed * LANE_OPS_AS_BUILT[probe_mix]
 
     def rate(obj, key):
         return None if peaks is None or obj not in peaks else peaks[obj].get(key)
 
     # The D-record fill is bound by LDS reads (4 bytes of the shifted row per update, an add and
-    # half a v_min3 beside it); the level-record fill by the vector ALU (four instructions per
-    # update).  Both objects are always reported; `roofline` is the binding one.  With at most 64
+    # half a v_min3 beside it); the level-record fill by the vector ALU (two and a half to four
+    # instructions per update).  Both objects are always reported; `roofline` is the binding one.  With at most 64
     # levels the D-record sweep reads 128 bits per lane, so its peak is the 128-bit one; the
     # fraction of the 32-bit-read peak (what a lane = bucket layout can reach at best) is beside it.
     wide_reads = args.record == "d" and S <= 64
@@ -393,7 +398,6 @@ def main() -> int:
         "frac_of_b32_nominal": lds_bytes / seconds / LDS_PEAK_B32,
         "peak_b32_measured": rate("lds_read_b32", "tb_per_s"),
     }
-    probe_mix = "valu_add_add_min3" if args.record == "d" else "valu_add_cmp_sel_min"
     valu_obj = {
         "bound": "alu",
         "kernel": "dp_fill",
@@ -402,7 +406,7 @@ def main() -> int:
         "unit": "Tlane-op/s",
         "frac": lane_ops / seconds / ALU_PEAK_LANE_OPS,
         "lane_ops_per_update": LANE_OPS_PER_UPDATE[args.record],
-        "as_built": {"lane_ops_per_update": LANE_OPS_AS_BUILT[args.record],
+        "as_built": {"lane_ops_per_update": LANE_OPS_AS_BUILT[probe_mix],
                      "achieved": lane_ops_built / seconds / 1e12,
                      "frac": lane_ops_built / seconds / ALU_PEAK_LANE_OPS},
         "peak_is": "nominal: 256 CU x 128 lane-instructions/clk x 2.4 GHz (157.3 TFLOP/s / 2)",

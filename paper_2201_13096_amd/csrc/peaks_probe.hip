@@ -98,6 +98,45 @@ __global__ __launch_bounds__(256) void valu_add_cmp_sel_min(float *out, float c,
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
+// Two level-record updates that share a comparison, twice: two adds, min3, compare, select of the pair
+// (5 instructions for two updates; without finding out which of a noted pair it was).
+__global__ __launch_bounds__(256) void valu_add_add_min3_cmp_sel(float *out, float c, int iters)
+{
+    float a[kChains], d[kChains], b[kChains];
+    int g[kChains];
+    for (int j = 0; j < kChains; ++j) {
+        a[j] = threadIdx.x * 0.5f + j;
+        d[j] = threadIdx.x * 0.25f + j;
+        b[j] = 1e30f;
+        g[j] = 0;
+    }
+    for (int i = 0; i < iters; ++i) {
+        int pair = i;
+        asm volatile("" : "+v"(pair));
+#pragma unroll
+        for (int j = 0; j < kChains; ++j) {
+            float m;
+            auto update = [&](float &to, float from) __attribute__((always_inline)) {
+                asm volatile("v_add_f32 %0, %0, %1" : "+v"(a[j]) : "v"(c));
+                asm volatile("v_add_f32 %0, %0, %1" : "+v"(d[j]) : "v"(c));
+                asm volatile("v_min3_f32 %0, %1, %2, %3"
+                             : "=&v"(to)
+                             : "v"(from), "v"(a[j]), "v"(d[j]));
+                asm volatile("v_cmp_lt_f32 vcc, %1, %2\n\tv_cndmask_b32 %0, %0, %3, vcc"
+                             : "+v"(g[j])
+                             : "v"(to), "v"(from), "v"(pair)
+                             : "vcc");
+            };
+            update(m, b[j]);
+            update(b[j], m);
+        }
+    }
+    float s = 0;
+    for (int j = 0; j < kChains; ++j)
+        s += b[j] + a[j] + d[j] + g[j];
+    out[blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+
 // Eight LDS reads of width sizeof(T) per iteration at immediate offsets; consecutive lanes read
 // consecutive elements, the base moves by `step` dwords per iteration inside the buffer.
 template <typename T>
@@ -266,6 +305,7 @@ int main()
     valu("valu_add_min", valu_add_min, 2);
     valu("valu_add_add_min3", valu_add_add_min3, 3);
     valu("valu_add_cmp_sel_min", valu_add_cmp_sel_min, 4);
+    valu("valu_add_add_min3_cmp_sel", valu_add_add_min3_cmp_sel, 10);
 
     const int words = 8192;    // 32 KB per workgroup, four workgroups (16 waves) per CU
     const int nb = cus * 4;
