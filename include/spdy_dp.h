@@ -43,7 +43,7 @@
  *     and a min per update, and the walk back re-derives the level of the L cells on the path
  *     (smallest s with D_{l-1}[t - tau[l][s]] + err[k][l][s] == D_l[t]);
  *   - spdy_dp_workspace_bytes_min(): the level P of Alg. 1 (one byte per cell, 4x smaller; the
- *     fill tracks the level with a compare and two selects per update).
+ *     fill tracks the level with a compare and a select, which two levels share from 14 on).
  * Both give the same profile and cost, bit for bit.
  *
  * Conventions for every entry point:
