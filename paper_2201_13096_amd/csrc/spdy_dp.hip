@@ -128,7 +128,7 @@ enum MetaWord {
     kMetaLdsWide = 16,   // its dynamic LDS bytes
     kMetaGlobalWaves = 17, // waves of the global-row launch
     kMetaTable = 18,    // 1: the call leaves the whole table in the record (0: scratch)
-    kMetaTiles = 19     // not 0: dp_tiles does the work (see there), not the launch of kMetaPath
+    kMetaTiles = 19     // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
@@ -887,7 +887,9 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 #include "dp_core.h"
 
 // One workgroup per candidate (and budget); the first L + 1 workgroups do what dp_prepare does, for
-// the launches of the full table that follow and take the candidates this one gives up.
+// the launches of the full table that follow and take the candidates this one gives up.  Their code comes
+// last (they are marked as unlikely): with it in front a change there moved the solve's loops, which
+// wait for instructions as much as for anything, and made calls 1.4 - 3.6 % slower.
 template <bool kFar>
 __global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restrict__ tau,
                                                         ErrSource src, int K, int L, int S,
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restric
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char core_lds[];
     __shared__ CoreShared sh;
-    if ((int)blockIdx.x <= L) {
+    if (__builtin_expect((int)blockIdx.x <= L, 0)) {
         prepare(tau, K, L, S, prep, blockIdx.x);
         return;
     }
