@@ -889,7 +889,8 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 // One workgroup per candidate (and budget); the first L + 1 workgroups do what dp_prepare does, for
 // the launches of the full table that follow and take the candidates this one gives up.  Their code comes
 // last (they are marked as unlikely): with it in front a change there moved the solve's loops, which
-// wait for instructions as much as for anything, and made calls 1.4 - 3.6 % slower.
+// wait for instructions as much as for anything, and made calls 1.4 - 3.6 % slower.  (16 bytes of s_nop ahead of
+// the solve: 1 - 2 % slower; 32 or 64: no change.)
 template <bool kFar>
 __global__ __launch_bounds__(kCoreThreads) void dp_core(const int32_t *__restrict__ tau,
                                                         ErrSource src, int K, int L, int S,
