@@ -154,7 +154,7 @@ __device__ __forceinline__ void tile_chunks(const float *from, float *to, const 
 // between the sweep and the barrier behind it, `after` behind that.
 template <int Q, class Meanwhile, class After>
 __device__ __forceinline__ void tile_units(float *row, int local, int start, LevelEntry first,
-                                           __amdgpu_buffer_rsrc_t rec, bool coherent, int lane,
+                                           const int2 *entries, __amdgpu_buffer_rsrc_t rec, bool coherent, int lane,
                                            Meanwhile meanwhile, After after)
 {
     if constexpr (Q == 0) {
@@ -169,17 +169,8 @@ __device__ __forceinline__ void tile_units(float *row, int local, int start, Lev
             for (int c = 0; c < 4; ++c)
                 bq[j][c] = __builtin_inff();
         const float4v *quads = reinterpret_cast<const float4v *>(row + local) + (lane - 1);
-        const unsigned long long use = __ballot(first.shift < start + local + Q * kQuadChunk);
-        const int residue = first.shift & 3;
-        __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): see fill_group_quads
-        const unsigned long long use0 = use & __ballot(residue == 0);
-        const unsigned long long use1 = use & __ballot(residue == 1);
-        const unsigned long long use2 = use & __ballot(residue == 2);
-        const unsigned long long use3 = use & __ballot(residue == 3);
-        sweep_residue<Q, 0, 0, false>(quads, nullptr, first, use0, false, bq, none);
-        sweep_residue<Q, 0, 1, false>(quads, nullptr, first, use1, false, bq, none);
-        sweep_residue<Q, 0, 2, false>(quads, nullptr, first, use2, false, bq, none);
-        sweep_residue<Q, 0, 3, false>(quads, nullptr, first, use3, false, bq, none);
+        sweep_layer<Q, 0, false, true>(quads, nullptr, entries, first,
+                                       start + local + Q * kQuadChunk - 1, 0, bq, none);
         wait_but<0>();                            // the last layer's record is in memory
         meanwhile();
         __syncthreads();
@@ -241,11 +232,12 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
     // that fetch aprons; waves that are left only meet the others at the barriers.
     const int sweepers = kLong ? kTileWaves : min(tile / kWave, kTileWaves - (tiles > 1 ? 4 : 2));
     const int fetchers = sweepers + 2, idlers = fetchers + (below_me ? 2 : 0);
-    // LDS: [apron | row] once (long) or twice, then the entries of `room` layers and their counts
+    // LDS: [apron | row] once (long) or twice, then the entries of `room` layers and their counts (a sweep
+    // reads two entries too far)
     const int line = apron + tile, lines = kLong ? line : 2 * line;
     float *const row0 = lds + apron, *const row1 = kLong ? row0 : row0 + line;
     const int s8 = tables.s8;
-    const int room = min((kLds / (int)sizeof(float) - lines) / (2 * s8 + 1), L);
+    const int room = min((kLds / (int)sizeof(float) - lines - 4) / (2 * s8 + 1), L);
     int2 *const entries = reinterpret_cast<int2 *>(lds + lines);
     int *const counts = reinterpret_cast<int *>(entries + room * s8);
 
@@ -313,15 +305,15 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
             merge(e, x);
         }
         __syncthreads();
-        if constexpr (!kLong) {                   // shifts in bytes; what is beyond the budget gives +inf
-            for (int i = tid; i < n * s8; i += kTileThreads) {
-                const int2 v = entries[i];
-                entries[i] = v.x == INT32_MAX
-                                 ? make_int2(0, __builtin_bit_cast(int, __builtin_inff()))
-                                 : make_int2(v.x * 4, v.y);
-            }
-            __syncthreads();
+        // shifts in bytes; what is beyond the budget gives +inf (short tiles) or stays out of reach (long
+        // ones, whose rows are far shorter than a fourth of that)
+        for (int i = tid; i < n * s8; i += kTileThreads) {
+            const int2 v = entries[i];
+            const int none = kLong ? INT32_MAX : 0;
+            const int error = kLong ? v.y : __builtin_bit_cast(int, __builtin_inff());
+            entries[i] = v.x == INT32_MAX ? make_int2(none, error) : make_int2(v.x * 4, v.y);
         }
+        __syncthreads();
     };
 
     // The apron for layer l: buckets [lo, start) of row l - 1.  Lane i watches tile p - 1 - i.
@@ -403,10 +395,8 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
             const int todo = __builtin_amdgcn_readlane(held_plan, l - base);
             const int2 *const own = entries + (l - (staged - room)) * s8;
             LevelEntry first{INT32_MAX, 0.0f};
-            if (lane < s8) {
-                const int2 v = own[lane];
-                first = LevelEntry{v.x, __builtin_bit_cast(float, v.y)};
-            }
+            if (lane < s8)
+                first.shift = own[lane].x >> 2;
             const int limit = active * kWave;
             const int lo = (start - span - 4) & ~3;        // of the next layer's apron
             const bool more = l + 1 < L;
@@ -440,13 +430,13 @@ __device__ __forceinline__ void fill_tile(const ErrSource src, const int32_t *__
             };
             const int local = (todo >> 4 & 0xFFF) * kQuadChunk;
             switch (todo & 15) {
-            case 0: tile_units<0>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 1: tile_units<1>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 2: tile_units<2>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 3: tile_units<3>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 4: tile_units<4>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 5: tile_units<5>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
-            case 6: tile_units<6>(row0, local, start, first, rec, above_me, lane, meanwhile, after); break;
+            case 0: tile_units<0>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 1: tile_units<1>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 2: tile_units<2>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 3: tile_units<3>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 4: tile_units<4>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 5: tile_units<5>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
+            case 6: tile_units<6>(row0, local, start, first, own, rec, above_me, lane, meanwhile, after); break;
             }
             __syncthreads();
         }

@@ -98,12 +98,36 @@ constexpr bool kInPlaceFits =
     2 * (kFillWavesLevel * kMaxGroupLevel * kWave + kWave + kHalo) * 4 > kLdsHalf;
 static_assert(kInPlaceFits, "path 1 must be exactly the in-place case");
 constexpr int kBatch = 8;                 // level tables are padded to a multiple of this
+// The 128-bit sweep (see fill_group_quads): a group of R chunks of 64 buckets is quad_chunks(R) quad chunks
+// and tail_chunks(R) ordinary ones.
+constexpr int kQuadLanes = kWave - 1;             // lanes of a quad chunk that own buckets
+constexpr int kQuadChunk = 4 * kQuadLanes;        // 252 buckets
+__host__ __device__ constexpr int quad_chunks(int R) { return R * kWave / kQuadChunk; }
+__host__ __device__ constexpr int tail_chunks(int R)
+{
+    return (R * kWave - quad_chunks(R) * kQuadChunk + kWave - 1) / kWave;
+}
+// What a group of R chunks costs, a quad chunk being 4: a tail chunk has a quarter of the adds and minima, and
+// half of the LDS time, its reads being a fourth as wide at half the rate.
+__host__ __device__ constexpr int sweep_cost(int R) { return 4 * quad_chunks(R) + 2 * tail_chunks(R); }
+// A share of whole quad chunks from bucket t on, as a word of the header (0: the share is what the chunk
+// boundaries say).  K = 1024, L = 54, S = 40, B = 10^4: 20 quad chunks instead of 80 chunks, which were 20 quad chunks
+// and as many tail chunks as waves: 434 us a solve and 428; parameters as cost: 642 and 600.
+constexpr int kMaxQuads = kMaxGroupTurns * kWave / kQuadChunk;
+__host__ __device__ constexpr int quad_share(int t, int quads)
+{
+    return 1 << 30 | quads << 20 | t / 4;
+}
+static_assert(kMaxFillWaves * kMaxGroupTurns * kWave / 4 < 1 << 20, "rows updated in place");
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
 constexpr int kMetaHeader = 20;      // int32 words before the per-layer arrays
 // meta: header | m_l [L] | chunks of row l [L] | chunk boundaries of the team waves [L][stride]
 //       | largest usable shift of layer l [L]
 constexpr int kRangeStride = kMaxFillWaves + 1;
+// shares of whole quad chunks, behind the boundaries of the usual workgroup's waves
+constexpr int kWholeWord = kFillWaves + 1;
+static_assert(kWholeWord + kFillWaves <= kRangeStride, "words of a layer");
 
 // kMetaPath: 0 = rows in global memory, 1 / 2 = rows in LDS, fill kernel launched with the
 // smaller / larger LDS allocation, 3 = one row in LDS updated in place by a workgroup of twice
@@ -285,7 +309,7 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
                       mine <= (is_long ? kTileUnits : kTileChunks) && (!is_long || S <= kWave) &&
                       (tiles == 1 || (long long)K * tiles * (2 + kTileFlags) + 2 <= ta.room) &&
                       apron < 1 << 20 &&
-                      lines + min(L, kTileLayers) * (2LL * s8 + 1) <= ta.lds;
+                      lines + min(L, kTileLayers) * (2LL * s8 + 1) + 4 <= ta.lds;
     // Clocks, fitted to measured fills (a lone S = 40 candidate of 4955 buckets in 1, 2, 4, 8 short
     // tiles: 8400, 5900, 3700, 2900 a layer; one of 49581 in 3, 4, 6, 8 long ones: 26300, 21000, 17300, 13000).
     // A SIMD issues an instruction every four clocks or so, whichever of its waves it is from.
@@ -334,11 +358,11 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
 __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots, int L, int S,
                                int B, int waves, int max_group, int lds_small, int lds_large,
                                int lds_stage, int split, int wide_waves, int wide_group,
-                               int lds_wide, int global_waves, const TileArgs &ta,
+                               int lds_wide, int global_waves, bool quads, const TileArgs &ta,
                                int32_t *words, int32_t *__restrict__ meta)
 {
     __shared__ long long s_sum[8];
-    __shared__ int s_span[4], s_team_waves, s_tiles, s_beyond;
+    __shared__ int s_span[4], s_team_waves, s_tiles, s_beyond, s_whole;
     int32_t *const s_least = words, *const s_most = words + 256;
     const int tid = threadIdx.x;
     if (tid == 0)
@@ -503,6 +527,8 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         meta[kMetaLdsWide] = lds_wide;
         meta[kMetaGlobalWaves] = global_waves;
         s_team_waves = plan_waves / teams;
+        // (not with a second half of waves, which leave their share of a bucket's minimum in one place)
+        s_whole = path == 1 && quads && split == 0 ? 1 : 0;
         if (ta.only_memory != 0 && path != 0 && path != 4)
             s_tiles = 0;
         meta[kMetaTiles] = s_tiles;
@@ -516,12 +542,25 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         if (tid == 0)
             ta.books[0] = 0;
     }
+    const bool whole_quads = s_whole != 0;
     for (int l = tid; l < L; l += 256) {
         // wave w of a team sweeps chunks [w n / tw, (w + 1) n / tw) of this row
         const int n = nact[l];
         int32_t *range = meta + kMetaHeader + 2 * L + (size_t)l * kRangeStride;
         for (int w = 0; w <= tw; ++w)
             range[w] = (int)((unsigned)(w * n) / (unsigned)tw);   // (16 rows of 2^25 chunks fit)
+        // or whole quad chunks, where the wave with the most has less to do that way; the last of
+        // them are moved down to the row's end and lie over the ones before
+        if (whole_quads) {
+            const int units = (n * kWave + kQuadChunk - 1) / kQuadChunk, most = (units + tw - 1) / tw;
+            const bool whole = most <= kMaxQuads && n * kWave >= most * kQuadChunk &&
+                               4 * most < sweep_cost((n + tw - 1) / tw);
+            for (int w = 0; w < tw; ++w) {
+                const int unit = w * units / tw, mine = (w + 1) * units / tw - unit;
+                const int first = min(unit * kQuadChunk, n * kWave - mine * kQuadChunk);
+                range[kWholeWord + w] = whole ? quad_share(first, mine) : 0;
+            }
+        }
     }
 }
 
@@ -640,7 +679,7 @@ __device__ __forceinline__ void prepare(const int32_t *__restrict__ tau, int K, 
     if (block == 0)
         prepare_budget(tau, K, a.slots, L, S, a.B, a.waves, a.max_group, a.lds_small, a.lds_large,
                        a.lds_stage, a.split, a.wide_waves, a.wide_group, a.lds_wide,
-                       a.global_waves, a.tiles, words, a.meta);
+                       a.global_waves, a.sorted == 2, a.tiles, words, a.meta);
     else
         prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of,
                       words);
@@ -856,12 +895,12 @@ __device__ __forceinline__ unsigned long long load_twins(LayerTable tl)
            ((unsigned long long)(uint32_t)tl.start[1] << 32);
 }
 
-// table[r] = smallest error among the levels of entry r (+inf for unused entries); one wave.
-__device__ __forceinline__ void publish_entries(float *table, const LevelFetch &f, int S, int lane)
+// table[r] = shift in bytes and smallest error among the levels of entry r (+inf for unused entries); one wave.
+__device__ __forceinline__ void publish_entries(int2 *table, const LevelFetch &f, int S, int lane)
 {
-    table[lane] = __builtin_inff();
+    table[lane] = make_int2((int)((unsigned)f.shift * 4u), __builtin_bit_cast(int, __builtin_inff()));
     if (lane < S)
-        __hip_atomic_fetch_min(&table[f.entry], f.raw, __ATOMIC_RELAXED,
+        __hip_atomic_fetch_min(reinterpret_cast<float *>(&table[f.entry].y), f.raw, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -1082,13 +1121,6 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
 //     chunks by up to 63 buckets, which are then computed twice with the same result.
 // R chunks of 64 thus become Q quad chunks and T tail chunks, 4 Q + T <= R + 1 registers.
 typedef float float4v __attribute__((ext_vector_type(4)));
-constexpr int kQuadLanes = kWave - 1;             // lanes of a quad chunk that own buckets
-constexpr int kQuadChunk = 4 * kQuadLanes;        // 252 buckets
-constexpr int quad_chunks(int R) { return R * kWave / kQuadChunk; }
-constexpr int tail_chunks(int R)
-{
-    return (R * kWave - quad_chunks(R) * kQuadChunk + kWave - 1) / kWave;
-}
 
 // x of the lane to the left (lane 0 gets 0.0f, which nothing uses)
 __device__ __forceinline__ float from_left(float x)
@@ -1097,115 +1129,183 @@ __device__ __forceinline__ float from_left(float x)
         __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138 /* wave_shr:1 */, 0xf, 0xf, true));
 }
 
-// The four values D_{l-1}[t - shift] for the four buckets t of a lane, from the aligned quad `own`
-// it has read and the quad the lane to its left has read; kRes = shift mod 4.
-template <int kRes>
-__device__ __forceinline__ void shifted_quad(float4v own, float e, float (&v)[4])
+// Two entries of a table in LDS (shift in bytes, error, and again), one read wherever the first of them lies.
+// (Two values of their own the compiler fetches one at a time, the second where it is needed.)
+constexpr int kLookAhead = 4;        // entries read behind the last one of a table, and not used
+typedef int EntryPair __attribute__((ext_vector_type(4), aligned(8)));
+
+// The entries of one residue that a group can use: `n` consecutive ones from `at` on, of which the
+// first two are here already.
+struct EntryRun {
+    const int2 *at;
+    int n;
+    EntryPair pair;
+};
+__device__ __forceinline__ EntryPair entry_pair(const int2 *at)
 {
-    const float o[4] = {own.x, own.y, own.z, own.w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        v[c] = (c >= kRes ? o[c - kRes] : from_left(o[4 + c - kRes])) + e;
+    return *reinterpret_cast<const EntryPair *>(at);
 }
 
 // kSplit: the waves of a workgroup come in two halves that sweep the same chunks, each visiting
 // every other pair of the run's entries (a run's odd last entry counts as a pair); `skip`: the
 // run's first pair is the other half's.
-template <int Q, int T, int kRes, bool kSplit>
-__device__ __forceinline__ void sweep_residue(const float4v *quads, const float *tail,
-                                              LevelEntry mine, unsigned long long use, bool skip,
-                                              float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
+template <bool kSplit>
+__device__ __forceinline__ EntryRun entry_run(const int2 *entries, unsigned long long use, bool skip)
 {
-    auto visit_two = [&](int i) {
-        const int s0 = __builtin_amdgcn_readlane(mine.shift, i);
-        const int s1 = __builtin_amdgcn_readlane(mine.shift, i + 1);
-        float e0 = lane_value(mine.err, i);
-        float e1 = lane_value(mine.err, i + 1);
-        asm volatile("" : "+v"(e0), "+v"(e1));    // addends of the cross-lane adds live in VGPRs
+    EntryRun r;
+    r.at = entries + (use ? __builtin_ctzll(use) : 0);
+    r.n = __builtin_popcountll(use);
+    if (kSplit && skip) {
+        r.at += 2;
+        r.n -= 2;
+    }
+    r.pair = entry_pair(r.at);
+    return r;
+}
+
+// bq[j][c] and bt[j] become the least over the run's entries, quads[j] and tail[j] being what an
+// entry of shift kRes and 0 reads.  Shifts and errors come from LDS as the same word for every lane, two entries
+// at a time and a trip ahead: moved from a lane by v_readlane (and the error back to a vector register)
+// they cost 28 clocks of the pipe that the mins need, more than four quads of mins do.  That pipe takes four
+// clocks for any instruction but fp32 adds and multiplies of vector registers only, which have a
+// second one (v_min3 4.0 clocks of a SIMD, v_add 2.0, v_add with a scalar or a lane to the left 4.0).
+template <int Q, int T, int kRes, bool kSplit>
+__device__ __forceinline__ void sweep_run(const float4v *quads, const float *tail,
+                                          EntryRun run, float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
+{
+    constexpr int kStep = kSplit ? 4 : 2;
+    auto quads_at = [&](int shift) {
+        return reinterpret_cast<const float4v *>(reinterpret_cast<const char *>(quads) - shift +
+                                                 4 * kRes);
+    };
+    auto tail_at = [&](int shift) {
+        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(tail) - shift);
+    };
+    for (; run.n >= 2; run.n -= kStep) {
+        const EntryPair now = run.pair;
+        run.at += kStep;
+        run.pair = entry_pair(run.at);
+        const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
         if constexpr (Q > 0) {
-            const float4v *q0 = quads - (s0 >> 2);
-            const float4v *q1 = quads - (s1 >> 2);
+            const float4v *q0 = quads_at(now.x), *q1 = quads_at(now.z);
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-                float a[4], b[4];
-                shifted_quad<kRes>(q0[j * kQuadLanes], e0, a);
-                shifted_quad<kRes>(q1[j * kQuadLanes], e1, b);
+                const float4v v0 = q0[j * kQuadLanes], v1 = q1[j * kQuadLanes];
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    vmin3(bq[j][c], a[c], b[c]);
+                    vmin3(bq[j][c], v0[c] + e0, v1[c] + e1);
             }
         }
         if constexpr (T > 0) {
-            const float *p0 = tail - s0;
-            const float *p1 = tail - s1;
+            const float *p0 = tail_at(now.x), *p1 = tail_at(now.z);
 #pragma unroll
             for (int j = 0; j < T; ++j)
                 vmin3(bt[j], p0[j * kWave] + e0, p1[j * kWave] + e1);
         }
-    };
-    auto visit_one = [&](int i) {
-        const int s0 = __builtin_amdgcn_readlane(mine.shift, i);
-        float e0 = lane_value(mine.err, i);
-        asm volatile("" : "+v"(e0));
+    }
+    if (run.n == 1) {
+        const float e = __int_as_float(run.pair.y);
         if constexpr (Q > 0) {
-            const float4v *q0 = quads - (s0 >> 2);
+            const float4v *q = quads_at(run.pair.x);
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-                float a[4];
-                shifted_quad<kRes>(q0[j * kQuadLanes], e0, a);
+                const float4v v = q[j * kQuadLanes];
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    vmin(bq[j][c], a[c]);
+                    vmin(bq[j][c], v[c] + e);
             }
         }
         if constexpr (T > 0) {
-            const float *p0 = tail - s0;
+            const float *p = tail_at(run.pair.x);
 #pragma unroll
             for (int j = 0; j < T; ++j)
-                vmin(bt[j], p0[j * kWave] + e0);
+                vmin(bt[j], p[j * kWave] + e);
         }
-    };
-    // the usable entries of a residue are consecutive positions of the visiting order
-    int i = use ? __builtin_ctzll(use) : 0;
-    int n = __builtin_popcountll(use);
-    if constexpr (kSplit) {
-        if (skip) {
-            i += 2;
-            n -= 2;
-        }
-        for (; n >= 2; n -= 4, i += 4)
-            visit_two(i);
-        if (n == 1)
-            visit_one(i);
-    } else {
-        for (; n >= 2; n -= 2, i += 2)
-            visit_two(i);
-        if (n)
-            visit_one(i);
     }
 }
 
-// One group of R chunks of one layer (D record, at most 64 levels): sweep with 128-bit reads,
-// store the record, write the new row values; the barrier protocol is fill_group's.
+// All entries of a layer (at most 64, `mine.shift`: that of entry `lane`) over one group.  An entry of
+// residue r adds to the whole quads it reads, four buckets from 4 q + r on; so the minima are kept shifted by
+// the residue, and moved by one bucket (which is a move of a fourth of them to the lane to the right,
+// the others only change their names) from one residue to the next, 3 to 0.  An operand from the left
+// lane in every add, as before, took the slow pipe.  What lane 0 gets from the left ends in buckets that are not
+// its own and never reaches lane 1.
+// kAhead: the first entries of all four runs are asked for at once (registers permitting).
+template <int Q, int T, bool kSplit, bool kAhead>
+__device__ __forceinline__ void sweep_layer(const float4v *quads, const float *tail,
+                                            const int2 *entries, LevelEntry mine, int last_bucket,
+                                            int half, float (&bq)[Q > 0 ? Q : 1][4],
+                                            float (&bt)[T > 0 ? T : 1])
+{
+    const unsigned long long use = __ballot(mine.shift <= last_bucket);
+    const int residue = mine.shift & 3;
+    const unsigned long long use0 = use & __ballot(residue == 0);
+    const unsigned long long use1 = use & __ballot(residue == 1);
+    const unsigned long long use2 = use & __ballot(residue == 2);
+    const unsigned long long use3 = use & __ballot(residue == 3);
+    // Scalar loads and LDS reads share one counter, and scalar loads return out of order: while
+    // one is in flight (the wall clock of the priority turns, the next layer's chunk range)
+    // every wait for an LDS read in the sweep has to be a wait for ALL of them, and a wave
+    // cannot start on the first quads while the later ones arrive.  Let them land first.
+    __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0), nothing else
+    // kSplit: the pairs of entries are numbered through the four runs; half h visits the
+    // pairs whose number is h mod 2, so both halves get every residue's kind of work
+    int turn = half;
+    auto pairs = [](unsigned long long u) { return (__builtin_popcountll(u) + 1) >> 1; };
+    EntryRun run3 = entry_run<kSplit>(entries, use3, turn & 1);
+    turn += kSplit ? pairs(use3) : 0;
+    EntryRun run2 = entry_run<kSplit>(entries, use2, turn & 1);
+    turn += kSplit ? pairs(use2) : 0;
+    EntryRun run1 = entry_run<kSplit>(entries, use1, turn & 1);
+    turn += kSplit ? pairs(use1) : 0;
+    EntryRun run0 = entry_run<kSplit>(entries, use0, turn & 1);
+    auto later = [](EntryRun &r) __attribute__((always_inline)) {
+        if (!kAhead) {
+            asm volatile("" ::: "memory");
+            r.pair = entry_pair(r.at);
+        }
+    };
+    auto next_residue = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const float carry = from_left(bq[j][3]);
+            bq[j][3] = bq[j][2];
+            bq[j][2] = bq[j][1];
+            bq[j][1] = bq[j][0];
+            bq[j][0] = carry;
+        }
+    };
+    sweep_run<Q, T, 3, kSplit>(quads, tail, run3, bq, bt);
+    next_residue();
+    later(run2);
+    sweep_run<Q, T, 2, kSplit>(quads, tail, run2, bq, bt);
+    next_residue();
+    later(run1);
+    sweep_run<Q, T, 1, kSplit>(quads, tail, run1, bq, bt);
+    next_residue();
+    later(run0);
+    sweep_run<Q, T, 0, kSplit>(quads, tail, run0, bq, bt);
+}
+
+// One group of one layer (D record, at most 64 levels), Q quad chunks and T ordinary ones from bucket
+// `tail0` of the group on: sweep with 128-bit reads, store the record, write the new row values; the barrier protocol is fill_group's.
 // prev + t0 is 16-byte aligned (rows, aprons and chunk starts are multiples of four floats).
 // kSplit (in place only): this wave has a twin in the other half of the workgroup with the same
 // group; the two visit alternate pairs of the layer's entries, the second half (`half` = 1)
 // leaves its minima in `part` (indexed like the row) before the barrier, and the first half
 // folds them into its own behind it.  min is exact and order-blind here, so the row is the one
 // a single wave would have computed.
-template <int R, bool inplace, bool kSplit>
+template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead>
 __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, float *rec,
-                                                 LevelEntry first, int t0, int lane,
-                                                 Pending pending, int half, float *part)
+                                                 LevelEntry first, const int2 *entries, int t0, int lane, Pending pending, int half,
+                                                 float *part)
 {
     static_assert(!kSplit || inplace, "the halves meet at the in-place barrier");
-    if constexpr (R == 0) {
+    if constexpr (Q + T == 0) {
         pending.settle();
         if (inplace)
             __syncthreads();
     } else {
-        constexpr int Q = quad_chunks(R), T = tail_chunks(R);
-        constexpr int tail0 = (R - T) * kWave;    // first bucket of the tail chunks in the group
         float bq[Q > 0 ? Q : 1][4], bt[T > 0 ? T : 1];
 #pragma unroll
         for (int j = 0; j < Q; ++j)
@@ -1215,33 +1315,11 @@ __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, 
 #pragma unroll
         for (int j = 0; j < T; ++j)
             bt[j] = __builtin_inff();
-        const int last = t0 + R * kWave - 1;      // last bucket of the group
+        // last bucket of the group
+        const int last = t0 + (T > 0 ? tail0 + T * kWave : Q * kQuadChunk) - 1;
         const float4v *quads = reinterpret_cast<const float4v *>(prev + t0) + (lane - 1);
         const float *tail = prev + t0 + tail0 + lane;
-        const unsigned long long use = __ballot(first.shift <= last);
-        const int residue = first.shift & 3;
-        // Scalar loads and LDS reads share one counter, and scalar loads return out of order: while
-        // one is in flight (the wall clock of the priority turns, the next layer's chunk range)
-        // every wait for an LDS read in the sweep has to be a wait for ALL of them, and a wave
-        // cannot start on the first quads while the later ones arrive.  Let them land first.
-        __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0), nothing else
-        const unsigned long long use0 = use & __ballot(residue == 0);
-        const unsigned long long use1 = use & __ballot(residue == 1);
-        const unsigned long long use2 = use & __ballot(residue == 2);
-        const unsigned long long use3 = use & __ballot(residue == 3);
-        // kSplit: the pairs of entries are numbered through the four runs; half h visits the
-        // pairs whose number is h mod 2, so both halves get every residue's kind of work
-        int turn = half;
-        sweep_residue<Q, T, 0, kSplit>(quads, tail, first, use0, turn & 1, bq, bt);
-        if constexpr (kSplit)
-            turn += (__builtin_popcountll(use0) + 1) >> 1;
-        sweep_residue<Q, T, 1, kSplit>(quads, tail, first, use1, turn & 1, bq, bt);
-        if constexpr (kSplit)
-            turn += (__builtin_popcountll(use1) + 1) >> 1;
-        sweep_residue<Q, T, 2, kSplit>(quads, tail, first, use2, turn & 1, bq, bt);
-        if constexpr (kSplit)
-            turn += (__builtin_popcountll(use2) + 1) >> 1;
-        sweep_residue<Q, T, 3, kSplit>(quads, tail, first, use3, turn & 1, bq, bt);
+        sweep_layer<Q, T, kSplit, kAhead>(quads, tail, entries, first, last, half, bq, bt);
         pending.settle();
         const int tq = t0 + 4 * (lane - 1);       // this lane's first bucket of quad chunk 0
         const int tt = t0 + tail0 + lane;
@@ -1337,11 +1415,11 @@ __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_
     }
 }
 
-template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kPairs>
+template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kAhead, bool kPairs>
 __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cur, uint8_t *choice,
-                                             float *rec, LevelEntry first, LayerTable tl,
-                                             ErrRow er, int s8, int t0, int lane, Pending pending,
-                                             int half = 0, float *part = nullptr)
+                                             float *rec, LevelEntry first, const int2 *entries,
+                                             LayerTable tl, ErrRow er, int s8, int t0, int lane,
+                                             Pending pending, int half = 0, float *part = nullptr)
 {
     static_assert(!kSplit || kQuads, "only the 128-bit sweep splits a layer's entries");
     switch (r) {
@@ -1349,8 +1427,9 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
     case RR:                                                                                   \
         if constexpr (RR <= kMax) {                                                            \
             if constexpr (kQuads)                                                              \
-                fill_group_quads<RR, inplace, kSplit>(prev, cur, rec, first, t0, lane,         \
-                                                      pending, half, part);                    \
+                fill_group_quads<quad_chunks(RR), tail_chunks(RR), (RR - tail_chunks(RR)) * kWave, \
+                                 inplace, kSplit, kAhead>(prev, cur, rec, first, entries, t0,  \
+                                                          lane, pending, half, part);          \
             else                                                                               \
                 fill_group<RR, kLevel, inplace, kPairs>(prev, cur, choice, rec, first, tl, er, s8, t0, \
                                                 lane, pending);                                \
@@ -1387,6 +1466,30 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
         SPDY_CASE(28)
 #undef SPDY_CASE
     }
+}
+
+// The same in place for a share of whole quad chunks.
+__device__ __forceinline__ void fill_quads_n(int share, float *row, float *rec, LevelEntry first,
+                                             const int2 *entries, int lane, Pending pending)
+{
+    const int t0 = (share & 0xFFFFF) * 4;
+    switch (share >> 20 & 0xF) {
+#define SPDY_CASE(QQ)                                                                          \
+    case QQ:                                                                                   \
+        fill_group_quads<QQ, 0, 0, true, false, true>(row, row, rec, first, entries, t0, lane, \
+                                                      pending, 0, nullptr);                    \
+        break;
+        SPDY_CASE(0)
+        SPDY_CASE(1)
+        SPDY_CASE(2)
+        SPDY_CASE(3)
+        SPDY_CASE(4)
+        SPDY_CASE(5)
+        SPDY_CASE(6)
+        SPDY_CASE(7)
+#undef SPDY_CASE
+    }
+    static_assert(kMaxQuads == 7, "a case for each");
 }
 
 // (value, t) pairs ordered by value, then by smaller t.
@@ -1566,10 +1669,11 @@ __device__ __forceinline__ float profile_cost(const ErrSource src, int L, int S,
 struct FillShared {      // static LDS of the kernels
     float best[kMaxFillWaves];
     int time[kMaxFillWaves];
-    // per team and for two layers: merged errors (D record), or in the same storage one 64-bit
-    // set of levels to visit (level record)
-    __attribute__((aligned(8))) float entries[2][kMaxFillWaves][kWave];
+    // per team and for two layers: the entries (D record, at most one team per planned wave), or in the
+    // same storage one 64-bit set of levels to visit (level record); a sweep looks kLookAhead entries too far
+    __attribute__((aligned(8))) int2 entries[2 * kFillWaves * kWave + kLookAhead];
 };
+static_assert(sizeof(FillShared) <= kLdsStatic, "static LDS");
 template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo, bool kTurns, bool kSplit,
           bool kPairs>
 __device__ __forceinline__ void fill_candidates(
@@ -1706,8 +1810,9 @@ __device__ __forceinline__ void fill_candidates(
     float *part = kSplit ? lds + kLdsHalf / (int)sizeof(float) + (size_t)(team < teams ? team : 0) * row
                          : nullptr;
     unsigned long long *keep =
-        reinterpret_cast<unsigned long long *>(&s_entries[0][0][0]) + (team < teams ? team : 0);
-    float *table = &s_entries[0][team < teams ? team : 0][0];
+        reinterpret_cast<unsigned long long *>(&s_entries[0]) + (team < teams ? team : 0);
+    int2 *const table = &s_entries[(team < teams && !kLevel ? team : 0) * kWave];
+    constexpr int kNextTable = kFillWaves * kWave;   // from an even layer's table to an odd one's
     LevelEntry next_first{INT32_MAX, 0.0f};
     LevelFetch next_fetch{INT32_MAX, 0.0f, 0};
     if constexpr (kNarrow) {
@@ -1720,7 +1825,7 @@ __device__ __forceinline__ void fill_candidates(
                 if (lane == 0)
                     keep[(lb & 1) * kMaxFillWaves] = visit;
             } else {
-                publish_entries(table + (lb & 1) * kMaxFillWaves * kWave, next_fetch, S, lane);
+                publish_entries(table + (lb & 1) * kNextTable, next_fetch, S, lane);
             }
         }
         __syncthreads();
@@ -1731,6 +1836,8 @@ __device__ __forceinline__ void fill_candidates(
     // chunk boundaries of this wave
     const int32_t *range = meta + kMetaHeader + 2 * L + (size_t)lb * kRangeStride + share;
     int c_next = range[0], c_end_next = range[1];
+    constexpr bool kWhole = kQuads && kPath == 1 && !kSplit;
+    int whole_next = kWhole ? range[kWholeWord] : 0;
     // Two workgroups share a compute unit, and the hardware serves the older one first: left
     // alone, the first `units` workgroups of a launch run at full speed, the second `units` on what
     // is left and then by themselves, at barely more than half the unit's LDS rate.  The
@@ -1758,9 +1865,10 @@ __device__ __forceinline__ void fill_candidates(
         LevelEntry first = next_first;
         if constexpr (kNarrow) {
             first.shift = next_fetch.shift;
-            first.err = kLevel ? next_fetch.raw : table[(l & 1) * kMaxFillWaves * kWave + lane];
-            if constexpr (kLevel)
+            if constexpr (kLevel) {
+                first.err = next_fetch.raw;
                 first.keep = keep[(l & 1) * kMaxFillWaves];
+            }
         }
         if (l + 1 < le) {
             const LayerTable tn = tables.layer(l + 1);
@@ -1778,15 +1886,18 @@ __device__ __forceinline__ void fill_candidates(
         }
         const float *prev = (l & 1) ? buf1 : buf0;
         float *cur = (l & 1) ? buf0 : buf1;
-        int c = 0, c_end = 0;                    // this wave's chunks of the row
+        int c = 0, c_end = 0, whole = 0;         // this wave's chunks of the row
         if (active && l >= l0) {
             c = c_next;
             c_end = c_end_next;
+            whole = whole_next;
         }
         if (l + 1 < le) {                        // the next layer's, read a layer ahead
             range += kRangeStride;
             c_next = range[0];
             c_end_next = range[1];
+            if constexpr (kWhole)
+                whole_next = range[kWholeWord];
         }
         uint8_t *choice_l = kLevel ? choice_k + (size_t)l * pitch : nullptr;
         float *drec_l = kLevel ? nullptr : drec_k + (size_t)l * pitch;
@@ -1802,12 +1913,15 @@ __device__ __forceinline__ void fill_candidates(
         }
         const LayerTable tl = tables.layer(l);
         const ErrRow er = mine.layer(l, S);
+        const int2 *const entries = table + (l & 1) * kNextTable;
         constexpr int kMax = group_limit<kLevel, kTurns>();
         const Pending pending{&next_fetch, &next_first};
-        if constexpr (inplace) {                 // c_end - c <= kMax by construction
-            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPairs>(
-                min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, tl, er, s8, c * kWave, lane,
-                pending, half, part);
+        if (kWhole && whole != 0) {
+            fill_quads_n(whole, cur, drec_l, first, entries, lane, pending);
+        } else if constexpr (inplace) {          // c_end - c <= kMax by construction
+            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, kPairs>(
+                min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, entries, tl, er, s8,
+                c * kWave, lane, pending, half, part);
         } else {
             // Rows in global memory: the row is computed in tiles of at most kMax chunks per
             // wave, and the part of the previous row a tile reads (the tile itself and the
@@ -1852,9 +1966,9 @@ __device__ __forceinline__ void fill_candidates(
                     __syncthreads();
                     const int cb = c0 + (int)((long long)share * nt / tw);
                     const int ce = c0 + (int)((long long)(share + 1) * nt / tw);
-                    fill_group_n<kLevel, false, kMax, kQuads, false, kPairs>(
-                        ce - cb, lds - lo, cur, choice_l, drec_l, first, tl, er, s8, cb * kWave, lane,
-                        pending);
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kPairs>(
+                        ce - cb, lds - lo, cur, choice_l, drec_l, first, entries, tl, er, s8,
+                        cb * kWave, lane, pending);
                     __syncthreads();             // the next tile overwrites the staged part
                 }
             } else {
@@ -1862,8 +1976,9 @@ __device__ __forceinline__ void fill_candidates(
                     const int n = c_end - c;
                     const int groups = (n + kMax - 1) / kMax;
                     const int r = (n + groups - 1) / groups;
-                    fill_group_n<kLevel, false, kMax, kQuads, false, kPairs>(
-                        r, prev, cur, choice_l, drec_l, first, tl, er, s8, c * kWave, lane, pending);
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kPairs>(
+                        r, prev, cur, choice_l, drec_l, first, entries, tl, er, s8, c * kWave, lane,
+                        pending);
                     c += r;
                 }
             }
@@ -1876,8 +1991,7 @@ __device__ __forceinline__ void fill_candidates(
                 if (lane == 0)
                     keep[((l + 1) & 1) * kMaxFillWaves] = visit;
             } else {
-                publish_entries(table + ((l + 1) & 1) * kMaxFillWaves * kWave, next_fetch, S,
-                                lane);
+                publish_entries(table + ((l + 1) & 1) * kNextTable, next_fetch, S, lane);
             }
         }
         __syncthreads();
