@@ -42,9 +42,10 @@ constexpr int kCoreMaxBudget = 1 << 22;  // times stay exact in fp32, a level an
 constexpr int kCoreShiftBits = 23;       // a shift is at most the budget
 static_assert(kCoreMaxBudget < 1 << kCoreShiftBits && 255ull << kCoreShiftBits <= UINT32_MAX,
               "a level and a shift share a word");
-constexpr int kCoreExtra = 32;           // levels beyond one per layer that are not worth halving
+constexpr int kCoreExtra = 128;          // levels beyond one per layer that are not worth halving
+constexpr int kCorePairs = 128;          // exchanges of which all pairs are tried, and none
 constexpr int kCoreNarrow = 2;           // chunks of a row that one wave does alone
-constexpr int kCoreTrips = 4;            // attempts, counting a halving before the first (two are usual)
+constexpr int kCoreTrips = 5;            // attempts, counting a halving before the first (one is usual)
 constexpr int kCoreBudgets = 64;         // budgets per launch
 constexpr float kCoreFar = kCoreMaxBudget + 1;   // "time" of a level that may not be chosen
 static_assert(kCoreMaxLayers * (long long)kCoreFar <= INT32_MAX, "times are summed in int");
@@ -62,6 +63,7 @@ struct CoreEntry {       // a surviving level
 struct CoreParams {
     int parts, parts_log2;       // threads per layer (a power of two <= 64)
     int per_part;        // levels per thread, a multiple of four (<= 128)
+    int share_log2;      // the same of a wave that has all layers to itself
     int pad;             // levels per layer past the last one that are scanned with it
     int step_layers;     // kCoreThreads / S
     int pitch;           // levels per layer in LDS (odd, so that a column of levels is conflict-free)
@@ -91,6 +93,16 @@ __device__ __forceinline__ unsigned long long pair_key(unsigned high, unsigned l
 // instructions, and the waits for LDS would wait for memory, too.)
 using FarRow = __attribute__((address_space(1))) float *;
 using FarBytes = __attribute__((address_space(1))) unsigned char *;
+
+// Loads for the next trip of a loop, above this, are asked for in this trip.  (Where nothing is in the way the
+// compiler makes one load of the first trip's and the later ones', at the head of the loop, and waits for it.)
+__device__ __forceinline__ void stay_ahead() { asm volatile("" ::: "memory"); }
+
+// The upper bits of `word`, and a place of three bits in the lower ones.
+__device__ __forceinline__ unsigned with_place(unsigned word, unsigned upper, int place)
+{
+    return (word & upper) | (unsigned)place;
+}
 
 struct CoreBooks {       // where the steps of the reduced table have got to
     int m, a, b, used, spilled, first_spilled, work, prev, failed, wide;
@@ -195,32 +207,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 next_v[q] = from[q];
+            stay_ahead();
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 f(v[q], i + q);
         }
     };
     int turn = 0;                                 // which half of the double-buffered words
-    // Error and time of the path on which this thread's layer has (e, t): sums over the layers.
-    // (fp32 is enough for the error: it only steers the choice of the multiplier.)
-    auto path_sum = [&](float e, float t, float &c, int &total) __attribute__((always_inline)) {
-        const float ce = from_lane(wave_scan(lead ? e : 0.0f, 0.0f, Add{}), kWave - 1);
-        const int ct = from_lane(wave_scan(lead ? (int)t : 0, 0, Add{}), kWave - 1);
-        if (lane == 0)
-            sh.sum[turn][wave] = make_float2(ce, __builtin_bit_cast(float, ct));
-        __syncthreads();
-        c = 0.0f;
-        total = 0;
-#pragma unroll
-        for (int w = 0; w < kCoreWaves; ++w) {
-            c += sh.sum[turn][w].x;
-            total += __builtin_bit_cast(int, sh.sum[turn][w].y);
-        }
-        c = uniform(c);
-        total = uniform(total);
-        turn ^= 1;
-    };
-
     // ---- the two ends of the multiplier's range: least error (lambda = 0), least time
     float lo_e, lo_t, hi_e, hi_t;                 // (err, tau) of this layer on either path
     float c_lo, c_hi;
@@ -273,128 +266,345 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
     float lambda_f = 0.0f;
     const bool fits = t_lo <= B;                  // the least-error profile meets the budget
     if (!fits) {
+        // Four multipliers a pass, one a wave, a lane (or `share` lanes, where layers are few) per layer:
+        // five passes, seven for deep networks, where one multiplier a pass took ten to fourteen.  The first
+        // wave takes the chord, which decides when to stop; the others where the logarithm of the multiplier,
+        // interpolated over the time, meets the budget, and on either side of that.  What a pass costs
+        // is instructions, so a level's place shares a word with the upper bits of its value, two and a half
+        // instructions a level: the level found is the least up to 2^-15 of its value at worst, which is as
+        // good for the choice of a multiplier (the bound is taken from that in fp64).  (Two multipliers per
+        // thread, layers split over all threads: six passes, each longer by as much.)
+        int2 *const picks = reinterpret_cast<int2 *>(steps);         // of the path above the budget, below it
+        if (lead)
+            picks[layer] = make_int2(-1, -1);
+        const int share = 1 << cp.share_log2, of_wave = lane & (share - 1);
+        const int levels = ((S + share - 1) / share + 3) & ~3;       // of a lane
+        const unsigned places = (1u << (32 - __builtin_clz(S | 4))) - 1u;
+        float lam_lo = 0.0f, lam_hi = __builtin_inff();
         for (int trip = 0; trip < 40; ++trip) {
             lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
-            float least = __builtin_inff();
-            int level = 0;
-            scan([&](float2 v, int i) {
-                const float r = __builtin_fmaf(lambda_f, v.y, v.x);
-                level = r < least ? i : level;
-                least = r < least ? r : least;
-            });
-            level = (int)(unsigned)group_join(pair_key(magnitude(least), s_begin + level), parts,
-                                              Smaller{});
-            const float2 v = mine[level];
-            float c;
-            int t;
-            path_sum(v.x, v.y, c, t);
-            if (!(t > t_hi && t < t_lo))
+            float lam = lambda_f;
+            if (wave > 0) {
+                if (lam_lo > 0.0f && lam_hi < __builtin_inff()) {
+                    const float f = (float)(t_lo - B) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
+                    const float x = wave == 1 ? f : (wave == 2 ? 0.8f * f : 0.2f + 0.8f * f);
+                    lam = lam_lo * __builtin_amdgcn_exp2f(
+                                       x * __builtin_amdgcn_logf(lam_hi * __builtin_amdgcn_rcpf(lam_lo)));
+                } else {
+                    lam *= wave == 1 ? 0.4f : (wave == 2 ? 0.15f : 2.0f);
+                }
+                lam = fminf(fmaxf(lam, lam_lo), lam_hi);
+            }
+            float ce = 0.0f;
+            int ct = 0, pick[kCoreMaxLayers / kWave];
+#pragma unroll
+            for (int b = 0; b < kCoreMaxLayers / kWave; ++b) {
+                if (b * kWave >= L)
+                    break;
+                const int layer_b = b * kWave + (lane >> cp.share_log2);
+                const float2 *const row = table + min(layer_b, L - 1) * cp.pitch;
+                const int start = of_wave * levels;
+                // Eight levels a trip (the last eight may be some of those before once more); the next
+                // trip's are asked for as soon as this trip's have been used, into the same registers.
+                const float2 *from = row + start;
+                unsigned key = ~0u;
+                float2 v[8];
+                auto eight = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        v[q] = from[(q < 4 ? i : min(i + 4, levels - 4)) + (q & 3)];
+                };
+                eight(0);
+                for (int i = 0; i < levels; i += 8) {
+                    unsigned k[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        k[q] = __builtin_bit_cast(unsigned, __builtin_fmaf(lam, v[q].y, v[q].x));
+                    eight(min(i + 8, levels - 4));
+                    stay_ahead();
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        k[q] = with_place(k[q], ~places, q);
+                    const unsigned low = min(min(min(k[0], k[1]), k[2]), k[3]);
+                    const unsigned high = min(min(min(k[4], k[5]), k[6]), k[7]);
+                    // (places of the upper four count from 4: where they are the lower four once more, they
+                    // lose against them)
+                    key = min(min(low, high) | i, key);
+                }
+                key += start;
+                pick[b] = (int)(group_join(key, share, Smaller{}) & places);
+                const float2 found = row[min(pick[b], S - 1)];
+                const bool counts = layer_b < L && of_wave == 0;
+                ce += counts ? found.x : 0.0f;
+                ct += counts ? (int)found.y : 0;
+            }
+            ce = wave_scan(ce, 0.0f, Add{});
+            ct = wave_scan(ct, 0, Add{});
+            if (lane == kWave - 1) {
+                sh.sum[turn][wave] = make_float2(ce, __builtin_bit_cast(float, ct));
+                sh.change[turn][wave].x = __builtin_bit_cast(int, lam);
+            }
+            __syncthreads();
+            const int t_chord = uniform(__builtin_bit_cast(int, sh.sum[turn][0].y));
+            if (!(t_chord > t_hi && t_chord < t_lo))
                 break;
-            if (t <= B) {
-                c_hi = c;
-                t_hi = t;
-                hi_e = v.x;
-                hi_t = v.y;
-            } else {
-                c_lo = c;
-                t_lo = t;
-                lo_e = v.x;
-                lo_t = v.y;
+            int hi_wave = -1, lo_wave = -1;
+#pragma unroll
+            for (int w = 0; w < kCoreWaves; ++w) {
+                const float cw = uniform(sh.sum[turn][w].x);
+                const int tw = uniform(__builtin_bit_cast(int, sh.sum[turn][w].y));
+                const float lw = uniform(__builtin_bit_cast(float, sh.change[turn][w].x));
+                if (tw <= B) {
+                    lam_hi = fminf(lam_hi, lw);
+                    hi_wave = tw > t_hi ? w : hi_wave;
+                    c_hi = tw > t_hi ? cw : c_hi;
+                    t_hi = tw > t_hi ? tw : t_hi;
+                } else {
+                    lam_lo = fmaxf(lam_lo, lw);
+                    lo_wave = tw < t_lo ? w : lo_wave;
+                    c_lo = tw < t_lo ? cw : c_lo;
+                    t_lo = tw < t_lo ? tw : t_lo;
+                }
+            }
+            turn ^= 1;
+#pragma unroll
+            for (int b = 0; b < kCoreMaxLayers / kWave; ++b) {
+                const int layer_b = b * kWave + (lane >> cp.share_log2);
+                if (b * kWave < L && layer_b < L && of_wave == 0) {
+                    if (wave == lo_wave)
+                        picks[layer_b].x = min(pick[b], S - 1);
+                    if (wave == hi_wave)
+                        picks[layer_b].y = min(pick[b], S - 1);
+                }
             }
         }
+        __syncthreads();                          // the paths are written, the words are read
+        const int2 path = picks[in_layer ? layer : 0];
+        const float2 lo = mine[max(path.x, 0)], hi = mine[max(path.y, 0)];
+        lo_e = path.x >= 0 ? lo.x : lo_e;
+        lo_t = path.x >= 0 ? lo.y : lo_t;
+        hi_e = path.y >= 0 ? hi.x : hi_e;
+        hi_t = path.y >= 0 ? hi.y : hi_t;
     }
     const double lambda = lambda_f;
 
-    // ---- a profile that meets the budget: from either path by the best single exchanges
-    // mode 0: from the path below the budget, the level that saves most error and fits, as long as
-    // there is one; 1: from the path above it, the level that costs least and brings it below;
-    // 2: then as 0.
-    float inc_e = lo_e;
-    if (!fits) {
-        float cur_e = hi_e, cur_t = hi_t, c = c_hi, c_inc = __builtin_inff();
-        int room = B - t_hi, mode = 0;
-        for (int trip = 0; trip < 24; ++trip) {
-            const bool must = mode == 1;
-            const float top = cur_t + (float)room;
-            unsigned long long best = must ? ~0ull : pair_key(magnitude(cur_e), magnitude(cur_t));
-            scan([&](float2 v, int) {
-                const unsigned long long o = pair_key(magnitude(v.x), magnitude(v.y));
-                best = v.y <= top ? Smaller{}(best, o) : best;
-            });
-            best = group_join(best, parts, Smaller{});
-            const float e = __builtin_bit_cast(float, (unsigned)(best >> 32));
-            const float t = __builtin_bit_cast(float, (unsigned)best);
-            const float change = e - cur_e;
-            const unsigned bits = __builtin_bit_cast(unsigned, change);
-            const unsigned up = (bits >> 31) ? ~bits : (bits | 0x80000000u);   // orders as `change`
-            const bool valid = lead && (must ? e < __builtin_inff() : change < 0.0f);
-            const unsigned long long key = valid ? pair_key(~up, tid + 1) : 0ull;
-            const unsigned long long top_key =
-                from_lane(wave_scan(key, 0ull, Larger{}), kWave - 1);
-            if (top_key == 0 ? lane == 0 : key == top_key) {
-                sh.key[turn][wave] = top_key;
-                sh.change[turn][wave] = make_int2((int)bits, (int)t - (int)cur_t);
-            }
-            __syncthreads();
-            unsigned long long win = 0;
-            int2 d = make_int2(0, 0);
-#pragma unroll
-            for (int w = 0; w < kCoreWaves; ++w) {
-                const unsigned long long o = sh.key[turn][w];
-                const int2 od = sh.change[turn][w];
-                d.x = o > win ? od.x : d.x;
-                d.y = o > win ? od.y : d.y;
-                win = o > win ? o : win;
-            }
-            win = uniform(win);
-            d.x = uniform(d.x);
-            d.y = uniform(d.y);
-            turn ^= 1;
-            if (win) {
-                if (layer == (int)((unsigned)win - 1u) >> cp.parts_log2) {
-                    cur_e = e;
-                    cur_t = t;
-                }
-                c += __builtin_bit_cast(float, d.x);
-                room -= d.y;
-                mode = must ? 2 : mode;
-            } else if (mode == 0) {
-                inc_e = cur_e;
-                c_inc = c;
-                cur_e = lo_e;
-                cur_t = lo_t;
-                c = c_lo;
-                room = B - t_lo;
-                mode = 1;
-            } else {
-                break;
-            }
-        }
-        if (mode != 1 && c < c_inc)               // (the last exchanges may have been cut short)
-            inc_e = cur_e;
-    }
-    if (lead)
-        single[layer] = inc_e;
-
-    // ---- the Lagrangian bound at lambda, in fp64
+    // ---- the Lagrangian bound at lambda, in fp64, and the best that one exchange makes of either path:
+    // of the one below the budget, the level that saves most error and still meets it; of the one
+    // above, the level that costs least and brings it there
     double least = __builtin_inf();               // min over the layer of err + lambda tau
-    scan([&](float2 v, int) {
-        least = Smaller{}(least, __builtin_fma(lambda, (double)v.y, (double)v.x));
-    });
+    unsigned long long one_hi = ~0ull, one_lo = ~0ull;        // error and time
+    {
+        const float top_hi = hi_t + (float)(B - t_hi), top_lo = lo_t + (float)(B - t_lo);
+        scan([&](float2 v, int) {
+            least = Smaller{}(least, __builtin_fma(lambda, (double)v.y, (double)v.x));
+            const unsigned long long o = pair_key(magnitude(v.x), magnitude(v.y));
+            one_hi = v.y <= top_hi ? Smaller{}(one_hi, o) : one_hi;
+            one_lo = v.y <= top_lo ? Smaller{}(one_lo, o) : one_lo;
+        });
+    }
     least = group_join(least, parts, Smaller{});
+    one_hi = group_join(one_hi, parts, Smaller{});
+    one_lo = group_join(one_lo, parts, Smaller{});
+    auto error_of = [](unsigned long long key) { return __builtin_bit_cast(float, (unsigned)(key >> 32)); };
+    auto time_of = [](unsigned long long key) { return __builtin_bit_cast(float, (unsigned)key); };
+    const float with_hi = c_hi + (error_of(one_hi) - hi_e);
+    const float with_lo = one_lo == ~0ull ? __builtin_inff() : c_lo + (error_of(one_lo) - lo_e);
+    const bool from_lo = with_lo < with_hi;
+    const unsigned long long one_key =            // about its cost, the layer's thread, the path
+        lead ? pair_key(magnitude(fmaxf(from_lo ? with_lo : with_hi, 0.0f)), tid << 1 | (from_lo ? 1 : 0))
+             : ~0ull;
     const double run_least = wave_scan(lead ? least : 0.0, 0.0, Add{});
-    if (lane == kWave - 1)
+    const unsigned long long run_one = wave_scan(one_key, ~0ull, Smaller{});
+    if (lane == kWave - 1) {
         sh.least[wave] = run_least;
-    __syncthreads();                              // (also publishes `single`)
+        sh.key[turn][wave] = run_one;
+    }
+    __syncthreads();
     double sum_least = 0.0, upto_least = run_least;
+    unsigned long long known_key = ~0ull;
 #pragma unroll
     for (int w = 0; w < kCoreWaves; ++w) {
         const double o = sh.least[w];
         upto_least += w < wave ? o : 0.0;
         sum_least += o;
+        known_key = Smaller{}(known_key, sh.key[turn][w]);
     }
     sum_least = uniform(sum_least);
-    float upper = -0.0f;                          // U: the profile's cost, summed as Alg. 1 does
+    known_key = uniform(known_key);
+    const float known = __builtin_bit_cast(float, (unsigned)(known_key >> 32));
+    turn ^= 1;
+    const double relaxed = sum_least - lambda * B;
+
+    // ---- a profile that meets the budget: from either path by the best exchange, or the best two
+    // of levels whose excess a profile of the cost known so far can afford, all pairs of up to kCorePairs
+    // of them; where there are more, of the nearest, and then once more from the profile found instead of
+    // the path below the budget.  Its cost is the least there is for more than half of the candidates here,
+    // and its distance from the bound a third of what the best exchanges one after the other leave (five
+    // passes of 2900 clocks), so the table that is left has half the steps and a third of the rows at the
+    // worst (searches of L = 52 - 54, S = 40 - 42: 88 - 300 row sweeps of 64 buckets before, 36 - 94 now).
+    // A second time for all with many levels made the slowest of searches up to 5 % slower, none at all
+    // up to 1.5 times.
+    if (!fits) {
+        struct Exchange {                         // against the path below the budget, and the one above
+            float hi;
+            uint32_t word_hi;                     // layer << 24 | time + kMiddle
+            float lo;
+            uint32_t word_lo;
+        };
+        constexpr int kMiddle = 1 << 23;
+        static_assert(kCoreMaxBudget < kMiddle && kCoreMaxLayers <= 256, "a layer and a time share a word");
+        Exchange *const exchange = reinterpret_cast<Exchange *>(list);
+        const int room = min(kCorePairs, cp.entries / 2);     // (an entry of the list is half as large)
+        float *const time_in = reinterpret_cast<float *>(row_at);        // beside `single`
+        float cost_known = known;
+        for (int round = 0; round < 2; ++round) {
+            double affords = fmax((double)cost_known - relaxed, 0.0) * 1.0001;
+            unsigned long long kept[2];
+            int listed = 0, first_place = 0, all = 0;
+            int trip = 0;
+            for (;; ++trip) {
+                const double keep_to = least + affords;
+                int count = 0;
+                kept[0] = kept[1] = 0;
+                scan([&](float2 v, int i) {
+                    const bool keep = __builtin_fma(lambda, (double)v.y, (double)v.x) <= keep_to;
+                    const unsigned long long bit = keep ? 1ull << (i & 63) : 0ull;
+                    kept[0] |= i < 64 ? bit : 0ull;
+                    kept[1] |= i < 64 ? 0ull : bit;
+                    count += keep ? 1 : 0;
+                });
+                const int of_layer = group_join(count, parts, Add{});
+                listed = of_layer > 1 && in_layer ? count : 0;
+                const int run = wave_scan(listed, 0, Add{});
+                const int run_t = wave_scan(lead ? (int)hi_t : 0, 0, Add{});
+                if (lane == kWave - 1)
+                    sh.place[turn][wave] = make_int2(run, run_t);
+                __syncthreads();
+                first_place = run - listed;
+                all = t_hi = 0;
+#pragma unroll
+                for (int w = 0; w < kCoreWaves; ++w) {
+                    const int2 o = sh.place[turn][w];
+                    first_place += w < wave ? o.x : 0;
+                    all += o.x;
+                    t_hi += o.y;
+                }
+                all = uniform(all);
+                t_hi = uniform(t_hi);
+                turn ^= 1;
+                if (all < room || trip == 2)
+                    break;
+                affords *= fmin(0.5, 0.8 * room / all);
+            }
+            all = min(all, room - 1);             // (what there is no room for is left out)
+            // calls f(level, place) for what this thread has listed
+            auto for_listed = [&](auto f) __attribute__((always_inline)) {
+                int place = first_place;
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    unsigned long long left = listed ? kept[half] : 0;
+                    while (left) {
+                        f(s_begin + 64 * half + __builtin_ctzll(left), place++);
+                        left &= left - 1;
+                    }
+                }
+            };
+            for_listed([&](int level, int place) {
+                const float2 v = mine[level];
+                const uint32_t word = (uint32_t)layer << 24;
+                if (place < all)
+                    exchange[place] = Exchange{v.x - hi_e, word | (uint32_t)(kMiddle + (int)(v.y - hi_t)),
+                                               v.x - lo_e, word | (uint32_t)(kMiddle + (int)(v.y - lo_t))};
+            });
+            if (tid == 0)                         // none: a pair with it is a single exchange
+                exchange[all] = Exchange{0.0f, 0xFF000000u | kMiddle, 0.0f, 0xFF000000u | kMiddle};
+            __syncthreads();
+            // Lane j holds exchanges j and 64 + j; every wave pairs a fourth of all with them.
+            Exchange own[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                own[c] = exchange[min(c * kWave + lane, all)];
+            constexpr int kOne = 1 << 17;         // the best exchange by itself
+            float best = cost_known;
+            int which = kOne;                     // or the two of a pair and (bit 16) the path
+            auto pair_with = [&](auto ci, auto cj) __attribute__((always_inline)) {
+                constexpr int kI = decltype(ci)::value, kJ = decltype(cj)::value;
+                const unsigned layer_j = own[kJ].word_hi >> 24;
+                const int hi_j = (int)(own[kJ].word_hi & 0xFFFFFF);
+                const int lo_j = (int)(own[kJ].word_lo & 0xFFFFFF);
+                const float with_hi_j = c_hi + own[kJ].hi, with_lo_j = c_lo + own[kJ].lo;
+                for (int i = wave; i < min(kWave, all - kI * kWave); i += kCoreWaves) {
+                    const unsigned word_hi = (unsigned)__builtin_amdgcn_readlane((int)own[kI].word_hi, i);
+                    const unsigned word_lo = (unsigned)__builtin_amdgcn_readlane((int)own[kI].word_lo, i);
+                    const int room_hi = B - t_hi + 2 * kMiddle - (int)(word_hi & 0xFFFFFF);
+                    const int room_lo = B - t_lo + 2 * kMiddle - (int)(word_lo & 0xFFFFFF);
+                    const bool two = layer_j != word_hi >> 24;    // (not twice the same layer)
+                    const float cost_hi = with_hi_j + lane_value(own[kI].hi, i);
+                    const float cost_lo = with_lo_j + lane_value(own[kI].lo, i);
+                    const int pair = (kI * kWave + i) | kJ * kWave << 8;
+                    const bool take_hi = two && hi_j <= room_hi && cost_hi < best;
+                    best = take_hi ? cost_hi : best;
+                    which = take_hi ? pair : which;
+                    const bool take_lo = two && lo_j <= room_lo && cost_lo < best;
+                    best = take_lo ? cost_lo : best;
+                    which = take_lo ? pair | 1 << 16 : which;
+                }
+            };
+            pair_with(Many<0>{}, Many<0>{});
+            if (all >= kWave) {
+                pair_with(Many<0>{}, Many<1>{});
+                pair_with(Many<1>{}, Many<1>{});
+            }
+            const unsigned long long key =
+                from_lane(wave_scan(pair_key(magnitude(fmaxf(best, 0.0f)),
+                                             (unsigned)(which & kOne ? which : which + (lane << 8))),
+                                    ~0ull, Smaller{}),
+                          kWave - 1);
+            if (lane == 0)
+                sh.key[turn][wave] = key;
+            __syncthreads();
+            unsigned long long win = ~0ull;
+#pragma unroll
+            for (int w = 0; w < kCoreWaves; ++w)
+                win = Smaller{}(win, sh.key[turn][w]);
+            which = (int)uniform((unsigned)win);
+            turn ^= 1;
+            if (round == 0 || !(which & kOne)) {
+                const bool lo_path = (which & kOne ? (int)known_key & 1 : which >> 16 & 1) != 0;
+                // (what is no exchange is nobody's and in no layer)
+                const int first = which & kOne ? all : which & 0xFF;
+                const int second = which & kOne ? all : which >> 8 & 0xFF;
+                const int first_layer = first < all ? (int)(exchange[first].word_hi >> 24) : -1;
+                const int second_layer = second < all ? (int)(exchange[second].word_hi >> 24) : -1;
+                if (lead && layer != first_layer && layer != second_layer) {
+                    const bool changed = which & kOne && (int)((unsigned)known_key >> 1) == tid;
+                    const unsigned long long one = lo_path ? one_lo : one_hi;
+                    single[layer] = changed ? error_of(one) : (lo_path ? lo_e : hi_e);
+                    time_in[layer] = changed ? time_of(one) : (lo_path ? lo_t : hi_t);
+                }
+                if (layer == first_layer || layer == second_layer)
+                    for_listed([&](int level, int place) {
+                        if (place < all && (place == first || place == second)) {
+                            single[layer] = mine[level].x;
+                            time_in[layer] = mine[level].y;
+                        }
+                    });
+            }
+            if (trip == 0 || round > 0)
+                break;
+            cost_known = __builtin_bit_cast(float, (unsigned)(uniform(win) >> 32));
+            __syncthreads();                      // the profile is written, the exchanges are read
+            c_hi = cost_known;
+            hi_e = single[in_layer ? layer : 0];
+            hi_t = time_in[in_layer ? layer : 0];
+        }
+    } else if (lead) {
+        single[layer] = lo_e;
+    }
+    __syncthreads();                              // `single` is written, the exchanges are read
+    // U: the profile's cost, summed as Alg. 1 does.  (A bound on that from `best` needs no sum over the layers,
+    // 3000 clocks, but the distance from the relaxed problem is 10^-5 of the cost: twice the levels survived.)
+    float upper = -0.0f;
     for (int base = 0; base < L; base += kWave) {
         const float e = base + lane < L ? single[base + lane] : -0.0f;   // (x + -0 is x)
         for (int i = 0; i < min(kWave, L - base); i += 8)
@@ -402,19 +612,19 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             for (int q = 0; q < 8; ++q)
                 upper += lane_value(e, i + q);
     }
-    const double relaxed = sum_least - lambda * B;
     const double hu = 0x1p-24 * (double)__builtin_bit_cast(
                                     float, __builtin_bit_cast(unsigned, upper) & 0x7F800000u);
     const double margin = 1e-11 * (sum_least + lambda * B + (double)upper);
 
     // ---- survivors: count, place, write
-    // `target`: the cost a profile must not exceed to be looked for.  U is safe, but often far above
-    // the least cost; where it leaves many levels, half the way from the bound to it is tried first,
-    // and is as good as U if a profile of at most that cost turns up (it usually does, and the
-    // rows are half as wide); if not, U comes next, or the cost that did turn up.  What exceeds the
-    // limits of the launch is halved, too.
+    // `target`: the cost a profile must not exceed to be looked for.  U is safe, and mostly the least cost or
+    // near it.  Where it leaves very many levels it is not, and half the way from the bound to it is tried
+    // first, which is as good as U if a profile of at most that cost turns up; if not, U comes next, or the
+    // cost that did turn up.  (From 64 levels on, or where U's distance from the bound is mostly rounding, as
+    // in deep networks, that finds one too seldom.)  What exceeds the limits of the launch is halved, too, and
+    // then what lies between the half and that.
     double target = (double)upper, beyond = __builtin_inf();   // (beyond: exceeded the limits)
-    bool first_try = true;
+    bool first_try = target - relaxed > 8.0 * (L - 1) * hu;
     int work = 0;                                 // of all attempts
     auto halved = [&](double x) { return relaxed + 0.5 * (x - relaxed); };
     const bool in_range = upper < 1e38f && lambda_f < 1e30f;   // (false for a NaN, too)
@@ -442,7 +652,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
         if (lane == kWave - 1)
             sh.place[turn][wave] = make_int2(run, run_t);
-        __syncthreads();                          // (every wave is through with `single`, too)
+        __syncthreads();                
         int before = run - listed, all = 0, upto_t = run_t, base_t = 0;
 #pragma unroll
         for (int w = 0; w < kCoreWaves; ++w) {
@@ -824,8 +1034,11 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         }
         if (failed) {
             beyond = wide ? target : beyond;
-            target = wide ? halved(target) : (double)upper;
-            if (!(target < beyond) || work > cp.work)
+            const double missed = target;
+            target = wide ? halved(target) : fmin((double)upper, relaxed + 2.0 * (target - relaxed));
+            if (!(target < beyond))               // between the one that found none and what is too much
+                target = 0.5 * (missed + beyond);
+            if (work > cp.work)
                 break;
             __syncthreads();                      // every wave is through with the rows
             stage();

@@ -2359,6 +2359,9 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
         parts *= 2;
     cp->parts = parts;
     cp->parts_log2 = __builtin_ctz(parts);
+    cp->share_log2 = 0;
+    while ((2 << cp->share_log2) * L <= kWave && 2 << cp->share_log2 <= parts)
+        ++cp->share_log2;
     cp->per_part = ((S + parts - 1) / parts + 3) / 4 * 4;
     cp->pad = parts * cp->per_part - S;
     if (cp->per_part > 128)
@@ -2397,7 +2400,16 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
     cp->record = (int)(table - 2 * sizeof(float) * (size_t)cp->window);
     const long long part = (long long)L * S * (B / kWave + 1) / 16;
     cp->work = part < kCoreWork ? kCoreWork : (part < INT32_MAX / 2 ? (int)part : INT32_MAX / 2);
-    *lds = (int)(table + lists);
+    size_t all = table + lists;
+    // as many entries again where that does not change how many workgroups share a compute unit (deep networks
+    // have candidates with five a layer)
+    const size_t more = all + room * sizeof(CoreEntry);
+    auto per_unit = [](size_t bytes) { return 160 * 1024 / align_up(bytes + kCoreStatic, 1280); };
+    if (cp->entries == room && more <= (size_t)kLdsBytes && per_unit(more) == per_unit(all)) {
+        cp->entries += room;
+        all = more;
+    }
+    *lds = (int)all;
     return true;
 }
 
