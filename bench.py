@@ -45,7 +45,7 @@ LANE_OPS_AS_BUILT = {"valu_add_add_min3": 1.5, "valu_add_cmp_sel_min": 4.0,
 LEVEL_PAIRS_FROM = 14            # kPairsFrom of csrc/spdy_dp.hip
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
-                  for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h")]
+                  for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h", "dp_small.h")]
 PROBE = os.path.join(ROOT, "paper_2201_13096_amd", "peaks_probe")
 
 

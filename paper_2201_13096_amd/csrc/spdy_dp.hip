@@ -1510,6 +1510,8 @@ __device__ __forceinline__ void write_result(float bv, int bt, int k, int32_t *t
     tstar[k] = (bv < __builtin_inff()) ? bt : -1;   // -1: no profile meets the budget
 }
 
+#include "dp_small.h"
+
 // ---------------------------------------------------------------------------------------------
 // Walk back through the D record: one wave per candidate.  At (l, t) the lanes try the levels in parallel: lane s
 // forms D_{l-1}[t - shift_s] + err[l][s] with the same single fp32 add as the fill and compares
@@ -2436,6 +2438,31 @@ bool table_is_short(int K, int L, int S, int B, bool one_fill)
     return one_fill && K >= 8 && L <= 9 && L * S <= 300 && updates * ((K + 255LL) / 256) <= 4000000;
 }
 
+// Whether dp_small takes the call: a candidate's tables, rows and levels fit LDS, every candidate has a
+// compute unit, and the whole takes less than 16 us by what was measured, 6 us and for every level of every
+// layer 0.06 us, 0.08 more per 1000 buckets from 512 on.  Anything else takes 20 us and more.  K = 1 and 200,
+// us a call with and without: L = S = 8, B = 256: 9.4 and 20.3, 9.7 and 24.2; L = S = 8, B = 1000: 12.7 and 21.1;
+// beyond the line L = 8, S = 16, B = 1000: 18.9 and 22.5; L = S = 16, B = 256: 22.0 and 24.1; L = 8, S = 40,
+// B = 1000: 36.7 and 26.2.
+bool small_call(int K, int L, int S, int B)
+{
+    DeviceState dev;
+    const long long beyond = B > 512 ? B - 512 : 0;
+    return S <= kWave && L <= 256 && B < 1 << 16 && (long long)L * S * (60000 + 80 * beyond) <= 10000000 &&
+           small_lds(L, S, B) <= (size_t)kSmallLds && device_state(false, &dev) == SPDY_DP_OK &&
+           K <= dev.units;
+}
+
+int launch_small(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int16_t *profile,
+                 float *cost, int32_t *tstar, int32_t *has_table, hipStream_t q)
+{
+    (void)hipGetLastError();
+    const int threads = small_row(B) < 256 ? 256 : (small_row(B) < kSmallThreads ? small_row(B) : kSmallThreads);
+    hipLaunchKernelGGL(dp_small, dim3(K), dim3(threads), small_lds(L, S, B), q, tau, src, L, S, B,
+                       profile, cost, tstar, has_table);
+    return launch_status();
+}
+
 // Sets up the call for the J budgets, the largest of which `lay` is for; false: the full table at
 // once.  `one_fill`: all that the full table would take is one fill and one walk back.
 bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, int J, bool one_fill,
@@ -2787,13 +2814,31 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     return launch_status();
 }
 
-// `scratch`: nobody looks at the workspace afterwards, so the table need not be in it.
+// What becomes of the workspace of a call.
+enum class Use {
+    kTable,         // the caller looks at the table
+    kScratch,       // nobody does, so the table need not be there; (a short one is: calls may resume from it)
+    kUnseen         // the same, and nothing resumes from it
+};
 int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int16_t *profile,
-               float *cost, void *workspace, size_t workspace_bytes, void *stream, bool scratch,
+               float *cost, void *workspace, size_t workspace_bytes, void *stream, Use use,
                Resume resume = Resume{})
 {
     if (!tau || !profile || !cost)
         return SPDY_DP_ERR_NULL;
+    const bool scratch = use != Use::kTable;
+    if (use == Use::kUnseen) {
+        const Layout lay = make_layout(K, L, S, B, workspace_bytes);
+        const int ok = validate(lay, workspace);
+        if (ok != SPDY_DP_OK)
+            return ok;
+        char *ws = static_cast<char *>(workspace);
+        if (small_call(K, L, S, B))
+            return launch_small(tau, src, K, L, S, B, profile, cost,
+                                reinterpret_cast<int32_t *>(ws + lay.tstar_off),
+                                reinterpret_cast<int32_t *>(ws + lay.meta_off) + kMetaTable,
+                                static_cast<hipStream_t>(stream));
+    }
     CoreCall core;
     Todo todo;
     if (scratch && core_call(make_layout(K, L, S, B, workspace_bytes), K, L, S, &B, 1,
@@ -2967,8 +3012,8 @@ int resume_impl(const int32_t *tau, ErrSource src, const int32_t *first_layer, i
         reinterpret_cast<const float *>(static_cast<const char *>(incumbent) + inc.record_off);
     resume.inc_meta =
         reinterpret_cast<const int32_t *>(static_cast<const char *>(incumbent) + inc.meta_off);
-    return solve_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream, true,
-                      resume);
+    return solve_impl(tau, src, K, L, S, B, profile, cost, workspace, workspace_bytes, stream,
+                      Use::kScratch, resume);
 }
 
 }  // namespace
@@ -3031,7 +3076,7 @@ int spdy_dp_solve_batched(const int32_t *tau, const float *err, int K, int L, in
     if (!err)
         return SPDY_DP_ERR_NULL;
     return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost, workspace,
-                      workspace_bytes, stream, false);
+                      workspace_bytes, stream, Use::kTable);
 }
 
 int spdy_dp_solve_profiles(const int32_t *tau, const float *err, int K, int L, int S, int B,
@@ -3041,7 +3086,7 @@ int spdy_dp_solve_profiles(const int32_t *tau, const float *err, int K, int L, i
     if (!err)
         return SPDY_DP_ERR_NULL;
     return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost, workspace,
-                      workspace_bytes, stream, true);
+                      workspace_bytes, stream, K > 1 ? Use::kUnseen : Use::kScratch);
 }
 
 int spdy_dp_solve_batched_static(const int32_t *tau, const float *err, int K, int L, int S, int B,
@@ -3060,7 +3105,7 @@ int spdy_dp_solve_batched_static(const int32_t *tau, const float *err, int K, in
     if (st != SPDY_DP_OK)
         return st;
     return solve_impl(tau, ErrSource{err, nullptr, nullptr}, K, L, S, B, profile, cost,
-                      dev.scratch, SPDY_DP_STATIC_WORKSPACE_BYTES, stream, true);
+                      dev.scratch, SPDY_DP_STATIC_WORKSPACE_BYTES, stream, Use::kUnseen);
 }
 
 int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float *w, int K, int L,
@@ -3070,7 +3115,7 @@ int spdy_dp_solve_sensitivities(const int32_t *tau, const float *c, const float 
     if (!c || !w)
         return SPDY_DP_ERR_NULL;
     return solve_impl(tau, ErrSource{nullptr, c, w}, K, L, S, B, profile, cost, workspace,
-                      workspace_bytes, stream, true);
+                      workspace_bytes, stream, Use::kScratch);
 }
 
 int spdy_dp_solve_budgets(const int32_t *tau, const float *err, int K, int L, int S,
