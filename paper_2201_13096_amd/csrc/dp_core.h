@@ -24,15 +24,16 @@
 // a negative time, sums near the end of the fp32 range, more surviving levels, rows wider than both LDS
 // and memory hold, or more work than the limits of the launch.
 //
-// What bounds it: latency.  A candidate of L = 54, S = 40 is about 11 passes over its table in LDS for
-// the multiplier (2300 clocks each: a scan of twelve levels per thread, two joins, a barrier),
-// five of 2900 for the known profile, then dependent steps for the reduced table, 15 usually, 20 to 45 for
-// the slowest candidates and some of those twice (2000 clocks each and 500 for each step back before the rows
-// of one chunk stayed in a register); one wave per SIMD issues an instruction every seven or eight clocks whatever
-// it is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Kernel time
-// against fill and walk back of the whole table: K = 100, L = 52, S = 42, B = 10^4: 73 us / 297 us;
-// K = 4096, L = 72, S = 40, B = 16384: 303 us / 3.34 ms; K = 333, S = 127: 104 us / 0.92 ms;
-// K = 256, L = 200, S = 64, B = 65536: 0.37 / 4.2 ms.
+// What bounds it: latency; one wave per SIMD issues an instruction every seven or eight clocks whatever it
+// is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Thousands of clocks of a
+// candidate by its own stamps, mean of 250 of L = 52, S = 42 (in all 64, the slowest 98): tables 5, the
+// two ends 2, multiplier 15 (five passes over the table in LDS, each with four multipliers), known profile
+// 13 (single exchanges, then pairs of them), survivors 7, then dependent steps for the reduced table 16
+// (nine of them, 20 to 45 for the slowest candidates), walk back 5.
+// us a call, by whole solves; before four multipliers a pass and the pairs, and now: K = 250 from an
+// incumbent: 72 and 51; K = 100, L = 52, S = 42, B = 10^4: 119 and 88 (mean of twelve seeds); K = 4096, L = 72,
+// S = 40, B = 16384: 292 and 245; K = 333, S = 127: 102 and 91; K = 256, L = 200, S = 64, B = 65536: 381
+// and 280.  The whole table takes 297, 3340, 920 and 4200.
 
 constexpr int16_t kGivenUp = -3;         // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
@@ -345,26 +346,32 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 sh.change[turn][wave].x = __builtin_bit_cast(int, lam);
             }
             __syncthreads();
-            const int t_chord = uniform(__builtin_bit_cast(int, sh.sum[turn][0].y));
+            // lane w holds what wave w found: of the paths that meet the budget the slowest, of the others the
+            // fastest, where these are nearer than the ones known
+            static_assert(kCoreWaves == 4, "a quad of lanes");
+            const float2 sum_w = sh.sum[turn][lane & 3];
+            const float lam_w = __builtin_bit_cast(float, sh.change[turn][lane & 3].x);
+            const int t_w = __builtin_bit_cast(int, sum_w.y);
+            const int t_chord = __builtin_amdgcn_readfirstlane(t_w);
             if (!(t_chord > t_hi && t_chord < t_lo))
                 break;
+            static_assert(kCoreMaxLayers * (long long)kCoreMaxBudget <= 1 << 30, "a time and a wave share a word");
+            const unsigned time_wave = min((unsigned)t_w, (1u << 30) - 1) << 2 | (lane & 3);
+            const unsigned under = t_w <= B ? time_wave : 0u, over = t_w <= B ? ~0u : time_wave;
+            const unsigned best_hi = uniform(group_join(under, 4, Larger{}));
+            const unsigned best_lo = uniform(group_join(over, 4, Smaller{}));
             int hi_wave = -1, lo_wave = -1;
-#pragma unroll
-            for (int w = 0; w < kCoreWaves; ++w) {
-                const float cw = uniform(sh.sum[turn][w].x);
-                const int tw = uniform(__builtin_bit_cast(int, sh.sum[turn][w].y));
-                const float lw = uniform(__builtin_bit_cast(float, sh.change[turn][w].x));
-                if (tw <= B) {
-                    lam_hi = fminf(lam_hi, lw);
-                    hi_wave = tw > t_hi ? w : hi_wave;
-                    c_hi = tw > t_hi ? cw : c_hi;
-                    t_hi = tw > t_hi ? tw : t_hi;
-                } else {
-                    lam_lo = fmaxf(lam_lo, lw);
-                    lo_wave = tw < t_lo ? w : lo_wave;
-                    c_lo = tw < t_lo ? cw : c_lo;
-                    t_lo = tw < t_lo ? tw : t_lo;
-                }
+            if (best_hi >> 2 > (unsigned)t_hi) {
+                hi_wave = best_hi & 3;
+                t_hi = __builtin_amdgcn_readlane(t_w, hi_wave);
+                c_hi = lane_value(sum_w.x, hi_wave);
+                lam_hi = lane_value(lam_w, hi_wave);
+            }
+            if ((best_lo >> 2) < (unsigned)t_lo) {
+                lo_wave = best_lo & 3;
+                t_lo = __builtin_amdgcn_readlane(t_w, lo_wave);
+                c_lo = lane_value(sum_w.x, lo_wave);
+                lam_lo = lane_value(lam_w, lo_wave);
             }
             turn ^= 1;
 #pragma unroll

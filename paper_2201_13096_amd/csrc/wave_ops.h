@@ -81,17 +81,25 @@ struct Smaller {
 // are uniform by then, so mirrors serve where no exchange of lanes at that distance exists.
 template <class T, class Op> __device__ __forceinline__ T group_join(T v, int parts, Op op)
 {
-    if (parts > 1)
-        v = op(v, dpp_from<0xB1, 0xf>(v, v));     // quad_perm 1 0 3 2
-    if (parts > 2)
-        v = op(v, dpp_from<0x4E, 0xf>(v, v));     // quad_perm 2 3 0 1
-    if (parts > 4)
-        v = op(v, dpp_from<0x141, 0xf>(v, v));    // row_half_mirror
-    if (parts > 8)
-        v = op(v, dpp_from<0x140, 0xf>(v, v));    // row_mirror
-    if (parts > 16)
-        v = op(v, __shfl_xor(v, 16, kWave));
-    if (parts > 32)
-        v = op(v, __shfl_xor(v, 32, kWave));
-    return v;
+    // (read here, or the compiler keeps the conditions as lane masks and turns them into branches again at
+    // every call, four instructions each)
+    const int p = __builtin_amdgcn_readfirstlane(parts);
+    if (p == 1)
+        return v;
+    v = op(v, dpp_from<0xB1, 0xf>(v, v));         // quad_perm 1 0 3 2
+    if (p == 2)
+        return v;
+    v = op(v, dpp_from<0x4E, 0xf>(v, v));         // quad_perm 2 3 0 1
+    if (p == 4)
+        return v;
+    v = op(v, dpp_from<0x141, 0xf>(v, v));        // row_half_mirror
+    if (p == 8)
+        return v;
+    v = op(v, dpp_from<0x140, 0xf>(v, v));        // row_mirror
+    if (p == 16)
+        return v;
+    v = op(v, __shfl_xor(v, 16, kWave));
+    if (p == 32)
+        return v;
+    return op(v, __shfl_xor(v, 32, kWave));
 }
