@@ -17,15 +17,14 @@
 //   * the time axis is cut into chunks of 64 buckets; a wave keeps a group of R chunks in
 //     registers (running minimum, and the level when tracked) and sweeps the layer once; lane i
 //     holds the i-th entry of the layer (a level, or with the D record all levels of one shift,
-//     which one update serves), ballots find the applicable entries and v_readlane moves shift
-//     and error to scalar registers, so the sweep issues no memory instruction besides the LDS
-//     reads;
+//     which one update serves) and ballots find the applicable entries, whose shifts and errors
+//     v_readlane moves to scalar registers or, below, come from LDS two entries at a time;
 //   * when D itself is recorded and a layer has at most 64 levels, a lane takes four consecutive
 //     buckets and reads them with one aligned ds_read_b128 (twice the LDS bytes per clock of
-//     narrower reads on this chip); the words a shift that is not a multiple of four needs from
-//     the quad below come from the lane to the left through a DPP operand of the add.  Otherwise
-//     lane i works on bucket 64*c + i of a chunk: every ds_read_b32 of the shifted row touches
-//     64 consecutive dwords (conflict-free for any shift);
+//     narrower reads on this chip); entries are visited by their shift modulo four, and the minima
+//     are kept shifted by that, so that no add needs a word from another lane (sweep_layer).
+//     Otherwise lane i works on bucket 64*c + i of a chunk: every ds_read_b32 of the shifted row
+//     touches 64 consecutive dwords (conflict-free for any shift);
 //   * the waves of a workgroup are split at run time into teams, one candidate per team, so
 //     that each wave owns as many chunks as its registers hold whatever the reduced row length
 //     is; when every wave holds all its chunks of the row in registers the row is updated in
@@ -1110,12 +1109,11 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
 //   * the first 252 Q buckets of a wave's group are Q "quad chunks": lane i >= 1 owns buckets
 //     252 j + 4 (i - 1) .. + 3 of quad chunk j, and one read gives it the four values
 //     row[4 q .. 4 q + 3] of the aligned quad q = (its own quad) - (shift / 4);
-//   * a shift that is not a multiple of four needs the last (shift mod 4) values of the quad
-//     below, which is exactly what the lane to the left has read: they come over with the add
-//     itself (DPP wave_shr:1).  Lane 0 has no bucket of its own: it reads the quad below lane
-//     1's and only serves as that left neighbour (63 of 64 lanes work);
-//   * the residue decides which operands cross lanes, so the entries of a layer are visited by
-//     residue (the prepare kernel orders them that way) and each residue has its own code;
+//   * for a shift that is not a multiple of four these are the values of four buckets that begin
+//     (shift mod 4) further on: the entries of a layer are visited by that residue (the prepare
+//     kernel orders them), and the minima move by a bucket from one to the next (sweep_layer).
+//     Lane 0 has no bucket of its own: it reads the quad below lane 1's and only serves as left
+//     neighbour of that move (63 of 64 lanes work);
 //   * the remaining buckets of the group, fewer than 252, are covered by T ordinary chunks of 64
 //     (32-bit reads, lane = bucket) placed at the END of the group; they may overlap the quad
 //     chunks by up to 63 buckets, which are then computed twice with the same result.
@@ -2198,6 +2196,225 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
                                             profile, cost, resume);
 }
 
+// ---------------------------------------------------------------------------------------
+// The walk of a candidate that has a compute unit to itself: one workgroup.  A wave that gathers its
+// levels' entries of the row below waits for memory once per layer, 0.63 us, because where it reads next
+// follows from what it read.  Which part of the rows below it can come to is known ahead, though: i layers
+// below time t, [t - the largest shifts of those layers, t - the smallest].  So a block of up to
+// kLoneBlock layers is taken at a time, as many as have all their windows in LDS: every wave copies its
+// share of them (memory to LDS, 256 floats an instruction, all in flight at once), then wave 0 walks
+// through LDS, about 0.12 us a layer, while the other waves fetch the levels of the next block.  Windows
+// grow by one layer's shifts from row to row; with few to a block a copy costs what it saves, and the
+// rows are read entry by entry as before (kLoneLeast).
+// us a walk, launch included, one wave by itself and so: K = 1, L = 54, S = 40, B = 10^4 (12 layers a block)
+// 33.2 and 21.0, B = 10^5 (windows too wide, entry by entry) 41.5 and 36.6; L = 17, S = 200, B = 10^4 22.6 and
+// 14.4; L = 400, S = 2 215 and 101; L = 10, S = 8, B = 1000 11.8 and 11.5.  About 0.15 us a layer is a copy's
+// share of the time, the rest instructions of wave 0 one after the other: a step that read a window's place and
+// bounds from several tables, with branches around what is out of bounds, took 0.28 us (28.6 us a walk).
+// ---------------------------------------------------------------------------------------
+constexpr int kLoneWaves = 16;
+constexpr int kLoneBlock = kLoneWaves - 1;      // layers of a block: waves 1 to 15 fetch one's levels each
+constexpr int kLoneLeast = 4;                   // fewest layers that are copied for
+constexpr int kPiece = 4 * kWave;               // floats of one copy
+constexpr int kFarShift = 1 << 27;              // bound of a shift in a window's sums: farther than any that fits
+template <int kLevelBlocks> constexpr int kLonePieces = kLevelBlocks == 1 ? 140 : 92;
+
+template <int kLevelBlocks>
+struct LoneShared {
+    __attribute__((aligned(16))) float window[kLonePieces<kLevelBlocks> * kPiece + 4];   // and row -1's -0
+    // What wave 0 needs at layer top - i for a level, in one read.  Where windows are copied: x, what to take
+    // from its place in the window above (from the time, for i = 0) for the place in this one; y, the error;
+    // z, the floats of the window; w, where it begins.  Otherwise x is the shift and z the row's end.  z = 0
+    // past S.  (Row kLoneBlock: read ahead and not used.)
+    int4 step[kLoneBlock + 1][kLevelBlocks * kWave];
+    int lowest[kLoneBlock], highest[kLoneBlock];         // shifts of layer top - i
+    int reach[kLoneBlock];
+    int t;
+    float target;
+};
+static_assert(sizeof(LoneShared<1>) <= 160 * 1024 && sizeof(LoneShared<4>) <= 160 * 1024, "LDS");
+
+template <int kLevelBlocks, bool kByItself>
+__global__ __launch_bounds__(kLoneWaves * kWave) void dp_backtrace_alone(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
+    int pitch, int16_t *__restrict__ profile, float *cost, Resume resume)
+{
+    constexpr int kMost = kLonePieces<kLevelBlocks>;
+    __shared__ LoneShared<kLevelBlocks> sh;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int solve = blockIdx.x, k = budgets > 1 ? solve % K : solve;
+    int16_t *prof = profile + (size_t)solve * L;
+    const ErrSource mine = src.of_candidate(k, L, S);
+    const float *drec_k = drec + (size_t)k * L * pitch;
+    const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
+    auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
+
+    // wave 1 + i holds the levels of layer top - i
+    LayerLevels<kLevelBlocks> levels{};
+    auto fetch = [&](int top) {
+        const int i = wave - 1;
+        if (i < 0 || i > top)
+            return;
+        levels = load_layer<kLevelBlocks>(tau, mine.layer(top - i, S), meta, top - i, L, S, lane);
+        int low = INT32_MAX, high = INT32_MIN;
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks; ++b) {
+            low = min(low, levels.shift[b]);     // (INT32_MAX past S)
+            high = max(high, b * kWave + lane < S ? levels.shift[b] : INT32_MIN);
+        }
+        low = wave_scan(low, INT32_MAX, Smaller{});
+        high = wave_scan(high, INT32_MIN, Larger{});
+        if (lane == kWave - 1) {
+            sh.lowest[i] = min(max(low, -kFarShift), kFarShift);
+            sh.highest[i] = min(max(high, -kFarShift), kFarShift);
+            sh.reach[i] = levels.reach;
+        }
+    };
+
+    int t = kByItself && !meta[kMetaTable] ? -2 : tstar[solve];
+    t = __builtin_amdgcn_readfirstlane(t);
+    float target = t >= 0 ? row_of(L - 1)[t] : 0.0f;
+    fetch(L - 1);
+    if (threadIdx.x == 0)
+        sh.window[kMost * kPiece] = -0.0f;
+    __syncthreads();             // tstar may be the words of the costs: every wave has read its own
+    if (t < 0) {
+        for (int l = threadIdx.x; l < L; l += kLoneWaves * kWave)
+            prof[l] = t == -1 ? -1 : -2;         // -1: no profile meets the budget
+        if (threadIdx.x == 0)
+            cost[solve] = t == -1 ? __builtin_inff() : __builtin_nanf("");
+        return;
+    }
+
+    for (int top = L - 1; top >= 0;) {
+        // lane i plans the window of the row below layer top - i, in pieces
+        const bool here = lane < kLoneBlock && lane <= top, rows = here && lane < top;
+        const int i = min(lane, kLoneBlock - 1);
+        const int reach = here ? sh.reach[i] : 0;
+        const int low = wave_scan(here ? sh.lowest[i] : 0, 0, Add{});
+        const int high = wave_scan(here ? sh.highest[i] : 0, 0, Add{});
+        const int from = rows && t > high ? (t - max(high, 0)) & ~3 : 0;
+        const int last = min(t - low, reach - 1);
+        const int pieces = rows && last >= from ? min((last - from) / kPiece, kMost) + 1 : 0;
+        const int ends = wave_scan(pieces, 0, Add{});
+        const int held = __popcll(__ballot(here && ends <= kMost));
+        const bool copied = held >= min(kLoneLeast, top + 1);
+        const int n = copied ? held : min(kLoneBlock, top + 1);
+        const int begin = rows ? (ends - pieces) * kPiece : kMost * kPiece;
+        const int width = rows ? max(min(pieces * kPiece, reach - from), 0) : min(reach, 1);
+        if (copied) {
+            // the first of the row's floats that are copied; and their end, a whole number of fours
+            const float *start = row_of(rows ? top - 1 - lane : 0) + from;
+            const int start_lo = (int)reinterpret_cast<uintptr_t>(start);
+            const int start_hi = (int)(reinterpret_cast<uintptr_t>(start) >> 32);
+            const int all = __builtin_amdgcn_readlane(ends, n - 1);
+            for (int p = wave; p < all; p += kLoneWaves) {
+                const int r = __popcll(__ballot(lane < n && ends <= p));     // the row of piece p
+                const int u = p * kPiece - __builtin_amdgcn_readlane(begin, r) + 4 * lane;
+                const uintptr_t at = (uintptr_t)(unsigned)__builtin_amdgcn_readlane(start_hi, r) << 32 |
+                                     (unsigned)__builtin_amdgcn_readlane(start_lo, r);
+                if (u < __builtin_amdgcn_readlane(width, r))
+                    __builtin_amdgcn_global_load_lds(
+                        (const __attribute__((address_space(1))) void *)(
+                            reinterpret_cast<const float *>(at) + u),
+                        (__attribute__((address_space(3))) void *)(sh.window + p * kPiece), 16, 0, 0);
+            }
+        }
+        if (wave > 0) {
+            const int r = wave - 1, above = r > 0 ? __builtin_amdgcn_readlane(from, max(r - 1, 0)) : 0;
+            const int by = copied ? __builtin_amdgcn_readlane(from, r) - above : 0;
+            const int z = __builtin_amdgcn_readlane(copied ? width : reach, r);
+            const int w = __builtin_amdgcn_readlane(begin, r);
+#pragma unroll
+            for (int b = 0; b < kLevelBlocks; ++b)
+                sh.step[r][b * kWave + lane] =
+                    int4{(int)((unsigned)levels.shift[b] + by), __float_as_int(levels.err[b]),
+                         b * kWave + lane < S ? z : 0, w};
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (wave > 0) {
+            fetch(top - n);
+        } else {
+            int at = t, found_of = -1;           // lane r: the level of layer top - r
+            bool damaged = false;
+            auto steps = [&](auto entry) __attribute__((always_inline)) {
+                int4 next[kLevelBlocks];
+#pragma unroll
+                for (int b = 0; b < kLevelBlocks; ++b)
+                    next[b] = sh.step[0][b * kWave + lane];
+                for (int r = 0; r < n; ++r) {
+                    unsigned u[kLevelBlocks];
+                    float pv[kLevelBlocks], err[kLevelBlocks];
+                    bool valid[kLevelBlocks];
+#pragma unroll
+                    for (int b = 0; b < kLevelBlocks; ++b) {
+                        u[b] = (unsigned)at - (unsigned)next[b].x;
+                        valid[b] = u[b] < (unsigned)next[b].z;
+                        pv[b] = entry(r, u[b], valid[b], next[b]);
+                        err[b] = __int_as_float(next[b].y);
+                    }
+#pragma unroll
+                    for (int b = 0; b < kLevelBlocks; ++b)
+                        next[b] = sh.step[r + 1][b * kWave + lane];
+                    int found = -1, to = 0;
+                    float value = 0.0f;
+#pragma unroll
+                    for (int b = kLevelBlocks - 1; b >= 0; --b) {
+                        const unsigned long long mask = __ballot(valid[b] && pv[b] + err[b] == target);
+                        if (mask) {              // (the lowest level there is)
+                            const int first = __builtin_ctzll(mask);
+                            found = b * kWave + first;
+                            to = __builtin_amdgcn_readlane((int)u[b], first);
+                            value = lane_value(pv[b], first);
+                        }
+                    }
+                    damaged = found < 0;         // (cannot happen on a filled record)
+                    if (damaged)
+                        return;
+                    found_of = lane == r ? found : found_of;
+                    at = to;
+                    target = value;
+                }
+            };
+            if (copied)
+                steps([&](int, unsigned u, bool, int4 s) __attribute__((always_inline)) {
+                    return sh.window[(unsigned)s.w + min(u, (unsigned)s.z)];
+                });
+            else
+                steps([&](int r, unsigned u, bool valid, int4) __attribute__((always_inline)) {
+                    const float *row = row_of(max(top - r - 1, 0));
+                    return top == r ? -0.0f
+                           : valid ? __builtin_nontemporal_load(&row[u]) : __builtin_inff();
+                });
+            if (lane < n)
+                prof[top - lane] = (int16_t)found_of;
+            if (lane == 0) {
+                sh.t = damaged ? -2 : at + (copied ? __builtin_amdgcn_readlane(from, n - 1) : 0);
+                sh.target = target;
+            }
+        }
+        __syncthreads();
+        t = __builtin_amdgcn_readfirstlane(sh.t);
+        target = sh.target;
+        if (t == -2) {
+            for (int l = lane; wave == 0 && l < L; l += kWave)
+                prof[l] = -2;
+            if (threadIdx.x == 0)
+                cost[solve] = __builtin_nanf("");
+            return;
+        }
+        top -= n;
+    }
+    if (wave > 0)
+        return;
+    const float acc = profile_cost(mine, L, S, prof);
+    if (lane == 0)
+        cost[solve] = acc;
+}
+
 // The walk through one block of layers [blocks.begin, blocks.end) of the small-record solve: rows
 // come from the block record, the row below the block from its checkpoint; tstar holds the time
 // to start from and receives the time below the block; the cost is summed after the first block
@@ -2776,8 +2993,21 @@ int fill_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, flo
 void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const float *drec,
                  const int32_t *tstar, int K, int budgets, int L, int S, int pitch,
                  int16_t *profile, float *cost, Resume resume, Todo todo, bool by_itself,
-                 hipStream_t q)
+                 int units, hipStream_t q)
 {
+    // A unit to every candidate, whose LDS the windows take: us a walk in this rule's two ways, L = 54, S = 40,
+    // B = 10^4: K = 1 33.2 and 21.0, K = 128 35.9 and 25.1, K = 256 47.4 and 32.3; beyond, workgroups would
+    // queue for units.  (Behind dp_core hardly any candidate is left to walk.  Copies are of 16 bytes: a record
+    // that does not lie so is walked entry by entry.)
+    auto whole = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+    if (!todo.profile && K * (long long)budgets <= units && whole(drec) && whole(resume.inc_rec)) {
+        auto alone = S <= kWave ? dp_backtrace_alone<1, false> : dp_backtrace_alone<4, false>;
+        if (by_itself)
+            alone = S <= kWave ? dp_backtrace_alone<1, true> : dp_backtrace_alone<4, true>;
+        hipLaunchKernelGGL(alone, dim3(K * budgets), dim3(kLoneWaves * kWave), 0, q, tau, src, meta,
+                           drec, tstar, K, budgets, L, S, pitch, profile, cost, resume);
+        return;
+    }
     const int per_block = kWalkThreads / kWave;
     auto walk = S <= kWave ? dp_backtrace_values<1, false> : dp_backtrace_values<4, false>;
     if (by_itself)
@@ -2808,8 +3038,12 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
                            tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
+        DeviceState dev;
+        const int ok = device_state(false, &dev);
+        if (ok != SPDY_DP_OK)
+            return ok;
         launch_walk(tau, src, meta, reinterpret_cast<const float *>(ws + lay.record_off), tstar, K,
-                    1, L, S, (int)lay.row, profile, cost, resume, todo, by_itself, q);
+                    1, L, S, (int)lay.row, profile, cost, resume, todo, by_itself, dev.units, q);
     }
     return launch_status();
 }
@@ -2961,6 +3195,10 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
                                    workspace_bytes, &core);
     if (reduced)
         todo = Todo{profile, 1};
+    DeviceState dev;
+    st = device_state(false, &dev);
+    if (st != SPDY_DP_OK)
+        return st;
     // one fill for the largest budget; its own costs are not used, and behind the reduced problem
     // they are not written (cost[0..K) holds what that found under the first budget)
     st = fill_impl(tau, src, K, L, S, bmax, reduced ? nullptr : cost, workspace, workspace_bytes,
@@ -2982,7 +3220,7 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
         hipLaunchKernelGGL(dp_budget_argmin, dim3(K * n), dim3(256), 0, q, meta, drec, K, L,
                            (int)lay.row, some, reinterpret_cast<int32_t *>(c), todo);
         launch_walk(tau, src, meta, drec, reinterpret_cast<const int32_t *>(c), K, n, L, S,
-                    (int)lay.row, prof, c, Resume{}, todo, false, q);
+                    (int)lay.row, prof, c, Resume{}, todo, false, dev.units, q);
     }
     return launch_status();
 }

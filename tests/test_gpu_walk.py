@@ -1,0 +1,110 @@
+"""The walk of a candidate that has a compute unit to itself (csrc/spdy_dp.hip, dp_backtrace_alone): blocks of
+one to 15 layers, windows cut at bucket 0 and at the end of a row, shifts too wide for windows, several words of
+levels, one candidate more than there are units, rows of an incumbent below, and a table that is not there."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from test_gpu_parity import assert_same
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dp():
+    import paper_2201_13096_amd as m
+    return m
+
+
+def instance(rng, K, L, S, B, widest):
+    tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=widest,
+                                            integer_err=int(rng.choice([0, 3])) or None,
+                                            inf_err_frac=0.05, over_budget_frac=0.05)
+    tau[L // 2] = np.minimum(tau[L // 2], 3)                 # rows of very different windows
+    tau[:, 0] = np.minimum(tau[:, 0], B // (2 * L))          # mostly feasible
+    return tau, err
+
+
+@pytest.mark.parametrize("L, S, B, widest", [
+    (1, 1, 0, 1), (1, 64, 300, 300), (2, 3, 65, 40), (4, 64, 63, 63), (5, 65, 1000, 400), (15, 64, 9000, 700),
+    (16, 64, 9001, 700), (17, 200, 9000, 700), (54, 40, 10000, 370), (40, 255, 3000, 90), (200, 2, 4000, 21),
+    (9, 20, 60000, 30000), (9, 70, 60000, 9000), (33, 16, 40000, 5000), (6, 8, 100000, 99000)])
+def test_walks(dp, L, S, B, widest):
+    rng = np.random.default_rng(L * 300 + S)
+    for K in (1, 3):
+        tau, err = instance(rng, K, L, S, B, widest)
+        err[K // 2, L // 2] = np.inf if K > 1 else err[0, L // 2]      # one candidate is not feasible
+        print(f"[walk] K={K} L={L} S={S} B={B} widest={widest}", flush=True)
+        tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+        want = oracle.solve_ref(tau, err, B)
+        ws = dp.alloc_workspace(K, L, S, B)
+        p, c = dp.spdy_dp_solve_batched(tau_d, err_d, B, workspace=ws)
+        assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"L={L} S={S} B={B}")
+        p.fill_(7)
+        dp.spdy_dp_backtrace(tau_d, err_d, B, p, c, ws)
+        assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"again L={L} S={S} B={B}")
+        if K > 1:
+            first = torch.from_numpy(np.array([0, L // 3, L], dtype=np.int32)).cuda()
+            inc = dp.alloc_workspace(1, L, S, B)
+            dp.spdy_dp_solve_batched(tau_d, err_d[:1].contiguous(), B, workspace=inc)
+            err[1, :L // 3] = err[0, :L // 3]
+            err[2] = err[0]
+            p, c = dp.spdy_dp_solve_from_incumbent(tau_d, torch.from_numpy(err).cuda(), first, B, inc)
+            assert_same(p.cpu().numpy(), c.cpu().numpy(), *oracle.solve_ref(tau, err, B),
+                        f"resumed L={L} S={S} B={B}")
+
+
+@pytest.mark.parametrize("K, J", [(256, 1), (257, 1), (128, 2), (43, 6)])
+def test_as_many_as_units(dp, K, J):
+    rng = np.random.default_rng(K)
+    L, S, B = 18, 20, 700
+    tau, err = instance(rng, K, L, S, B, 90)
+    budgets = [B - 37 * j for j in range(J)]
+    print(f"[walk] K={K} budgets={J}", flush=True)
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+    ws = dp.alloc_workspace(K, L, S, B)
+    if J == 1:
+        p, c = dp.spdy_dp_solve_batched(tau_d, err_d, B, workspace=ws)
+        p, c = p[None], c[None]
+    else:
+        p, c = dp.spdy_dp_solve_budgets(tau_d, err_d, budgets, workspace=ws)
+    for j, b in enumerate(budgets):
+        assert_same(p[j].cpu().numpy(), c[j].cpu().numpy(), *oracle.solve_ref(tau, err, b), f"B={b}")
+
+
+def test_no_table(dp):
+    rng = np.random.default_rng(5)
+    K, L, S, B = 2, 20, 8, 3000
+    tau, err = instance(rng, K, L, S, B, 500)
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+    ws = dp.alloc_workspace(K, L, S, B)
+    dp.spdy_dp_solve_profiles(tau_d, err_d, B, workspace=ws)           # leaves none
+    profile = torch.full((K, L), 7, dtype=torch.int16, device="cuda")
+    cost = torch.full((K,), 7.0, dtype=torch.float32, device="cuda")
+    dp.spdy_dp_backtrace(tau_d, err_d, B, profile, cost, ws)
+    assert (profile == -2).all() and torch.isnan(cost).all()
+
+
+def test_replays_from_a_graph(dp):
+    rng = np.random.default_rng(6)
+    K, L, S, B = 1, 30, 16, 6000
+    tau, err = instance(rng, K, L, S, B, 500)
+    other = instance(rng, K, L, S, B, 500)[1]
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+    profile = torch.empty((K, L), dtype=torch.int16, device="cuda")
+    cost = torch.empty((K,), dtype=torch.float32, device="cuda")
+    ws = dp.alloc_workspace(K, L, S, B)
+    dp.spdy_dp_solve_batched(tau_d, err_d, B, profile, cost, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dp.spdy_dp_solve_batched(tau_d, err_d, B, profile, cost, workspace=ws,
+                                 stream=torch.cuda.current_stream())
+    for now in (err, other, err, other):
+        err_d.copy_(torch.from_numpy(now))
+        profile.fill_(9)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_same(profile.cpu().numpy(), cost.cpu().numpy(), *oracle.solve_ref(tau, now, B), "replay")
