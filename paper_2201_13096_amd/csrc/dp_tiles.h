@@ -15,7 +15,7 @@
 //          few pairs ahead, so that a short sweep is neither a chain of LDS round trips nor
 //          spends its instructions on moving entries to scalar registers and sorting out residues.
 //          Two waves only store rows, two only fetch aprons: memory takes longer than a layer.
-//   long   One row in place, two barriers per layer, 128-bit reads (see sweep_residue; at most 64
+//   long   One row in place, two barriers per layer, 128-bit reads (see sweep_layer; at most 64
 //          levels): what a wave sweeps is long, and LDS is short.  The waves that are through first (a
 //          SIMD serves its oldest wave first) fetch the apron while the others sweep.
 //

@@ -171,20 +171,18 @@ __global__ __launch_bounds__(256) void lds_read(int *out, int step, int iters, i
 // LDS read and one add per entry and one v_min3.  Two layouts:
 //   sweep_b32:  lane = bucket, 16 chunks of 64 buckets per wave, 32-bit reads;
 //   sweep_b128: lane = four consecutive buckets, 4 chunks of 256 buckets per wave, one aligned
-//               128-bit read per entry; a shift that is not a multiple of four takes its last
-//               kRes values from the lane to the left with the add (DPP wave_shr:1).
+//               128-bit read per entry, whatever the shift's residue (the fill moves its minima
+//               by a bucket between residues); shifts and errors of a pair come from LDS, one read
+//               ahead.
 // Eight waves per workgroup, two workgroups per compute unit, as the fill runs.
 constexpr int kSweepRow = 8 * 16 * 64;   // floats swept per workgroup
 constexpr int kSweepHalo = 2048;         // shifts stay below this
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef int int4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void min3(float &b, float x, float y)
 {
     asm("v_min3_f32 %0, %0, %1, %2" : "+v"(b) : "v"(x), "v"(y));
-}
-__device__ __forceinline__ float from_left(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float lane_float(float v, int lane)
 {
@@ -220,11 +218,15 @@ __global__ __launch_bounds__(512, 2) void sweep_b32(float *out, const int *shift
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-template <int kRes>
 __global__ __launch_bounds__(512, 2) void sweep_b128(float *out, const int *shifts,
                                                      const float *errs, int pairs, int iters)
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
+    __shared__ __attribute__((aligned(16))) int entries[64][2];   // bytes of whole quads, error
+    if (threadIdx.x < 64) {
+        entries[threadIdx.x][0] = (shifts[threadIdx.x] >> 2) * 16;
+        entries[threadIdx.x][1] = __float_as_int(errs[threadIdx.x]);
+    }
     for (int i = threadIdx.x; i < kSweepRow + kSweepHalo; i += blockDim.x)
         row[i] = (float)(i & 1023);
     __syncthreads();
@@ -234,26 +236,25 @@ __global__ __launch_bounds__(512, 2) void sweep_b128(float *out, const int *shif
     for (int j = 0; j < 4; ++j)
         for (int c = 0; c < 4; ++c)
             best[j][c] = 1e30f;
-    const int sh = shifts[lane] >> 2;    // in quads
-    const float er = errs[lane];
-    for (int it = 0; it < iters; ++it)
-        for (int i = 0; i < 2 * pairs; i += 2) {
-            const float4v *p0 = mine - __builtin_amdgcn_readlane(sh, i);
-            const float4v *p1 = mine - __builtin_amdgcn_readlane(sh, i + 1);
-            float e0 = lane_float(er, i), e1 = lane_float(er, i + 1);
-            asm volatile("" : "+v"(e0), "+v"(e1));
+    const int4v *const pair = reinterpret_cast<const int4v *>(entries);
+    for (int it = 0; it < iters; ++it) {
+        int4v next = pair[0];
+        for (int i = 0; i < pairs; ++i) {
+            const int4v now = next;
+            next = pair[i + 1 < pairs ? i + 1 : 0];
+            const char *const at = reinterpret_cast<const char *>(mine);
+            const float4v *p0 = reinterpret_cast<const float4v *>(at - now.x);
+            const float4v *p1 = reinterpret_cast<const float4v *>(at - now.z);
+            const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float4v a = p0[j * 64], b = p1[j * 64];
-                const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float x = (c >= kRes ? av[c - kRes] : from_left(av[4 + c - kRes])) + e0;
-                    const float y = (c >= kRes ? bv[c - kRes] : from_left(bv[4 + c - kRes])) + e1;
-                    min3(best[j][c], x, y);
-                }
+                for (int c = 0; c < 4; ++c)
+                    min3(best[j][c], a[c] + e0, b[c] + e1);
             }
         }
+    }
     float s = 0;
     for (int j = 0; j < 4; ++j)
         for (int c = 0; c < 4; ++c)
@@ -357,12 +358,8 @@ int main()
             return updates / (ms * 1e-3) / clk / cus;
         };
         const double u32 = sweep(sweep_b32);
-        const double u0 = sweep(sweep_b128<0>), u1 = sweep(sweep_b128<1>);
-        const double u2 = sweep(sweep_b128<2>), u3 = sweep(sweep_b128<3>);
         printf(", \"sweep_b32\": {\"updates_per_clk_cu\": %.2f}", u32);
-        printf(", \"sweep_b128\": {\"updates_per_clk_cu\": %.2f, \"by_shift_mod_4\": [%.2f, %.2f, %.2f, "
-               "%.2f]}",
-               4.0 / (1.0 / u0 + 1.0 / u1 + 1.0 / u2 + 1.0 / u3), u0, u1, u2, u3);
+        printf(", \"sweep_b128\": {\"updates_per_clk_cu\": %.2f}", sweep(sweep_b128));
         CHECK(hipFree(sh));
         CHECK(hipFree(er));
     }
