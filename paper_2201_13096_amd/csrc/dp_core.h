@@ -26,14 +26,14 @@
 //
 // What bounds it: latency; one wave per SIMD issues an instruction every seven or eight clocks whatever it
 // is, so fewer instructions per pass and fewer passes are what counts, not bytes.  Thousands of clocks of a
-// candidate by its own stamps, mean of 250 of L = 52, S = 42 (in all 64, the slowest 98): tables 5, the
+// candidate by its own stamps, mean of 250 of L = 52, S = 42 (in all 62, the slowest 89): tables 5, the
 // two ends 2, multiplier 15 (five passes over the table in LDS, each with four multipliers), known profile
-// 13 (single exchanges, then pairs of them), survivors 7, then dependent steps for the reduced table 16
+// 13 (single exchanges, then pairs of them), survivors 7, then dependent steps for the reduced table 15
 // (nine of them, 20 to 45 for the slowest candidates), walk back 5.
-// us a call, by whole solves; before four multipliers a pass and the pairs, and now: K = 250 from an
-// incumbent: 72 and 51; K = 100, L = 52, S = 42, B = 10^4: 119 and 88 (mean of twelve seeds); K = 4096, L = 72,
-// S = 40, B = 16384: 292 and 245; K = 333, S = 127: 102 and 91; K = 256, L = 200, S = 64, B = 65536: 381
-// and 280.  The whole table takes 297, 3340, 920 and 4200.
+// us a call; before four multipliers a pass, the pairs and rows of two chunks in registers, and now: K = 250
+// from an incumbent: 71 and 45; K = 100, L = 52, S = 42, B = 10^4: 93 and 72; K = 4096, L = 72, S = 40,
+// B = 16384: 293 and 235; K = 333, S = 127: 104 and 65; K = 256, L = 200, S = 64, B = 65536: 387 and 240.
+// The whole table takes 297 (K = 100), 3340, 920 and 4200.
 
 constexpr int16_t kGivenUp = -3;         // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
@@ -720,14 +720,16 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         const int budget = B - base_t;            // buckets are counted from the smallest times
         int held_at = 0;                          // lane i holds `single` of layer held_at + i
         float held = lane < L ? single[lane] : 0.0f;
-        auto add_singles = [&](float v, int from, int to) __attribute__((always_inline)) {
-            for (int l = from; l < to; ++l) {
-                if ((l & ~(kWave - 1)) != held_at) {
-                    held_at = l & ~(kWave - 1);
-                    held = held_at + lane < L ? single[held_at + lane] : 0.0f;
-                }
-                v += lane_value(held, l & (kWave - 1));
+        auto single_of = [&](int l) __attribute__((always_inline)) {
+            if ((l & ~(kWave - 1)) != held_at) {
+                held_at = l & ~(kWave - 1);
+                held = held_at + lane < L ? single[held_at + lane] : 0.0f;
             }
+            return lane_value(held, l & (kWave - 1));
+        };
+        auto add_singles = [&](float v, int from, int to) __attribute__((always_inline)) {
+            for (int l = from; l < to; ++l)
+                v += single_of(l);
             return v;
         };
         auto none = []() __attribute__((always_inline)) { return CoreEntry{__builtin_inff(), 0}; };
@@ -863,6 +865,98 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         };
+        // The same for rows of two chunks, in two registers: `off` + x is the place of bucket a + x in both. A
+        // cell and the one 64 buckets above lie in the same lane, so an entry takes two exchanges.  Thousands of
+        // clocks of the slowest candidate, mean of eight seeds, through LDS and so: K = 256, L = 200, S = 64
+        // (the mean candidate's 109 steps: 239 and 156) 607 and 536; K = 250, L = 52, S = 42 115 and 100; 384
+        // solves under six budgets 119 and 106; K = 4096, L = 72 206 and 184; K = 100 204 and 199.
+        auto two_chunks = [&]() __attribute__((always_inline)) {
+            float row0_v = prev[min(lane, b - a)], row1_v = prev[min(kWave + lane, b - a)];
+            int off = 0;
+            for (;;) {
+                if (m - base_step >= kWave)
+                    load_steps(m);
+                const int i_m = m - base_step;
+                const int n = __builtin_amdgcn_readlane(held_step.count, i_m);
+                const int top = min(b + __builtin_amdgcn_readlane(held_step.span, i_m), budget);
+                const int width = top - a + 1;
+                if (width <= kWave || width > 2 * kWave || n > kWave || used + width > cp.record ||
+                    work + 2 * n > cp.work)
+                    break;
+                const int first = __builtin_amdgcn_readlane(held_step.first, i_m);
+                const int layers_m = __builtin_amdgcn_readlane(held_step.layer, i_m);
+                const double lim = from_lane(held_limit, i_m);
+                const CoreEntry en = lane < n ? next : none();
+                const int follow = first + n + lane;
+                next = follow < total ? list[follow] : none();
+                work += 2 * n;
+                row_at[m] = used - a;             // (every lane, the same)
+                const int shift = (int)(en.word & ((1u << kCoreShiftBits) - 1u));
+                const int reach = b - a;
+                float best0 = __builtin_inff(), best1 = __builtin_inff();
+                int arg0 = 0, arg1 = 0;
+                const int at = lane + off;
+                auto some = [&](int i, auto many) __attribute__((always_inline)) {
+                    constexpr int kMany = decltype(many)::value;
+                    float v0[kMany], v1[kMany];
+#pragma unroll
+                    for (int q = 0; q < kMany; ++q) {
+                        const int by = __builtin_amdgcn_readlane(shift, i + q);
+                        const int u = lane - by, place = at - by;
+                        const float x0 = __builtin_bit_cast(
+                            float, __builtin_amdgcn_ds_bpermute(place * 4, __builtin_bit_cast(int, row0_v)));
+                        const float x1 = __builtin_bit_cast(
+                            float, __builtin_amdgcn_ds_bpermute(place * 4, __builtin_bit_cast(int, row1_v)));
+                        const float err = lane_value(en.err, i + q);
+                        const float d0 = place < kWave ? x0 : x1, d1 = place < 0 ? x0 : x1;
+                        v0[q] = ((unsigned)u <= (unsigned)reach ? d0 : __builtin_inff()) + err;
+                        v1[q] = ((unsigned)(u + kWave) <= (unsigned)reach ? d1 : __builtin_inff()) + err;
+                    }
+#pragma unroll
+                    for (int q = 0; q < kMany; ++q) {
+                        const bool take0 = v0[q] < best0, take1 = v1[q] < best1;
+                        best0 = take0 ? v0[q] : best0;
+                        arg0 = take0 ? i + q : arg0;
+                        best1 = take1 ? v1[q] : best1;
+                        arg1 = take1 ? i + q : arg1;
+                    }
+                };
+                for (int i = 0; i < n; i += 2)
+                    some(i, Many<2>{});
+                for (int l = (layers_m & 0xFFFF) + 1; l < layers_m >> 16; ++l) {
+                    const float single_l = single_of(l);
+                    best0 += single_l;
+                    best1 += single_l;
+                }
+                const bool in1 = kWave + lane < width;
+                rec[used + lane] = (unsigned char)arg0;
+                if (in1)
+                    rec[used + kWave + lane] = (unsigned char)arg1;
+                const unsigned long long set0 = __ballot(
+                    __builtin_fma(lambda, (double)(a + lane), (double)best0) <= lim);
+                const unsigned long long set1 = __ballot(
+                    in1 && __builtin_fma(lambda, (double)(a + kWave + lane), (double)best1) <= lim);
+                used += width;
+                row0_v = best0;
+                row1_v = best1;
+                ++m;
+                if ((set0 | set1) == 0) {         // no profile costs as little as `target`
+                    failed = true;
+                    break;
+                }
+                off = set0 ? __builtin_ctzll(set0) : kWave + __builtin_ctzll(set1);
+                b = a + (set1 ? 2 * kWave - 1 - __builtin_clzll(set1) : kWave - 1 - __builtin_clzll(set0));
+                a += off;
+                if (m == nsteps)
+                    break;
+            }
+            float *const to = prev >= row1 ? row0 : row1;
+            to[lane] = row0_v;
+            to[kWave + lane] = row1_v;
+            prev = to + off;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
         while (m < nsteps && !failed) {
             // One step.  A row of one or two chunks is done by wave 0 alone, as are the narrow ones
             // after it, without a barrier: the others wait for where it has got to.
@@ -887,9 +981,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                     break;
                 }
                 alone = narrow;
-                if ((!kFar || far_prev < 0) && chunks == 1 && n <= kWave &&
-                    first_spilled == nsteps && used + width <= cp.record && work + n <= cp.work) {
-                    one_chunk();
+                if ((!kFar || far_prev < 0) && narrow && n <= kWave && first_spilled == nsteps &&
+                    used + width <= cp.record && work + n * chunks <= cp.work &&
+                    chunks * kWave <= cp.window) {
+                    if (chunks == 1)
+                        one_chunk();
+                    else
+                        two_chunks();
                     if (failed || m == nsteps)
                         break;
                     continue;
