@@ -26,6 +26,8 @@
 // L = 54, S = 40, B = 10000: 224 -> 143; K = 64: 247 -> 175; K = 128: 250 -> 199; K = 6, L = 173, S = 35,
 // B = 1500: 430 -> 318; B = 100000, K = 1: 1630 -> 430, K = 64: 1700 -> 665, K = 128: 1780 -> 1220, K = 300:
 // 3690 -> 2770; S = 100, L = 100, B = 4000, K = 60: 883 -> 305.
+// (Then, with a sweep without lane exchanges in its adds and a walk in blocks of layers: B = 10000, K = 1
+// 143 -> 131, K = 128 280 -> 253; B = 100000, K = 1 520 -> 452, K = 300 1575 -> 1356.)
 
 constexpr int kTileThreads = kTileWaves * kWave;
 constexpr int kTileEarly = 8;        // waves that fetch the apron of a long tile
