@@ -1873,11 +1873,11 @@ __device__ __forceinline__ void fill_candidates(
         if (l + 1 < le) {
             const LayerTable tn = tables.layer(l + 1);
             const ErrRow en = mine.layer(l + 1, S);
-            // Rows in memory with the level record need all of their 64 registers for the sweep: addresses of
-            // a lane that stayed in registers over all layers (these, and those of the copy to LDS below)
-            // drove four others to scratch memory.
+            // Rows in memory need all of their registers for the sweep: addresses of a lane that stayed in
+            // registers over all layers (these, and with the level record those of the copy to LDS below) drove
+            // four others to scratch memory.
             int mine_of = lane;
-            if constexpr (kGlobal && kLevel)
+            if constexpr (kGlobal)
                 asm("" : "+v"(mine_of));
             if constexpr (kNarrow)
                 next_fetch = fetch_levels<kLevel>(tn, en, S, s8, mine_of, producer);
