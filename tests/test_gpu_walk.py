@@ -56,11 +56,12 @@ def test_walks(dp, L, S, B, widest):
                         f"resumed L={L} S={S} B={B}")
 
 
-@pytest.mark.parametrize("K, J", [(256, 1), (257, 1), (128, 2), (43, 6)])
-def test_as_many_as_units(dp, K, J):
+# (several budgets over a table of eight layers are not tried by the reduced solve first)
+@pytest.mark.parametrize("K, J, L", [(256, 1, 18), (257, 1, 18), (128, 2, 8), (42, 6, 8), (43, 6, 8), (128, 2, 18)])
+def test_as_many_as_units(dp, K, J, L):
     rng = np.random.default_rng(K)
-    L, S, B = 18, 20, 700
-    tau, err = instance(rng, K, L, S, B, 90)
+    S, B = 20, 700
+    tau, err = instance(rng, K, L, S, B, 1600 // L)
     budgets = [B - 37 * j for j in range(J)]
     print(f"[walk] K={K} budgets={J}", flush=True)
     tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
