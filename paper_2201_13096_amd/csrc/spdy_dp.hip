@@ -2200,7 +2200,7 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
 // The walk of a candidate that has a compute unit to itself: one workgroup.  A wave that gathers its
 // levels' entries of the row below waits for memory once per layer, 0.63 us, because where it reads next
 // follows from what it read.  Which part of the rows below it can come to is known ahead, though: i layers
-// below time t, [t - the largest shifts of those layers, t - the smallest].  So a block of up to
+// below time t, [t - the largest shifts of those layers, t] (a layer's smallest shift is 0).  So a block of up to
 // kLoneBlock layers is taken at a time, as many as have all their windows in LDS: every wave copies its
 // share of them (memory to LDS, 256 floats an instruction, all in flight at once), then wave 0 walks
 // through LDS, about 0.12 us a layer, while the other waves fetch the levels of the next block.  Windows
@@ -2216,7 +2216,9 @@ constexpr int kLoneWaves = 16;
 constexpr int kLoneBlock = kLoneWaves - 1;      // layers of a block: waves 1 to 15 fetch one's levels each
 constexpr int kLoneLeast = 4;                   // fewest layers that are copied for
 constexpr int kPiece = 4 * kWave;               // floats of one copy
-constexpr int kFarShift = 1 << 27;              // bound of a shift in a window's sums: farther than any that fits
+// A window's sum counts no more than this of a shift, so that 15 of them fit; a window whose sum has come to it
+// begins at bucket 0.
+constexpr int kFarShift = 1 << 27;
 template <int kLevelBlocks> constexpr int kLonePieces = kLevelBlocks == 1 ? 140 : 92;
 
 template <int kLevelBlocks>
@@ -2227,12 +2229,12 @@ struct LoneShared {
     // z, the floats of the window; w, where it begins.  Otherwise x is the shift and z the row's end.  z = 0
     // past S.  (Row kLoneBlock: read ahead and not used.)
     int4 step[kLoneBlock + 1][kLevelBlocks * kWave];
-    int lowest[kLoneBlock], highest[kLoneBlock];         // shifts of layer top - i
-    int reach[kLoneBlock];
+    int highest[kLoneBlock], reach[kLoneBlock];          // largest shift of layer top - i, row below it
     int t;
     float target;
 };
 static_assert(sizeof(LoneShared<1>) <= 160 * 1024 && sizeof(LoneShared<4>) <= 160 * 1024, "LDS");
+static_assert((long long)kLoneBlock * kFarShift <= INT32_MAX, "sums of a window");
 
 template <int kLevelBlocks, bool kByItself>
 __global__ __launch_bounds__(kLoneWaves * kWave) void dp_backtrace_alone(
@@ -2258,17 +2260,13 @@ __global__ __launch_bounds__(kLoneWaves * kWave) void dp_backtrace_alone(
         if (i < 0 || i > top)
             return;
         levels = load_layer<kLevelBlocks>(tau, mine.layer(top - i, S), meta, top - i, L, S, lane);
-        int low = INT32_MAX, high = INT32_MIN;
+        int high = 0;
 #pragma unroll
-        for (int b = 0; b < kLevelBlocks; ++b) {
-            low = min(low, levels.shift[b]);     // (INT32_MAX past S)
-            high = max(high, b * kWave + lane < S ? levels.shift[b] : INT32_MIN);
-        }
-        low = wave_scan(low, INT32_MAX, Smaller{});
-        high = wave_scan(high, INT32_MIN, Larger{});
+        for (int b = 0; b < kLevelBlocks; ++b)   // (INT32_MAX past S)
+            high = max(high, b * kWave + lane < S ? levels.shift[b] : 0);
+        high = wave_scan(high, 0, Larger{});
         if (lane == kWave - 1) {
-            sh.lowest[i] = min(max(low, -kFarShift), kFarShift);
-            sh.highest[i] = min(max(high, -kFarShift), kFarShift);
+            sh.highest[i] = min(high, kFarShift);
             sh.reach[i] = levels.reach;
         }
     };
@@ -2293,10 +2291,9 @@ __global__ __launch_bounds__(kLoneWaves * kWave) void dp_backtrace_alone(
         const bool here = lane < kLoneBlock && lane <= top, rows = here && lane < top;
         const int i = min(lane, kLoneBlock - 1);
         const int reach = here ? sh.reach[i] : 0;
-        const int low = wave_scan(here ? sh.lowest[i] : 0, 0, Add{});
         const int high = wave_scan(here ? sh.highest[i] : 0, 0, Add{});
-        const int from = rows && t > high ? (t - max(high, 0)) & ~3 : 0;
-        const int last = min(t - low, reach - 1);
+        const int from = rows && high < min(t, kFarShift) ? (t - high) & ~3 : 0;
+        const int last = min(t, reach - 1);
         const int pieces = rows && last >= from ? min((last - from) / kPiece, kMost) + 1 : 0;
         const int ends = wave_scan(pieces, 0, Add{});
         const int held = __popcll(__ballot(here && ends <= kMost));
