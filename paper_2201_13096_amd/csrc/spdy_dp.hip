@@ -755,9 +755,9 @@ struct Resume {
     const int32_t *first_layer;   // [K] in [0, L], or nullptr: every candidate starts at layer 0
     const float *inc_rec;         // the incumbent's D record, float [L][pitch]
     const int32_t *inc_meta;      // its header: without a whole table there is nothing to resume from
-    template <bool kChecked = true> __device__ __forceinline__ int start(int k, int L) const
+    __device__ __forceinline__ int start(int k, int L) const
     {
-        if (!first_layer || (kChecked && !inc_meta[kMetaTable]))
+        if (!first_layer || !inc_meta[kMetaTable])
             return 0;
         const int f = first_layer[k];
         return f < 0 ? 0 : (f > L ? L : f);
@@ -1762,8 +1762,7 @@ __device__ __forceinline__ void fill_candidates(
 
     // a candidate that shares its first l0 layers with the incumbent starts from the incumbent's
     // row l0 - 1, placed where layer l0 reads its previous row
-    // (a call that does not go through dp_core resumes from one that did not either, see table_is_short)
-    const int l0 = active ? resume.start<kTodo>(k, L) : 0;
+    const int l0 = active ? resume.start(k, L) : 0;
     if (l0 > 0 && lead) {
         float *dst = (l0 & 1) ? buf1 : buf0;
         const float *from = resume.inc_rec + (size_t)(l0 - 1) * pitch;
@@ -2640,10 +2639,10 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
 //     of them sets dp_core's time, the table's hardly grows.  Of 631 drawn calls (L = 4 - 200) 58 were more
 //     than 5 % slower than the better side without this line, 36 are with it.  K = 2247, L = 8, S = 10,
 //     B = 982: 52 and 84; K = 428, L = 6, S = 16, B = 134: 31 and 41; K = 188, L = 9, S = 15, B = 15627: 58
-//     and 77.  (Not for a call that resumes from an incumbent: its fill takes the rows below
-//     first_layer as they are, so it may only be direct where the incumbent's call, K = 1, was whatever
-//     entry point that went through.  The first line is one of the sizes alone and holds for K = 1 where
-//     it holds for K; a check of the incumbent's header in those fills costs the others half a per cent.)
+//     and 77.  (Not for a call that resumes from an incumbent: it may only be direct where the incumbent's
+//     call, K = 1, was whatever entry point that went through, or there are no rows to take and every
+//     candidate is filled from layer 0.  The first line is one of the sizes alone and holds for K = 1 where it
+//     holds for K.)
 bool table_is_short(int K, int L, int S, int B, bool one_fill)
 {
     const long long updates = (long long)L * S * (B + 1LL);
