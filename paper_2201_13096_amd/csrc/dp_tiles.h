@@ -171,7 +171,7 @@ __device__ __forceinline__ void tile_units(float *row, int local, int start, Lev
             for (int c = 0; c < 4; ++c)
                 bq[j][c] = __builtin_inff();
         const float4v *quads = reinterpret_cast<const float4v *>(row + local) + (lane - 1);
-        sweep_layer<Q, 0, false, true>(quads, nullptr, entries, first,
+        sweep_layer<Q, 0, false, true, false>(quads, nullptr, entries, first,
                                        start + local + Q * kQuadChunk - 1, 0, bq, none);
         wait_but<0>();                            // the last layer's record is in memory
         meanwhile();

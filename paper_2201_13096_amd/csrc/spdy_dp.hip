@@ -894,10 +894,11 @@ __device__ __forceinline__ unsigned long long load_twins(LayerTable tl)
            ((unsigned long long)(uint32_t)tl.start[1] << 32);
 }
 
-// table[r] = shift in bytes and smallest error among the levels of entry r (+inf for unused entries); one wave.
-__device__ __forceinline__ void publish_entries(int2 *table, const LevelFetch &f, int S, int lane)
+// table[r] = shift in units of 1 / `scale` buckets and smallest error among the levels of entry r (+inf for unused
+// entries); one wave.
+__device__ __forceinline__ void publish_entries(int2 *table, const LevelFetch &f, unsigned scale, int S, int lane)
 {
-    table[lane] = make_int2((int)((unsigned)f.shift * 4u), __builtin_bit_cast(int, __builtin_inff()));
+    table[lane] = make_int2((int)((unsigned)f.shift * scale), __builtin_bit_cast(int, __builtin_inff()));
     if (lane < S)
         __hip_atomic_fetch_min(reinterpret_cast<float *>(&table[f.entry].y), f.raw, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1127,7 +1128,8 @@ __device__ __forceinline__ float from_left(float x)
         __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138 /* wave_shr:1 */, 0xf, 0xf, true));
 }
 
-// Two entries of a table in LDS (shift in bytes, error, and again), one read wherever the first of them lies.
+// Two entries of a table in LDS (shift, error, and again), one read wherever the first of them lies.
+// Shifts are in bytes, but in buckets where a row is read from memory (kBuckets): bytes would pass 2^31.
 // (Two values of their own the compiler fetches one at a time, the second where it is needed.)
 constexpr int kLookAhead = 4;        // entries read behind the last one of a table, and not used
 typedef int EntryPair __attribute__((ext_vector_type(4), aligned(8)));
@@ -1167,17 +1169,19 @@ __device__ __forceinline__ EntryRun entry_run(const int2 *entries, unsigned long
 // they cost 28 clocks of the pipe that the mins need, more than four quads of mins do.  That pipe takes four
 // clocks for any instruction but fp32 adds and multiplies of vector registers only, which have a
 // second one (v_min3 4.0 clocks of a SIMD, v_add 2.0, v_add with a scalar or a lane to the left 4.0).
-template <int Q, int T, int kRes, bool kSplit>
+template <int Q, int T, int kRes, bool kSplit, bool kBuckets>
 __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tail,
                                           EntryRun run, float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
 {
     constexpr int kStep = kSplit ? 4 : 2;
-    auto quads_at = [&](int shift) {
-        return reinterpret_cast<const float4v *>(reinterpret_cast<const char *>(quads) - shift +
+    using Shift = std::conditional_t<kBuckets, ptrdiff_t, int>;
+    constexpr Shift kBytes = kBuckets ? 4 : 1;    // of a unit
+    auto quads_at = [&](Shift shift) {
+        return reinterpret_cast<const float4v *>(reinterpret_cast<const char *>(quads) - shift * kBytes +
                                                  4 * kRes);
     };
-    auto tail_at = [&](int shift) {
-        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(tail) - shift);
+    auto tail_at = [&](Shift shift) {
+        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(tail) - shift * kBytes);
     };
     for (; run.n >= 2; run.n -= kStep) {
         const EntryPair now = run.pair;
@@ -1229,7 +1233,7 @@ __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tai
 // lane in every add, as before, took the slow pipe.  What lane 0 gets from the left ends in buckets that are not
 // its own and never reaches lane 1.
 // kAhead: the first entries of all four runs are asked for at once (registers permitting).
-template <int Q, int T, bool kSplit, bool kAhead>
+template <int Q, int T, bool kSplit, bool kAhead, bool kBuckets>
 __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *tail,
                                             const int2 *entries, LevelEntry mine, int last_bucket,
                                             int half, float (&bq)[Q > 0 ? Q : 1][4],
@@ -1273,16 +1277,16 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
             bq[j][0] = carry;
         }
     };
-    sweep_run<Q, T, 3, kSplit>(quads, tail, run3, bq, bt);
+    sweep_run<Q, T, 3, kSplit, kBuckets>(quads, tail, run3, bq, bt);
     next_residue();
     later(run2);
-    sweep_run<Q, T, 2, kSplit>(quads, tail, run2, bq, bt);
+    sweep_run<Q, T, 2, kSplit, kBuckets>(quads, tail, run2, bq, bt);
     next_residue();
     later(run1);
-    sweep_run<Q, T, 1, kSplit>(quads, tail, run1, bq, bt);
+    sweep_run<Q, T, 1, kSplit, kBuckets>(quads, tail, run1, bq, bt);
     next_residue();
     later(run0);
-    sweep_run<Q, T, 0, kSplit>(quads, tail, run0, bq, bt);
+    sweep_run<Q, T, 0, kSplit, kBuckets>(quads, tail, run0, bq, bt);
 }
 
 // One group of one layer (D record, at most 64 levels), Q quad chunks and T ordinary ones from bucket
@@ -1293,10 +1297,10 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
 // leaves its minima in `part` (indexed like the row) before the barrier, and the first half
 // folds them into its own behind it.  min is exact and order-blind here, so the row is the one
 // a single wave would have computed.
-template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead>
+template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead, bool kBuckets>
 __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, float *rec,
-                                                 LevelEntry first, const int2 *entries, int t0, int lane, Pending pending, int half,
-                                                 float *part)
+                                                 LevelEntry first, const int2 *entries, int t0,
+                                                 int lane, Pending pending, int half, float *part)
 {
     static_assert(!kSplit || inplace, "the halves meet at the in-place barrier");
     if constexpr (Q + T == 0) {
@@ -1317,7 +1321,7 @@ __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, 
         const int last = t0 + (T > 0 ? tail0 + T * kWave : Q * kQuadChunk) - 1;
         const float4v *quads = reinterpret_cast<const float4v *>(prev + t0) + (lane - 1);
         const float *tail = prev + t0 + tail0 + lane;
-        sweep_layer<Q, T, kSplit, kAhead>(quads, tail, entries, first, last, half, bq, bt);
+        sweep_layer<Q, T, kSplit, kAhead, kBuckets>(quads, tail, entries, first, last, half, bq, bt);
         pending.settle();
         const int tq = t0 + 4 * (lane - 1);       // this lane's first bucket of quad chunk 0
         const int tt = t0 + tail0 + lane;
@@ -1413,7 +1417,7 @@ __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_
     }
 }
 
-template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kAhead, bool kPairs>
+template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kAhead, bool kBuckets, bool kPairs>
 __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cur, uint8_t *choice,
                                              float *rec, LevelEntry first, const int2 *entries,
                                              LayerTable tl, ErrRow er, int s8, int t0, int lane,
@@ -1426,8 +1430,8 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
         if constexpr (RR <= kMax) {                                                            \
             if constexpr (kQuads)                                                              \
                 fill_group_quads<quad_chunks(RR), tail_chunks(RR), (RR - tail_chunks(RR)) * kWave, \
-                                 inplace, kSplit, kAhead>(prev, cur, rec, first, entries, t0,  \
-                                                          lane, pending, half, part);          \
+                                 inplace, kSplit, kAhead, kBuckets>(                           \
+                    prev, cur, rec, first, entries, t0, lane, pending, half, part);            \
             else                                                                               \
                 fill_group<RR, kLevel, inplace, kPairs>(prev, cur, choice, rec, first, tl, er, s8, t0, \
                                                 lane, pending);                                \
@@ -1474,8 +1478,8 @@ __device__ __forceinline__ void fill_quads_n(int share, float *row, float *rec, 
     switch (share >> 20 & 0xF) {
 #define SPDY_CASE(QQ)                                                                          \
     case QQ:                                                                                   \
-        fill_group_quads<QQ, 0, 0, true, false, true>(row, row, rec, first, entries, t0, lane, \
-                                                      pending, 0, nullptr);                    \
+        fill_group_quads<QQ, 0, 0, true, false, true, false>(row, row, rec, first, entries, t0, \
+                                                             lane, pending, 0, nullptr);       \
         break;
         SPDY_CASE(0)
         SPDY_CASE(1)
@@ -1812,6 +1816,15 @@ __device__ __forceinline__ void fill_candidates(
         reinterpret_cast<unsigned long long *>(&s_entries[0]) + (team < teams ? team : 0);
     int2 *const table = &s_entries[(team < teams && !kLevel ? team : 0) * kWave];
     constexpr int kNextTable = kFillWaves * kWave;   // from an even layer's table to an odd one's
+    constexpr int kMax = group_limit<kLevel, kTurns>();
+    // Rows in memory: chunks of a tile of layer l, whose window in LDS holds the layer's largest shift; fewer
+    // than one per wave: there is no room for any, and the layer is swept from memory.
+    auto tile_of = [&](int l) {
+        const int span = meta[kMetaHeader + (2 + (size_t)kRangeStride) * L + l];
+        const int tile = (meta[kMetaStage] / (int)sizeof(float) - span - 8) / kWave / tw * tw;
+        return min(tile, tw * kMax);
+    };
+    auto unit = [&](int l) { return kGlobal && tile_of(l) < tw ? 1u : (unsigned)sizeof(float); };
     LevelEntry next_first{INT32_MAX, 0.0f};
     LevelFetch next_fetch{INT32_MAX, 0.0f, 0};
     if constexpr (kNarrow) {
@@ -1824,7 +1837,7 @@ __device__ __forceinline__ void fill_candidates(
                 if (lane == 0)
                     keep[(lb & 1) * kMaxFillWaves] = visit;
             } else {
-                publish_entries(table + (lb & 1) * kNextTable, next_fetch, S, lane);
+                publish_entries(table + (lb & 1) * kNextTable, next_fetch, unit(lb), S, lane);
             }
         }
         __syncthreads();
@@ -1913,12 +1926,11 @@ __device__ __forceinline__ void fill_candidates(
         const LayerTable tl = tables.layer(l);
         const ErrRow er = mine.layer(l, S);
         const int2 *const entries = table + (l & 1) * kNextTable;
-        constexpr int kMax = group_limit<kLevel, kTurns>();
         const Pending pending{&next_fetch, &next_first};
         if (kWhole && whole != 0) {
             fill_quads_n(whole, cur, drec_l, first, entries, lane, pending);
         } else if constexpr (inplace) {          // c_end - c <= kMax by construction
-            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, kPairs>(
+            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs>(
                 min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, entries, tl, er, s8,
                 c * kWave, lane, pending, half, part);
         } else {
@@ -1926,14 +1938,9 @@ __device__ __forceinline__ void fill_candidates(
             // wave, and the part of the previous row a tile reads (the tile itself and the
             // layer's largest usable shift to its left) is first copied to LDS, so the sweep
             // reads LDS as in the resident case.  One candidate per workgroup here, so every
-            // wave takes the same number of trips.  A layer whose largest shift leaves no room
-            // for a tile is swept from global memory.
-            int tile = 0, span = 0;
-            if constexpr (kGlobal) {
-                span = meta[kMetaHeader + (2 + (size_t)kRangeStride) * L + l];
-                tile = (meta[kMetaStage] / (int)sizeof(float) - span - 8) / kWave / tw * tw;
-                tile = min(tile, tw * kMax);
-            }
+            // wave takes the same number of trips.
+            const int tile = kGlobal ? tile_of(l) : 0;
+            const int span = kGlobal ? meta[kMetaHeader + (2 + (size_t)kRangeStride) * L + l] : 0;
             if (kGlobal && tile >= tw) {
                 const int n_l = (active && l >= l0) ? nact[l] : 0;
                 if (n_l == 0)
@@ -1965,7 +1972,7 @@ __device__ __forceinline__ void fill_candidates(
                     __syncthreads();
                     const int cb = c0 + (int)((long long)share * nt / tw);
                     const int ce = c0 + (int)((long long)(share + 1) * nt / tw);
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kPairs>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, false, kPairs>(
                         ce - cb, lds - lo, cur, choice_l, drec_l, first, entries, tl, er, s8,
                         cb * kWave, lane, pending);
                     __syncthreads();             // the next tile overwrites the staged part
@@ -1975,7 +1982,7 @@ __device__ __forceinline__ void fill_candidates(
                     const int n = c_end - c;
                     const int groups = (n + kMax - 1) / kMax;
                     const int r = (n + groups - 1) / groups;
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kPairs>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kGlobal, kPairs>(
                         r, prev, cur, choice_l, drec_l, first, entries, tl, er, s8, c * kWave, lane,
                         pending);
                     c += r;
@@ -1990,7 +1997,7 @@ __device__ __forceinline__ void fill_candidates(
                 if (lane == 0)
                     keep[((l + 1) & 1) * kMaxFillWaves] = visit;
             } else {
-                publish_entries(table + ((l + 1) & 1) * kNextTable, next_fetch, S, lane);
+                publish_entries(table + ((l + 1) & 1) * kNextTable, next_fetch, unit(l + 1), S, lane);
             }
         }
         __syncthreads();

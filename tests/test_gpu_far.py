@@ -59,3 +59,18 @@ def test_walks_of_far_levels(dp, times, B, S):
     profile.fill_(7)
     dp.spdy_dp_backtrace(tau_d, err_d, B, profile, cost, ws)
     check(profile, cost, want, "walk by itself")
+
+
+# layers swept from memory by a shift whose bytes pass 2^31 and 2^32 - 1, at every residue
+@pytest.mark.parametrize("far", [(1 << 29) - 1, 1 << 29, (1 << 29) + 1, (1 << 29) + 2, 600_000_003])
+@pytest.mark.parametrize("third", [[[0, 1]], [[0, 5]]])
+def test_rows_in_memory_and_far_shifts(dp, far, third):
+    tau, err = tables([[0, 4100], [0, far]] + third)
+    B = far + 6000
+    print(f"[far] far={far} third={third}", flush=True)
+    for budget in (B, far - 1):                   # (without the far level, and with it)
+        want = best(tau, err, budget)
+        tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+        profile, cost = dp.spdy_dp_solve_batched(tau_d, err_d, budget,
+                                                 workspace=dp.alloc_workspace(1, *tau.shape, budget))
+        check(profile, cost, want, f"far={far} B={budget}")
