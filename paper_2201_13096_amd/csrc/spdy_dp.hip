@@ -995,7 +995,7 @@ __device__ __forceinline__ void sweep_group(const float *__restrict__ prev, Leve
     __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): see fill_group_quads
     const char *pl = reinterpret_cast<const char *>(prev + t0 + lane);
     auto row_at = [&](int shift) {
-        return reinterpret_cast<const float *>(pl - (size_t)((unsigned)shift * 4u));
+        return reinterpret_cast<const float *>(pl - (size_t)(unsigned)shift * 4u);
     };
 
     // (with S <= 64 this loop runs once; telling the compiler so made the code slower)
@@ -1742,9 +1742,9 @@ __device__ __forceinline__ void fill_candidates(
 
     // rows: [apron | row] once (in place) or twice per team
     const int stride = kHalo + (kLds ? row : pitch);
-    const int team_floats = inplace ? stride : 2 * stride;
+    const int team_floats = inplace ? stride : (kLds ? 2 * stride : 0);    // (in LDS)
     float *base = kLds ? lds + (size_t)(team < teams ? team : 0) * team_floats
-                       : rows + (size_t)blockIdx.x * team_floats;
+                       : rows + (size_t)blockIdx.x * 2 * stride;
     float *buf0 = base + kHalo;
     float *buf1 = inplace ? buf0 : buf0 + stride;
 
@@ -1755,9 +1755,10 @@ __device__ __forceinline__ void fill_candidates(
         for (int i = tid; i < teams * team_floats; i += nthreads)
             lds[i] = (i % team_floats == kHalo) ? -0.0f : __builtin_inff();
     } else {
-        for (int i = tid; i < team_floats; i += nthreads)
-            if (i % stride < kHalo + row)
-                base[i] = (i == kHalo) ? -0.0f : __builtin_inff();
+        for (int i = tid; i < kHalo + row; i += nthreads) {
+            base[i] = (i == kHalo) ? -0.0f : __builtin_inff();
+            base[(size_t)stride + i] = __builtin_inff();
+        }
     }
     __syncthreads();
 

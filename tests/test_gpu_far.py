@@ -74,3 +74,18 @@ def test_rows_in_memory_and_far_shifts(dp, far, third):
         profile, cost = dp.spdy_dp_solve_batched(tau_d, err_d, budget,
                                                  workspace=dp.alloc_workspace(1, *tau.shape, budget))
         check(profile, cost, want, f"far={far} B={budget}")
+
+
+# two rows in memory that are more than 2^31 floats together, and shifts whose bytes pass 2^32: either record, entries
+# from LDS and from lanes
+@pytest.mark.parametrize("S, compact", [(0, False), (66, False), (0, True)])
+@pytest.mark.parametrize("far", [(1 << 30) + 1, 1_500_000_003])
+def test_rows_of_more_than_a_billion_buckets(dp, far, S, compact):
+    tau, err = tables([[0, 4100], [0, far]], S)
+    B = far + 5000
+    print(f"[far] far={far} S={tau.shape[1]} compact={compact}", flush=True)
+    want = best(tau, err, B)
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+    profile, cost = dp.spdy_dp_solve_batched(tau_d, err_d, B,
+                                             workspace=dp.alloc_workspace(1, *tau.shape, B, compact=compact))
+    check(profile, cost, want, f"far={far}")
