@@ -99,10 +99,13 @@ using FarBytes = __attribute__((address_space(1))) unsigned char *;
 // compiler makes one load of the first trip's and the later ones', at the head of the loop, and waits for it.)
 __device__ __forceinline__ void stay_ahead() { asm volatile("" ::: "memory"); }
 
-// The upper bits of `word`, and a place of three bits in the lower ones.
-__device__ __forceinline__ unsigned with_place(unsigned word, unsigned upper, int place)
+// a * b + c in a register of its own.  (In the one that c was read to, as the compiler does it, c's neighbours of the
+// same read are moved out of the way as soon as they arrive, and waited for.)
+__device__ __forceinline__ float fma_apart(float a, float b, float c)
 {
-    return (word & upper) | (unsigned)place;
+    float sum;
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(sum) : "v"(a), "v"(b), "v"(c));
+    return sum;
 }
 
 struct CoreBooks {       // where the steps of the reduced table have got to
@@ -271,16 +274,14 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         // five passes, seven for deep networks, where one multiplier a pass took ten to fourteen.  The first
         // wave takes the chord, which decides when to stop; the others where the logarithm of the multiplier,
         // interpolated over the time, meets the budget, and on either side of that.  What a pass costs
-        // is instructions, so a level's place shares a word with the upper bits of its value, two and a half
-        // instructions a level: the level found is the least up to 2^-15 of its value at worst, which is as
-        // good for the choice of a multiplier (the bound is taken from that in fp64).  (Two multipliers per
-        // thread, layers split over all threads: six passes, each longer by as much.)
+        // is instructions: the least of all levels takes two a level, and only the four that it is among are
+        // compared with it.  (Two multipliers per thread, layers split over all threads: six
+        // passes, each longer by as much.)
         int2 *const picks = reinterpret_cast<int2 *>(steps);         // of the path above the budget, below it
         if (lead)
             picks[layer] = make_int2(-1, -1);
         const int share = 1 << cp.share_log2, of_wave = lane & (share - 1);
         const int levels = ((S + share - 1) / share + 3) & ~3;       // of a lane
-        const unsigned places = (1u << (32 - __builtin_clz(S | 4))) - 1u;
         float lam_lo = 0.0f, lam_hi = __builtin_inff();
         for (int trip = 0; trip < 40; ++trip) {
             lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
@@ -305,37 +306,52 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                 const int layer_b = b * kWave + (lane >> cp.share_log2);
                 const float2 *const row = table + min(layer_b, L - 1) * cp.pitch;
                 const int start = of_wave * levels;
-                // Eight levels a trip (the last eight may be some of those before once more); the next
+                // Eight levels a trip (the last four may be the ones before once more); the next
                 // trip's are asked for as soon as this trip's have been used, into the same registers.
-                const float2 *from = row + start;
-                unsigned key = ~0u;
+                const float2 *const from = row + start;
+                auto cost_of = [&](float2 v) __attribute__((always_inline)) {
+                    return fma_apart(lam, v.y, v.x);
+                };
                 float2 v[8];
                 auto eight = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
                         v[q] = from[(q < 4 ? i : min(i + 4, levels - 4)) + (q & 3)];
                 };
+                float least_b = __builtin_inff();
+                int at = 0;                       // the first of the four that it is among
                 eight(0);
-                for (int i = 0; i < levels; i += 8) {
-                    unsigned k[8];
+                int i = 0;
+                do {
+                    float r[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
-                        k[q] = __builtin_bit_cast(unsigned, __builtin_fmaf(lam, v[q].y, v[q].x));
+                        r[q] = cost_of(v[q]);
                     eight(min(i + 8, levels - 4));
                     stay_ahead();
+                    const float low = min3(min3(r[0], r[1], r[2]), r[3], least_b);
+                    at = low < least_b ? i : at;
+                    least_b = min3(min3(r[4], r[5], r[6]), r[7], low);
+                    at = least_b < low ? min(i + 4, levels - 4) : at;
+                    i += 8;
+                } while (i < levels);
+                float2 found = from[at + 3];
+                int place = start + at + 3;       // of the first level that is the least
 #pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        k[q] = with_place(k[q], ~places, q);
-                    const unsigned low = min(min(min(k[0], k[1]), k[2]), k[3]);
-                    const unsigned high = min(min(min(k[4], k[5]), k[6]), k[7]);
-                    // (places of the upper four count from 4: where they are the lower four once more, they
-                    // lose against them)
-                    key = min(min(low, high) | i, key);
+                for (int q = 2; q >= 0; --q) {
+                    const float2 one = from[at + q];
+                    const bool is = cost_of(one) == least_b;
+                    place = is ? start + at + q : place;
+                    found.x = is ? one.x : found.x;
+                    found.y = is ? one.y : found.y;
                 }
-                key += start;
-                pick[b] = (int)(group_join(key, share, Smaller{}) & places);
-                const float2 found = row[min(pick[b], S - 1)];
-                const bool counts = layer_b < L && of_wave == 0;
+                pick[b] = place;
+                if (__builtin_amdgcn_readfirstlane(share) > 1) {    // (see group_join)
+                    const unsigned own = magnitude(least_b);
+                    pick[b] = own == group_join(own, share, Smaller{}) ? place : INT32_MAX;
+                    pick[b] = group_join(pick[b], share, Smaller{});
+                }
+                const bool counts = layer_b < L && place == pick[b];
                 ce += counts ? found.x : 0.0f;
                 ct += counts ? (int)found.y : 0;
             }
@@ -659,7 +675,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
         const int run_t = wave_scan(lead ? first_t : 0, 0, Add{});
         if (lane == kWave - 1)
             sh.place[turn][wave] = make_int2(run, run_t);
-        __syncthreads();                
+        __syncthreads();
         int before = run - listed, all = 0, upto_t = run_t, base_t = 0;
 #pragma unroll
         for (int w = 0; w < kCoreWaves; ++w) {
