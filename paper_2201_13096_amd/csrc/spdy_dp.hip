@@ -118,13 +118,24 @@ __host__ __device__ constexpr int quad_share(int t, int quads)
     return 1 << 30 | quads << 20 | t / 4;
 }
 static_assert(kMaxFillWaves * kMaxGroupTurns * kWave / 4 < 1 << 20, "rows updated in place");
+// Or a share of ordinary chunks alone, where a wave has few of them and few levels (see sweep_tails): up to
+// kFewChunks, and kFewUpdates of levels and chunks.  us a solve with quad chunks and entries from LDS, and so:
+// K = 1500, L = 66, S = 8, B = 300 149 and 131, B = 586 163 and 138; K = 400, L = 60, B = 1500 147 and 123; S = 20,
+// K = 1500, B = 586 172 and 151, K = 1200, L = 93, B = 1132 261 and 231; S = 40, K = 1500, B = 300 180 and 162.  Of 254 calls
+// around the line none is more than 0.7 % slower; with twice the updates S = 32 and 40 are up to 4 %.
+constexpr int kFewChunks = 6, kFewUpdates = 120;
+__host__ __device__ constexpr int tail_share(int t, int chunks)
+{
+    return quad_share(t, chunks > 0 ? kMaxQuads + chunks : 0);
+}
+static_assert(kMaxQuads + kFewChunks < 1 << 4, "four bits of the word");
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
 constexpr int kMetaHeader = 20;      // int32 words before the per-layer arrays
 // meta: header | m_l [L] | chunks of row l [L] | chunk boundaries of the team waves [L][stride]
 //       | largest usable shift of layer l [L]
 constexpr int kRangeStride = kMaxFillWaves + 1;
-// shares of whole quad chunks, behind the boundaries of the usual workgroup's waves
+// shares of one kind of chunk, behind the boundaries of the usual workgroup's waves
 constexpr int kWholeWord = kFillWaves + 1;
 static_assert(kWholeWord + kFillWaves <= kRangeStride, "words of a layer");
 
@@ -357,7 +368,7 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
 __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots, int L, int S,
                                int B, int waves, int max_group, int lds_small, int lds_large,
                                int lds_stage, int split, int wide_waves, int wide_group,
-                               int lds_wide, int global_waves, bool quads, const TileArgs &ta,
+                               int lds_wide, int global_waves, bool quads, bool tails, const TileArgs &ta,
                                int32_t *words, int32_t *__restrict__ meta)
 {
     __shared__ long long s_sum[8];
@@ -552,12 +563,16 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         // them are moved down to the row's end and lie over the ones before
         if (whole_quads) {
             const int units = (n * kWave + kQuadChunk - 1) / kQuadChunk, most = (units + tw - 1) / tw;
+            const int chunks = (n + tw - 1) / tw;
+            const bool few = tails && chunks <= kFewChunks && S * chunks <= kFewUpdates;
             const bool whole = most <= kMaxQuads && n * kWave >= most * kQuadChunk &&
-                               4 * most < sweep_cost((n + tw - 1) / tw);
+                               4 * most < sweep_cost(chunks);
             for (int w = 0; w < tw; ++w) {
                 const int unit = w * units / tw, mine = (w + 1) * units / tw - unit;
                 const int first = min(unit * kQuadChunk, n * kWave - mine * kQuadChunk);
-                range[kWholeWord + w] = whole ? quad_share(first, mine) : 0;
+                const int c = range[w], c_end = range[w + 1];
+                range[kWholeWord + w] = few ? tail_share(c * kWave, c_end - c)
+                                            : (whole ? quad_share(first, mine) : 0);
             }
         }
     }
@@ -664,7 +679,7 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
 
 struct PrepareArgs {
     int slots, s8, B, waves, max_group, lds_small, lds_large, lds_stage, sorted, split;
-    int wide_waves, wide_group, lds_wide, global_waves, table;
+    int wide_waves, wide_group, lds_wide, global_waves, table, tails;
     int32_t *meta, *shifts, *order, *start, *entry_of;
     TileArgs tiles;
 };
@@ -678,7 +693,7 @@ __device__ __forceinline__ void prepare(const int32_t *__restrict__ tau, int K, 
     if (block == 0)
         prepare_budget(tau, K, a.slots, L, S, a.B, a.waves, a.max_group, a.lds_small, a.lds_large,
                        a.lds_stage, a.split, a.wide_waves, a.wide_group, a.lds_wide,
-                       a.global_waves, a.sorted == 2, a.tiles, words, a.meta);
+                       a.global_waves, a.sorted == 2, a.tails != 0, a.tiles, words, a.meta);
     else
         prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of,
                       words);
@@ -1226,6 +1241,42 @@ __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tai
     }
 }
 
+// The same for all entries of a layer (`shift`: that of entry `lane`) over a group of ordinary chunks alone, where
+// residues do not matter.  Few cells of few levels would wait for a round trip to LDS per residue, and another for
+// the entries: here shifts come from lanes, four entries a trip, and the errors arrive beside the cells.  An
+// entry that the group cannot use reads the cell itself and adds +inf.
+template <int T>
+__device__ __forceinline__ void sweep_tails(const float *tail, const int2 *entries, int shift,
+                                            int last_bucket, int lane, float (&bt)[T])
+{
+    float err = __int_as_float(entries[lane].y);
+    const bool use = shift <= last_bucket;
+    const int usable = use ? shift * (int)sizeof(float) : 0;
+    const int n = kWave - __builtin_clzll(__ballot(use) | 1);
+    for (int i = 0; i < n; i += 4) {
+        const float *p[4];
+        float v[4][T];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            p[q] = reinterpret_cast<const float *>(reinterpret_cast<const char *>(tail) -
+                                                   __builtin_amdgcn_readlane(usable, i + q));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < T; ++j)
+                v[q][j] = p[q][j * kWave];
+        if (i == 0)
+            err = use ? err : __builtin_inff();
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+            const float e0 = lane_value(err, i + q), e1 = lane_value(err, i + q + 1);
+#pragma unroll
+            for (int j = 0; j < T; ++j)
+                vmin3(bt[j], v[q][j] + e0, v[q + 1][j] + e1);
+        }
+    }
+}
+
 // All entries of a layer (at most 64, `mine.shift`: that of entry `lane`) over one group.  An entry of
 // residue r adds to the whole quads it reads, four buckets from 4 q + r on; so the minima are kept shifted by
 // the residue, and moved by one bucket (which is a move of a fourth of them to the lane to the right,
@@ -1297,12 +1348,14 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
 // leaves its minima in `part` (indexed like the row) before the barrier, and the first half
 // folds them into its own behind it.  min is exact and order-blind here, so the row is the one
 // a single wave would have computed.
-template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead, bool kBuckets>
+// kTails: sweep_tails does it.
+template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead, bool kBuckets, bool kTails = false>
 __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, float *rec,
                                                  LevelEntry first, const int2 *entries, int t0,
                                                  int lane, Pending pending, int half, float *part)
 {
     static_assert(!kSplit || inplace, "the halves meet at the in-place barrier");
+    static_assert(!kTails || (Q == 0 && !kSplit && !kBuckets), "ordinary chunks of a row in LDS");
     if constexpr (Q + T == 0) {
         pending.settle();
         if (inplace)
@@ -1321,7 +1374,10 @@ __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, 
         const int last = t0 + (T > 0 ? tail0 + T * kWave : Q * kQuadChunk) - 1;
         const float4v *quads = reinterpret_cast<const float4v *>(prev + t0) + (lane - 1);
         const float *tail = prev + t0 + tail0 + lane;
-        sweep_layer<Q, T, kSplit, kAhead, kBuckets>(quads, tail, entries, first, last, half, bq, bt);
+        if constexpr (kTails)
+            sweep_tails<T>(tail, entries, first.shift, last, lane, bt);
+        else
+            sweep_layer<Q, T, kSplit, kAhead, kBuckets>(quads, tail, entries, first, last, half, bq, bt);
         pending.settle();
         const int tq = t0 + 4 * (lane - 1);       // this lane's first bucket of quad chunk 0
         const int tt = t0 + tail0 + lane;
@@ -1470,16 +1526,21 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
     }
 }
 
-// The same in place for a share of whole quad chunks.
-__device__ __forceinline__ void fill_quads_n(int share, float *row, float *rec, LevelEntry first,
+// The same in place for a share of whole quad chunks, or (kTails) of ordinary ones.
+template <bool kTails>
+__device__ __forceinline__ void fill_share_n(int share, float *row, float *rec, LevelEntry first,
                                              const int2 *entries, int lane, Pending pending)
 {
     const int t0 = (share & 0xFFFFF) * 4;
     switch (share >> 20 & 0xF) {
-#define SPDY_CASE(QQ)                                                                          \
-    case QQ:                                                                                   \
-        fill_group_quads<QQ, 0, 0, true, false, true, false>(row, row, rec, first, entries, t0, \
-                                                             lane, pending, 0, nullptr);       \
+#define SPDY_CASE(NN)                                                                          \
+    case NN:                                                                                   \
+        if constexpr (NN <= kMaxQuads)                                                         \
+            fill_group_quads<NN, 0, 0, true, false, true, false>(                              \
+                row, row, rec, first, entries, t0, lane, pending, 0, nullptr);                 \
+        else if constexpr (kTails)                                                             \
+            fill_group_quads<0, NN - kMaxQuads, 0, true, false, false, false, true>(           \
+                row, row, rec, first, entries, t0, lane, pending, 0, nullptr);                 \
         break;
         SPDY_CASE(0)
         SPDY_CASE(1)
@@ -1489,9 +1550,15 @@ __device__ __forceinline__ void fill_quads_n(int share, float *row, float *rec, 
         SPDY_CASE(5)
         SPDY_CASE(6)
         SPDY_CASE(7)
+        SPDY_CASE(8)
+        SPDY_CASE(9)
+        SPDY_CASE(10)
+        SPDY_CASE(11)
+        SPDY_CASE(12)
+        SPDY_CASE(13)
 #undef SPDY_CASE
     }
-    static_assert(kMaxQuads == 7, "a case for each");
+    static_assert(kMaxQuads + kFewChunks == 13, "a case for each");
 }
 
 // (value, t) pairs ordered by value, then by smaller t.
@@ -1929,7 +1996,7 @@ __device__ __forceinline__ void fill_candidates(
         const int2 *const entries = table + (l & 1) * kNextTable;
         const Pending pending{&next_fetch, &next_first};
         if (kWhole && whole != 0) {
-            fill_quads_n(whole, cur, drec_l, first, entries, lane, pending);
+            fill_share_n<!kTodo>(whole, cur, drec_l, first, entries, lane, pending);
         } else if constexpr (inplace) {          // c_end - c <= kMax by construction
             fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs>(
                 min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, entries, tl, er, s8,
@@ -2881,7 +2948,8 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     }
     const PrepareArgs prep{2 * units, s8, B, waves, max_group, lds_small, lds_large, lds_stage,
                            kLevel ? 0 : (kNarrow ? 2 : (tiles_sure ? 3 : 1)), split ? 1 : 0, wide_waves, wide_group,
-                           lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1, meta, shifts, order, start, entry, ta};
+                           lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1,
+                           kTodo ? 0 : 1, meta, shifts, order, start, entry, ta};
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};

@@ -53,3 +53,25 @@ def test_runs_of_entries(dp, K, S, residues):
         p, c, ws = gpu_solve(dp, tau, err, B)
         assert_same(p, c, *oracle.solve_ref(tau, err, B, threads=CPU_THREADS), what)
         check_tables(dp, tau, err[K - 1], B, ws, K - 1, K)
+
+
+# one to 49 levels in up to six chunks of 64 buckets a wave and one more, for teams of eight and of two waves
+@pytest.mark.parametrize("K", [260, 1100])
+@pytest.mark.parametrize("S", [1, 3, 4, 5, 8, 9, 12, 16, 24, 48, 49])
+def test_few_levels_and_chunks(dp, K, S):
+    rng = np.random.default_rng(S * 10000 + K)
+    waves, L = (8 if K == 260 else 2), 4
+    for chunks in (1, 2, 3, 4, 6, 7):
+        B = 64 * chunks * waves - int(rng.integers(0, 3))
+        tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=max(1, B // 2), integer_err=5,
+                                                inf_err_frac=0.02, over_budget_frac=0.05)
+        tau[:, 0] = 0
+        if S > 1:
+            tau[0, 1] = B
+        err[::2] = err[::2] / np.float32(3.0) - np.float32(0.5)       # some without ties, some negative
+        what = f"K={K} S={S} B={B}"
+        print(f"[sweep] {what}", flush=True)
+        p, c, ws = gpu_solve(dp, tau, err, B)
+        assert_same(p, c, *oracle.solve_ref(tau, err, B, threads=CPU_THREADS), what)
+        for k in (0, K - 1):
+            check_tables(dp, tau, err[k], B, ws, k, K)
