@@ -27,7 +27,6 @@ __global__ __launch_bounds__(kSmallThreads) void dp_small(const int32_t *__restr
                                                           int L, int S, int B,
                                                           int16_t *__restrict__ profile,
                                                           float *__restrict__ cost,
-                                                          int32_t *__restrict__ tstar,
                                                           int32_t *__restrict__ has_table)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char small_bytes[];
@@ -39,7 +38,7 @@ __global__ __launch_bounds__(kSmallThreads) void dp_small(const int32_t *__restr
     float *prev = reinterpret_cast<float *>(table + L * S), *cur = prev + cells;
     unsigned char *const rec = reinterpret_cast<unsigned char *>(cur + cells);       // [L][cells]
     const ErrSource mine = src.of_candidate(k, L, S);
-    if (has_table && k == 0 && tid == 0)
+    if (k == 0 && tid == 0)
         *has_table = 0;                           // the workspace holds none
     for (int i = tid; i < L * S; i += threads) {
         const int l = i / S;
@@ -119,17 +118,5 @@ __global__ __launch_bounds__(kSmallThreads) void dp_small(const int32_t *__restr
         }
         if (base + lane < L)
             prof[base + lane] = (int16_t)chosen;
-    }
-    if (tstar) {                                  // as the fill leaves it: above the sum of the least times
-        int least = 0;
-        for (int l = lane; l < L; l += kWave) {
-            int m = INT32_MAX;
-            for (int s = 0; s < S; ++s)
-                m = min(m, table[l * S + s].x);
-            least += m;
-        }
-        least = from_lane(wave_scan(least, 0, Add{}), kWave - 1);
-        if (lane == 0)
-            tstar[k] = feasible ? bt - least : -1;
     }
 }

@@ -2742,12 +2742,12 @@ bool small_call(int K, int L, int S, int B)
 }
 
 int launch_small(const int32_t *tau, ErrSource src, int K, int L, int S, int B, int16_t *profile,
-                 float *cost, int32_t *tstar, int32_t *has_table, hipStream_t q)
+                 float *cost, int32_t *has_table, hipStream_t q)
 {
     (void)hipGetLastError();
     const int threads = small_row(B) < 256 ? 256 : (small_row(B) < kSmallThreads ? small_row(B) : kSmallThreads);
     hipLaunchKernelGGL(dp_small, dim3(K), dim3(threads), small_lds(L, S, B), q, tau, src, L, S, B,
-                       profile, cost, tstar, has_table);
+                       profile, cost, has_table);
     return launch_status();
 }
 
@@ -3141,7 +3141,6 @@ int solve_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B, in
         char *ws = static_cast<char *>(workspace);
         if (small_call(K, L, S, B))
             return launch_small(tau, src, K, L, S, B, profile, cost,
-                                reinterpret_cast<int32_t *>(ws + lay.tstar_off),
                                 reinterpret_cast<int32_t *>(ws + lay.meta_off) + kMetaTable,
                                 static_cast<hipStream_t>(stream));
     }
