@@ -21,13 +21,11 @@
 //
 // What bounds it: the issue of instructions, one per four clocks and SIMD, and for a few candidates the lag
 // of a tile behind the one below (store, counter, load: about one and a half layers).  A candidate of 4955
-// reduced buckets and S = 40 takes 8400 clocks a layer in one short tile, 3700 in four, 2900 in eight; one
-// of 49581 takes 21000 in four long ones.  Whole solves against one workgroup per candidate, us: K = 1,
-// L = 54, S = 40, B = 10000: 224 -> 143; K = 64: 247 -> 175; K = 128: 250 -> 199; K = 6, L = 173, S = 35,
-// B = 1500: 430 -> 318; B = 100000, K = 1: 1630 -> 430, K = 64: 1700 -> 665, K = 128: 1780 -> 1220, K = 300:
-// 3690 -> 2770; S = 100, L = 100, B = 4000, K = 60: 883 -> 305.
-// (Then, with a sweep without lane exchanges in its adds and a walk in blocks of layers: B = 10000, K = 1
-// 143 -> 131, K = 128 280 -> 253; B = 100000, K = 1 520 -> 452, K = 300 1575 -> 1356.)
+// reduced buckets and S = 40 takes 8400 clocks a layer in one short tile, 3700 in four, 2900 in eight.  Whole
+// solves by one workgroup per candidate and so, us (all other parts the same): K = 1, L = 54, S = 40, B = 10000 216
+// and 129; K = 64 221 and 145; K = 128 225 and 171; K = 6, L = 173, S = 35, B = 1500 337 and 271; B = 100000, K = 1
+// 1326 and 352, K = 64 1404 and 558, K = 128 1501 and 1046, K = 300 3134 and 2363; S = 100, L = 100, B = 4000, K = 60
+// 802 and 223.
 
 constexpr int kTileThreads = kTileWaves * kWave;
 constexpr int kTileEarly = 8;        // waves that fetch the apron of a long tile

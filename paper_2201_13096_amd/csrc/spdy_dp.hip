@@ -23,8 +23,9 @@
 //     buckets and reads them with one aligned ds_read_b128 (twice the LDS bytes per clock of
 //     narrower reads on this chip); entries are visited by their shift modulo four, and the minima
 //     are kept shifted by that, so that no add needs a word from another lane (sweep_layer).
-//     Otherwise lane i works on bucket 64*c + i of a chunk: every ds_read_b32 of the shifted row
-//     touches 64 consecutive dwords (conflict-free for any shift);
+//     Otherwise, and in short rows of few levels (sweep_tails), lane i works on bucket 64*c + i of a
+//     chunk: every ds_read_b32 of the shifted row touches 64 consecutive dwords (conflict-free for
+//     any shift);
 //   * the waves of a workgroup are split at run time into teams, one candidate per team, so
 //     that each wave owns as many chunks as its registers hold whatever the reduced row length
 //     is; when every wave holds all its chunks of the row in registers the row is updated in
@@ -120,9 +121,10 @@ __host__ __device__ constexpr int quad_share(int t, int quads)
 static_assert(kMaxFillWaves * kMaxGroupTurns * kWave / 4 < 1 << 20, "rows updated in place");
 // Or a share of ordinary chunks alone, where a wave has few of them and few levels (see sweep_tails): up to
 // kFewChunks, and kFewUpdates of levels and chunks.  us a solve with quad chunks and entries from LDS, and so:
-// K = 1500, L = 66, S = 8, B = 300 149 and 131, B = 586 163 and 138; K = 400, L = 60, B = 1500 147 and 123; S = 20,
-// K = 1500, B = 586 172 and 151, K = 1200, L = 93, B = 1132 261 and 231; S = 40, K = 1500, B = 300 180 and 162.  Of 254 calls
-// around the line none is more than 0.7 % slower; with twice the updates S = 32 and 40 are up to 4 %.
+// K = 1500, L = 66, S = 8, B = 300 149 and 131, B = 586 163 and 138; K = 400, L = 60, B = 1500 147 and 123;
+// S = 20, K = 1500, B = 586 172 and 151, K = 1200, L = 93, B = 1132 261 and 231; S = 40, K = 1500, B = 300 180
+// and 162.  Of 254 calls around the line none is more than 0.7 % slower; with twice the updates S = 32 and 40
+// are up to 4 %.
 constexpr int kFewChunks = 6, kFewUpdates = 120;
 __host__ __device__ constexpr int tail_share(int t, int chunks)
 {
@@ -321,7 +323,8 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
                       apron < 1 << 20 &&
                       lines + min(L, kTileLayers) * (2LL * s8 + 1) + 4 <= ta.lds;
     // Clocks, fitted to measured fills (a lone S = 40 candidate of 4955 buckets in 1, 2, 4, 8 short
-    // tiles: 8400, 5900, 3700, 2900 a layer; one of 49581 in 3, 4, 6, 8 long ones: 26300, 21000, 17300, 13000).
+    // tiles: 8400, 5900, 3700, 2900 a layer; one of 49581 in 3, 4, 6, 8 long ones, with a sweep that took a
+    // seventh longer than the present one: 26300, 21000, 17300, 13000).
     // A SIMD issues an instruction every four clocks or so, whichever of its waves it is from.
     const float pairs = 0.42f * S;                // entries are fewer than levels
     const float of_simd = (float)((units + 3) / 4), waves_of_simd = (float)((min(waves, units) + 3) / 4);
@@ -345,8 +348,10 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
     for (int off = 1; off < kWave; off <<= 1)
         best = fminf(best, __shfl_xor(best, off, kWave));
     const unsigned long long set = __ballot(fits && clocks == best);
-    // rows in memory, one workgroup per candidate: 21 updates a clock (K = 200: 1.90 ms, 2.10 in tiles;
-    // K = 300: 3.69 and 2.79; K = 1000: 7.47 and 8.10)
+    // Rows in memory, one workgroup per candidate: 21 updates a clock.  ms a solve of L = 54, S = 40 so and in
+    // tiles, B = 10^5: K = 140 1.50 and 1.18, K = 200 1.56 and 1.77, K = 300 3.14 and 2.34, K = 512 3.47 and
+    // 3.68, K = 1000 6.87 and 7.01; B = 60000: 1.04 and 0.83, 1.07 and 0.97 (not taken), 2.05 and 1.60, 2.16
+    // and 2.21, 4.31 and 4.21.
     const float untiled = (float)((K + ta.units - 1) / ta.units) * L *
                           (1500.0f + row_chunks * pairs * 6.15f);
     const bool tiled = set != 0 && (ta.only_memory == 0 || best < untiled);
@@ -1341,7 +1346,8 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
 }
 
 // One group of one layer (D record, at most 64 levels), Q quad chunks and T ordinary ones from bucket
-// `tail0` of the group on: sweep with 128-bit reads, store the record, write the new row values; the barrier protocol is fill_group's.
+// `tail0` of the group on: sweep with 128-bit reads, store the record, write the new row values; the barrier
+// protocol is fill_group's.
 // prev + t0 is 16-byte aligned (rows, aprons and chunk starts are multiples of four floats).
 // kSplit (in place only): this wave has a twin in the other half of the workgroup with the same
 // group; the two visit alternate pairs of the layer's entries, the second half (`half` = 1)
@@ -2705,19 +2711,21 @@ bool core_params(int L, int S, int B, long long workgroups, int units, CoreParam
 
 // Where the full table is taken at once: tables of a handful of layers with short rows are through it
 // before dp_core is through its dozen passes.
-//   - Whatever the call, up to 256 candidates, in 0.1 us of latency: the table 1.2 us a layer for its
-//     barriers, 0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a
-//     layer.  K = 1, L = 4, S = 10, B = 4351: 20 us with the table, 29 with dp_core; K = 3, L = 5, S = 54,
-//     B = 382: 27 and 40; four budgets, K = 61, L = 8, S = 51, B = 420: 41 and 61; L = S = 8, B = 256: 22 and
-//     22 - 23.
-//   - Where one fill and one walk back are all that the table takes, more candidates, too: the slowest
-//     of them sets dp_core's time, the table's hardly grows.  Of 631 drawn calls (L = 4 - 200) 58 were more
-//     than 5 % slower than the better side without this line, 36 are with it.  K = 2247, L = 8, S = 10,
-//     B = 982: 52 and 84; K = 428, L = 6, S = 16, B = 134: 31 and 41; K = 188, L = 9, S = 15, B = 15627: 58
-//     and 77.  (Not for a call that resumes from an incumbent: it may only be direct where the incumbent's
-//     call, K = 1, was whatever entry point that went through, or there are no rows to take and every
-//     candidate is filled from layer 0.  The first line is one of the sizes alone and holds for K = 1 where it
-//     holds for K.)
+//   - Whatever the call, up to 256 candidates, in 0.1 us of latency: the table 1.2 us a layer for its barriers,
+//     0.7 us for its hop of the walk back, 5000 updates in 0.1 us; dp_core 14 us and 0.6 us a layer (as both
+//     were when the line was drawn).  us with the table and with dp_core, now: K = 1, L = 4, S = 10, B = 4351
+//     22 and 25; K = 3, L = 5, S = 54, B = 382 24 and 24; K = 200, L = 8, S = 20, B = 1000 24 and 28; four
+//     budgets, K = 61, L = 8, S = 51, B = 420 30 and 34; beyond the line K = 1, L = 8, S = 30, B = 1500 26 and
+//     24, S = 40, B = 2000 31 and 23, K = 200, L = 12, S = 8, B = 500 24 and 25.
+//   - Where one fill and one walk back are all that the table takes, more candidates, too: the slowest of them
+//     sets dp_core's time, the table's hardly grows.  Of 631 drawn calls (L = 4 - 200) 58 were more than 5 %
+//     slower than the better side without this line, 36 are with it.  Now K = 2247, L = 8, S = 10, B = 982 41
+//     and 76; K = 428, L = 6, S = 16, B = 134 24 and 28; K = 1000, L = 9, S = 12, B = 2000 38 and 44; and on
+//     the other side of where the line would lie today, K = 188, L = 9, S = 15, B = 15627 52 and 48, K = 300,
+//     L = 9, S = 30, B = 1000 38 and 31, K = 2000, L = 10, S = 12, B = 1000 42 and 65 (not taken).  (Not for a
+//     call that resumes from an incumbent: it may only be direct where the incumbent's call, K = 1, was
+//     whatever entry point that went through, or there are no rows to take and every candidate is filled from
+//     layer 0.  The first line is one of the sizes alone and holds for K = 1 where it holds for K.)
 bool table_is_short(int K, int L, int S, int B, bool one_fill)
 {
     const long long updates = (long long)L * S * (B + 1LL);
@@ -2922,10 +2930,11 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
 
-    // Several workgroups per candidate, or one with less to do between the layers (see dp_tiles.h): where
-    // each has two compute units, and up to one per unit where rows are short (B = 8000 of S = 40, K = 256:
-    // 224 us and 234 otherwise; B = 1000: 107 and 156; B = 10000: 262 and 256); and where rows may have to lie
-    // in memory otherwise.
+    // Several workgroups per candidate, or one with less to do between the layers (see dp_tiles.h): where each
+    // has two compute units, and up to one per unit where rows are short (K = 256, L = 54, us so and by a
+    // workgroup with all of its waves on one candidate: S = 40, B = 1000 71 and 123, B = 4000 132 and 164,
+    // B = 8000 199 and 208, B = 10000 240 and 235, B = 16000 294 and 300; S = 20, B = 8000 159 and 173,
+    // B = 10000 189 and 191, B = 16000 223 and 234); and where rows may have to lie in memory otherwise.
     const bool tiles_do = can_tile && !resume.first_layer &&
                           (2LL * K <= units || (K <= units && B <= kTileLone));
     const bool tiles_sure = tiles_do && B <= (kNarrow ? kTileSure : kTileSureWide);
@@ -3071,6 +3080,11 @@ void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const f
     // B = 10^4: K = 1 33.2 and 21.0, K = 128 35.9 and 25.1, K = 256 47.4 and 32.3; beyond, workgroups would
     // queue for units.  (Behind dp_core hardly any candidate is left to walk.  Copies are of 16 bytes: a record
     // that does not lie so is walked entry by entry.)
+    // The price: it waits for a unit whose LDS is free, where four waves without LDS would start beside a fill
+    // of another stream.  us a step, the walk of one step beside the fill of the next, four waves and so:
+    // K = 64 165 and 137, K = 100 155 and 166, K = 192 211 and 225, K = 256 258 and 234; K = 200, L = 30,
+    // S = 100, B = 12000 326 and 473.  On one stream: 169 and 142, 194 and 168, 251 and 231, 253 and 236, 352
+    // and 345.
     auto whole = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
     if (!todo.profile && K * (long long)budgets <= units && whole(drec) && whole(resume.inc_rec)) {
         auto alone = S <= kWave ? dp_backtrace_alone<1, false> : dp_backtrace_alone<4, false>;
