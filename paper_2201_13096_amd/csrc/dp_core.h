@@ -284,6 +284,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
             picks[layer] = make_int2(-1, -1);
         const int share = 1 << cp.share_log2, of_wave = lane & (share - 1);
         const int levels = ((S + share - 1) / share + 3) & ~3;       // of a lane
+        const unsigned long long before = ((1ull << of_wave) - 1ull) << (lane - of_wave);   // lanes of the same layer
         float lam_lo = 0.0f, lam_hi = __builtin_inff();
         for (int trip = 0; trip < 40; ++trip) {
             lambda_f = fmaxf(c_hi - c_lo, 0.0f) * __builtin_amdgcn_rcpf((float)(t_lo - t_hi));
@@ -347,13 +348,13 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
                     found.x = is ? one.x : found.x;
                     found.y = is ? one.y : found.y;
                 }
-                pick[b] = place;
+                pick[b] = layer_b < L ? place : -1;
                 if (__builtin_amdgcn_readfirstlane(share) > 1) {    // (see group_join)
                     const unsigned own = magnitude(least_b);
-                    pick[b] = own == group_join(own, share, Smaller{}) ? place : INT32_MAX;
-                    pick[b] = group_join(pick[b], share, Smaller{});
+                    const bool is = own == group_join(own, share, Smaller{});
+                    pick[b] = is && !(__ballot(is) & before) ? pick[b] : -1;
                 }
-                const bool counts = layer_b < L && place == pick[b];
+                const bool counts = pick[b] >= 0;
                 ce += counts ? found.x : 0.0f;
                 ct += counts ? (int)found.y : 0;
             }
@@ -395,7 +396,7 @@ __device__ __forceinline__ void solve_core(const int32_t *__restrict__ tau, cons
 #pragma unroll
             for (int b = 0; b < kCoreMaxLayers / kWave; ++b) {
                 const int layer_b = b * kWave + (lane >> cp.share_log2);
-                if (b * kWave < L && layer_b < L && of_wave == 0) {
+                if (b * kWave < L && pick[b] >= 0) {
                     if (wave == lo_wave)
                         picks[layer_b].x = min(pick[b], S - 1);
                     if (wave == hi_wave)
