@@ -31,11 +31,11 @@
 // 13 (single exchanges, then pairs of them), survivors 7, then dependent steps for the reduced table 15
 // (nine of them, 20 to 45 for the slowest candidates), walk back 5.
 // us a call, mean of eight sets of inputs; with one multiplier a pass, exchanges one at a time and only rows of
-// one chunk in a register, and now: K = 250 from an incumbent 75 and 46; K = 100, L = 52, S = 42, B = 10^4 123
-// and 84 (without the worst of the eight 92 and 77); 384 solves under six budgets 76 and 53; K = 4096, L = 72,
-// S = 40, B = 16384 295 and 235; K = 333, S = 127 106 and 71; K = 256, L = 200, S = 64, B = 65536 388 and 216.
-// The whole table takes 239 (resumed), 213, 184, 3130, 903 and 3830.  (The stamps are from before whole values
-// were compared in the multiplier's passes, which takes as long.)
+// one chunk in a register, and now: K = 250 from an incumbent 75 and 47; K = 100, L = 52, S = 42, B = 10^4 93
+// and 85; 384 solves under six budgets 74 and 52; K = 4096, L = 72, S = 40, B = 16384 291 and 236; K = 333,
+// S = 127 109 and 68; K = 256, L = 200, S = 64, B = 65536 389 and 214.  The whole table takes 239 (resumed), 213,
+// 184, 3130, 903 and 3830.  (The stamps are from before whole values were compared in the multiplier's
+// passes, which takes as long.)
 
 constexpr int16_t kGivenUp = -3;         // profile[0] of a candidate the full table has to solve
 constexpr int kCoreThreads = 256;
