@@ -1,5 +1,5 @@
 """The reduced problem's multiplier and known profile (csrc/dp_core.h) at the sizes where their mapping
-changes: lanes per layer and blocks of 64 layers, places of a level in three to eight bits, lists of
+changes: lanes per layer and blocks of 64 layers, levels of a lane that are no whole number of eight, lists of
 exchanges that are empty, that need two registers a lane, and that do not fit."""
 import numpy as np
 import pytest

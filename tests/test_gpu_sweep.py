@@ -23,7 +23,8 @@ def dp():
 @pytest.mark.parametrize("row", [64, 252, 504, 1008, 1260, 2016, 3528, 5040, 7056, 13300])
 def test_rows_around_whole_quad_chunks(dp, K, row):
     rng = np.random.default_rng(100 * row + K)
-    for B, S in ((row - 2, 13), (row - 1, 8), (row, 3)):
+    # (rows of up to six chunks a wave only take quad chunks if levels times chunks are more than 120)
+    for B, S in ((row - 2, 13), (row - 1, 8), (row, 3), (row - 1, 64), (row, 41)):
         L = 4
         tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=max(1, B // 2), integer_err=5,
                                                 inf_err_frac=0.02)
