@@ -22,7 +22,9 @@
 //   * when D itself is recorded and a layer has at most 64 levels, a lane takes four consecutive
 //     buckets and reads them with one aligned ds_read_b128 (twice the LDS bytes per clock of
 //     narrower reads on this chip); entries are visited by their shift modulo four, and the minima
-//     are kept shifted by that, so that no add needs a word from another lane (sweep_layer).
+//     are kept shifted by that, so that no add needs a word from another lane (sweep_layer);
+//   * the level record, and the D record of more than 64 levels, have four buckets a lane that lie a
+//     quarter of the row apart, side by side in LDS, where there are two workgroups to a unit (dp_columns).
 //     Otherwise, and in short rows of few levels (sweep_tails), lane i works on bucket 64*c + i of a
 //     chunk: every ds_read_b32 of the shifted row touches 64 consecutive dwords (conflict-free for
 //     any shift);
@@ -45,6 +47,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "spdy_dp.h"
 
@@ -133,7 +136,7 @@ __host__ __device__ constexpr int tail_share(int t, int chunks)
 static_assert(kMaxQuads + kFewChunks < 1 << 4, "four bits of the word");
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
-constexpr int kMetaHeader = 20;      // int32 words before the per-layer arrays
+constexpr int kMetaHeader = 21;      // int32 words before the per-layer arrays
 // meta: header | m_l [L] | chunks of row l [L] | chunk boundaries of the team waves [L][stride]
 //       | largest usable shift of layer l [L]
 constexpr int kRangeStride = kMaxFillWaves + 1;
@@ -164,10 +167,56 @@ enum MetaWord {
     kMetaLdsWide = 16,   // its dynamic LDS bytes
     kMetaGlobalWaves = 17, // waves of the global-row launch
     kMetaTable = 18,    // 1: the call leaves the whole table in the record (0: scratch)
-    kMetaTiles = 19     // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
+    kMetaTiles = 19,    // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
+    kMetaColumns = 20   // buckets of a position, 4 or 1, where dp_columns is the launch of path 1 (see there)
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
+
+// dp_columns (see there): chunks of 64 positions that a wave holds at most, and of 64 buckets where the row is not
+// folded; candidates of a workgroup at most; entries that are read behind the last of a table, and not used.
+enum Columns { kNoColumns = 0, kValueColumns = 1, kLevelColumns = 2 };       // which record it is enqueued for
+template <bool kLevel> constexpr int column_chunks() { return kLevel ? 5 : 7; }
+constexpr int kPlainChunks = 6;
+constexpr int kFoldLevels = 16, kFoldBudget = 800, kFoldWork = 300;   // least, level record
+constexpr int kColumnTeams = 8;
+constexpr int kLookAhead = 4;
+// Whether a row of `n` chunks is better not folded, `tw` waves to a row: where whole chunks of positions are more
+// than what the wider reads save.
+__device__ __forceinline__ bool plain_is_better(int n, int tw)
+{
+    const int plain = (n + tw - 1) / tw, folded = ((n + 3) / 4 + tw - 1) / tw;
+    return plain <= kPlainChunks && 40 * folded > 14 * plain;
+}
+// Floats of LDS: of a candidate's row, ghost or apron included, and with its entries of two layers.
+__device__ __forceinline__ int column_row(int n, int tw, bool plain)
+{
+    const int n4 = (n + 3) / 4;
+    return plain ? (n + (n + tw - 1) / tw) * kWave : 4 * (kWave * (n4 + (n4 + tw - 1) / tw) + 1);
+}
+__device__ __forceinline__ int column_entries(int S) { return (S + kWave - 1) / kWave * kWave + kLookAhead; }
+__device__ __forceinline__ int column_floats(int n, int tw, bool plain, int S, bool level)
+{
+    return column_row(n, tw, plain) + 2 * (level ? 3 : 2) * column_entries(S);
+}
+// Teams and fold of a row of `n` chunks, at most `teams` of them: as many as their rows have LDS and registers for.
+__device__ __forceinline__ int plan_columns(int n, int S, bool level, int teams, bool *plain)
+{
+    const int most = level ? column_chunks<true>() : column_chunks<false>();
+    for (teams = min(teams, kColumnTeams);; --teams) {
+        const int tw = kFillWaves / teams;
+        *plain = plain_is_better(n, tw);
+        if (teams == 1 || ((*plain || ((n + 3) / 4 + tw - 1) / tw <= most) &&
+                           teams * column_floats(n, tw, *plain, S, level) * (int)sizeof(float) <= kLdsHalf))
+            return teams;
+    }
+}
+// one team: any row that a workgroup of either record may have in place, with all the entries there may be
+static_assert(kFillWavesLevel * kMaxGroupLevel <= 4 * kFillWaves * column_chunks<true>() &&
+                  kFillWaves * kMaxGroupTurns <= 4 * kFillWaves * column_chunks<false>() &&
+                  (4 * (kWave * (kFillWaves + 1) * column_chunks<false>() + 1) + 2 * 3 * (256 + kLookAhead)) * 4 <=
+                      kLdsHalf, "rows in place fit dp_columns");
+
 
 // ---------------------------------------------------------------------------------------------
 // Workspace layout (host side, shared by every entry point)
@@ -373,7 +422,7 @@ __device__ __forceinline__ void plan_tiles(int K, int L, int S, int bp, int chun
 __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots, int L, int S,
                                int B, int waves, int max_group, int lds_small, int lds_large,
                                int lds_stage, int split, int wide_waves, int wide_group,
-                               int lds_wide, int global_waves, bool quads, bool tails, const TileArgs &ta,
+                               int lds_wide, int global_waves, bool quads, bool tails, int columns, const TileArgs &ta,
                                int32_t *words, int32_t *__restrict__ meta)
 {
     __shared__ long long s_sum[8];
@@ -526,6 +575,14 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
                     teams = spread;
             }
         }
+        int cells = 0;                            // of a position
+        if (columns != kNoColumns && path == 1 && bp >= 0) {
+            bool plain;
+            teams = plan_columns((int)(((reach < bp ? reach : bp) + kWave) / kWave), S,
+                                 columns == kLevelColumns, teams, &plain);
+            cells = plain ? 1 : 4;
+        }
+        meta[kMetaColumns] = cells;
         meta[kMetaPath] = path;
         meta[kMetaTeams] = teams;
         meta[kMetaTeamWaves] = plan_waves / teams;
@@ -684,7 +741,7 @@ __device__ void prepare_order(const int32_t *__restrict__ tau, int l, int S, int
 
 struct PrepareArgs {
     int slots, s8, B, waves, max_group, lds_small, lds_large, lds_stage, sorted, split;
-    int wide_waves, wide_group, lds_wide, global_waves, table, tails;
+    int wide_waves, wide_group, lds_wide, global_waves, table, tails, columns;
     int32_t *meta, *shifts, *order, *start, *entry_of;
     TileArgs tiles;
 };
@@ -698,7 +755,7 @@ __device__ __forceinline__ void prepare(const int32_t *__restrict__ tau, int K, 
     if (block == 0)
         prepare_budget(tau, K, a.slots, L, S, a.B, a.waves, a.max_group, a.lds_small, a.lds_large,
                        a.lds_stage, a.split, a.wide_waves, a.wide_group, a.lds_wide,
-                       a.global_waves, a.sorted == 2, a.tails != 0, a.tiles, words, a.meta);
+                       a.global_waves, a.sorted == 2, a.tails != 0, a.columns, a.tiles, words, a.meta);
     else
         prepare_order(tau, block - 1, S, a.s8, a.sorted, a.shifts, a.order, a.start, a.entry_of,
                       words);
@@ -1151,7 +1208,6 @@ __device__ __forceinline__ float from_left(float x)
 // Two entries of a table in LDS (shift, error, and again), one read wherever the first of them lies.
 // Shifts are in bytes, but in buckets where a row is read from memory (kBuckets): bytes would pass 2^31.
 // (Two values of their own the compiler fetches one at a time, the second where it is needed.)
-constexpr int kLookAhead = 4;        // entries read behind the last one of a table, and not used
 typedef int EntryPair __attribute__((ext_vector_type(4), aligned(8)));
 
 // The entries of one residue that a group can use: `n` consecutive ones from `at` on, of which the
@@ -1586,6 +1642,7 @@ __device__ __forceinline__ void write_result(float bv, int bt, int k, int32_t *t
 }
 
 #include "dp_small.h"
+#include "dp_columns.h"
 
 // ---------------------------------------------------------------------------------------------
 // Walk back through the D record: one wave per candidate.  At (l, t) the lanes try the levels in parallel: lane s
@@ -1787,7 +1844,7 @@ __device__ __forceinline__ void fill_candidates(
         return;                                  // the first ceil(K / teams) workgroups suffice
     if constexpr (kTodo) {
         bool any = false;
-        for (int i = 0; i < teams && blockIdx.x * teams + i < (unsigned)K; ++i)
+        for (int i = 0; i < teams && blockIdx.x * teams + i < K; ++i)
             any |= todo.has_wave(blockIdx.x * teams + i, K, L);
         if (!any)
             return;                              // solved already
@@ -2882,6 +2939,17 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
              : need > (size_t)kLdsBytes;
     auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, true, false, kPairs>
                           : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, false, kPairs>;
+    // Two workgroups to a unit, whose rows are folded for wide reads (dp_columns).  The level record only with
+    // something to sweep, and not many candidates of few levels and layers, of which a unit has room for fewer: us a
+    // solve by dp_fill and so, S = 12, L = 82, B = 920, K = 2655 386 and 452; S = 38, L = 11, B = 423, K = 4029 136
+    // and 142; S = 70, L = 86, B = 304, K = 331 505 and 566; S = 25, L = 10, B = 2516, K = 3284 163 and 202; S = 17,
+    // L = 14, B = 3357, K = 1144 126 and 137; and where it is taken S = 16, L = 124, B = 1585, K = 1534 691 and 646;
+    // S = 35, L = 37, B = 833, K = 1378 246 and 191; S = 20, L = 9, B = 1396, K = 312 55 and 43; S = 33, L = 19,
+    // B = 3271, K = 1890 269 and 244.
+    constexpr bool can_fold = (!kNarrow || (kLevel && kPairs)) && !kBlocks && !kTodo;
+    const bool columns = can_fold && K > units && !resume.first_layer &&
+                         (!kLevel || (S >= kFoldLevels && B >= kFoldBudget &&
+                                      (K <= 4 * (long long)units || L * S >= kFoldWork)));
     // A candidate that has a compute unit to itself gets twice the waves (the second half takes
     // every other pair of each layer's entries and needs a second row in LDS for its minima).
     constexpr bool can_split = !kLevel && kNarrow && !kBlocks;       // (behind dp_core: dp_rest)
@@ -2958,7 +3026,8 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     const PrepareArgs prep{2 * units, s8, B, waves, max_group, lds_small, lds_large, lds_stage,
                            kLevel ? 0 : (kNarrow ? 2 : (tiles_sure ? 3 : 1)), split ? 1 : 0, wide_waves, wide_group,
                            lds_wide, global_waves, kBlocks || core || resume.first_layer ? 0 : 1,
-                           kTodo ? 0 : 1, meta, shifts, order, start, entry, ta};
+                           kTodo ? 0 : 1, !columns ? kNoColumns : (kLevel ? kLevelColumns : kValueColumns),
+                           meta, shifts, order, start, entry, ta};
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
@@ -3002,7 +3071,15 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     }
     if (tiles_sure)
         return launch_status();
-    if (!kNarrow || !tiles_do)
+    if constexpr (can_fold) {
+        if (columns) {
+            auto folded = turns ? dp_columns<kLevel, true, kNarrow ? 1 : 4>
+                                : dp_columns<kLevel, false, kNarrow ? 1 : 4>;
+            hipLaunchKernelGGL(folded, dim3(K), dim3(kFillWaves * kWave), kLdsHalf, q, src, meta, tables, units,
+                               K, L, S, pitch, choice, drec, tstar, cost);
+        }
+    }
+    if (!columns && (!kNarrow || !tiles_do))
         hipLaunchKernelGGL(in_place, dim3(K), dim3(place_threads), place_lds, q, src, meta, tables,
                            units, K, L, S, pitch, choice, drec, rows, tstar, cost, resume, blocks,
                            todo);
