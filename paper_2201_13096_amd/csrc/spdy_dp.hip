@@ -1245,7 +1245,10 @@ __device__ __forceinline__ EntryRun entry_run(const int2 *entries, unsigned long
 // they cost 28 clocks of the pipe that the mins need, more than four quads of mins do.  That pipe takes four
 // clocks for any instruction but fp32 adds and multiplies of vector registers only, which have a
 // second one (v_min3 4.0 clocks of a SIMD, v_add 2.0, v_add with a scalar or a lane to the left 4.0).
-template <int Q, int T, int kRes, bool kSplit, bool kBuckets>
+// kBatched: all quads of a pair are asked for before the first of them is used.  Where the compiler asks for them one by
+// one, and few waves are there to wait in turn, a fill of few candidates takes a fifth longer (eleven of 1024 that
+// the reduced problem gives up: 399 us a call and 338); with all waves there it is the same.
+template <int Q, int T, int kRes, bool kSplit, bool kBuckets, bool kBatched>
 __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tail,
                                           EntryRun run, float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
 {
@@ -1266,12 +1269,27 @@ __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tai
         const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
         if constexpr (Q > 0) {
             const float4v *q0 = quads_at(now.x), *q1 = quads_at(now.z);
+            if constexpr (kBatched) {
+                float4v v0[Q], v1[Q];
 #pragma unroll
-            for (int j = 0; j < Q; ++j) {
-                const float4v v0 = q0[j * kQuadLanes], v1 = q1[j * kQuadLanes];
+                for (int j = 0; j < Q; ++j) {
+                    v0[j] = q0[j * kQuadLanes];
+                    v1[j] = q1[j * kQuadLanes];
+                }
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    vmin3(bq[j][c], v0[c] + e0, v1[c] + e1);
+                for (int j = 0; j < Q; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        vmin3(bq[j][c], v0[j][c] + e0, v1[j][c] + e1);
+            } else {
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const float4v v0 = q0[j * kQuadLanes], v1 = q1[j * kQuadLanes];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        vmin3(bq[j][c], v0[c] + e0, v1[c] + e1);
+                }
             }
         }
         if constexpr (T > 0) {
@@ -1345,7 +1363,7 @@ __device__ __forceinline__ void sweep_tails(const float *tail, const int2 *entri
 // lane in every add, as before, took the slow pipe.  What lane 0 gets from the left ends in buckets that are not
 // its own and never reaches lane 1.
 // kAhead: the first entries of all four runs are asked for at once (registers permitting).
-template <int Q, int T, bool kSplit, bool kAhead, bool kBuckets>
+template <int Q, int T, bool kSplit, bool kAhead, bool kBuckets, bool kBatched = false>
 __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *tail,
                                             const int2 *entries, LevelEntry mine, int last_bucket,
                                             int half, float (&bq)[Q > 0 ? Q : 1][4],
@@ -1389,16 +1407,16 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
             bq[j][0] = carry;
         }
     };
-    sweep_run<Q, T, 3, kSplit, kBuckets>(quads, tail, run3, bq, bt);
+    sweep_run<Q, T, 3, kSplit, kBuckets, kBatched>(quads, tail, run3, bq, bt);
     next_residue();
     later(run2);
-    sweep_run<Q, T, 2, kSplit, kBuckets>(quads, tail, run2, bq, bt);
+    sweep_run<Q, T, 2, kSplit, kBuckets, kBatched>(quads, tail, run2, bq, bt);
     next_residue();
     later(run1);
-    sweep_run<Q, T, 1, kSplit, kBuckets>(quads, tail, run1, bq, bt);
+    sweep_run<Q, T, 1, kSplit, kBuckets, kBatched>(quads, tail, run1, bq, bt);
     next_residue();
     later(run0);
-    sweep_run<Q, T, 0, kSplit, kBuckets>(quads, tail, run0, bq, bt);
+    sweep_run<Q, T, 0, kSplit, kBuckets, kBatched>(quads, tail, run0, bq, bt);
 }
 
 // One group of one layer (D record, at most 64 levels), Q quad chunks and T ordinary ones from bucket
@@ -1411,7 +1429,8 @@ __device__ __forceinline__ void sweep_layer(const float4v *quads, const float *t
 // folds them into its own behind it.  min is exact and order-blind here, so the row is the one
 // a single wave would have computed.
 // kTails: sweep_tails does it.
-template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead, bool kBuckets, bool kTails = false>
+template <int Q, int T, int tail0, bool inplace, bool kSplit, bool kAhead, bool kBuckets, bool kBatched,
+          bool kTails = false>
 __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, float *rec,
                                                  LevelEntry first, const int2 *entries, int t0,
                                                  int lane, Pending pending, int half, float *part)
@@ -1439,7 +1458,7 @@ __device__ __forceinline__ void fill_group_quads(const float *prev, float *cur, 
         if constexpr (kTails)
             sweep_tails<T>(tail, entries, first.shift, last, lane, bt);
         else
-            sweep_layer<Q, T, kSplit, kAhead, kBuckets>(quads, tail, entries, first, last, half, bq, bt);
+            sweep_layer<Q, T, kSplit, kAhead, kBuckets, kBatched>(quads, tail, entries, first, last, half, bq, bt);
         pending.settle();
         const int tq = t0 + 4 * (lane - 1);       // this lane's first bucket of quad chunk 0
         const int tt = t0 + tail0 + lane;
@@ -1535,7 +1554,8 @@ __device__ __forceinline__ void fill_group(const float *prev, float *cur, uint8_
     }
 }
 
-template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kAhead, bool kBuckets, bool kPairs>
+template <bool kLevel, bool inplace, int kMax, bool kQuads, bool kSplit, bool kAhead, bool kBuckets, bool kPairs,
+          bool kBatched>
 __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cur, uint8_t *choice,
                                              float *rec, LevelEntry first, const int2 *entries,
                                              LayerTable tl, ErrRow er, int s8, int t0, int lane,
@@ -1548,7 +1568,7 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
         if constexpr (RR <= kMax) {                                                            \
             if constexpr (kQuads)                                                              \
                 fill_group_quads<quad_chunks(RR), tail_chunks(RR), (RR - tail_chunks(RR)) * kWave, \
-                                 inplace, kSplit, kAhead, kBuckets>(                           \
+                                 inplace, kSplit, kAhead, kBuckets, kBatched>(                 \
                     prev, cur, rec, first, entries, t0, lane, pending, half, part);            \
             else                                                                               \
                 fill_group<RR, kLevel, inplace, kPairs>(prev, cur, choice, rec, first, tl, er, s8, t0, \
@@ -1589,7 +1609,7 @@ __device__ __forceinline__ void fill_group_n(int r, const float *prev, float *cu
 }
 
 // The same in place for a share of whole quad chunks, or (kTails) of ordinary ones.
-template <bool kTails>
+template <bool kTails, bool kBatched>
 __device__ __forceinline__ void fill_share_n(int share, float *row, float *rec, LevelEntry first,
                                              const int2 *entries, int lane, Pending pending)
 {
@@ -1598,10 +1618,10 @@ __device__ __forceinline__ void fill_share_n(int share, float *row, float *rec, 
 #define SPDY_CASE(NN)                                                                          \
     case NN:                                                                                   \
         if constexpr (NN <= kMaxQuads)                                                         \
-            fill_group_quads<NN, 0, 0, true, false, true, false>(                              \
+            fill_group_quads<NN, 0, 0, true, false, true, false, kBatched>(                    \
                 row, row, rec, first, entries, t0, lane, pending, 0, nullptr);                 \
         else if constexpr (kTails)                                                             \
-            fill_group_quads<0, NN - kMaxQuads, 0, true, false, false, false, true>(           \
+            fill_group_quads<0, NN - kMaxQuads, 0, true, false, false, false, kBatched, true>( \
                 row, row, rec, first, entries, t0, lane, pending, 0, nullptr);                 \
         break;
         SPDY_CASE(0)
@@ -1844,7 +1864,7 @@ __device__ __forceinline__ void fill_candidates(
         return;                                  // the first ceil(K / teams) workgroups suffice
     if constexpr (kTodo) {
         bool any = false;
-        for (int i = 0; i < teams && blockIdx.x * teams + i < K; ++i)
+        for (int i = 0; i < teams && blockIdx.x * teams + i < (unsigned)K; ++i)
             any |= todo.has_wave(blockIdx.x * teams + i, K, L);
         if (!any)
             return;                              // solved already
@@ -2059,9 +2079,9 @@ __device__ __forceinline__ void fill_candidates(
         const int2 *const entries = table + (l & 1) * kNextTable;
         const Pending pending{&next_fetch, &next_first};
         if (kWhole && whole != 0) {
-            fill_share_n<!kTodo>(whole, cur, drec_l, first, entries, lane, pending);
+            fill_share_n<!kTodo, kTodo>(whole, cur, drec_l, first, entries, lane, pending);
         } else if constexpr (inplace) {          // c_end - c <= kMax by construction
-            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs>(
+            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs, kTodo>(
                 min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, entries, tl, er, s8,
                 c * kWave, lane, pending, half, part);
         } else {
@@ -2103,7 +2123,7 @@ __device__ __forceinline__ void fill_candidates(
                     __syncthreads();
                     const int cb = c0 + (int)((long long)share * nt / tw);
                     const int ce = c0 + (int)((long long)(share + 1) * nt / tw);
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, false, kPairs>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, false, kPairs, kTodo>(
                         ce - cb, lds - lo, cur, choice_l, drec_l, first, entries, tl, er, s8,
                         cb * kWave, lane, pending);
                     __syncthreads();             // the next tile overwrites the staged part
@@ -2113,7 +2133,7 @@ __device__ __forceinline__ void fill_candidates(
                     const int n = c_end - c;
                     const int groups = (n + kMax - 1) / kMax;
                     const int r = (n + groups - 1) / groups;
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kGlobal, kPairs>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kGlobal, kPairs, kTodo>(
                         r, prev, cur, choice_l, drec_l, first, entries, tl, er, s8, c * kWave, lane,
                         pending);
                     c += r;
@@ -2233,6 +2253,31 @@ __global__ __launch_bounds__(256) void dp_budget_argmin(const int32_t *__restric
     }
 }
 
+// The same for candidate k by one wave, which gets the time in every lane.
+__device__ __forceinline__ int budget_time(const int32_t *__restrict__ meta, const float *__restrict__ drec, int k,
+                                           int L, int pitch, int budget)
+{
+    const int lane = threadIdx.x & (kWave - 1), bp = meta[kMetaBudget];
+    if (bp < 0)
+        return -1;
+    const long long reduced = (long long)budget - meta[kMetaMinTime];
+    const long long computed = (long long)meta[kMetaHeader + 2 * L - 1] * kWave - 1;
+    long long top = reduced < bp ? reduced : bp;
+    top = top < computed ? top : computed;
+    float bv = __builtin_inff();
+    int bt = INT32_MAX;
+    const float *const last = drec + ((size_t)k * L + (L - 1)) * pitch;
+    for (int t = lane; t <= top; t += kWave)
+        argmin_merge(bv, bt, last[t], t);
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const float ov = __shfl_xor(bv, off, kWave);
+        const int ot = __shfl_xor(bt, off, kWave);
+        argmin_merge(bv, bt, ov, ot);
+    }
+    return __builtin_amdgcn_readfirstlane(bv < __builtin_inff() ? bt : -1);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Walk back (last loop of Alg. 1).  kByItself: not enqueued by the call that filled the record, whose
 // workspace may therefore have been scratch since; it then holds no table, and t* anything.  (Not a
@@ -2291,11 +2336,11 @@ __global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource s
     cost[k] = acc;
 }
 
-// One wave walks solve `solve`, which is candidate k under some budget.
+// One wave walks solve `solve`, which is candidate k under some budget, from time `tstar`.
 template <int kLevelBlocks, bool kByItself>
 __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrSource src,
                                            const int32_t *__restrict__ meta,
-                                           const float *__restrict__ drec, const int32_t *tstar,
+                                           const float *__restrict__ drec, int tstar,
                                            int solve, int k, int L, int S, int pitch,
                                            int16_t *__restrict__ profile, float *cost,
                                            Resume resume)
@@ -2306,7 +2351,7 @@ __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrS
     const float *drec_k = drec + (size_t)k * L * pitch;
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
     auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
-    const int from = kByItself && !meta[kMetaTable] ? -2 : tstar[solve];
+    const int from = kByItself && !meta[kMetaTable] ? -2 : tstar;
     const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, from, 0, L, L, S, prof);
     if (t < 0) {
         if (lane == 0)
@@ -2329,7 +2374,7 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
     const int k = budgets > 1 ? solve % K : solve;
     if (solve < K * budgets && todo.has_wave(solve, K, L))
-        walk_table<kLevelBlocks, kByItself>(tau, src, meta, drec, tstar, solve, k, L, S, pitch,
+        walk_table<kLevelBlocks, kByItself>(tau, src, meta, drec, tstar[solve], solve, k, L, S, pitch,
                                             profile, cost, resume);
 }
 
@@ -2593,44 +2638,74 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
         walk_block<kLevelBlocks>(tau, src, meta, tstar, k, L, S, pitch, profile, cost, blocks);
 }
 
-// Behind dp_core, D record, no more candidates than compute units: fill and walk back of the few
-// candidates it gave up, in one launch.  A candidate has a unit to itself then whatever LDS its
-// workgroup asks for, so the launches for rows of different lengths need not be kept apart, and its
-// walk only needs its own rows.  Nearly always there is nothing to do, and what counts is the number of
-// launches, 1.9 us each: K = 256, L = 200, S = 64, B = 65536 with checkpoints has 15 instead of 59.
-// (With more candidates a table that does not reduce is filled by workgroups that share a unit.)
-// `profile`: nullptr where there are budgets to choose from first.
-template <bool kNarrow, bool kBlocks>
-__global__ __launch_bounds__((kBlocks ? 1 : 2) * kFillWaves * kWave, 4) void dp_rest(
-    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
-    LevelTables tables, int units, int K, int L, int S, int pitch, float *drec, float *rows,
-    int32_t *tstar, int16_t *profile, float *cost, Resume resume, Blocks blocks, Todo todo)
+// Behind dp_core, D record: fill and walk back of the few candidates it gave up, under one or several budgets or
+// with checkpoints, in one launch, or two where rows may be longer than a workgroup of the usual size has in place.
+// Nearly always there is nothing to do, and what counts is the number of launches, 1.9 us each and more with many
+// workgroups.  us a call with a launch for each step and row length, and so: K = 256, L = 200, S = 64, B = 65536 with
+// checkpoints 212 and 190 (15 launches then); K = 1069, L = 21, S = 112, B = 29856 with checkpoints 143 and 98; 64
+// candidates under six budgets 53.8 and 50.7; K = 333, S = 127 70.1 and 68.2.  Where nothing reduces, calls with
+// checkpoints take 0.9 - 1.1 times as long as they did, others 0.95 - 1.06 times.
+//   kShape 0: no more candidates than compute units, one to a workgroup; rows of any length.  A candidate has a unit
+//             to itself then whatever LDS its workgroup asks for, and its walk only needs its own rows.
+//          1: more of them, rows in place (path 1), two workgroups to a unit, `teams` candidates to each
+//          2: more of them, longer rows
+// (A fill that is a function by itself, called in a loop over few workgroups, keeps registers in scratch memory, and
+// launches that find nothing to do cost 8 us more.)
+template <bool kNarrow, bool kBlocks, int kShape>
+__global__ __launch_bounds__((kBlocks || kShape == 1 ? 1 : 2) * kFillWaves * kWave, 4) void dp_rest(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units,
+    int K, int L, int S, int pitch, float *drec, float *rows, int32_t *tstar, int16_t *profile, float *cost,
+    Resume resume, Blocks blocks, Todo todo, int budgets, Budgets budget)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ FillShared sh;
-    const int k = blockIdx.x;
-    if (!todo.has_wave(k, K, L))
+    constexpr int kLevelBlocks = kNarrow ? 1 : 4;
+    if constexpr (kShape > 0)
+        if ((meta[kMetaPath] == 1) != (kShape == 1))
+            return;
+    const int teams = kShape == 1 ? meta[kMetaTeams] : 1, first = blockIdx.x * teams;
+    bool any = false;
+    for (int i = 0; i < teams && first + i < K; ++i)
+        any |= todo.has_wave(first + i, K, L);
+    if (!any)
         return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
     auto fill = [&](auto path) __attribute__((always_inline)) {
         constexpr int kPath = decltype(path)::value;
-        fill_candidates<false, kPath, kNarrow, kBlocks, true, false,
-                        kPath == 1 && kNarrow && !kBlocks, false>(
-            src, meta, tables, units, K, L, S, pitch, nullptr, drec, rows, tstar, cost, resume,
+        fill_candidates<false, kPath, kNarrow, kBlocks, true, kShape == 1,
+                        kPath == 1 && kNarrow && !kBlocks && kShape == 0, false>(
+            src, meta, tables, units, K, L, S, pitch, nullptr, drec, rows, tstar, budgets ? nullptr : cost, resume,
             blocks, todo, lds, sh);
     };
-    fill(Many<1>{});                              // (each only where the path is its own)
-    fill(Many<kBlocks ? 2 : 3>{});
-    fill(Many<kBlocks ? 0 : 4>{});
-    if (!profile || (kBlocks && blocks.pass == 0))
-        return;
-    __syncthreads();                              // the rows and the final time are written
-    if (threadIdx.x >= kWave)
-        return;
-    if constexpr (kBlocks)
-        walk_block<kNarrow ? 1 : 4>(tau, src, meta, tstar, k, L, S, pitch, profile, cost, blocks);
-    else
-        walk_table<kNarrow ? 1 : 4, false>(tau, src, meta, drec, tstar, k, k, L, S, pitch, profile,
-                                           cost, resume);
+    for (;;) {
+        if constexpr (kShape != 2)                // (each only where the path is its own)
+            fill(Many<1>{});
+        if constexpr (kShape != 1) {
+            fill(Many<kBlocks ? 2 : 3>{});
+            fill(Many<kBlocks ? 0 : 4>{});
+        }
+        __syncthreads();                          // the rows and the final time are written
+        if constexpr (!kBlocks)
+            break;
+        if (blocks.pass == 1 && wave < teams && first + wave < K && todo.has_wave(first + wave, K, L))
+            walk_block<kLevelBlocks>(tau, src, meta, tstar, first + wave, L, S, pitch, profile, cost, blocks);
+        __syncthreads();                          // the block's rows are read
+        if (blocks.pass == 0) {
+            blocks.pass = 1;
+            blocks.begin = L;
+        }
+        if (blocks.begin == 0)
+            return;
+        blocks.end = blocks.begin;
+        blocks.begin = (blocks.end - 1) / blocks.stride * blocks.stride;
+    }
+    for (int i = wave; i < teams * max(budgets, 1); i += waves) {
+        const int j = i / teams, k = first + (i - j * teams), solve = j * K + k;
+        if (k >= K || __builtin_amdgcn_readfirstlane(profile[(size_t)solve * L]) != kGivenUp)
+            continue;
+        const int t = budgets ? budget_time(meta, drec, k, L, pitch, budget.at[j]) : tstar[k];
+        walk_table<kLevelBlocks, false>(tau, src, meta, drec, t, solve, k, L, S, pitch, profile, cost, resume);
+    }
 }
 
 int launch_status()
@@ -2682,7 +2757,7 @@ struct CoreCall {
     int budgets;
     unsigned char *spill;             // the record's memory
     size_t spill_bytes;
-    bool rest;                        // dp_rest does what is left, except the walks under several budgets
+    bool rest;                        // dp_rest does what is left
 };
 
 // LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
@@ -2835,7 +2910,7 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
                      workspace_bytes - lay.record_off,
-                     lay.variant == kValueRecord && K <= dev.units};
+                     lay.variant == kValueRecord};
     return true;
 }
 
@@ -2881,6 +2956,9 @@ int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const Pr
     }
     return launch_status();
 }
+
+// Of several budgets, those that dp_rest walks back under.
+int first_budgets(int J) { return J < kCoreBudgets ? J : kCoreBudgets; }
 
 template <bool kLevel, bool kNarrow, bool kBlocks, bool kPairs, bool kTodo>
 int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
@@ -2937,8 +3015,8 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
         wide ? ((long long)nchunks > (long long)wide_waves * wide_group ||
                 row_bytes > (size_t)kLdsBytes)
              : need > (size_t)kLdsBytes;
-    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, true, false, kPairs>
-                          : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, false, kPairs>;
+    auto in_place = turns ? dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo && kLevel, true, false, kPairs>
+                          : dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo && kLevel, false, false, kPairs>;
     // Two workgroups to a unit, whose rows are folded for wide reads (dp_columns).  The level record only with
     // something to sweep, and not many candidates of few levels and layers, of which a unit has room for fewer: us a
     // solve by dp_fill and so, S = 12, L = 82, B = 920, K = 2655 386 and 452; S = 38, L = 11, B = 423, K = 4029 136
@@ -2946,6 +3024,7 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // L = 14, B = 3357, K = 1144 126 and 137; and where it is taken S = 16, L = 124, B = 1585, K = 1534 691 and 646;
     // S = 35, L = 37, B = 833, K = 1378 246 and 191; S = 20, L = 9, B = 1396, K = 312 55 and 43; S = 33, L = 19,
     // B = 3271, K = 1890 269 and 244.
+    constexpr bool kLeft = kTodo && kLevel;       // (the D record's are dp_rest's)
     constexpr bool can_fold = (!kNarrow || (kLevel && kPairs)) && !kBlocks && !kTodo;
     const bool columns = can_fold && K > units && !resume.first_layer &&
                          (!kLevel || (S >= kFoldLevels && B >= kFoldBudget &&
@@ -2962,15 +3041,15 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     }
     if constexpr (can_split && !kTodo) {
         if (split) {
-            in_place = dp_fill<kLevel, 1, kNarrow, kBlocks, kTodo, false, true>;
+            in_place = dp_fill<kLevel, 1, kNarrow, kBlocks, kLeft, false, true>;
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(in_place),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     kLdsBytes) != hipSuccess)
                 return SPDY_DP_ERR_LAUNCH;
         }
     }
-    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kTodo, false, false, kPairs>;
-    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kTodo, false, false,
+    auto two_rows = dp_fill<kLevel, 2, kNarrow, kBlocks, kLeft, false, false, kPairs>;
+    auto wide_place = dp_fill<kLevel, can_widen ? 3 : 1, kNarrow, kBlocks, kLeft, false, false,
                               kPairs>;           // (3 when it exists)
     // The D record's global-row launch also has twice the waves (one workgroup per compute unit
     // with all of its LDS for the window; measured against two workgroups of the usual size with
@@ -2979,7 +3058,7 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     const int global_waves = wide_global ? 2 * waves : waves;
     // (rows that may lie in memory are long: `waves` is the full number then)
     constexpr bool can_tile = !kLevel && !kBlocks && !kTodo;
-    auto in_global = dp_fill<kLevel, can_widen ? 4 : 0, kNarrow, kBlocks, kTodo, false, false, kPairs>;
+    auto in_global = dp_fill<kLevel, can_widen ? 4 : 0, kNarrow, kBlocks, kLeft, false, false, kPairs>;
     if (wide &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(wide_place),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
@@ -3041,21 +3120,27 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     }
     const LevelTables tables{shifts, order, start, entry, s8};
     if constexpr (kTodo && !kLevel) {
-        if (core->rest) {
-            auto rest = dp_rest<kNarrow, kBlocks>;
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(rest),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) !=
-                hipSuccess)
-                return SPDY_DP_ERR_LAUNCH;
-            int lds = place_lds > lds_wide ? place_lds : lds_wide;
-            lds = lds_large > lds ? lds_large : lds;
-            lds = in_memory && lds_stage > lds ? lds_stage : lds;
-            const int threads = wide ? wide_waves * kWave : place_threads;
-            hipLaunchKernelGGL(rest, dim3(K), dim3(threads), lds, q, tau, src, meta, tables, units, K, L,
-                               S, pitch, drec, rows, tstar, cost ? core->profile : nullptr, cost,
-                               resume, blocks, todo);
-            return launch_status();
-        }
+        const int budgets = cost ? 0 : first_budgets(core->budgets);
+        Budgets budget{};
+        for (int j = 0; j < budgets; ++j)
+            budget.at[j] = core->budget[j];
+        auto launch = [&](auto kernel, int threads, int lds) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) == hipSuccess)
+                hipLaunchKernelGGL(kernel, dim3(K), dim3(threads), lds, q, tau, src, meta, tables, units, K, L, S,
+                                   pitch, drec, rows, tstar, core->profile, core->cost, resume, blocks, todo,
+                                   budgets, budget);
+        };
+        int lds = lds_wide > lds_large ? lds_wide : lds_large;
+        lds = in_memory && lds_stage > lds ? lds_stage : lds;
+        const int threads = wide ? wide_waves * kWave : waves * kWave;
+        if (K <= units)
+            launch(dp_rest<kNarrow, kBlocks, 0>, wide ? threads : place_threads, place_lds > lds ? place_lds : lds);
+        else
+            launch(dp_rest<kNarrow, kBlocks, 1>, waves * kWave, kLdsHalf);
+        if (K > units && lds > 0)                 // (rows may be longer)
+            launch(dp_rest<kNarrow, kBlocks, 2>, threads, lds);
+        return launch_status();
     }
     if constexpr (can_tile) {
         if (ta.most > 0 && !in_memory) {
@@ -3303,8 +3388,8 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.begin = 0;
     blocks.end = L;
     st = fill();
-    if (st != SPDY_DP_OK)
-        return st;
+    if (st != SPDY_DP_OK || (reduced && core.rest))
+        return st;                                // (all passes were in that)
     const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
     int32_t *tstar = reinterpret_cast<int32_t *>(ws + lay.tstar_off);
     const int per_block = kWalkThreads / kWave;
@@ -3315,8 +3400,6 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
         st = fill();
         if (st != SPDY_DP_OK)
             return st;
-        if (reduced && core.rest)
-            continue;                             // walked already
         auto walk = S <= kWave ? dp_backtrace_blocks<1> : dp_backtrace_blocks<4>;
         hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
                            tau, src, meta, tstar, K, L, S, (int)lay.row, profile, cost, blocks,
@@ -3369,9 +3452,9 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
         return st;
     hipStream_t q = static_cast<hipStream_t>(stream);
     const int most = budgets_per_launch(K, L);
-    for (int j0 = 0; j0 < J; j0 += most) {
+    for (int j0 = reduced ? first_budgets(J) : 0; j0 < J; j0 += most) {
         const int n = J - j0 < most ? J - j0 : most;
-        Budgets some;
+        Budgets some{};
         for (int j = 0; j < n; ++j)
             some.at[j] = budgets[j0 + j];
         int16_t *prof = profile + (size_t)j0 * K * L;

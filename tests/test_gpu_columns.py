@@ -31,8 +31,8 @@ def compare(dp, tau, err, B, compact, what):
         check_tables(dp, tau, err[k], B, ws, k, K)
 
 
-# more candidates than compute units, one, two and four or more to a workgroup
-@pytest.mark.parametrize("K", [260, 600, 2100])
+# up to one to a compute unit, and more: one, two and four or more to a workgroup
+@pytest.mark.parametrize("K", [3, 200, 260, 600, 2100])
 @pytest.mark.parametrize("compact, S", KINDS)
 def test_rows_around_whole_chunks(dp, compact, S, K):
     rng = np.random.default_rng(S * 3000 + K)
