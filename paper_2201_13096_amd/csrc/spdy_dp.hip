@@ -2283,57 +2283,98 @@ __device__ __forceinline__ int budget_time(const int32_t *__restrict__ meta, con
 // workspace may therefore have been scratch since; it then holds no table, and t* anything.  (Not a
 // run-time flag: the load that it guards was issued all the same, 0.3 us of a walk of 6 us.)
 
-// Level record: one lane per candidate, L dependent one-byte reads; the cost is re-summed over
-// the profile in layer order (exactly the sum Alg. 1's strict "<" sweep carries to the cell).
-template <bool kByItself>
-__global__ void dp_backtrace_levels(const int32_t *__restrict__ tau, ErrSource src,
-                                    const int32_t *__restrict__ meta,
-                                    const uint8_t *__restrict__ choice,
-                                    const int32_t *__restrict__ tstar, int K, int L, int S,
-                                    int pitch, int16_t *__restrict__ profile,
-                                    float *__restrict__ cost, Todo todo)
+// Level record: one wave per candidate, two layers a trip to memory.  With the level of layer l at time t all levels
+// of layer l - 1 that it may lead to are read, lane s the one at t - shift_s, and what these lead on by is there
+// before.  us a walk, a lane per candidate, which reads a level, then its shift, then the next level, and so: L = 54,
+// S = 40, B = 10^4, K = 1 29.7 and 16.7, K = 1024 68.5 and 27.0, K = 4096 91.9 and 50.6; L = 400, S = 2, K = 4000 478
+// and 299; L = 30, S = 100, K = 600 37.5 and 18.0.  The cost is re-summed over the profile in layer order (exactly
+// the sum Alg. 1's strict "<" sweep carries to the cell).
+// kLevelBlocks: see LayerLevels.
+template <int kLevelBlocks> struct LevelShifts {
+    int shift[kLevelBlocks];
+    __device__ __forceinline__ void load(const int32_t *__restrict__ tau, const int32_t *__restrict__ meta, int l,
+                                         int S, int lane)
+    {
+        const int m = meta[kMetaHeader + l];
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks; ++b)
+            shift[b] = tau[(size_t)l * S + min(b * kWave + lane, S - 1)] - m;
+    }
+};
+// Level s of what the lanes hold.
+template <int kLevelBlocks> __device__ __forceinline__ int of_level(const int (&held)[kLevelBlocks], int s)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K || !todo.has(k, K, L))
+    int v = from_lane(held[0], s & (kWave - 1));
+#pragma unroll
+    for (int b = 1; b < kLevelBlocks; ++b)
+        if (s / kWave == b)
+            v = from_lane(held[b], s & (kWave - 1));
+    return v;
+}
+
+template <int kLevelBlocks, bool kByItself>
+__global__ __launch_bounds__(kWalkThreads) void dp_backtrace_levels(
+    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
+    const uint8_t *__restrict__ choice, const int32_t *__restrict__ tstar, int K, int L, int S, int pitch,
+    int16_t *__restrict__ profile, float *__restrict__ cost, Todo todo)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int k = uniform((int)(blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave));
+    if (k >= K || !todo.has_wave(k, K, L))
         return;
     int16_t *prof = profile + (size_t)k * L;
-    int t = tstar[k];
-    if (kByItself && !meta[kMetaTable]) {
-        for (int l = 0; l < L; ++l)
-            prof[l] = -2;
-        cost[k] = __builtin_nanf("");
+    int t = uniform(tstar[k]);
+    const bool none = kByItself && !meta[kMetaTable];
+    if (none || t < 0) {
+        for (int l = lane; l < L; l += kWave)
+            prof[l] = none ? -2 : -1;
+        if (none && lane == 0)
+            cost[k] = __builtin_nanf("");
         return;
     }
-    if (t < 0) {
-        for (int l = 0; l < L; ++l)
-            prof[l] = -1;
-        return;
-    }
-    const int32_t *mn = meta + kMetaHeader;
     const uint8_t *choice_k = choice + (size_t)k * L * pitch;
+    LevelShifts<kLevelBlocks> upper, lower;
+    upper.load(tau, meta, L - 1, S, lane);
+    lower.load(tau, meta, max(L - 2, 0), S, lane);
     bool ok = true;
-    for (int l = L - 1; l >= 0; --l) {
-        const int s = choice_k[(size_t)l * pitch + t];
-        prof[l] = (int16_t)s;
-        if (s >= S) {        // cannot happen on a filled table; never index tau out of range
-            ok = false;
-            break;
+    for (int l = L - 1; l >= 0; l -= 2) {
+        int level[kLevelBlocks];
+        const int here = choice_k[(size_t)l * pitch + t];
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks; ++b) {
+            level[b] = kNoLevel;
+            // (a time that the lane's level leads to, or none)
+            if (l > 0 && b * kWave + lane < S && upper.shift[b] <= t)
+                level[b] = choice_k[(size_t)(l - 1) * pitch + (t - upper.shift[b])];
         }
-        t -= tau[(size_t)l * S + s] - mn[l];
-        if (t < 0) {
-            ok = false;
+        const LevelShifts<kLevelBlocks> upper_now = upper, lower_now = lower;
+        upper.load(tau, meta, max(l - 2, 0), S, lane);
+        lower.load(tau, meta, max(l - 3, 0), S, lane);
+        // a level that there is not, or that leads below time 0: cannot happen on a filled table
+        const int s = uniform(here);
+        ok = s < S;
+        if (!ok)
             break;
-        }
+        t -= of_level(upper_now.shift, s);
+        ok = t >= 0;
+        if (lane == 0)
+            prof[l] = (int16_t)s;
+        if (!ok || l == 0)
+            break;
+        const int below = of_level(level, s);
+        ok = below < S;
+        if (!ok)
+            break;
+        t -= of_level(lower_now.shift, below);
+        ok = t >= 0;
+        if (!ok)
+            break;
+        if (lane == 0)
+            prof[l - 1] = (int16_t)below;
     }
-    if (!ok) {
-        cost[k] = __builtin_nanf("");
-        return;
-    }
-    __threadfence_block();
-    float acc = -0.0f;
-    for (int l = 0; l < L; ++l)
-        acc += src.row(k, l, L, S).at(prof[l]);
-    cost[k] = acc;
+    const float sum = ok ? profile_cost(src.of_candidate(k, L, S), L, S, prof) : __builtin_nanf("");
+    if (lane == 0)
+        cost[k] = sum;
 }
 
 // One wave walks solve `solve`, which is candidate k under some budget, from time `tstar`.
@@ -3281,8 +3322,11 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     const int32_t *tstar = reinterpret_cast<const int32_t *>(ws + lay.tstar_off);
     (void)hipGetLastError();
     if (lay.variant == kLevelRecord) {
-        auto walk = by_itself ? dp_backtrace_levels<true> : dp_backtrace_levels<false>;
-        hipLaunchKernelGGL(walk, dim3((K + kWave - 1) / kWave), dim3(kWave), 0, q,
+        auto walk = S <= kWave ? dp_backtrace_levels<1, false> : dp_backtrace_levels<4, false>;
+        if (by_itself)
+            walk = S <= kWave ? dp_backtrace_levels<1, true> : dp_backtrace_levels<4, true>;
+        const int per_block = kWalkThreads / kWave;
+        hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
                            tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
