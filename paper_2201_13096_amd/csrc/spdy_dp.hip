@@ -1764,6 +1764,171 @@ __device__ __forceinline__ int walk_layers(const int32_t *__restrict__ tau, cons
     return t;
 }
 
+// ---------------------------------------------------------------------------------------
+// The same for all layers of at most 64 levels by a guess of the path.  A walk that gathers a layer's entries of
+// the row below and then knows where the next layer's are waits for memory once per layer, 0.97 us with a
+// thousand candidates.  Which level the next layers take is nearly always known before, though: on a path of
+// least cost all layers trade cost for time at about the same price, the slope of the last row at its final time,
+// and take the level of least error + price * shift.  So the entries of up to kGuessed layers are asked for at once,
+// each where the guesses above it lead; then the layers are decided as ever, by comparing their entries, and
+// where one takes another shift than was guessed, those below are asked for again.  A guess only says what is read
+// ahead, never what is taken.
+// Of a layer's entries, those beyond the guessed level by more than kGuessSlack are only asked for where none
+// before them fits: the least level that fits counts.  Where guesses fail, fewer layers are asked for at once.
+// What bounds it: a trip to memory a block, and as long again for the instructions of a wave by itself.  us a
+// walk, L = 54, S = 40, B = 10^4, a layer a trip and so: K = 300 51.8 and 34.3, K = 1024 54.6 and 37.5, K = 2048
+// 71.4 and 42.4, K = 4096 87.4 and 57.4; L = 200, S = 64, B = 3000, K = 600 202 and 94.  (As plain code, with
+// branches around every load and scans one after the other, it took 55 at K = 1024 and 118 at K = 4096.)
+//   Price: the least fall of the last row per bucket over the 64 samples between 1/200 and 1/8 of the final
+//   time below it.  (A row is not quite convex: from the next bucket below on, one of 64 samples is nearly as
+//   low as the last one now and then, and every third guess or more is wrong.  1 - 4 of 54 layers are so.)
+// ---------------------------------------------------------------------------------------
+constexpr int kGuessed = 8, kGuessSlack = 4, kGuessLayers = 24;
+
+struct GuessedLayers {           // of layers top, top - 1, ...; below the first one, the first once more
+    int shift[kGuessed];         // of level `lane`; until settle() with what lane j has in `least`
+    float err[kGuessed];
+    int least, reach;            // of layer top - j in lane j (see LayerLevels)
+    __device__ __forceinline__ void load(const int32_t *__restrict__ tau, const ErrSource &src,
+                                         const int32_t *__restrict__ meta, int top, int L, int S, int lane)
+    {
+        const int s = min(lane, S - 1), mine = max(top - (lane & (kGuessed - 1)), 0);
+        least = meta[kMetaHeader + mine];
+        reach = meta[kMetaHeader + L + max(mine - 1, 0)];
+#pragma unroll
+        for (int j = 0; j < kGuessed; ++j)
+            shift[j] = tau[(size_t)max(top - j, 0) * S + s];
+        if (src.err) {
+#pragma unroll
+            for (int j = 0; j < kGuessed; ++j)
+                err[j] = src.err[(size_t)max(top - j, 0) * S + s];
+        } else {
+            const float w = src.w[s];
+#pragma unroll
+            for (int j = 0; j < kGuessed; ++j)
+                err[j] = __fmul_rn(src.c[max(top - j, 0)], w);
+        }
+    }
+    __device__ __forceinline__ void settle(int top, int S, int lane)
+    {
+        reach = top - (lane & (kGuessed - 1)) > 0 ? reach * kWave : 1;
+#pragma unroll
+        for (int j = 0; j < kGuessed; ++j)
+            shift[j] = lane < S ? shift[j] - from_lane(least, j) : INT32_MAX;
+    }
+};
+
+template <class RowOf>
+__device__ __forceinline__ int walk_guessed(const int32_t *__restrict__ tau, const ErrSource src,
+                                            const int32_t *__restrict__ meta, RowOf row_of, int t, int L, int S,
+                                            int16_t *__restrict__ prof)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    t = uniform(t);
+    if (t < 0) {
+        for (int l = lane; l < L; l += kWave)
+            prof[l] = t == -1 ? -1 : -2;         // (see walk_layers)
+        return t;
+    }
+    GuessedLayers cur, next;
+    cur.load(tau, src, meta, L - 1, L, S, lane);
+    const float *const last = row_of(L - 1);
+    const int back = t / 200 + 1 + lane * max(t >> 9, 1);
+    const float below = last[max(t - back, 0)];
+    float target = uniform(last[t]);
+    float price = back <= t ? (below - target) / (float)back : __builtin_inff();
+    price = fminf(from_lane(wave_scan(price, __builtin_inff(), Smaller{}), kWave - 1), 3.4e38f);
+    int ahead = kGuessed;                        // layers that are asked for at once
+    for (int top = L - 1; top >= 0; top -= kGuessed) {
+        cur.settle(top, S, lane);
+        // The least score as a word that orders like it, the level in its lowest bits.  (Step by step over all
+        // layers: eight chains, not one after the other.)
+        unsigned key[kGuessed];
+#pragma unroll
+        for (int j = 0; j < kGuessed; ++j) {
+            const int bits = __float_as_int(__builtin_fmaf(price, (float)cur.shift[j], cur.err[j]));
+            const unsigned up = (unsigned)(bits ^ (bits >> 31 | INT32_MIN));
+            key[j] = lane < S ? (up & ~63u) | (unsigned)lane : ~0u;
+        }
+        auto least_of = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < kGuessed; ++j)
+                key[j] = min(key[j], dpp_from<decltype(ctrl)::value, decltype(rows)::value>(~0u, key[j]));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        least_of(Many<0x111>{}, Many<0xf>{});    // (see wave_scan)
+        least_of(Many<0x112>{}, Many<0xf>{});
+        least_of(Many<0x114>{}, Many<0xf>{});
+        least_of(Many<0x118>{}, Many<0xf>{});
+        least_of(Many<0x142>{}, Many<0xa>{});
+        least_of(Many<0x143>{}, Many<0xc>{});
+        int by[kGuessed], near[kGuessed];        // the guessed level's shift; shifts that are asked for
+#pragma unroll
+        for (int j = 0; j < kGuessed; ++j) {
+            const int level = (int)(from_lane(key[j], kWave - 1) & 63u);
+            by[j] = from_lane(cur.shift[j], level);
+            near[j] = lane <= level + kGuessSlack ? cur.shift[j] : INT32_MAX;
+        }
+        const int n = min(kGuessed, top + 1);
+        int pos = 0, whole = -1;                 // layers that are decided; the one with all levels asked for
+        int held = 0;                            // the level of layer top - j, in lane j
+        float from[kGuessed] = {};
+        do {
+            const unsigned want = ((1u << min(n, pos + ahead)) - 1) & ~((1u << pos) - 1);
+            int at = t;
+#pragma unroll
+            for (int j = 0; j < kGuessed; ++j)
+                if (want >> j & 1) {
+                    // (what is out of reach is not read; rows of a batch are far shorter than 2^29 buckets)
+                    const __amdgpu_buffer_rsrc_t row =
+                        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row_of(max(top - j - 1, 0))), 0,
+                                                          from_lane(cur.reach, j) * 4, 0x20000);
+                    const unsigned u = min((unsigned)(at - near[j]), 0x3FFFFFFFu);
+                    from[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, u * 4, 0, 2));
+                    at = max(at - by[j], -1);    // (-1: nowhere)
+                }
+            if (pos == 0 && whole < 0)           // (the first time)
+                next.load(tau, src, meta, top - kGuessed, L, S, lane);
+            bool as_guessed = true, none = false;
+#pragma unroll
+            for (int j = 0; j < kGuessed; ++j)
+                if (as_guessed && (want >> j & 1)) {
+                    const float v = top > j ? from[j] : -0.0f;
+                    const unsigned long long fits =
+                        __ballot((unsigned)(t - near[j]) < (unsigned)from_lane(cur.reach, j) &&
+                                 v + cur.err[j] == target);
+                    if (fits) {
+                        const int found = __builtin_ctzll(fits), shift = from_lane(cur.shift[j], found);
+                        held = lane == j ? found : held;
+                        target = from_lane(v, found);
+                        t -= shift;
+                        as_guessed = shift == by[j];
+                        pos = j + 1;
+                    } else {
+                        as_guessed = false;
+                        none = true;
+                    }
+                }
+            ahead = as_guessed ? min(4 * ahead, kGuessed) : (ahead + 1) / 2;
+            if (none) {
+                if (whole == pos) {              // cannot happen on a filled record
+                    for (int i = lane; i < L; i += kWave)
+                        prof[i] = -2;
+                    return -2;
+                }
+                whole = pos;
+#pragma unroll
+                for (int j = 0; j < kGuessed; ++j)
+                    near[j] = j == pos ? cur.shift[j] : near[j];
+            }
+        } while (pos < n);
+        if (lane < n)
+            prof[top - lane] = (int16_t)held;
+        cur = next;
+    }
+    return t;
+}
+
 // The cost of a walked profile, summed in layer order.  Lane 0 wrote the profile; it is made visible
 // to the wave first.  Lane i fetches the error of layer 64 b + i (all layers of a block of 64 in one
 // round trip instead of one after the other); the sum itself runs over the lanes in order.
@@ -2378,7 +2543,7 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_levels(
 }
 
 // One wave walks solve `solve`, which is candidate k under some budget, from time `tstar`.
-template <int kLevelBlocks, bool kByItself>
+template <int kLevelBlocks, bool kByItself, bool kGuess = false>
 __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrSource src,
                                            const int32_t *__restrict__ meta,
                                            const float *__restrict__ drec, int tstar,
@@ -2393,7 +2558,11 @@ __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrS
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
     auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
     const int from = kByItself && !meta[kMetaTable] ? -2 : tstar;
-    const int t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, from, 0, L, L, S, prof);
+    int t;
+    if constexpr (kGuess)
+        t = walk_guessed(tau, mine, meta, row_of, from, L, S, prof);
+    else
+        t = walk_layers<kLevelBlocks>(tau, mine, meta, row_of, from, 0, L, L, S, prof);
     if (t < 0) {
         if (lane == 0)
             cost[solve] = t == -1 ? __builtin_inff() : __builtin_nanf("");
@@ -2406,17 +2575,18 @@ __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrS
 
 // `budgets` > 1 (solve_budgets): solve j * K + k is candidate k under budget j, and its final time
 // comes in through cost (dp_budget_argmin).
-template <int kLevelBlocks, bool kByItself>
+// kGuess: see walk_guessed.
+template <int kLevelBlocks, bool kByItself, bool kGuess>
 __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
     const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
     int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
 {
-    const int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    const int solve = uniform(blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave);
     const int k = budgets > 1 ? solve % K : solve;
     if (solve < K * budgets && todo.has_wave(solve, K, L))
-        walk_table<kLevelBlocks, kByItself>(tau, src, meta, drec, tstar[solve], solve, k, L, S, pitch,
-                                            profile, cost, resume);
+        walk_table<kLevelBlocks, kByItself, kGuess>(tau, src, meta, drec, tstar[solve], solve, k, L, S, pitch,
+                                                    profile, cost, resume);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -3279,13 +3449,14 @@ void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const f
                  int16_t *profile, float *cost, Resume resume, Todo todo, bool by_itself,
                  int units, hipStream_t q)
 {
-    // A unit to every candidate, whose LDS the windows take: us a walk in this rule's two ways, L = 54, S = 40,
-    // B = 10^4: K = 1 33.2 and 21.0, K = 128 35.9 and 25.1, K = 256 47.4 and 32.3; beyond, workgroups would
-    // queue for units.  (Behind dp_core hardly any candidate is left to walk.  Copies are of 16 bytes: a record
-    // that does not lie so is walked entry by entry.)
+    // A unit to every candidate, whose LDS the windows take: us a walk by a wave's guesses and so, L = 54, S = 40,
+    // B = 10^4: K = 1 26.0 and 23.0, K = 64 31.3 and 24.7, K = 256 34.2 and 33.9; L = 200, S = 64, B = 3000, K = 250
+    // 92.7 and 62.9 (a wave layer by layer: K = 1 33.2, K = 256 47.4); beyond, workgroups would queue for units.
+    // (Behind dp_core hardly any candidate is left to walk.  Copies are of 16 bytes: a record that does not lie
+    // so is walked entry by entry.)
     // The price: it waits for a unit whose LDS is free, where four waves without LDS would start beside a fill
-    // of another stream.  us a step, the walk of one step beside the fill of the next, four waves and so:
-    // K = 64 165 and 137, K = 100 155 and 166, K = 192 211 and 225, K = 256 258 and 234; K = 200, L = 30,
+    // of another stream.  us a step, the walk of one step beside the fill of the next, four waves layer by layer
+    // and so: K = 64 165 and 137, K = 100 155 and 166, K = 192 211 and 225, K = 256 258 and 234; K = 200, L = 30,
     // S = 100, B = 12000 326 and 473.  On one stream: 169 and 142, 194 and 168, 251 and 231, 253 and 236, 352
     // and 345.
     auto whole = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
@@ -3298,9 +3469,14 @@ void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const f
         return;
     }
     const int per_block = kWalkThreads / kWave;
-    auto walk = S <= kWave ? dp_backtrace_values<1, false> : dp_backtrace_values<4, false>;
+    auto walk = S <= kWave ? dp_backtrace_values<1, false, false> : dp_backtrace_values<4, false, false>;
     if (by_itself)
-        walk = S <= kWave ? dp_backtrace_values<1, true> : dp_backtrace_values<4, true>;
+        walk = S <= kWave ? dp_backtrace_values<1, true, false> : dp_backtrace_values<4, true, false>;
+    // By guesses from kGuessLayers on (us a walk, layer by layer and so, K = 600: L = 9, S = 64 14.1 and 18.0;
+    // L = 17, S = 8 19.3 and 21.7; L = 54, S = 40 52 and 35).  Rows of 2 GB and more, whose buckets a buffer
+    // does not reach, and the few candidates that the reduced solve leaves: layer by layer.
+    if (S <= kWave && L >= kGuessLayers && pitch < 1 << 29 && !todo.profile)
+        walk = by_itself ? dp_backtrace_values<1, true, true> : dp_backtrace_values<1, false, true>;
     hipLaunchKernelGGL(walk, dim3((K * budgets + per_block - 1) / per_block), dim3(kWalkThreads), 0,
                        q, tau, src, meta, drec, tstar, K, budgets, L, S, pitch, profile, cost,
                        resume, todo);

@@ -56,6 +56,35 @@ def test_walks(dp, L, S, B, widest):
                         f"resumed L={L} S={S} B={B}")
 
 
+# More candidates than units: the walk by guesses (blocks of eight layers, cut at the first one; guesses that hold for
+# smooth tables and fail in every layer for others; levels far from the guess; ties), and the level record's two
+# layers at a time (odd and even numbers of layers, levels around the words of 64).
+@pytest.mark.parametrize("S", [1, 2, 40, 63, 64, 65, 200])
+@pytest.mark.parametrize("L", [1, 2, 7, 8, 9, 17, 40])
+def test_walks_of_many(dp, L, S):
+    rng = np.random.default_rng(L * 500 + S)
+    K, B = 300, 60 * L + 200
+    for smooth, values in ((True, None), (False, None), (False, 2)):
+        tau, err, _ = workloads.random_instance(rng, K, L, S, B, tau_max=240, integer_err=values,
+                                                inf_err_frac=0.0 if smooth else 0.05, over_budget_frac=0.05)
+        if smooth:                                # less time, more error, at falling returns
+            q = np.linspace(1.0, 0.05, S)
+            tau = np.round(rng.uniform(40, 240, (L, 1)) * q).astype(np.int32)
+            err = (rng.random((K, L, 1)) * (1.0 - q) ** 2).astype(np.float32)
+        tau[:, -1] = np.minimum(tau[:, -1], 60)   # mostly feasible
+        err[K // 3, L // 2] = np.inf              # one is not
+        print(f"[walk] L={L} S={S} smooth={smooth} values={values}", flush=True)
+        tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
+        want = oracle.solve_ref(tau, err, B)
+        for compact in (False, True):
+            ws = dp.alloc_workspace(K, L, S, B, compact=compact)
+            p, c = dp.spdy_dp_solve_batched(tau_d, err_d, B, workspace=ws)
+            assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"L={L} S={S} compact={compact}")
+            p.fill_(7)
+            dp.spdy_dp_backtrace(tau_d, err_d, B, p, c, ws)
+            assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"again L={L} S={S} compact={compact}")
+
+
 # (several budgets over a table of eight layers are not tried by the reduced solve first)
 @pytest.mark.parametrize("K, J, L", [(256, 1, 18), (257, 1, 18), (128, 2, 8), (42, 6, 8), (43, 6, 8), (128, 2, 18)])
 def test_as_many_as_units(dp, K, J, L):
