@@ -136,7 +136,7 @@ __host__ __device__ constexpr int tail_share(int t, int chunks)
 static_assert(kMaxQuads + kFewChunks < 1 << 4, "four bits of the word");
 constexpr unsigned kNoLevel = 0xFF;
 constexpr size_t kAlign = 256;
-constexpr int kMetaHeader = 21;      // int32 words before the per-layer arrays
+constexpr int kMetaHeader = 20;      // int32 words before the per-layer arrays
 // meta: header | m_l [L] | chunks of row l [L] | chunk boundaries of the team waves [L][stride]
 //       | largest usable shift of layer l [L]
 constexpr int kRangeStride = kMaxFillWaves + 1;
@@ -155,6 +155,7 @@ enum MetaWord {
     kMetaBudget = 0, kMetaMinTime = 1, kMetaRow = 2, kMetaPath = 3, kMetaTeamWaves = 4,
     kMetaTeams = 5, kMetaInPlace = 6,
     kMetaStage = 7,     // bytes of LDS the global-row launch has for the windows of its tiles
+    kMetaColumns = 7,   // path 1: buckets of a position, 4 or 1, where dp_columns is its launch (see there)
     // what the choice of the path was made from (read back by tests, not by the kernels)
     kMetaWaves = 8,     // waves of a fill workgroup
     kMetaMaxGroup = 9,  // most chunks a wave keeps in registers
@@ -167,8 +168,7 @@ enum MetaWord {
     kMetaLdsWide = 16,   // its dynamic LDS bytes
     kMetaGlobalWaves = 17, // waves of the global-row launch
     kMetaTable = 18,    // 1: the call leaves the whole table in the record (0: scratch)
-    kMetaTiles = 19,    // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
-    kMetaColumns = 20   // buckets of a position, 4 or 1, where dp_columns is the launch of path 1 (see there)
+    kMetaTiles = 19     // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
@@ -582,12 +582,14 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
                                  columns == kLevelColumns, teams, &plain);
             cells = plain ? 1 : 4;
         }
-        meta[kMetaColumns] = cells;
         meta[kMetaPath] = path;
         meta[kMetaTeams] = teams;
         meta[kMetaTeamWaves] = plan_waves / teams;
         meta[kMetaInPlace] = inplace;
-        meta[kMetaStage] = lds_stage;
+        if (cells)
+            meta[kMetaColumns] = cells;
+        else
+            meta[kMetaStage] = lds_stage;
         meta[kMetaWaves] = waves;
         meta[kMetaMaxGroup] = max_group;
         meta[kMetaLdsSmall] = lds_small;

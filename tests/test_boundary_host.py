@@ -100,6 +100,14 @@ def test_workspace_size(binding):
         assert f(2 ** 31 - 1, 2 ** 31 - 1, 255, 2 ** 31 - 2000) == 0
 
 
+# (a header of one word more would take 256 bytes more at 15 and 31 layers: buffers of a fixed size would be refused)
+@pytest.mark.parametrize("L, sizes", [(15, (1820928, 464640, 856320)), (31, (3762176, 958976, 1350656))])
+def test_workspace_size_stays(binding, L, sizes):
+    shape = (3, L, 40, 10000)
+    assert sizes == (binding.spdy_dp_workspace_bytes(*shape), binding.spdy_dp_workspace_bytes_min(*shape),
+                     binding.spdy_dp_workspace_bytes_checkpointed(*shape))
+
+
 def test_argument_errors_are_reported_before_any_launch(binding):
     lib = binding.lib()
     fake = 0x1000  # never dereferenced: every call below must fail validation first
