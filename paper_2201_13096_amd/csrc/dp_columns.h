@@ -172,7 +172,8 @@ __device__ __forceinline__ void column_levels(const char *from, const int2 *entr
     };
     EntryPair next = entry_pair(entries);
     unsigned word = words[0];
-    for (; n >= 4; n -= 4) {                  // two pairs a trip, so that no minimum is moved
+    // two pairs a trip, so that no minimum is moved (the longest shares have no registers for it)
+    for (; Q < column_chunks<true>() && n >= 4; n -= 4) {
         const EntryPair a = next, b = entry_pair(entries + 2);
         const unsigned word_a = word, word_b = words[2];
         entries += 4;
@@ -182,13 +183,14 @@ __device__ __forceinline__ void column_levels(const char *from, const int2 *entr
         pair(a, word_a);
         pair(b, word_b);
     }
-    if (n >= 2) {
+    for (; n >= 2; n -= 2) {
         const EntryPair a = next;
         const unsigned word_a = word;
-        next = entry_pair(entries + 2);
-        word = words[2];
+        entries += 2;
+        words += 2;
+        next = entry_pair(entries);
+        word = words[0];
         pair(a, word_a);
-        n -= 2;
     }
     if (n == 1)                               // (a pair with itself)
         single(next.x, __int_as_float(next.y), (word & 0xFFFF00FFu) | (word & 0xFFu) << 8);
@@ -446,6 +448,8 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
     // order.
     const bool producer = share == 0 && team < teams;
     const int s8 = tables.s8;
+    // (levels in several blocks of 64 have no registers to wait in during the sweep)
+    constexpr bool kFetchAhead = !kLevel || kBlocks == 1;
     ColumnFetch<kBlocks> fetched;
 #pragma unroll
     for (int b = 0; b < kBlocks; ++b) {
@@ -453,7 +457,10 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
         fetched.entry[b] = 0;
         fetched.raw[b] = __builtin_inff();
     }
+    // (Lanes anew in every layer: addresses and masks that stay in registers drive others to scratch memory.)
     auto fetch = [&](int l) __attribute__((always_inline)) {
+        int lane = tid & (kWave - 1);
+        asm volatile("" : "+v"(lane));
         const LayerTable tl = tables.layer(l);
         const ErrRow er = mine.layer(l, S);
 #pragma unroll
@@ -466,6 +473,8 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
         }
     };
     auto publish = [&](int l) __attribute__((always_inline)) {
+        int lane = tid & (kWave - 1);
+        asm volatile("" : "+v"(lane));
         int2 *const to = table + (l & 1) * room;
         constexpr float kNone = __builtin_inff();
         int count = 0;
@@ -537,7 +546,7 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
         asm("" : "+v"(here));
         const int2 *const entries = table + (l & 1) * room;
         const int2 of_lane = entries[here];
-        if (producer && l + 1 < L)
+        if (kFetchAhead && producer && l + 1 < L)
             fetch(l + 1);
         const Fold next = l + 1 < L ? fold(cells_next) : now;
         cells_next = nact[min(l + 2, L - 1)];    // (read a layer ahead)
@@ -550,7 +559,7 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
         auto take = [&](auto cells, auto chunks) __attribute__((always_inline)) {
             fill_share<kLevel, kBlocks, decltype(cells)::value, decltype(chunks)::value>(
                 row, now, next, begin, of_lane, (S + kWave - 1) / kWave, entries, words + (l & 1) * room, rec, here,
-                fetched);
+                kFetchAhead ? fetched : ColumnFetch<kBlocks>{});
         };
         if (plain) {
             switch (n) {
@@ -586,8 +595,11 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
                 for (int chunk = 4 * now.width + wv; chunk < 4 * next.width; chunk += tw)
                     put_chunk(row, chunk, lane, __builtin_inff(), next);
         }
-        if (producer && l + 1 < L)               // the barrier that ends this layer publishes it
+        if (producer && l + 1 < L) {             // the barrier that ends this layer publishes it
+            if constexpr (!kFetchAhead)
+                fetch(l + 1);
             publish(l + 1);
+        }
         now = next;
         __syncthreads();
     }

@@ -1250,6 +1250,7 @@ __device__ __forceinline__ EntryRun entry_run(const int2 *entries, unsigned long
 // kBatched: all quads of a pair are asked for before the first of them is used.  Where the compiler asks for them one by
 // one, and few waves are there to wait in turn, a fill of few candidates takes a fifth longer (eleven of 1024 that
 // the reduced problem gives up: 399 us a call and 338); with all waves there it is the same.
+constexpr int kMaxBatched = 4;       // (more quads than that: registers in scratch memory)
 template <int Q, int T, int kRes, bool kSplit, bool kBuckets, bool kBatched>
 __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tail,
                                           EntryRun run, float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
@@ -1271,7 +1272,7 @@ __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tai
         const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
         if constexpr (Q > 0) {
             const float4v *q0 = quads_at(now.x), *q1 = quads_at(now.z);
-            if constexpr (kBatched) {
+            if constexpr (kBatched && Q <= kMaxBatched) {
                 float4v v0[Q], v1[Q];
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {
@@ -2011,13 +2012,17 @@ __device__ __forceinline__ void fill_candidates(
     static_assert(kPath < 3 || (!kLevel && !kBlocks && !kTurns && !kSplit),
                   "the launches of twice the waves are plain D-record fills");
     constexpr bool kQuads = !kLevel && kNarrow;  // the D-record sweep with 128-bit LDS reads
+    constexpr bool kBatched = kTodo && !kBlocks; // (see sweep_run)
     constexpr bool kCanTile = !kLevel && !kBlocks && !kTodo && !(kPath == 1 && kNarrow);
     static_assert(!kSplit || (kQuads && kPath == 1 && !kBlocks && !kTurns),
                   "the split launch is the plain in-place D-record fill");
     if (meta[kMetaPath] != kPath || (kCanTile && meta[kMetaTiles] != 0))
         return;                                  // another launch does the work (or dp_tiles)
     const int bp = meta[kMetaBudget];
-    const int tid = threadIdx.x, nthreads = blockDim.x;
+    int tid = threadIdx.x;
+    if constexpr (kTodo)                         // (nothing of it kept in registers from block to block of dp_rest)
+        asm volatile("" : "+v"(tid));
+    const int nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
         if (tid == 0 && !(kBlocks && blocks.pass == 1) &&
             (!kTodo || todo.has_wave(blockIdx.x, K, L)))
@@ -2246,9 +2251,9 @@ __device__ __forceinline__ void fill_candidates(
         const int2 *const entries = table + (l & 1) * kNextTable;
         const Pending pending{&next_fetch, &next_first};
         if (kWhole && whole != 0) {
-            fill_share_n<!kTodo, kTodo>(whole, cur, drec_l, first, entries, lane, pending);
+            fill_share_n<!kTodo, kBatched>(whole, cur, drec_l, first, entries, lane, pending);
         } else if constexpr (inplace) {          // c_end - c <= kMax by construction
-            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs, kTodo>(
+            fill_group_n<kLevel, true, kMax, kQuads, kSplit, kPath == 1, false, kPairs, kBatched>(
                 min(c_end - c, kMax), prev, cur, choice_l, drec_l, first, entries, tl, er, s8,
                 c * kWave, lane, pending, half, part);
         } else {
@@ -2290,7 +2295,7 @@ __device__ __forceinline__ void fill_candidates(
                     __syncthreads();
                     const int cb = c0 + (int)((long long)share * nt / tw);
                     const int ce = c0 + (int)((long long)(share + 1) * nt / tw);
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, false, kPairs, kTodo>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, false, kPairs, kBatched>(
                         ce - cb, lds - lo, cur, choice_l, drec_l, first, entries, tl, er, s8,
                         cb * kWave, lane, pending);
                     __syncthreads();             // the next tile overwrites the staged part
@@ -2300,7 +2305,7 @@ __device__ __forceinline__ void fill_candidates(
                     const int n = c_end - c;
                     const int groups = (n + kMax - 1) / kMax;
                     const int r = (n + groups - 1) / groups;
-                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kGlobal, kPairs, kTodo>(
+                    fill_group_n<kLevel, false, kMax, kQuads, false, false, kGlobal, kPairs, kBatched>(
                         r, prev, cur, choice_l, drec_l, first, entries, tl, er, s8, c * kWave, lane,
                         pending);
                     c += r;
