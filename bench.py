@@ -45,7 +45,7 @@ LANE_OPS_AS_BUILT = {"valu_add_add_min3": 1.5, "valu_add_cmp_sel_min": 4.0,
 LEVEL_PAIRS_FROM = 14            # kPairsFrom of csrc/spdy_dp.hip
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2201_13096_amd", "csrc", f)
-                  for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h", "dp_small.h")]
+                  for f in ("spdy_dp.hip", "wave_ops.h", "dp_core.h", "dp_tiles.h", "dp_small.h", "dp_columns.h")]
 PROBE = os.path.join(ROOT, "paper_2201_13096_amd", "peaks_probe")
 
 
@@ -378,7 +378,8 @@ def main() -> int:
     # instructions per update).  Both objects are always reported; `roofline` is the binding one.  With at most 64
     # levels the D-record sweep reads 128 bits per lane, so its peak is the 128-bit one; the
     # fraction of the 32-bit-read peak (what a lane = bucket layout can reach at best) is beside it.
-    wide_reads = args.record == "d" and S <= 64
+    # So it is with more levels where there are more candidates than compute units (folded rows).
+    wide_reads = args.record == "d" and (S <= 64 or K > COMPUTE_UNITS)
     lds_peak = LDS_PEAK_B128 if wide_reads else LDS_PEAK_B32
     lds_probe = "lds_read_b128" if wide_reads else "lds_read_b32"
     lds_obj = {
