@@ -13,7 +13,7 @@
 // wave, so it is a matter of which registers are added, and entries are swept in runs of equal k, in any order.
 // A row that grows from layer to layer, as the first ones of a network do, is folded anew where W changes, chunk
 // by chunk, behind the barrier that ends the sweep.  Short rows, whose waves would have hardly a position each,
-// are not folded (kMetaColumns is 1 then, and not 4): lane = bucket, 32-bit reads.
+// are not folded (a position is one bucket then, and not four): lane = bucket, 32-bit reads.
 //
 // What bounds it: the level record issues vector instructions (add, min3, compare, select: 16 clocks of a SIMD for two
 // updates of 64 cells), the D record of many levels waits for LDS reads.  Bare loops, updates per clock and
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ ColumnShared sh;
-    if (meta[kMetaPath] != 1 || (!kLevel && meta[kMetaTiles] != 0))
+    if (meta[kMetaPath] != 1 || meta[kMetaTiles] >= 0)
         return;                                  // another launch does the work
     const int bp = meta[kMetaBudget];
     const int tid = threadIdx.x;
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kFillWaves * kWave, 4) void dp_columns(
     const int teams = meta[kMetaTeams];
     if ((long long)blockIdx.x * teams >= K)
         return;                                  // the first ceil(K / teams) workgroups suffice
-    const bool plain = meta[kMetaColumns] == 1;
+    const bool plain = meta[kMetaTiles] == -1;
     const int32_t *nact = meta + kMetaHeader + L;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);

@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void dp_wide(
         FillShared fill;
         TileShared tile;
     } sh;
-    if (meta[kMetaTiles] != 0)
+    if (meta[kMetaTiles] > 0)
         take_tiles<kLdsBytes>(src, meta, tables, K, L, S, pitch, drec, tstar, cost, books, lds, sh.tile);
     else
         fill_candidates<false, 3, kNarrow, false, false, false, false, false>(

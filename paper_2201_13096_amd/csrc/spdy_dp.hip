@@ -155,7 +155,6 @@ enum MetaWord {
     kMetaBudget = 0, kMetaMinTime = 1, kMetaRow = 2, kMetaPath = 3, kMetaTeamWaves = 4,
     kMetaTeams = 5, kMetaInPlace = 6,
     kMetaStage = 7,     // bytes of LDS the global-row launch has for the windows of its tiles
-    kMetaColumns = 7,   // path 1: buckets of a position, 4 or 1, where dp_columns is its launch (see there)
     // what the choice of the path was made from (read back by tests, not by the kernels)
     kMetaWaves = 8,     // waves of a fill workgroup
     kMetaMaxGroup = 9,  // most chunks a wave keeps in registers
@@ -168,7 +167,9 @@ enum MetaWord {
     kMetaLdsWide = 16,   // its dynamic LDS bytes
     kMetaGlobalWaves = 17, // waves of the global-row launch
     kMetaTable = 18,    // 1: the call leaves the whole table in the record (0: scratch)
-    kMetaTiles = 19     // not 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath
+    // > 0: dp_tiles or dp_wide does the work (see there), not the launch of kMetaPath; < 0: dp_columns, and not
+    // dp_fill, is the launch of path 1 (see there), the buckets of a position negated
+    kMetaTiles = 19
 };
 
 enum Variant { kValueRecord = 0, kLevelRecord = 1 };
@@ -576,20 +577,20 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
             }
         }
         int cells = 0;                            // of a position
-        if (columns != kNoColumns && path == 1 && bp >= 0) {
-            bool plain;
-            teams = plan_columns((int)(((reach < bp ? reach : bp) + kWave) / kWave), S,
-                                 columns == kLevelColumns, teams, &plain);
+        if (columns != kNoColumns && path == 1) {
+            bool plain = true;
+            if (bp >= 0)
+                teams = plan_columns((int)(((reach < bp ? reach : bp) + kWave) / kWave), S,
+                                     columns == kLevelColumns, teams, &plain);
             cells = plain ? 1 : 4;
+            plan_waves = waves = kFillWaves;
+            max_group = 4 * (columns == kLevelColumns ? column_chunks<true>() : column_chunks<false>());
         }
         meta[kMetaPath] = path;
         meta[kMetaTeams] = teams;
         meta[kMetaTeamWaves] = plan_waves / teams;
         meta[kMetaInPlace] = inplace;
-        if (cells)
-            meta[kMetaColumns] = cells;
-        else
-            meta[kMetaStage] = lds_stage;
+        meta[kMetaStage] = lds_stage;
         meta[kMetaWaves] = waves;
         meta[kMetaMaxGroup] = max_group;
         meta[kMetaLdsSmall] = lds_small;
@@ -605,7 +606,7 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         s_whole = path == 1 && quads && split == 0 ? 1 : 0;
         if (ta.only_memory != 0 && path != 0 && path != 4)
             s_tiles = 0;
-        meta[kMetaTiles] = s_tiles;
+        meta[kMetaTiles] = cells ? -cells : s_tiles;
     }
     __syncthreads();
     const int tw = s_team_waves;
