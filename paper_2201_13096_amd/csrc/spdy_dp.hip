@@ -182,35 +182,71 @@ constexpr int kPlainChunks = 6;
 constexpr int kFoldLevels = 16, kFoldBudget = 800, kFoldWork = 300;   // least, level record
 constexpr int kColumnTeams = 8;
 constexpr int kLookAhead = 4;
+// Waves of a team, a power of two, and the chunks of `n` that the one with the most has.
+__device__ __forceinline__ int column_waves(int teams) { return teams == 1 ? 8 : (teams == 2 ? 4 : (teams <= 4 ? 2 : 1)); }
+static_assert(kFillWaves == 8, "column_waves");
+__device__ __forceinline__ int column_share(int n, int tw) { return (n + tw - 1) >> __builtin_ctz(tw); }
 // Whether a row of `n` chunks is better not folded, `tw` waves to a row: where whole chunks of positions are more
 // than what the wider reads save.
 __device__ __forceinline__ bool plain_is_better(int n, int tw)
 {
-    const int plain = (n + tw - 1) / tw, folded = ((n + 3) / 4 + tw - 1) / tw;
+    const int plain = column_share(n, tw), folded = column_share((n + 3) / 4, tw);
     return plain <= kPlainChunks && 40 * folded > 14 * plain;
 }
 // Floats of LDS: of a candidate's row, ghost or apron included, and with its entries of two layers.
 __device__ __forceinline__ int column_row(int n, int tw, bool plain)
 {
     const int n4 = (n + 3) / 4;
-    return plain ? (n + (n + tw - 1) / tw) * kWave : 4 * (kWave * (n4 + (n4 + tw - 1) / tw) + 1);
+    return plain ? (n + column_share(n, tw)) * kWave : 4 * (kWave * (n4 + column_share(n4, tw)) + 1);
 }
 __device__ __forceinline__ int column_entries(int S) { return (S + kWave - 1) / kWave * kWave + kLookAhead; }
 __device__ __forceinline__ int column_floats(int n, int tw, bool plain, int S, bool level)
 {
     return column_row(n, tw, plain) + 2 * (level ? 3 : 2) * column_entries(S);
 }
-// Teams and fold of a row of `n` chunks, at most `teams` of them: as many as their rows have LDS and registers for.
-__device__ __forceinline__ int plan_columns(int n, int S, bool level, int teams, bool *plain)
+// What the fill of rows of `n` chunks costs with `teams` of them to a workgroup, in chunks of positions that are
+// swept; infinite where they do not have the LDS or the registers.  `slots`: workgroups the chip holds at once.
+// Rounds of workgroups times what a workgroup has to do, where a rest that finds every workgroup a compute unit to
+// itself is 0.7 of a round, a chunk of buckets 0.35 of one of positions, a wave's own share counts besides (its reads
+// wait for each other) and so does what every layer takes.  Only compared with itself.  D record: the same for
+// every number that there is room for.
+__device__ __forceinline__ float column_cost(int K, int n, int S, bool level, int slots, int teams)
 {
     const int most = level ? column_chunks<true>() : column_chunks<false>();
-    for (teams = min(teams, kColumnTeams);; --teams) {
-        const int tw = kFillWaves / teams;
-        *plain = plain_is_better(n, tw);
-        if (teams == 1 || ((*plain || ((n + 3) / 4 + tw - 1) / tw <= most) &&
-                           teams * column_floats(n, tw, *plain, S, level) * (int)sizeof(float) <= kLdsHalf))
-            return teams;
-    }
+    const int tw = column_waves(teams), n4 = (n + 3) / 4;
+    const bool plain = plain_is_better(n, tw);
+    if (teams > 1 && ((!plain && column_share(n4, tw) > most) ||
+                      teams * column_floats(n, tw, plain, S, level) * (int)sizeof(float) > kLdsHalf))
+        return __builtin_inff();
+    if (!level)
+        return 0.0f;
+    const float row = plain ? 0.35f * n : n4, share = plain ? 0.35f * column_share(n, tw) : column_share(n4, tw);
+    // (whole numbers by fp32 divisions: integer ones took 1 us)
+    const float groups = floorf((K + (teams - 0.5f)) / teams), full = floorf((groups + 0.5f) / slots);
+    const float rest = groups - full * slots;
+    const float rounds = full + (rest < 0.5f ? 0.0f : (2.0f * rest > slots ? 1.0f : 0.7f));
+    return rounds * (8.0f + teams * row + 4.0f * share);
+}
+// Teams of a workgroup, at most `teams`: as many as there is room for, or fewer where these cost less by a twentieth.
+// (As many as there is room for are often a few more than one round of workgroups takes, and the second round takes
+// nearly as long.)  us a fill with the most and so, L = 16: S = 128, K = 3000, 17 chunks 885 (5 teams) and 610 (4),
+// K = 4000, 19 chunks 1190 and 811; S = 40, K = 4000, 13 chunks 285 (6) and 235 (4), K = 2100, 25 chunks 253 (4) and
+// 245 (3).  Of 624 fills none was more than 0.1 % slower.
+// `cost`: column_cost of 1, 2, ... teams.
+__device__ __forceinline__ int plan_columns(const float *cost, int teams)
+{
+    float of[kColumnTeams], limit = __builtin_inff();
+#pragma unroll
+    for (int i = 0; i < kColumnTeams; ++i)       // (read together)
+        of[i] = cost[i];
+    int best = 0;
+#pragma unroll
+    for (int i = kColumnTeams; i > 0; --i)
+        if (i <= teams && of[i - 1] < limit) {
+            limit = best == 0 ? 0.95f * of[i - 1] : of[i - 1];
+            best = i;
+        }
+    return best;
 }
 // one team: any row that a workgroup of either record may have in place, with all the entries there may be
 static_assert(kFillWavesLevel * kMaxGroupLevel <= 4 * kFillWaves * column_chunks<true>() &&
@@ -428,6 +464,7 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
 {
     __shared__ long long s_sum[8];
     __shared__ int s_span[4], s_team_waves, s_tiles, s_beyond, s_whole;
+    __shared__ float s_columns[kColumnTeams];
     int32_t *const s_least = words, *const s_most = words + 256;
     const int tid = threadIdx.x;
     if (tid == 0)
@@ -530,12 +567,15 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
     if (lane == kWave - 1)
         s_span[wave] = widest;
     __syncthreads();
-    if (tid < kWave) {
-        const long long top = reach < bp ? reach : bp;
-        plan_tiles(K, L, S, bp, bp < 0 ? 0 : (int)((top + kWave) / kWave), (bp + kWave) / kWave,
+    const long long top = reach < bp ? reach : bp;
+    const int last_chunks = bp < 0 ? 0 : (int)((top + kWave) / kWave);     // of the last row
+    if (tid < kWave)
+        plan_tiles(K, L, S, bp, last_chunks, (bp + kWave) / kWave,
                    max(max(s_span[0], s_span[1]), max(s_span[2], s_span[3])), (int)(reach / L), ta,
                    &s_tiles);
-    }
+    else if (columns != kNoColumns && tid < kWave + kColumnTeams)
+        s_columns[tid - kWave] =
+            column_cost(K, min(last_chunks, 1 << 12), S, columns == kLevelColumns, slots, tid - kWave + 1);
     __syncthreads();
     if (tid == 0) {
         const int rowp = bp < 0 ? 0 : (bp + kWave) / kWave * kWave;
@@ -578,11 +618,9 @@ __device__ void prepare_budget(const int32_t *__restrict__ tau, int K, int slots
         }
         int cells = 0;                            // of a position
         if (columns != kNoColumns && path == 1) {
-            bool plain = true;
             if (bp >= 0)
-                teams = plan_columns((int)(((reach < bp ? reach : bp) + kWave) / kWave), S,
-                                     columns == kLevelColumns, teams, &plain);
-            cells = plain ? 1 : 4;
+                teams = plan_columns(s_columns, teams);
+            cells = plain_is_better(last_chunks, column_waves(teams)) ? 1 : 4;
             plan_waves = waves = kFillWaves;
             max_group = 4 * (columns == kLevelColumns ? column_chunks<true>() : column_chunks<false>());
         }
@@ -3243,6 +3281,15 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // L = 14, B = 3357, K = 1144 126 and 137; and where it is taken S = 16, L = 124, B = 1585, K = 1534 691 and 646;
     // S = 35, L = 37, B = 833, K = 1378 246 and 191; S = 20, L = 9, B = 1396, K = 312 55 and 43; S = 33, L = 19,
     // B = 3271, K = 1890 269 and 244.
+    // The budget's length counts, and not that of the reduced row: a workgroup of dp_fill has a wave for every chunk of the
+    // budget, and where those are sixteen it is slower on short rows too.  us a fill by dp_fill and so, B = 3000, rows of
+    // 250 buckets: S = 70, L = 86, K = 300 569 and 476, S = 16, L = 54, K = 1024 173 and 137, S = 40, L = 54, K = 4000
+    // 388 and 347.  Slower on rows of one chunk with 65 to 100 levels (S = 70, K = 4000, L = 54 420 and 476) and for some
+    // numbers of candidates beyond 4 x units on rows of 13 to 45 chunks, few levels above all (L = 20, K = 2100, 26
+    // chunks: S = 16 175 and 206, S = 40 297 and 320).  Both launches, for the prepare kernel to choose from, would save
+    // 0.2 % over 441 fills of more than 4 x units candidates, less than the idle one takes (2 us and more).
+    // D record of more than 64 levels: always.  us by dp_fill and so, K = 4000: S = 65, L = 10, B = 800 179 and 150;
+    // S = 255, L = 10, B = 800 390 and 306; S = 100, L = 12, B = 61 505 and 150; the worst of 370 on 1 - 80 chunks 0.92.
     constexpr bool kLeft = kTodo && kLevel;       // (the D record's are dp_rest's)
     constexpr bool can_fold = (!kNarrow || (kLevel && kPairs)) && !kBlocks && !kTodo;
     const bool columns = can_fold && K > units && !resume.first_layer &&

@@ -155,3 +155,17 @@ def test_which_launch(dp, compact, K, L, S, B, folded):
     words = compare(dp, tau, err, B, compact, f"not feasible K={K} L={L} S={S} B={B}", copies=K)[1]
     assert words[0] == -1
 
+
+# As many candidates to a workgroup as there is room for, but fewer where that saves most of a round of workgroups
+@pytest.mark.parametrize("K, S, n, teams", [(3000, 128, 17, 4), (4000, 70, 19, 4), (4000, 40, 13, 4), (4000, 40, 17, 4),
+                                            (2100, 40, 25, 3), (4000, 40, 6, 8), (2100, 40, 12, 5), (600, 40, 13, 2)])
+def test_candidates_of_a_workgroup(dp, K, S, n, teams):
+    rng = np.random.default_rng(K + S + n)
+    L, B = 8, 64 * n - 3
+    L = -(-300 // S) if L * S < 300 else L
+    tau, err, _ = workloads.random_instance(rng, 37, L, S, B, tau_max=B // 2, integer_err=9)
+    tau[:, 0] = 0
+    tau[0, 1] = B
+    tau[-1] += 900                                # a budget that is long enough for the level record
+    folded, words = compare(dp, tau, err, B + 900, True, f"K={K} S={S} row={B}", copies=K)
+    assert folded and words[5] == teams, words
