@@ -2588,6 +2588,52 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_levels(
         cost[k] = sum;
 }
 
+// The same by one lane per candidate, which reads a level, then its shift, then the next level: what a trip takes
+// counts less the more waves there are, and these are 64 times fewer.
+template <bool kByItself>
+__global__ void dp_backtrace_levels_by_lanes(const int32_t *__restrict__ tau, ErrSource src,
+                                             const int32_t *__restrict__ meta,
+                                             const uint8_t *__restrict__ choice,
+                                             const int32_t *__restrict__ tstar, int K, int L, int S,
+                                             int pitch, int16_t *__restrict__ profile,
+                                             float *__restrict__ cost, Todo todo)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= K || !todo.has(k, K, L))
+        return;
+    int16_t *prof = profile + (size_t)k * L;
+    int t = tstar[k];
+    const bool none = kByItself && !meta[kMetaTable];
+    if (none || t < 0) {
+        for (int l = 0; l < L; ++l)
+            prof[l] = none ? -2 : -1;
+        if (none)
+            cost[k] = __builtin_nanf("");
+        return;
+    }
+    const int32_t *mn = meta + kMetaHeader;
+    const uint8_t *choice_k = choice + (size_t)k * L * pitch;
+    bool ok = true;
+    for (int l = L - 1; ok && l >= 0; --l) {
+        const int s = choice_k[(size_t)l * pitch + t];
+        prof[l] = (int16_t)s;
+        ok = s < S;          // cannot fail on a filled table; never index tau out of range
+        if (ok) {
+            t -= tau[(size_t)l * S + s] - mn[l];
+            ok = t >= 0;
+        }
+    }
+    __threadfence_block();
+    float acc = ok ? -0.0f : __builtin_nanf("");
+    for (int l = 0; ok && l < L; ++l)
+        acc += src.row(k, l, L, S).at(prof[l]);
+    cost[k] = acc;
+}
+// Up to how many candidates a unit has a wave for each.  us a walk by lanes and by waves, L = 54, S = 40: K = 8192 67
+// and 44, 12000 71 and 61, 16384 82 and 85, 32768 131 and 179; L = 24, S = 130: K = 8192 30 and 28, 12000 31 and 38;
+// L = 8, S = 20: K = 4096 7.7 and 7.4, 6000 7.8 and 8.4, 16384 11 and 17; L = 4, S = 4, K = 200000 15 and 98.
+constexpr int kLevelWaves = 32, kLevelWavesShort = 16, kLevelShort = 16;
+
 // One wave walks solve `solve`, which is candidate k under some budget, from time `tstar`.
 template <int kLevelBlocks, bool kByItself, bool kGuess = false>
 __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrSource src,
@@ -3552,19 +3598,23 @@ int backtrace_impl(const int32_t *tau, ErrSource src, int K, int L, int S, int B
     const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
     const int32_t *tstar = reinterpret_cast<const int32_t *>(ws + lay.tstar_off);
     (void)hipGetLastError();
+    DeviceState dev;
+    const int ok = device_state(false, &dev);
+    if (ok != SPDY_DP_OK)
+        return ok;
     if (lay.variant == kLevelRecord) {
         auto walk = S <= kWave ? dp_backtrace_levels<1, false> : dp_backtrace_levels<4, false>;
         if (by_itself)
             walk = S <= kWave ? dp_backtrace_levels<1, true> : dp_backtrace_levels<4, true>;
-        const int per_block = kWalkThreads / kWave;
-        hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
+        int per_block = kWalkThreads / kWave, threads = kWalkThreads;
+        if (K > (long long)(L < kLevelShort ? kLevelWavesShort : kLevelWaves) * dev.units) {
+            walk = by_itself ? dp_backtrace_levels_by_lanes<true> : dp_backtrace_levels_by_lanes<false>;
+            per_block = threads = kWave;
+        }
+        hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(threads), 0, q,
                            tau, src, meta, reinterpret_cast<const uint8_t *>(ws + lay.record_off),
                            tstar, K, L, S, (int)lay.row, profile, cost, todo);
     } else {
-        DeviceState dev;
-        const int ok = device_state(false, &dev);
-        if (ok != SPDY_DP_OK)
-            return ok;
         launch_walk(tau, src, meta, reinterpret_cast<const float *>(ws + lay.record_off), tstar, K,
                     1, L, S, (int)lay.row, profile, cost, resume, todo, by_itself, dev.units, q);
     }

@@ -85,6 +85,32 @@ def test_walks_of_many(dp, L, S):
             assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"again L={L} S={S} compact={compact}")
 
 
+# As many candidates as have a wave each, and one more: the level record goes to a lane per candidate (at fewer
+# candidates where layers are few).  One in seven is not feasible.
+@pytest.mark.parametrize("K, L, S", [(4096, 49, 6), (4097, 49, 6), (4096, 9, 70), (4097, 9, 70), (4097, 15, 3),
+                                     (8192, 16, 70), (8193, 16, 70), (8193, 17, 5), (9000, 45, 2)])
+def test_walks_of_very_many(dp, K, L, S):
+    rng = np.random.default_rng(K + L + S)
+    n, B = 35, 25 * L + 60
+    tau, err, _ = workloads.random_instance(rng, n, L, S, B, tau_max=90, integer_err=7, inf_err_frac=0.05)
+    tau[:, -1] = np.minimum(tau[:, -1], 25)
+    err[::7, L // 2] = np.inf
+    which = np.arange(K) % n
+    want_p, want_c = (x[which] for x in oracle.solve_ref(tau, err, B))
+    tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err[which]).cuda()
+    for compact in (False, True):
+        print(f"[walk] K={K} L={L} S={S} compact={compact}", flush=True)
+        ws = dp.alloc_workspace(K, L, S, B, compact=compact)
+        p, c = dp.spdy_dp_solve_batched(tau_d, err_d, B, workspace=ws)
+        assert_same(p.cpu().numpy(), c.cpu().numpy(), want_p, want_c, f"compact={compact}")
+        p.fill_(7)
+        dp.spdy_dp_backtrace(tau_d, err_d, B, p, c, ws)
+        assert_same(p.cpu().numpy(), c.cpu().numpy(), want_p, want_c, f"again compact={compact}")
+        dp.spdy_dp_solve_profiles(tau_d, err_d, B, workspace=ws)            # leaves no table
+        dp.spdy_dp_backtrace(tau_d, err_d, B, p, c, ws)
+        assert (p == -2).all() and torch.isnan(c).all()
+
+
 # (several budgets over a table of eight layers are not tried by the reduced solve first)
 @pytest.mark.parametrize("K, J, L", [(256, 1, 18), (257, 1, 18), (128, 2, 8), (42, 6, 8), (43, 6, 8), (128, 2, 18)])
 def test_as_many_as_units(dp, K, J, L):
