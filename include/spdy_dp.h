@@ -218,8 +218,9 @@ int spdy_dp_solve_checkpointed(const int32_t *tau, const float *err, int K, int 
  *   out[1] byte offset of the int32 header: [0] B - M (or -1 if M > B: nobody is feasible),
  *          [1] M, [2] reduced row length (B - M + 1 padded to 64), [3] which launch of the fill
  *          did the work: 0 rows in global memory, 1 one row per candidate in LDS updated in
- *          place, 2 two rows in LDS, 3 / 4 as 1 / 0 in a workgroup of twice the waves (D record:
- *          rows too long for launch 1); [4] waves per candidate, [5] candidates per workgroup,
+ *          place (see also [19]), 2 two rows in LDS, 3 / 4 as 1 / 0 in a workgroup of twice the
+ *          waves (D record: rows too long for launch 1); [4] waves per candidate, [5] candidates
+ *          per workgroup,
  *          [6] 1 if rows are updated in place; and what that choice was made from: [7] bytes of
  *          LDS for the windows of launch 0, [8] waves per workgroup, [9] most 64-bucket chunks a
  *          wave keeps in registers, [10] / [11] dynamic LDS bytes of launches 1 / 2 (0: not
@@ -228,7 +229,11 @@ int spdy_dp_solve_checkpointed(const int32_t *tau, const float *err, int K, int 
  *          (D record, S <= 64, no more candidates than compute units), [14] waves of launch 3
  *          (0: not enqueued), [15] most chunks one of them keeps in registers, [16] its dynamic
  *          LDS bytes, [17] waves of the global-row launch, [18] 1 if the call left the whole table
- *          in the record, 0 if the workspace was scratch.  Per-layer arrays follow the
+ *          in the record, 0 if the workspace was scratch, [19] > 0 if a launch of tiles (one or
+ *          several workgroups per candidate) did the work instead of [3], < 0 if launch 1 was the
+ *          one of folded rows (level record, or more than 64 levels; more candidates than
+ *          compute units): -[19] buckets lie side by side, 4 or, in short rows, 1, and [4], [5],
+ *          [8] and [9] are that launch's.  Per-layer arrays follow the
  *          out[6] header words: m_l at [out[6] + l], the number of computed 64-bucket chunks of
  *          layer l at [out[6] + L + l], the largest usable shift of layer l at
  *          [out[6] + (2 + out[7]) L + l]
