@@ -1825,7 +1825,7 @@ __device__ __forceinline__ int walk_layers(const int32_t *__restrict__ tau, cons
 //   time below it.  (A row is not quite convex: from the next bucket below on, one of 64 samples is nearly as
 //   low as the last one now and then, and every third guess or more is wrong.  1 - 4 of 54 layers are so.)
 // ---------------------------------------------------------------------------------------
-constexpr int kGuessed = 8, kGuessSlack = 4, kGuessLayers = 24;
+constexpr int kGuessed = 8, kGuessSlack = 4, kGuessLayers = 48, kGuessWaves = 16;
 
 struct GuessedLayers {           // of layers top, top - 1, ...; below the first one, the first once more
     int shift[kGuessed];         // of level `lane`; until settle() with what lane j has in `least`
@@ -2634,11 +2634,11 @@ __global__ void dp_backtrace_levels_by_lanes(const int32_t *__restrict__ tau, Er
 // L = 8, S = 20: K = 4096 7.7 and 7.4, 6000 7.8 and 8.4, 16384 11 and 17; L = 4, S = 4, K = 200000 15 and 98.
 constexpr int kLevelWaves = 32, kLevelWavesShort = 16, kLevelShort = 16;
 
-// One wave walks solve `solve`, which is candidate k under some budget, from time `tstar`.
-template <int kLevelBlocks, bool kByItself, bool kGuess = false>
+// One wave walks solve `solve`, which is candidate k under some budget, from the time that tstar() gives.
+template <int kLevelBlocks, bool kByItself, bool kGuess = false, class Time>
 __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrSource src,
                                            const int32_t *__restrict__ meta,
-                                           const float *__restrict__ drec, int tstar,
+                                           const float *__restrict__ drec, Time tstar,
                                            int solve, int k, int L, int S, int pitch,
                                            int16_t *__restrict__ profile, float *cost,
                                            Resume resume)
@@ -2649,7 +2649,7 @@ __device__ __forceinline__ void walk_table(const int32_t *__restrict__ tau, ErrS
     const float *drec_k = drec + (size_t)k * L * pitch;
     const int l0 = resume.start(k, L);           // rows below l0 are the incumbent's
     auto row_of = [&](int l) { return (l < l0 ? resume.inc_rec : drec_k) + (size_t)l * pitch; };
-    const int from = kByItself && !meta[kMetaTable] ? -2 : tstar;
+    const int from = kByItself && !meta[kMetaTable] ? -2 : tstar();
     int t;
     if constexpr (kGuess)
         t = walk_guessed(tau, mine, meta, row_of, from, L, S, prof);
@@ -2674,11 +2674,14 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_values(
     const float *__restrict__ drec, const int32_t *tstar, int K, int budgets, int L, int S,
     int pitch, int16_t *__restrict__ profile, float *cost, Resume resume, Todo todo)
 {
-    const int solve = uniform(blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave);
+    int solve = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
+    if constexpr (kGuess)
+        solve = uniform(solve);
     const int k = budgets > 1 ? solve % K : solve;
     if (solve < K * budgets && todo.has_wave(solve, K, L))
-        walk_table<kLevelBlocks, kByItself, kGuess>(tau, src, meta, drec, tstar[solve], solve, k, L, S, pitch,
-                                                    profile, cost, resume);
+        walk_table<kLevelBlocks, kByItself, kGuess>(
+            tau, src, meta, drec, [=]() __attribute__((always_inline)) { return tstar[solve]; }, solve, k, L, S,
+            pitch, profile, cost, resume);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -3007,7 +3010,9 @@ __global__ __launch_bounds__((kBlocks || kShape == 1 ? 1 : 2) * kFillWaves * kWa
         if (k >= K || __builtin_amdgcn_readfirstlane(profile[(size_t)solve * L]) != kGivenUp)
             continue;
         const int t = budgets ? budget_time(meta, drec, k, L, pitch, budget.at[j]) : tstar[k];
-        walk_table<kLevelBlocks, false>(tau, src, meta, drec, t, solve, k, L, S, pitch, profile, cost, resume);
+        walk_table<kLevelBlocks, false>(
+            tau, src, meta, drec, [=]() __attribute__((always_inline)) { return t; }, solve, k, L, S, pitch, profile,
+            cost, resume);
     }
 }
 
@@ -3573,10 +3578,17 @@ void launch_walk(const int32_t *tau, ErrSource src, const int32_t *meta, const f
     auto walk = S <= kWave ? dp_backtrace_values<1, false, false> : dp_backtrace_values<4, false, false>;
     if (by_itself)
         walk = S <= kWave ? dp_backtrace_values<1, true, false> : dp_backtrace_values<4, true, false>;
-    // By guesses from kGuessLayers on (us a walk, layer by layer and so, K = 600: L = 9, S = 64 14.1 and 18.0;
-    // L = 17, S = 8 19.3 and 21.7; L = 54, S = 40 52 and 35).  Rows of 2 GB and more, whose buckets a buffer
-    // does not reach, and the few candidates that the reduced solve leaves: layer by layer.
-    if (S <= kWave && L >= kGuessLayers && pitch < 1 << 29 && !todo.profile)
+    // By guesses from kGuessLayers on and up to kGuessWaves candidates to a unit, beyond which the waves that a unit
+    // holds at once have two each.  us a walk, layer by layer and so, of tables at falling returns and of tables where
+    // most guesses fail (errors like the root of the time saved): K = 1024, S = 40 L = 24 24 and 20, 24 and 30; L = 32
+    // 31 and 23, 31 and 33; L = 48 44 and 30, 44 and 45; L = 54 50 and 33, 50 and 55; K = 600, S = 8, L = 40 36 and 30,
+    // 36 and 42; L = 48 43 and 34, 42 and 46; L = 80 68 and 45, 67 and 66.  S = 40: K = 4096, L = 54 76 and 50, L = 24
+    // 32 and 28; K = 6000 75 and 73, 35 and 42; K = 16384, L = 30 98 and 110.  (Going on layer by layer after a few
+    // wrong guesses was not kept: with both walks in it the kernel took 55 where this takes 35.)
+    // Rows of 2 GB and more, whose buckets a buffer does not reach, and the few candidates that the reduced solve
+    // leaves: layer by layer.
+    if (S <= kWave && L >= kGuessLayers && pitch < 1 << 29 && !todo.profile &&
+        (long long)K * budgets <= (long long)kGuessWaves * units)
         walk = by_itself ? dp_backtrace_values<1, true, true> : dp_backtrace_values<1, false, true>;
     hipLaunchKernelGGL(walk, dim3((K * budgets + per_block - 1) / per_block), dim3(kWalkThreads), 0,
                        q, tau, src, meta, drec, tstar, K, budgets, L, S, pitch, profile, cost,

@@ -56,11 +56,12 @@ def test_walks(dp, L, S, B, widest):
                         f"resumed L={L} S={S} B={B}")
 
 
-# More candidates than units: the walk by guesses (blocks of eight layers, cut at the first one; guesses that hold for
-# smooth tables and fail in every layer for others; levels far from the guess; ties), and the level record's two
-# layers at a time (odd and even numbers of layers, levels around the words of 64).
+# More candidates than units: layer by layer, and from 48 layers on by guesses (blocks of eight layers, the last of them of
+# one, seven or all eight; guesses that hold for smooth tables and fail in every layer for others; levels far from the
+# guess; ties), and the level record's two layers at a time (odd and even numbers of layers, levels around the words of
+# 64).
 @pytest.mark.parametrize("S", [1, 2, 40, 63, 64, 65, 200])
-@pytest.mark.parametrize("L", [1, 2, 7, 8, 9, 17, 40])
+@pytest.mark.parametrize("L", [1, 2, 7, 8, 9, 17, 40, 47, 48, 49, 52, 55, 65])
 def test_walks_of_many(dp, L, S):
     rng = np.random.default_rng(L * 500 + S)
     K, B = 300, 60 * L + 200
@@ -75,7 +76,7 @@ def test_walks_of_many(dp, L, S):
         err[K // 3, L // 2] = np.inf              # one is not
         print(f"[walk] L={L} S={S} smooth={smooth} values={values}", flush=True)
         tau_d, err_d = torch.from_numpy(tau).cuda(), torch.from_numpy(err).cuda()
-        want = oracle.solve_ref(tau, err, B)
+        want = oracle.solve_ref(tau, err, B, threads=16)
         for compact in (False, True):
             ws = dp.alloc_workspace(K, L, S, B, compact=compact)
             p, c = dp.spdy_dp_solve_batched(tau_d, err_d, B, workspace=ws)
@@ -85,8 +86,8 @@ def test_walks_of_many(dp, L, S):
             assert_same(p.cpu().numpy(), c.cpu().numpy(), *want, f"again L={L} S={S} compact={compact}")
 
 
-# As many candidates as have a wave each, and one more: the level record goes to a lane per candidate (at fewer
-# candidates where layers are few).  One in seven is not feasible.
+# As many candidates as have a wave each, and one more: the D record goes back to layer by layer, the level record to a
+# lane per candidate (at fewer candidates where layers are few).  One in seven is not feasible.
 @pytest.mark.parametrize("K, L, S", [(4096, 49, 6), (4097, 49, 6), (4096, 9, 70), (4097, 9, 70), (4097, 15, 3),
                                      (8192, 16, 70), (8193, 16, 70), (8193, 17, 5), (9000, 45, 2)])
 def test_walks_of_very_many(dp, K, L, S):
