@@ -44,6 +44,7 @@
 // computed tile by tile, the part of the previous row a tile reads being staged in LDS first.
 #include <hip/hip_runtime.h>
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <mutex>
@@ -1286,10 +1287,11 @@ __device__ __forceinline__ EntryRun entry_run(const int2 *entries, unsigned long
 // they cost 28 clocks of the pipe that the mins need, more than four quads of mins do.  That pipe takes four
 // clocks for any instruction but fp32 adds and multiplies of vector registers only, which have a
 // second one (v_min3 4.0 clocks of a SIMD, v_add 2.0, v_add with a scalar or a lane to the left 4.0).
-// kBatched: all quads of a pair are asked for before the first of them is used.  Where the compiler asks for them one by
-// one, and few waves are there to wait in turn, a fill of few candidates takes a fifth longer (eleven of 1024 that
-// the reduced problem gives up: 399 us a call and 338); with all waves there it is the same.
-constexpr int kMaxBatched = 4;       // (more quads than that: registers in scratch memory)
+// kBatched: all quads of a pair are asked for before the first of them is used.  The compiler does so by itself, but not
+// in the loop over blocks of layers of dp_rest, where it runs out of scalar registers and reads a quad at a time.  us a call
+// with checkpoints of which eleven candidates are given up, so and batched: K = 1024, L = 54, S = 40, B = 10^4 788 and 697;
+// K = 2000, B = 3000 833 and 692.
+constexpr int kMaxBatched = 5;       // (more quads at once than that: registers in scratch memory)
 template <int Q, int T, int kRes, bool kSplit, bool kBuckets, bool kBatched>
 __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tail,
                                           EntryRun run, float (&bq)[Q > 0 ? Q : 1][4], float (&bt)[T > 0 ? T : 1])
@@ -1311,19 +1313,23 @@ __device__ __forceinline__ void sweep_run(const float4v *quads, const float *tai
         const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
         if constexpr (Q > 0) {
             const float4v *q0 = quads_at(now.x), *q1 = quads_at(now.z);
-            if constexpr (kBatched && Q <= kMaxBatched) {
-                float4v v0[Q], v1[Q];
+            if constexpr (kBatched) {
+                constexpr int kAtOnce = Q <= kMaxBatched ? Q : (Q + 1) / 2;
 #pragma unroll
-                for (int j = 0; j < Q; ++j) {
-                    v0[j] = q0[j * kQuadLanes];
-                    v1[j] = q1[j * kQuadLanes];
+                for (int j0 = 0; j0 < Q; j0 += kAtOnce) {
+                    float4v v0[kAtOnce], v1[kAtOnce];
+#pragma unroll
+                    for (int j = 0; j < kAtOnce && j0 + j < Q; ++j) {
+                        v0[j] = q0[(j0 + j) * kQuadLanes];
+                        v1[j] = q1[(j0 + j) * kQuadLanes];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < kAtOnce && j0 + j < Q; ++j)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            vmin3(bq[j0 + j][c], v0[j][c] + e0, v1[j][c] + e1);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = 0; j < Q; ++j)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        vmin3(bq[j][c], v0[j][c] + e0, v1[j][c] + e1);
             } else {
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {
@@ -2036,7 +2042,7 @@ struct FillShared {      // static LDS of the kernels
 };
 static_assert(sizeof(FillShared) <= kLdsStatic, "static LDS");
 template <bool kLevel, int kPath, bool kNarrow, bool kBlocks, bool kTodo, bool kTurns, bool kSplit,
-          bool kPairs>
+          bool kPairs, bool kBatched = false>
 __device__ __forceinline__ void fill_candidates(
     ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units, int K, int L,
     int S, int pitch, uint8_t *__restrict__ choice, float *__restrict__ drec,
@@ -2051,17 +2057,13 @@ __device__ __forceinline__ void fill_candidates(
     static_assert(kPath < 3 || (!kLevel && !kBlocks && !kTurns && !kSplit),
                   "the launches of twice the waves are plain D-record fills");
     constexpr bool kQuads = !kLevel && kNarrow;  // the D-record sweep with 128-bit LDS reads
-    constexpr bool kBatched = kTodo && !kBlocks; // (see sweep_run)
     constexpr bool kCanTile = !kLevel && !kBlocks && !kTodo && !(kPath == 1 && kNarrow);
     static_assert(!kSplit || (kQuads && kPath == 1 && !kBlocks && !kTurns),
                   "the split launch is the plain in-place D-record fill");
     if (meta[kMetaPath] != kPath || (kCanTile && meta[kMetaTiles] != 0))
         return;                                  // another launch does the work (or dp_tiles)
     const int bp = meta[kMetaBudget];
-    int tid = threadIdx.x;
-    if constexpr (kTodo)                         // (nothing of it kept in registers from block to block of dp_rest)
-        asm volatile("" : "+v"(tid));
-    const int nthreads = blockDim.x;
+    const int tid = threadIdx.x, nthreads = blockDim.x;
     if (bp < 0) {                                // even the fastest levels exceed the budget
         if (tid == 0 && !(kBlocks && blocks.pass == 1) &&
             (!kTodo || todo.has_wave(blockIdx.x, K, L)))
@@ -2073,7 +2075,7 @@ __device__ __forceinline__ void fill_candidates(
     const int tw = meta[kMetaTeamWaves];
     if ((long long)blockIdx.x * teams >= K)
         return;                                  // the first ceil(K / teams) workgroups suffice
-    if constexpr (kTodo) {
+    if constexpr (kTodo && kLevel) {             // (dp_rest has looked)
         bool any = false;
         for (int i = 0; i < teams && blockIdx.x * teams + i < (unsigned)K; ++i)
             any |= todo.has_wave(blockIdx.x * teams + i, K, L);
@@ -2249,9 +2251,9 @@ __device__ __forceinline__ void fill_candidates(
             const ErrRow en = mine.layer(l + 1, S);
             // Rows in memory need all of their registers for the sweep: addresses of a lane that stayed in
             // registers over all layers (these, and with the level record those of the copy to LDS below) drove
-            // four others to scratch memory.
+            // four others to scratch memory.  (dp_rest keeps the index of a thread besides.)
             int mine_of = lane;
-            if constexpr (kGlobal)
+            if constexpr (kGlobal || (kTodo && !kLevel))
                 asm("" : "+v"(mine_of));
             if constexpr (kNarrow)
                 next_fetch = fetch_levels<kLevel>(tn, en, S, s8, mine_of, producer);
@@ -2478,8 +2480,17 @@ __device__ __forceinline__ int budget_time(const int32_t *__restrict__ meta, con
     float bv = __builtin_inff();
     int bt = INT32_MAX;
     const float *const last = drec + ((size_t)k * L + (L - 1)) * pitch;
-    for (int t = lane; t <= top; t += kWave)
-        argmin_merge(bv, bt, last[t], t);
+    constexpr int kLoads = 16;                   // at once
+    const int end = (int)top;
+    for (int t0 = lane; t0 <= end; t0 += kLoads * kWave) {
+        float v[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)         // (past the end: the last one again)
+            v[i] = last[min(t0 + i * kWave, end)];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            argmin_merge(bv, bt, v[i], min(t0 + i * kWave, end));
+    }
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         const float ov = __shfl_xor(bv, off, kWave);
@@ -2945,74 +2956,121 @@ __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
 }
 
 // Behind dp_core, D record: fill and walk back of the few candidates it gave up, under one or several budgets or
-// with checkpoints, in one launch, or two where rows may be longer than a workgroup of the usual size has in place.
-// Nearly always there is nothing to do, and what counts is the number of launches, 1.9 us each and more with many
-// workgroups.  us a call with a launch for each step and row length, and so: K = 256, L = 200, S = 64, B = 65536 with
-// checkpoints 212 and 190 (15 launches then); K = 1069, L = 21, S = 112, B = 29856 with checkpoints 143 and 98; 64
-// candidates under six budgets 53.8 and 50.7; K = 333, S = 127 70.1 and 68.2.  Where nothing reduces, calls with
-// checkpoints take 0.9 - 1.1 times as long as they did, others 0.95 - 1.06 times.
+// with checkpoints, in one launch, or two or three where rows may be longer than a workgroup of the usual size has in
+// place.  Nearly always there is nothing to do, and what counts is the number of launches, 1.9 us each and more with
+// many workgroups.  us a call with a launch for each step and row length, and so:
+// Nothing given up, L = 54, S = 40, B = 10^4: with checkpoints K = 64 56 and 45, K = 300 77 and 49, K = 1024 106 and
+// 72, K = 256, L = 200, S = 64, B = 65536 219 and 194; 64 candidates under six budgets 56.6 and 53.4; under one, K = 1024
+// 74 and 72.  Eleven of 1024 given up: 384 and 379, with checkpoints 720 and 700.  All of them: K = 64 364 and 364, K = 700
+// 726 and 780, K = 1024 941 and 943; with checkpoints K = 300 981 and 918, K = 1024 1812 and 1851, L = 200 29600 and
+// 27900, K = 300, B = 60000 3860 and 3730, B = 15000 1190 and 1260; 64 candidates under six budgets 386 and 399.  (K = 700
+// and B = 15000 are the worst of 80 shapes.)
 //   kShape 0: no more candidates than compute units, one to a workgroup; rows of any length.  A candidate has a unit
 //             to itself then whatever LDS its workgroup asks for, and its walk only needs its own rows.
 //          1: more of them, rows in place (path 1), two workgroups to a unit, `teams` candidates to each
-//          2: more of them, longer rows
-// (A fill that is a function by itself, called in a loop over few workgroups, keeps registers in scratch memory, and
-// launches that find nothing to do cost 8 us more.)
+//          2: more of them, longer rows; with checkpoints those that fit LDS (path 2)
+//          3: with checkpoints, rows in memory (path 0), whose workgroups take half of a unit's LDS each
+// The arguments are read again where a fill or a walk begins.  Kept from block to block, they and what is made of them
+// took all scalar registers, the rest of which moved to lanes of vector registers and back within the sweep:
+// eleven of 1024 given up took 433 us, all of K = 250, L = 30, S = 100, B = 9000 with checkpoints 1410 (969 so).
+struct Rest {
+    ErrSource src;
+    LevelTables tables;
+    int units, K, L, S, pitch;
+    float *drec, *rows;
+    int32_t *tstar;
+    int16_t *profile;
+    float *cost;
+    Resume resume;
+    Blocks blocks;
+    Todo todo;
+    int budgets;                 // 0: one, and its walk; several, and theirs; -1: the walks are other launches'
+    Budgets budget;
+};
 template <bool kNarrow, bool kBlocks, int kShape>
 __global__ __launch_bounds__((kBlocks || kShape == 1 ? 1 : 2) * kFillWaves * kWave, 4) void dp_rest(
-    const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta, LevelTables tables, int units,
-    int K, int L, int S, int pitch, float *drec, float *rows, int32_t *tstar, int16_t *profile, float *cost,
-    Resume resume, Blocks blocks, Todo todo, int budgets, Budgets budget)
+    const int32_t *__restrict__ tau, const int32_t *__restrict__ meta, const Rest)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ FillShared sh;
     constexpr int kLevelBlocks = kNarrow ? 1 : 4;
-    if constexpr (kShape > 0)
-        if ((meta[kMetaPath] == 1) != (kShape == 1))
+    constexpr int kRestAt = 2 * sizeof(void *);  // behind tau and meta
+    auto args = []() __attribute__((always_inline)) {
+        auto at = __builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(at));             // (an address of its own: read anew)
+        return *(const Rest *)((const char *)at + kRestAt);
+    };
+    auto budget_of = [](int j) __attribute__((always_inline)) {
+        return *(const int32_t *)((const char *)__builtin_amdgcn_kernarg_segment_ptr() + kRestAt +
+                                  offsetof(Rest, budget) + j * sizeof(int32_t));
+    };
+    auto teams_of = [=]() __attribute__((always_inline)) { return kShape == 1 ? meta[kMetaTeams] : 1; };
+    {
+        const Rest a = args();
+        const int path = meta[kMetaPath];
+        if ((kShape > 0 && (path == 1) != (kShape == 1)) ||
+            (kBlocks && kShape > 1 && (path == 2) != (kShape == 2)))
             return;
-    const int teams = kShape == 1 ? meta[kMetaTeams] : 1, first = blockIdx.x * teams;
-    bool any = false;
-    for (int i = 0; i < teams && first + i < K; ++i)
-        any |= todo.has_wave(first + i, K, L);
-    if (!any)
-        return;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
+        const int teams = teams_of(), first = blockIdx.x * teams;
+        bool any = false;
+        for (int i = 0; i < teams && first + i < a.K; ++i)
+            any |= a.todo.has_wave(first + i, a.K, a.L);
+        if (!any)
+            return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int pass = 0, begin = 0, end = 0;             // with checkpoints: pass 1 for each block of layers [begin, end)
     auto fill = [&](auto path) __attribute__((always_inline)) {
         constexpr int kPath = decltype(path)::value;
+        Rest a = args();
+        if constexpr (kBlocks) {
+            a.blocks.pass = pass;
+            a.blocks.begin = begin;
+            a.blocks.end = pass == 0 ? a.L : end;
+        }
         fill_candidates<false, kPath, kNarrow, kBlocks, true, kShape == 1,
-                        kPath == 1 && kNarrow && !kBlocks && kShape == 0, false>(
-            src, meta, tables, units, K, L, S, pitch, nullptr, drec, rows, tstar, budgets ? nullptr : cost, resume,
-            blocks, todo, lds, sh);
+                        kPath == 1 && kNarrow && !kBlocks && kShape == 0, false, kBlocks && (kShape == 1 || kShape == 2)>(
+            a.src, meta, a.tables, a.units, a.K, a.L, a.S, a.pitch, nullptr, a.drec, a.rows, a.tstar,
+            a.budgets ? nullptr : a.cost, a.resume, a.blocks, a.todo, lds, sh);
     };
     for (;;) {
-        if constexpr (kShape != 2)                // (each only where the path is its own)
+        if constexpr (kShape < 2)                 // (each only where the path is its own)
             fill(Many<1>{});
-        if constexpr (kShape != 1) {
+        if constexpr (kShape == 0 || kShape == 2)
             fill(Many<kBlocks ? 2 : 3>{});
+        if constexpr (kShape == 0 || kShape == (kBlocks ? 3 : 2))
             fill(Many<kBlocks ? 0 : 4>{});
-        }
         __syncthreads();                          // the rows and the final time are written
         if constexpr (!kBlocks)
             break;
-        if (blocks.pass == 1 && wave < teams && first + wave < K && todo.has_wave(first + wave, K, L))
-            walk_block<kLevelBlocks>(tau, src, meta, tstar, first + wave, L, S, pitch, profile, cost, blocks);
-        __syncthreads();                          // the block's rows are read
-        if (blocks.pass == 0) {
-            blocks.pass = 1;
-            blocks.begin = L;
+        Rest a = args();
+        if (pass == 1) {
+            const int teams = teams_of(), k = blockIdx.x * teams + wave;
+            a.blocks.begin = begin;
+            a.blocks.end = end;
+            if (wave < teams && k < a.K && a.todo.has_wave(k, a.K, a.L))
+                walk_block<kLevelBlocks>(tau, a.src, meta, a.tstar, k, a.L, a.S, a.pitch, a.profile, a.cost,
+                                         a.blocks);
+            __syncthreads();                      // the block's rows are read
+            if (begin == 0)
+                return;
+            end = begin;
+        } else {
+            pass = 1;
+            end = a.L;
         }
-        if (blocks.begin == 0)
-            return;
-        blocks.end = blocks.begin;
-        blocks.begin = (blocks.end - 1) / blocks.stride * blocks.stride;
+        begin = (end - 1) / a.blocks.stride * a.blocks.stride;
     }
-    for (int i = wave; i < teams * max(budgets, 1); i += waves) {
-        const int j = i / teams, k = first + (i - j * teams), solve = j * K + k;
-        if (k >= K || __builtin_amdgcn_readfirstlane(profile[(size_t)solve * L]) != kGivenUp)
+    const Rest a = args();
+    const int teams = teams_of(), first = blockIdx.x * teams, waves = blockDim.x / kWave;
+    for (int i = wave; a.budgets >= 0 && i < teams * max(a.budgets, 1); i += waves) {
+        const int j = i / teams, k = first + (i - j * teams), solve = j * a.K + k;
+        if (k >= a.K || __builtin_amdgcn_readfirstlane(a.profile[(size_t)solve * a.L]) != kGivenUp)
             continue;
-        const int t = budgets ? budget_time(meta, drec, k, L, pitch, budget.at[j]) : tstar[k];
+        const int t = a.budgets ? budget_time(meta, a.drec, k, a.L, a.pitch, budget_of(j)) : a.tstar[k];
         walk_table<kLevelBlocks, false>(
-            tau, src, meta, drec, [=]() __attribute__((always_inline)) { return t; }, solve, k, L, S, pitch, profile,
-            cost, resume);
+            tau, a.src, meta, a.drec, [=]() __attribute__((always_inline)) { return t; }, solve, k, a.L, a.S, a.pitch,
+            a.profile, a.cost, a.resume);
     }
 }
 
@@ -3066,6 +3124,7 @@ struct CoreCall {
     unsigned char *spill;             // the record's memory
     size_t spill_bytes;
     bool rest;                        // dp_rest does what is left
+    bool walks;                       // also the walks under several budgets
 };
 
 // LDS and limits of dp_core for these sizes; false where the full table has to be used at once.
@@ -3199,6 +3258,17 @@ int launch_small(const int32_t *tau, ErrSource src, int K, int L, int S, int B, 
     return launch_status();
 }
 
+// Whether dp_rest walks back under J budgets too: where each of its waves has one walk at most.  A walk waits for memory
+// once a layer, and a second one behind it as long again.  us a call of eight candidates, all given up, L = 54, S = 40,
+// B = 10^4, by launches of their own and so: six budgets 380 and 394 (and 57 and 53 where nothing is given up, K = 64),
+// 64 budgets 407 and 690; K = 700, L = 30, S = 20, B = 1000, 16 budgets 229 and 290.
+bool rest_walks(const Layout &lay, int K, int J, int units)
+{
+    const long long teams = (K + 2LL * units - 1) / (2LL * units);         // at most, of a workgroup
+    const size_t waves = lay.row / kWave < (size_t)kFillWaves ? lay.row / kWave : (size_t)kFillWaves;
+    return J * teams <= (long long)waves;
+}
+
 // Sets up the call for the J budgets, the largest of which `lay` is for; false: the full table at
 // once.  `one_fill`: all that the full table would take is one fill and one walk back.
 bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, int J, bool one_fill,
@@ -3218,7 +3288,7 @@ bool core_call(const Layout &lay, int K, int L, int S, const int32_t *budget, in
     *call = CoreCall{profile, cost, budget, J,
                      static_cast<unsigned char *>(workspace) + lay.record_off,
                      workspace_bytes - lay.record_off,
-                     lay.variant == kValueRecord};
+                     lay.variant == kValueRecord, rest_walks(lay, K, J, dev.units)};
     return true;
 }
 
@@ -3264,9 +3334,6 @@ int launch_core(const int32_t *tau, ErrSource src, int K, int L, int S, const Pr
     }
     return launch_status();
 }
-
-// Of several budgets, those that dp_rest walks back under.
-int first_budgets(int J) { return J < kCoreBudgets ? J : kCoreBudgets; }
 
 template <bool kLevel, bool kNarrow, bool kBlocks, bool kPairs, bool kTodo>
 int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume resume, int K, int L,
@@ -3437,26 +3504,31 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     }
     const LevelTables tables{shifts, order, start, entry, s8};
     if constexpr (kTodo && !kLevel) {
-        const int budgets = cost ? 0 : first_budgets(core->budgets);
-        Budgets budget{};
-        for (int j = 0; j < budgets; ++j)
-            budget.at[j] = core->budget[j];
+        Rest rest{src, tables, units, K, L, S, pitch, drec, rows, tstar, core->profile, core->cost, resume, blocks,
+                  todo, cost ? 0 : (core->walks ? core->budgets : -1), {}};
+        for (int j = 0; j < rest.budgets; ++j)
+            rest.budget.at[j] = core->budget[j];
         auto launch = [&](auto kernel, int threads, int lds) {
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) == hipSuccess)
-                hipLaunchKernelGGL(kernel, dim3(K), dim3(threads), lds, q, tau, src, meta, tables, units, K, L, S,
-                                   pitch, drec, rows, tstar, core->profile, core->cost, resume, blocks, todo,
-                                   budgets, budget);
+                hipLaunchKernelGGL(kernel, dim3(K), dim3(threads), lds, q, tau, meta, rest);
         };
+        const int threads = wide ? wide_waves * kWave : waves * kWave;
         int lds = lds_wide > lds_large ? lds_wide : lds_large;
         lds = in_memory && lds_stage > lds ? lds_stage : lds;
-        const int threads = wide ? wide_waves * kWave : waves * kWave;
-        if (K <= units)
+        if (K <= units) {
             launch(dp_rest<kNarrow, kBlocks, 0>, wide ? threads : place_threads, place_lds > lds ? place_lds : lds);
-        else
+        } else {
             launch(dp_rest<kNarrow, kBlocks, 1>, waves * kWave, kLdsHalf);
-        if (K > units && lds > 0)                 // (rows may be longer)
-            launch(dp_rest<kNarrow, kBlocks, 2>, threads, lds);
+            if constexpr (kBlocks) {              // (rows may be longer)
+                if (lds_large)
+                    launch(dp_rest<kNarrow, kBlocks, 2>, threads, lds_large);
+                if (in_memory)
+                    launch(dp_rest<kNarrow, kBlocks, 3>, threads, lds_stage);
+            } else if (lds > 0) {
+                launch(dp_rest<kNarrow, kBlocks, 2>, threads, lds);
+            }
+        }
         return launch_status();
     }
     if constexpr (can_tile) {
@@ -3789,7 +3861,7 @@ int budgets_impl(const int32_t *tau, ErrSource src, int K, int L, int S, const i
         return st;
     hipStream_t q = static_cast<hipStream_t>(stream);
     const int most = budgets_per_launch(K, L);
-    for (int j0 = reduced ? first_budgets(J) : 0; j0 < J; j0 += most) {
+    for (int j0 = reduced && core.walks ? J : 0; j0 < J; j0 += most) {
         const int n = J - j0 < most ? J - j0 : most;
         Budgets some{};
         for (int j = 0; j < n; ++j)
