@@ -2948,10 +2948,10 @@ template <int kLevelBlocks>
 __global__ __launch_bounds__(kWalkThreads) void dp_backtrace_blocks(
     const int32_t *__restrict__ tau, ErrSource src, const int32_t *__restrict__ meta,
     int32_t *__restrict__ tstar, int K, int L, int S, int pitch, int16_t *__restrict__ profile,
-    float *__restrict__ cost, Blocks blocks, Todo todo)
+    float *__restrict__ cost, Blocks blocks)
 {
     const int k = blockIdx.x * (kWalkThreads / kWave) + threadIdx.x / kWave;
-    if (k < K && todo.has_wave(k, K, L))
+    if (k < K)
         walk_block<kLevelBlocks>(tau, src, meta, tstar, k, L, S, pitch, profile, cost, blocks);
 }
 
@@ -3408,7 +3408,7 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // 0.2 % over 441 fills of more than 4 x units candidates, less than the idle one takes (2 us and more).
     // D record of more than 64 levels: always.  us by dp_fill and so, K = 4000: S = 65, L = 10, B = 800 179 and 150;
     // S = 255, L = 10, B = 800 390 and 306; S = 100, L = 12, B = 61 505 and 150; the worst of 370 on 1 - 80 chunks 0.92.
-    constexpr bool kLeft = kTodo && kLevel;       // (the D record's are dp_rest's)
+    constexpr bool kLeft = kTodo && kLevel, kRest = kTodo && !kLevel;      // (the D record's are dp_rest's)
     constexpr bool can_fold = (!kNarrow || (kLevel && kPairs)) && !kBlocks && !kTodo;
     const bool columns = can_fold && K > units && !resume.first_layer &&
                          (!kLevel || (S >= kFoldLevels && B >= kFoldBudget &&
@@ -3443,12 +3443,12 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // (rows that may lie in memory are long: `waves` is the full number then)
     constexpr bool can_tile = !kLevel && !kBlocks && !kTodo;
     auto in_global = dp_fill<kLevel, can_widen ? 4 : 0, kNarrow, kBlocks, kLeft, false, false, kPairs>;
-    if (wide &&
+    if (!kRest && wide &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(wide_place),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
     // always the same limit, so that calls from several host threads cannot undo each other's
-    if (lds_large &&
+    if (!kRest && lds_large &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(two_rows),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
@@ -3456,7 +3456,7 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     // compute unit; workgroups of the usual size take half of it when there are candidates for
     // two per unit (one sweeps while the other copies).
     const int lds_stage = (K > units && !wide_global) ? kLdsHalf : kLdsBytes;
-    if (in_memory &&
+    if (!kRest && in_memory &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(in_global),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
         return SPDY_DP_ERR_LAUNCH;
@@ -3494,16 +3494,14 @@ int enqueue_fill(const Layout &lay, const int32_t *tau, ErrSource src, Resume re
     Todo todo;
     if (core) {
         todo = Todo{core->profile, core->budgets};
-        if (!(kBlocks && blocks.pass == 1)) {
-            const int st = launch_core(tau, src, K, L, S, prep, *core, units, q);
-            if (st != SPDY_DP_OK)
-                return st;
-        }
+        const int st = launch_core(tau, src, K, L, S, prep, *core, units, q);
+        if (st != SPDY_DP_OK)
+            return st;
     } else if (!(kBlocks && blocks.pass == 1)) { // the block passes reuse pass 0's tables
         hipLaunchKernelGGL(dp_prepare, dim3(L + 1), dim3(256), 0, q, tau, K, L, S, prep);
     }
     const LevelTables tables{shifts, order, start, entry, s8};
-    if constexpr (kTodo && !kLevel) {
+    if constexpr (kRest) {
         Rest rest{src, tables, units, K, L, S, pitch, drec, rows, tstar, core->profile, core->cost, resume, blocks,
                   todo, cost ? 0 : (core->walks ? core->budgets : -1), {}};
         for (int j = 0; j < rest.budgets; ++j)
@@ -3784,7 +3782,6 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     CoreCall core;
     const bool reduced =
         core_call(lay, K, L, S, &B, 1, false, profile, cost, workspace, workspace_bytes, &core);
-    const Todo todo = reduced ? Todo{profile, 1} : Todo{};
     auto fill = [&]() {
         const CoreCall *first = reduced ? &core : nullptr;
         return S <= kWave
@@ -3797,8 +3794,8 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
     blocks.begin = 0;
     blocks.end = L;
     st = fill();
-    if (st != SPDY_DP_OK || (reduced && core.rest))
-        return st;                                // (all passes were in that)
+    if (st != SPDY_DP_OK || reduced)
+        return st;                                // (dp_rest does all passes)
     const int32_t *meta = reinterpret_cast<const int32_t *>(ws + lay.meta_off);
     int32_t *tstar = reinterpret_cast<int32_t *>(ws + lay.tstar_off);
     const int per_block = kWalkThreads / kWave;
@@ -3811,8 +3808,7 @@ int checkpointed_impl(const int32_t *tau, ErrSource src, int K, int L, int S, in
             return st;
         auto walk = S <= kWave ? dp_backtrace_blocks<1> : dp_backtrace_blocks<4>;
         hipLaunchKernelGGL(walk, dim3((K + per_block - 1) / per_block), dim3(kWalkThreads), 0, q,
-                           tau, src, meta, tstar, K, L, S, (int)lay.row, profile, cost, blocks,
-                           todo);
+                           tau, src, meta, tstar, K, L, S, (int)lay.row, profile, cost, blocks);
         st = launch_status();
         if (st != SPDY_DP_OK)
             return st;
