@@ -77,6 +77,22 @@ def tracked_traffic(workload: str, record: str):
     return None
 
 
+def fill_launch(words, record: str, S: int):
+    """What did the fill, from the header words that it leaves in its workspace (see the header of the
+    library, spdy_dp_workspace_layout): the kernel's name, and whether its sweep reads 128 bits per lane."""
+    tiles = int(words[19])
+    if tiles < 0:                                 # rows folded into -tiles parts
+        return "dp_columns", tiles == -4
+    return "dp_tiles" if tiles > 0 else "dp_fill", record == "d" and S <= 64
+
+
+def bare_sweep(kernel: str, wide_reads: bool, record: str) -> str:
+    """The loop of the rate probe that is this kernel's sweep by itself."""
+    if kernel == "dp_columns" and wide_reads:
+        return "sweep_folded" if record == "d" else "sweep_folded_levels"
+    return "sweep_b128" if wide_reads else "sweep_b32"
+
+
 def measured_peaks():
     """Run the rate probe (a separate executable) as a child process; None if it is not built or
     fails.  Called before this process touches the GPU."""
@@ -337,6 +353,10 @@ def main() -> int:
     p_gpu = profile.cpu().numpy()
     c_gpu = cost.cpu().numpy()
 
+    at = 0 if args.checkpoints is not None else \
+        dp.spdy_dp_workspace_layout(K, L, S, B, ws.numel())["meta_offset"]
+    header = ws[at:at + 4 * 20].cpu().numpy().view(np.int32)
+
     # the same again, after the timed region, once the clocks have settled (reported beside it)
     steady = None
     if args.settle_steps > 0:
@@ -376,15 +396,15 @@ def main() -> int:
     # The D-record fill is bound by LDS reads (4 bytes of the shifted row per update, an add and
     # half a v_min3 beside it); the level-record fill by the vector ALU (two and a half to four
     # instructions per update).  Both objects are always reported; `roofline` is the binding one.  With at most 64
-    # levels the D-record sweep reads 128 bits per lane, so its peak is the 128-bit one; the
-    # fraction of the 32-bit-read peak (what a lane = bucket layout can reach at best) is beside it.
-    # So it is with more levels where there are more candidates than compute units (folded rows).
-    wide_reads = args.record == "d" and (S <= 64 or K > COMPUTE_UNITS)
+    # levels the D-record sweep reads 128 bits per lane, and so does that of folded rows; its peak is the
+    # 128-bit one then, and the fraction of the 32-bit-read peak (what a lane = bucket layout can reach at
+    # best) is beside it.
+    kernel, wide_reads = fill_launch(header, args.record, S)
     lds_peak = LDS_PEAK_B128 if wide_reads else LDS_PEAK_B32
     lds_probe = "lds_read_b128" if wide_reads else "lds_read_b32"
     lds_obj = {
         "bound": "lds",
-        "kernel": "dp_fill",
+        "kernel": kernel,
         "achieved": lds_bytes / seconds / 1e12,
         "peak": lds_peak / 1e12,
         "unit": "TB/s",
@@ -401,7 +421,7 @@ def main() -> int:
     }
     valu_obj = {
         "bound": "alu",
-        "kernel": "dp_fill",
+        "kernel": kernel,
         "achieved": lane_ops / seconds / 1e12,
         "peak": ALU_PEAK_LANE_OPS / 1e12,
         "unit": "Tlane-op/s",
@@ -423,7 +443,7 @@ def main() -> int:
         # per clock and compute unit, beside what the sweep loop alone reaches in the rate probe
         # (no barriers, stores or table hand-over): the practical ceiling of this instruction mix
         "updates_per_clk_cu": executed / seconds / CLOCK_HZ / COMPUTE_UNITS,
-        "bare_sweep_updates_per_clk_cu": rate("sweep_b128" if wide_reads else "sweep_b32",
+        "bare_sweep_updates_per_clk_cu": rate(bare_sweep(kernel, wide_reads, args.record),
                                               "updates_per_clk_cu"),
         "traffic": tracked_traffic(cfg.name, args.record) if K == cfg.K else None,
     })

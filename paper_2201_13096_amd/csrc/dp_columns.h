@@ -16,8 +16,12 @@
 // are not folded (a position is one bucket then, and not four): lane = bucket, 32-bit reads.
 //
 // What bounds it: the level record issues vector instructions (add, min3, compare, select: 16 clocks of a SIMD for two
-// updates of 64 cells), the D record of many levels waits for LDS reads.  Bare loops, updates per clock and
-// compute unit: level record 30.5, 24.0 a bucket to a lane; D record 49.2, 27.6.
+// updates of 64 cells), the D record of many levels waits for LDS reads.  Loops of the rate probe (sweep_folded_levels,
+// sweep_folded), updates per clock and compute unit: level record 27.3, 24.0 a bucket to a lane; D record 48.4, 27.6.
+// Counted: level record, K = 1001, L = 52, S = 42, B = 9973: a SIMD issues 5.6e5 vector instructions, at 3.2 clocks each
+// three quarters of the launch; waves wait for half of their time, barriers included, 0.04 of it for LDS, whose conflicts
+// are 0.11 of its active clocks; D record, S = 128, K = 1024, L = 54, B = 10^4: LDS is active for three quarters of the
+// launch, waves wait for 0.28 of their time, most of it for LDS.
 // us a fill by dp_fill, a bucket to a lane, and so: level record, K = 1001, L = 52, S = 42, B = 9973 1263 and 1025; S = 128,
 // K = 1024, L = 54, B = 10^4 2462 and 1950; D record of the same 1226 and 766; S = 100, K = 4000, B = 1000 1108 and
 // 353.

@@ -170,13 +170,14 @@ __global__ __launch_bounds__(256) void lds_read(int *out, int step, int iters, i
 // wave keeps a running minimum per bucket and visits pairs of entries; per pair and bucket one
 // LDS read and one add per entry and one v_min3.  Two layouts:
 //   sweep_b32:  lane = bucket, 16 chunks of 64 buckets per wave, 32-bit reads;
-//   sweep_b128: lane = four consecutive buckets, 4 chunks of 256 buckets per wave, one aligned
-//               128-bit read per entry, whatever the shift's residue (the fill moves its minima
-//               by a bucket between residues); shifts and errors of a pair come from LDS, one read
-//               ahead.
+//   sweep_b128: lane = four buckets, chunks of 256 buckets, one aligned 128-bit read per entry; shifts and errors of
+//               a pair come from LDS, one read ahead.  4 chunks per wave: four consecutive buckets, whatever the
+//               shift's residue (the fill moves its minima by a bucket between residues); 7 chunks: rows folded
+//               into four parts; with the level record, 5 chunks: compare and select of the pair besides (without
+//               finding out which of a noted pair it was).
 // Eight waves per workgroup, two workgroups per compute unit, as the fill runs.
-constexpr int kSweepRow = 8 * 16 * 64;   // floats swept per workgroup
 constexpr int kSweepHalo = 2048;         // shifts stay below this
+constexpr int sweep_row(int chunks) { return 8 * chunks * 256; }         // floats swept per workgroup
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef int int4v __attribute__((ext_vector_type(4)));
 
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(512, 2) void sweep_b32(float *out, const int *shift
                                                     const float *errs, int pairs, int iters)
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
-    for (int i = threadIdx.x; i < kSweepRow + kSweepHalo; i += blockDim.x)
+    for (int i = threadIdx.x; i < sweep_row(4) + kSweepHalo; i += blockDim.x)
         row[i] = (float)(i & 1023);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -218,8 +219,9 @@ __global__ __launch_bounds__(512, 2) void sweep_b32(float *out, const int *shift
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-__global__ __launch_bounds__(512, 2) void sweep_b128(float *out, const int *shifts,
-                                                     const float *errs, int pairs, int iters)
+template <int Q, bool kLevel>
+__global__ __launch_bounds__(512, kLevel ? 4 : 2) void sweep_b128(float *out, const int *shifts,
+                                                                  const float *errs, int pairs, int iters)
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ __attribute__((aligned(16))) int entries[64][2];   // bytes of whole quads, error
@@ -227,13 +229,14 @@ __global__ __launch_bounds__(512, 2) void sweep_b128(float *out, const int *shif
         entries[threadIdx.x][0] = (shifts[threadIdx.x] >> 2) * 16;
         entries[threadIdx.x][1] = __float_as_int(errs[threadIdx.x]);
     }
-    for (int i = threadIdx.x; i < kSweepRow + kSweepHalo; i += blockDim.x)
+    for (int i = threadIdx.x; i < sweep_row(Q) + kSweepHalo; i += blockDim.x)
         row[i] = (float)(i & 1023);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float4v *mine = reinterpret_cast<const float4v *>(row + kSweepHalo) + wave * 4 * 64 + lane;
-    float best[4][4];
-    for (int j = 0; j < 4; ++j)
+    const float4v *mine = reinterpret_cast<const float4v *>(row + kSweepHalo) + wave * Q * 64 + lane;
+    float best[Q][4];
+    unsigned arg[kLevel ? Q : 1][4] = {};
+    for (int j = 0; j < Q; ++j)
         for (int c = 0; c < 4; ++c)
             best[j][c] = 1e30f;
     const int4v *const pair = reinterpret_cast<const int4v *>(entries);
@@ -247,18 +250,26 @@ __global__ __launch_bounds__(512, 2) void sweep_b128(float *out, const int *shif
             const float4v *p1 = reinterpret_cast<const float4v *>(at - now.z);
             const float e0 = __int_as_float(now.y), e1 = __int_as_float(now.w);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < Q; ++j) {
                 const float4v a = p0[j * 64], b = p1[j * 64];
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    min3(best[j][c], a[c] + e0, b[c] + e1);
+                for (int c = 0; c < 4; ++c) {
+                    if constexpr (kLevel) {
+                        float m;
+                        asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(best[j][c]), "v"(a[c] + e0), "v"(b[c] + e1));
+                        arg[j][c] = m < best[j][c] ? (unsigned)now.x : arg[j][c];
+                        best[j][c] = m;
+                    } else {
+                        min3(best[j][c], a[c] + e0, b[c] + e1);
+                    }
+                }
             }
         }
     }
     float s = 0;
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < Q; ++j)
         for (int c = 0; c < 4; ++c)
-            s += best[j][c];
+            s += best[j][c] + (kLevel ? (float)arg[kLevel ? j : 0][c] : 0.0f);
     out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
@@ -344,9 +355,9 @@ int main()
         CHECK(hipMalloc(&er, sizeof he));
         CHECK(hipMemcpy(sh, hs, sizeof hs, hipMemcpyHostToDevice));
         CHECK(hipMemcpy(er, he, sizeof he, hipMemcpyHostToDevice));
-        const size_t bytes = (kSweepRow + kSweepHalo) * sizeof(float);
-        const double updates = (double)wgs * wg_threads * 16 * (2.0 * pairs) * iters;
-        auto sweep = [&](auto kernel) {
+        auto sweep = [&](const char *name, auto kernel, int chunks) {
+            const size_t bytes = (sweep_row(chunks) + kSweepHalo) * sizeof(float);
+            const double updates = (double)wgs * wg_threads * 4 * chunks * (2.0 * pairs) * iters;
             CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
             const float ms = time_ms(
@@ -355,11 +366,12 @@ int main()
                                        pairs, iters);
                 },
                 20);
-            return updates / (ms * 1e-3) / clk / cus;
+            printf(", \"%s\": {\"updates_per_clk_cu\": %.2f}", name, updates / (ms * 1e-3) / clk / cus);
         };
-        const double u32 = sweep(sweep_b32);
-        printf(", \"sweep_b32\": {\"updates_per_clk_cu\": %.2f}", u32);
-        printf(", \"sweep_b128\": {\"updates_per_clk_cu\": %.2f}", sweep(sweep_b128));
+        sweep("sweep_b32", sweep_b32, 4);
+        sweep("sweep_b128", sweep_b128<4, false>, 4);
+        sweep("sweep_folded", sweep_b128<7, false>, 7);
+        sweep("sweep_folded_levels", sweep_b128<5, true>, 5);
         CHECK(hipFree(sh));
         CHECK(hipFree(er));
     }

@@ -297,6 +297,18 @@ def test_source_id_covers_every_kernel_source(tmp_path, monkeypatch):
     assert len(ids) == 1 + len(copies)
 
 
+# the kernel and the width of its reads by header word 19, not by the sizes: rows that are folded or not, rows beyond them
+@pytest.mark.parametrize("word, record, S, kernel, wide, loop", [
+    (0, "d", 64, "dp_fill", True, "sweep_b128"), (0, "d", 65, "dp_fill", False, "sweep_b32"),
+    (-4, "d", 65, "dp_columns", True, "sweep_folded"), (-1, "d", 65, "dp_columns", False, "sweep_b32"),
+    (-4, "level", 40, "dp_columns", True, "sweep_folded_levels"), (-1, "level", 40, "dp_columns", False, "sweep_b32"),
+    (0, "level", 40, "dp_fill", False, "sweep_b32"), (3 | 1 << 11, "d", 40, "dp_tiles", True, "sweep_b128")])
+def test_bench_names_what_did_the_fill(word, record, S, kernel, wide, loop):
+    import bench
+    assert bench.fill_launch([0] * 19 + [word], record, S) == (kernel, wide)
+    assert bench.bare_sweep(kernel, wide, record) == loop
+
+
 def test_rate_probe_output_is_optional(monkeypatch, tmp_path):
     import bench
     monkeypatch.setattr(bench, "PROBE", str(tmp_path / "no_such_probe"))
