@@ -79,7 +79,9 @@ def tracked_traffic(workload: str, record: str):
 
 def fill_launch(words, record: str, S: int):
     """What did the fill, from the header words that it leaves in its workspace (see the header of the
-    library, spdy_dp_workspace_layout): the kernel's name, and whether its sweep reads 128 bits per lane."""
+    library, spdy_dp_workspace_layout): the kernel's name, and whether its sweep reads 128 bits per lane.
+    (dp_wide, which runs tiles or a row in place where rows may lie in memory, goes by what it ran as:
+    dp_tiles or dp_fill.)"""
     tiles = int(words[19])
     if tiles < 0:                                 # rows folded into -tiles parts
         return "dp_columns", tiles == -4
